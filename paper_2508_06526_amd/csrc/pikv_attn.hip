@@ -54,10 +54,6 @@ struct AttnParams {
 
 // Raw scores of at most this many bytes per block are staged in LDS (plain-ALU kernel).
 constexpr int kScoreStageBytes = 16384;
-// LDS the matrix-core kernel's blocks hold for their tile staging (K tile, two P tiles, rescale
-// factors and wave statistics of 4 waves); their score stage comes on top
-constexpr size_t kGqaStaticLds = 4 * (32 * 272 + 2 * 16 * 80 + 16 * 4 + 2 * 16 * 4);
-
 // Resolve the j-th selected shard of a routing row with ONE round trip to memory: the
 // expert id is fetched while lanes 0..E-1 fetch the entry count and the K/V base address of
 // every expert of the sequence; the selected lane's values are then broadcast.
@@ -376,34 +372,75 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, plain_blocks_per_cu(W * (int
 }
 
 // ---------------------------------------------------------------------------------------
-// Grouped-query variant on the matrix cores (bf16 rows of 128 values, one routing decision
-// per token, 2..64 query rows per kv head: the heads of the group times the draft queries of
-// a multi-query step).  With G query rows sharing every K/V byte the plain-ALU kernel above
+// Grouped-query variant on the matrix cores (bf16 rows of W values, one routing decision per
+// token, 2..64 query rows per kv head: the heads of the group times the draft queries of a
+// multi-query step).  With G query rows sharing every K/V byte the plain-ALU kernel above
 // spends ~G times more instructions per byte and stops being memory-bound; here the G rows
-// (padded to whole tiles of 16) form the second dimension of 16x16x32 bf16 MFMA tiles, so the
+// (padded to whole tiles of 16) form one dimension of 16x16x32 bf16 MFMA tiles, so the
 // instruction count per byte does not depend on G within a row tile.
 //
-// Per wave and per tile of 32 entries:
-//   * K and V rows arrive with the same coalesced 16-byte lane loads as above; lane
-//     (r = lane/16, c = lane%16) takes rows 8r..8r+7 and byte chunk c of each.
-//   * scores, transposed: S^T[entry][head] = K . Q^T.  The MFMA wants lane%16 to index the
-//     entry, so the K registers make one trip through a padded wave-private LDS tile
-//     (write row-major, read one entry per lane); Q sits in registers as the other operand.
-//     Result: lane (head c, group r) holds 8 entries of head c - the softmax is lane-local
-//     except for two cross-group steps.
-//   * probabilities go back through LDS (as a bf16 high part plus a bf16 residual, so the
-//     product is exact to ~2^-17) into the row-operand layout: lane (head c, group r) gets
-//     P[head c][entries 8r..8r+7].
-//   * output: O[head][d] += P . V.  V needs no transpose at all: for output column set i the
-//     column operand of lane (c, r) is V[entries 8r..8r+7][d = 8c + i], i.e. the i-th value
-//     of each of its own 8 loaded rows, packed by byte-permutes.
-constexpr int kGqaTile = 32;
-// Bytes per staged K row: 256 + 16 of padding, so that the 16 lanes reading one 16-byte column
-// of 16 different rows do not all start in the same bank.  The pass waits on memory, not on LDS:
-// a pitch of 288, which halves the bank-conflict cycles the counters report, runs in the same
-// time to the nanosecond, so the smaller pitch stays.
-constexpr int kGqaKPitch = 272;
-constexpr int kGqaPPitch = 80;    // bytes per staged P row (32 bf16 + 16 pad)
+// Per wave and per tile of entries (sub-tiles of 32):
+//   * K rows arrive with coalesced 16-byte lane loads and make one trip through a padded
+//     wave-private LDS tile (write row-major, read one entry per lane); Q sits in registers.
+//     S^T[entry][row] = K . Q^T: lane (query row c = lane % 16, group r = lane / 16) ends up
+//     with the scores of entries 4r..4r+3 and 16+4r..16+4r+3 of the sub-tile.
+//   * The order of the contraction index of an MFMA is free as long as both operands agree on
+//     it.  With entry order e(r, 0..7) = {4r..4r+3, 16+4r..16+4r+3} those scores, turned into
+//     probabilities, ARE the lane's slice of the operand P^T[entry][row] of the second product:
+//     nothing moves between lanes.  (They are split into bf16 parts, see kProbParts.)
+//   * O^T[d][row] += V^T . P^T.  V needs no transpose either: lane (c, r) loads the rows e(r, t)
+//     of the sub-tile, W/8 bytes of each, and output set i takes the i-th value of each of its
+//     own 8 rows (packed by byte-permutes).  The accumulators of lane (c, r) belong to query row
+//     c, like the lane's scores: the online-softmax rescale is lane-local.
+// Bound by memory up to 16 rows per kv head; by then the plain-ALU kernel is bound by vector issue.
+// Measured, pass and merge, 128 MiB of K/V (64 MiB for rank 16 and the 64-row group), against the
+// kernel that took the shape before: rows of 64 values x 8 heads 55.2 -> 33.8 us, x 3 heads (which
+// streamed K/V once per head) 56.9 -> 30.6, x 32 heads 430 -> 53, x 64 heads 318 -> 43; rank-32
+// codes x 4 heads 42.7 -> 37.8, x 16 heads 127 -> 34; rank 64 x 4 heads (256 MiB) 69.7 -> 58.8, rank
+// 16 x 4 heads 28.9 -> 25.1; even at 2 heads.  Rows of 128 values (before: probabilities through
+// LDS) x 4 heads 29.7 -> 29.1, 8 heads 35.0 -> 31.8, 64 rows 45.1 -> 41.6.
+constexpr int kSubTile = 32;
+constexpr int gqa_tile(int width, int row_tiles) {
+    if (width == 128 || (width == 64 && row_tiles == 4)) return kSubTile;
+    return kSubTile * (width == 16 ? 4 : 2);
+}
+constexpr int kClampRows = 128;   // the loads address at most a tile past a shard's last row before they are clamped
+
+// Bytes per staged K row: the row plus 16 of padding, so that the 16 lanes reading one 16-byte
+// column of 16 different rows do not all start in the same bank.
+template <int W, int RT>
+struct RowShape {
+    static constexpr int kRowBytes = 2 * W;
+    static constexpr int kPitch = kRowBytes + 16;
+    static constexpr int kKLanes = kRowBytes / 16;         // lanes of a K load that cover one row
+    static constexpr int kKRows = kWave / kKLanes;         // rows of a K load
+    // sub-tiles per tile: 16 KiB of K and V rows in flight per wave, 8 KiB for codes of rank 32
+    // and 16 (four blocks per CU instead of three, as in the plain-ALU kernel)
+    static constexpr int kTile = gqa_tile(W, RT);
+    static constexpr int kSubs = kTile / kSubTile;
+    static constexpr int kKLoads = kTile / kKRows;
+    // V per sub-tile: 8 loads of W/8 bytes.  W = 16: 2 bytes would be left for a lane; there lanes
+    // m < 8 and m + 8 load the same word of two neighbouring rows (4 loads) and swap halves.
+    static constexpr bool kPairs = W == 16;
+    static constexpr int kVLoads = kPairs ? 4 : 8;
+    static constexpr int kVWords = kPairs ? 1 : kRowBytes / 64;      // 32-bit words per load
+    static constexpr int kSets = W / 16;                   // output sets
+    static constexpr int kQSteps = W >= 32 ? W / 32 : 1;   // MFMA steps of a score
+    // row t of the lane's loads, relative to its first (entry e(r, t) or, in pairs, e(r, 2t))
+    static constexpr int v_step(int t) { return kPairs ? (t & 1) * 2 + (t >> 1) * 16 : (t & 3) + (t >> 2) * 16; }
+};
+
+// A lane's slice of an MFMA operand with contraction length 32 (8 values), or 16 for rows of 16
+// values (4 values).
+template <int W>
+struct OperandOf {
+    typedef uint4 type;
+};
+template <>
+struct OperandOf<16> {
+    typedef uint2 type;
+};
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
 typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
@@ -418,20 +455,97 @@ __device__ __forceinline__ void wave_lds_order() {
     __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
 }
 
+// max over the four lanes c, c + 16, c + 32, c + 48, in all of them, without LDS: the swaps leave
+// the two halves (then the two rows of each half) side by side in two registers.
+__device__ __forceinline__ float group_max(float x) {
+    const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    x = fmaxf(__uint_as_float(h[0]), __uint_as_float(h[1]));
+    const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+    return fmaxf(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+
+// fp32 values (8 for uint4, 4 for uint2) as PARTS bf16 operands whose sum they are: each part
+// rounds what the parts before it left (2 parts carry 16 bits of a value, 3 parts all 24).
+template <int PARTS, typename OP>
+__device__ __forceinline__ void split_bf16(const float *v, OP (&out)[PARTS]) {
+    constexpr int NW = sizeof(OP) / 4;
+    struct Words {
+        uint32_t w[NW];
+    } words[PARTS];
+#pragma unroll
+    for (int u = 0; u < NW; ++u) {
+        f32x2_t rest = {v[2 * u], v[2 * u + 1]};
+#pragma unroll
+        for (int k = 0; k < PARTS; ++k) {
+            const bf16x2_t part = __builtin_convertvector(rest, bf16x2_t);
+            words[k].w[u] = __builtin_bit_cast(uint32_t, part);
+            if (k + 1 < PARTS) rest = rest - f32x2_t{(float)part[0], (float)part[1]};
+        }
+    }
+#pragma unroll
+    for (int k = 0; k < PARTS; ++k) out[k] = __builtin_bit_cast(OP, words[k]);
+}
+
+__device__ __forceinline__ f32x4_t mfma_rows(uint4 a, uint4 b, f32x4_t acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+                                                   acc, 0, 0, 0);
+}
+__device__ __forceinline__ f32x4_t mfma_rows(uint2 a, uint2 b, f32x4_t acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a), __builtin_bit_cast(s16x4_t, b),
+                                                     acc, 0, 0, 0);
+}
+
+// Consecutive bf16 query values as an operand; a caller's q need not be 16-byte aligned.
+template <typename OP>
+__device__ __forceinline__ OP load_query(const bf16 *q, bool aligned) {
+    if (aligned) return *reinterpret_cast<const OP *>(q);
+    struct {
+        uint16_t v[sizeof(OP) / 2];
+    } parts;
+#pragma unroll
+    for (unsigned i = 0; i < sizeof(OP) / 2; ++i) parts.v[i] = q[i].bits;
+    return __builtin_bit_cast(OP, parts);
+}
+
+__device__ __forceinline__ void hold_operand(uint4 &v) {
+    asm volatile("" : "+v"(v.x), "+v"(v.y), "+v"(v.z), "+v"(v.w));
+}
+__device__ __forceinline__ void hold_operand(uint2 &v) { asm volatile("" : "+v"(v.x), "+v"(v.y)); }
+
 // RT = number of 16-row tiles the query group occupies (group rows = query heads per kv head
 // times the draft queries of a multi-query step): 1, 2 or 4.  Every row tile reuses the K tile
 // staged in LDS and the V rows in registers, so the streamed bytes do not grow with RT; the
-// accumulators do (32 registers per row tile), which is why a CU holds 3 blocks at RT = 1 and 2
+// accumulators do (W/4 registers per row tile), which is why a CU holds 3 blocks at RT = 1 and 2
 // above.  For RT = 4 the query operands live in LDS instead of registers.
-template <int RT>
+constexpr int gqa_blocks_per_cu(int width, int row_tiles, bool codes) {
+    if (codes && width == 64 && row_tiles == 4) return 1;      // 96 registers of query operand
+    if (width <= 32) return row_tiles == 1 ? 4 : row_tiles == 2 ? 3 : 2;
+    return row_tiles == 1 ? 3 : 2;
+}
+// CODES: the rows are rank-W codes.  Their query is U_K q, formed in fp32 by MFMAs in the kernel's
+// prologue - W/16 tiles of (code column, query row), whose result layout is again the operand
+// layout up to the order of the contraction index - and split into 3 bf16 parts, so that its
+// products with the codes stay exact to 24 bits.
+template <int W, int RT, bool CODES>
 struct GqaShape {
-    static constexpr int kBlocksPerCU = RT == 1 ? 3 : 2;
-    static constexpr bool kQueryInLds = RT > 2;
-    // RT = 4: the 128 accumulator registers leave no room to hold the next K tile across the
-    // whole tile's arithmetic; K is then loaded where it is used and the CU's other waves hide
+    static constexpr bool kQueryInLds = W == 128 && RT > 2;
+    // W = 128, RT = 4: the 128 accumulator registers leave no room to hold the next K tile across
+    // the whole tile's arithmetic; K is then loaded where it is used and the CU's other waves hide
     // the latency (at four row tiles the kernel is bound by the matrix cores, not by memory).
-    static constexpr bool kPrefetchK = RT < 4;
+    static constexpr bool kPrefetchK = !kQueryInLds;
+    static constexpr int kQueryParts = CODES ? 3 : 1;
+    // Probabilities: 3 parts are the fp32 value, 2 parts differ from it by 2^-17.  Rows of 128
+    // values have always used 2 (y is 1.9e-6 off 64 bits); the narrower rows were summed in fp32
+    // on the vector units (2e-7) and keep that.
+    static constexpr int kProbParts = W == 128 ? 2 : 3;
 };
+
+// LDS a block holds besides the score stage: a K tile per wave and the wave statistics, and the
+// query tile at four row tiles.
+constexpr size_t gqa_static_lds(int width, int tile, int row_tiles) {
+    return (size_t)kWavesPerBlock * (tile * (2 * width + 16) + 2 * 16 * 4) +
+           (width == 128 && row_tiles == 4 ? (size_t)64 * (2 * width + 16) : 16);
+}
 
 // SC: what happens to the raw scores - kScoresNone (not asked for), kScoresStaged (kept in LDS,
 // one burst per row at the block's end) or kScoresDirect (written from the loop).  A template
@@ -439,12 +553,16 @@ struct GqaShape {
 // of them is reloaded inside the loop by a scratch load, which the wait counters cannot tell
 // from the tile loads in flight - the wave then waits for all of them.
 constexpr int kScoresNone = 0, kScoresStaged = 1, kScoresDirect = 2;
-template <int RT, int SC>
-__global__ __launch_bounds__(kWavesPerBlock *kWave, GqaShape<RT>::kBlocksPerCU) void attn_partial_gqa128(
+template <int W, int RT, int SC, bool CODES>
+__global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, CODES)) void attn_partial_gqa(
     AttnParams p) {
-    constexpr int W = 128;
-    constexpr bool QLDS = GqaShape<RT>::kQueryInLds;
-    constexpr bool KPRE = GqaShape<RT>::kPrefetchK;
+    using Row = RowShape<W, RT>;
+    constexpr int TILE = Row::kTile, SUBS = Row::kSubs, SETS = Row::kSets, PITCH = Row::kPitch;
+    using Shape = GqaShape<W, RT, CODES>;
+    typedef typename OperandOf<W>::type Operand;
+    constexpr bool QLDS = Shape::kQueryInLds;
+    constexpr bool KPRE = Shape::kPrefetchK;
+    constexpr int PP = Shape::kProbParts, QP = Shape::kQueryParts, KS = Row::kQSteps;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1);
     const int wave = tid >> 6;
@@ -466,17 +584,42 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, GqaShape<RT>::kBlocksPerCU) 
     const int hk = bid % hgroups;
     const int b = bid / hgroups;
     const int h0 = hk * gb;
+
+    // Query operand of row tile rt: lane (row c, group r) holds Q[row rt*16 + c][32 s + 8 r .. +7]
+    // (codes: columns 32 s + 4 r .. +3 and 32 s + 16 + 4 r .. +3; rows of 16 values: 4 r .. +3).
+    // The group's rows are the query rows h0 .. h0 + gb - 1 of the sequence; query_row() maps a
+    // group row to where the caller keeps it.  Rows past the group repeat the last one; nothing
+    // reads what they lead to.
+    const bool q_aligned = (reinterpret_cast<uintptr_t>(p.q) & 15) == 0;
+    auto query = [&](int rt) {
+        return static_cast<const bf16 *>(p.q) + query_row(p, b, h0 + min(rt * 16 + c, gb - 1)) * p.D;
+    };
+    constexpr int DS = CODES ? 4 : 1;          // steps of 32 over the head dimension (D <= 128)
+    Operand qop[QLDS ? 1 : RT][KS][QP];
+    uint4 q_raw[CODES ? RT : 1][DS], u_raw[CODES ? W / 16 : 1][DS];
+    if constexpr (CODES) {
+        // what the projection reads is requested ahead of everything: loads come back in order,
+        // and behind a tile's rows it would hold the first scores up (31.7 -> 31.4 us for 128 MiB
+        // of rank-32 codes; the plain query, requested here, costs 0.7 us instead)
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int s = 0; s < DS; ++s) q_raw[rt][s] = load_query<uint4>(query(rt) + min(32 * s + 8 * r, p.D - 8), q_aligned);
+        const bf16 *U = static_cast<const bf16 *>(p.U_K) + ((int64_t)hk * W + c) * p.D;
+#pragma unroll
+        for (int ct = 0; ct < W / 16; ++ct)
+#pragma unroll
+            for (int s = 0; s < DS; ++s) u_raw[ct][s] = load16(U + (int64_t)16 * ct * p.D + min(32 * s + 8 * r, p.D - 8));
+    }
     const ShardRef sh = resolve_shard(p, b, b, j, lane);
     const int n = sh.n;
     const int r0 = split * p.chunk;
     const int r1 = min(n, r0 + p.chunk);
 
-    __shared__ __attribute__((aligned(16))) unsigned char lds_k[kWavesPerBlock][kGqaTile * kGqaKPitch];
-    __shared__ __attribute__((aligned(16))) unsigned char lds_p[kWavesPerBlock][2][16 * kGqaPPitch];
-    __shared__ __attribute__((aligned(16))) float lds_corr[kWavesPerBlock][16];
+    __shared__ __attribute__((aligned(16))) unsigned char lds_k[kWavesPerBlock][TILE * PITCH];
     __shared__ float sm_m[kWavesPerBlock][16];
     __shared__ float sm_l[kWavesPerBlock][16];
-    __shared__ __attribute__((aligned(16))) unsigned char lds_q[QLDS ? RT * 16 * kGqaKPitch : 16];
+    __shared__ __attribute__((aligned(16))) unsigned char lds_q[QLDS ? RT * 16 * PITCH : 16];
     // Raw scores of the block's rows, [rows of the group][chunk], when p.stage_scores (see
     // attn_partial): written to memory in one contiguous burst per row after the streaming loop.
     extern __shared__ __attribute__((aligned(16))) float gqa_stage[];
@@ -496,250 +639,285 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, GqaShape<RT>::kBlocksPerCU) 
         return;
     }
 
-    const int64_t row_bytes = p.stride_s * 2;
     const char *Kb = sh.K + (int64_t)hk * p.stride_h * 2;
     const char *Vb = sh.V + (int64_t)hk * p.stride_h * 2;
-    // lane part of every address: rows 8r.. of the tile, byte chunk c (fits 32 bits)
-    const uint32_t lane_off = (uint32_t)(8 * r) * (uint32_t)row_bytes + 16u * c;
+    // Byte offsets of the lane's rows from the kv head's base, in 32 bits (the host admits this
+    // kernel only where they fit): rows past the end are clamped onto the last valid row - one
+    // minimum per load, no branch around any - and masked out of the softmax.  (Two forms of the
+    // loads, full tiles from a wave-uniform base and clamped ones for the last tile, cost 20
+    // registers more: 124 bytes of spills at one row tile of 128 values.)
+    const uint32_t rb = (uint32_t)(p.stride_s * 2);
+    const int k_row = lane / Row::kKLanes;
+    const uint32_t k_col = 16u * (lane & (Row::kKLanes - 1));
+    const uint32_t v_col = 4u * Row::kVWords * (Row::kPairs ? c & 7 : c);
+    const uint32_t k_lane = (uint32_t)k_row * rb + k_col, v_lane = (uint32_t)(4 * r + (Row::kPairs ? c >> 3 : 0)) * rb + v_col;
+    const uint32_t last = (uint32_t)(r1 - 1) * rb;
 
-    uint4 kr[8], vr[8];
-    auto load_tile = [&](uint4(&dst)[8], const char *base, int t0) {
-        if (t0 + kGqaTile <= r1) {     // full tile: wave-uniform base + constant lane offset
-            const char *bp = base + (int64_t)t0 * row_bytes;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) dst[t] = load16_stream(bp + t * row_bytes + lane_off);
-        } else {                        // ragged tail: clamp onto the last valid row, mask later
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const int row = min(t0 + 8 * r + t, r1 - 1);
-                dst[t] = load16_stream(base + (int64_t)row * row_bytes + 16 * c);
-            }
-        }
+    // (Each tile's offset is hidden from the optimiser: it would otherwise carry one running
+    // address per load through the loop, 16 registers instead of one.)
+    auto opaque = [](uint32_t v) {
+        asm volatile("" : "+v"(v));
+        return v;
     };
-    int t0 = r0 + __builtin_amdgcn_readfirstlane(wave) * kGqaTile;
-    if (t0 < r1) {
-        if constexpr (KPRE) load_tile(kr, Kb, t0);
-        load_tile(vr, Vb, t0);
+    uint4 kr[Row::kKLoads];
+    uint32_t vr[SUBS][Row::kVLoads][Row::kVWords];
+    auto load_k = [&](int t0) {
+        const uint32_t at = opaque((uint32_t)t0 * rb + k_lane);
+#pragma unroll
+        for (int t = 0; t < Row::kKLoads; ++t)
+            kr[t] = load16_stream(Kb + (size_t)min(at + (uint32_t)(t * Row::kKRows) * rb, last + k_col));
+    };
+    auto load_v = [&](int t0) {
+        const uint32_t at = opaque((uint32_t)t0 * rb + v_lane);
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+            for (int t = 0; t < Row::kVLoads; ++t)
+                load_words_stream<Row::kVWords>(
+                    vr[sub][t], Vb + (size_t)min(at + (uint32_t)(sub * kSubTile + Row::v_step(t)) * rb, last + v_col));
+    };
+    if constexpr (!CODES && !QLDS) {         // ahead of the tile's rows: loads come back in order
+        auto load_q = [&](auto aligned) {
+#pragma unroll
+            for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+                for (int s = 0; s < KS; ++s)
+                    qop[rt][s][0] = load_query<Operand>(query(rt) + 32 * s + (W >= 32 ? 8 : 4) * r, aligned);
+        };
+        if (q_aligned) load_q(std::true_type{});
+        else load_q(std::false_type{});
     }
+    int t0 = r0 + __builtin_amdgcn_readfirstlane(wave) * TILE;
+    if constexpr (KPRE) load_k(t0);           // (a wave without rows loads the last one)
+    load_v(t0);
 
-    // query operand of row tile rt: lane (row c, group r) holds Q[row rt*16 + c][32 s + 8 r .. +7],
-    // s = 0..3 (zero for rows past the group).  The group's rows are the query rows
-    // h0 .. h0 + gb - 1 of the sequence; query_row() maps a group row to where the caller keeps it.
-    bf16x8_t qop[QLDS ? 1 : RT][4];
-    if constexpr (QLDS) {
-        for (int idx = tid; idx < RT * 16 * 16; idx += blockDim.x) {     // (row, 16-byte chunk)
-            const int row = idx >> 4, ch = idx & 15;
-            uint4 v = make_uint4(0, 0, 0, 0);
-            if (row < gb) v = load16(static_cast<const bf16 *>(p.q) + query_row(p, b, h0 + row) * W + 8 * ch);
-            *reinterpret_cast<uint4 *>(lds_q + row * kGqaKPitch + 16 * ch) = v;
-        }
-        __syncthreads();
-    } else {
+    if constexpr (CODES) {
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
-            const int row = rt * 16 + c;
-            const bf16 *qrow = static_cast<const bf16 *>(p.q) + query_row(p, b, h0 + min(row, gb - 1)) * W;
+            float proj[W / 4];               // proj[4 ct + x]: code column 16 ct + 4 r + x of row c
 #pragma unroll
-            for (int s = 0; s < 4; ++s) {
-                uint4 v = load16(qrow + 32 * s + 8 * r);
-                if (row >= gb) v = make_uint4(0, 0, 0, 0);
-                qop[rt][s] = __builtin_bit_cast(bf16x8_t, v);
+            for (int ct = 0; ct < W / 16; ++ct) {
+                f32x4_t acc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int s = 0; s < DS; ++s) {
+                    uint4 qv = q_raw[rt][s];
+                    if (32 * s + 8 * r >= p.D) qv = make_uint4(0, 0, 0, 0);
+                    acc = mfma_rows(u_raw[ct][s], qv, acc);
+                }
+#pragma unroll
+                for (int x = 0; x < 4; ++x) proj[4 * ct + x] = acc[x] * p.scale;
             }
+#pragma unroll
+            for (int s = 0; s < KS; ++s) split_bf16(proj + 8 * s, qop[rt][s]);
         }
+    } else if constexpr (QLDS) {
+        for (int idx = tid; idx < RT * 16 * (W / 8); idx += blockDim.x) {     // (row, 16-byte chunk)
+            const int row = idx / (W / 8), ch = idx % (W / 8);
+            *reinterpret_cast<uint4 *>(lds_q + row * PITCH + 16 * ch) = load_query<uint4>(
+                static_cast<const bf16 *>(p.q) + query_row(p, b, h0 + min(row, gb - 1)) * W + 8 * ch, q_aligned);
+        }
+        __syncthreads();
     }
+    // Every operand the loop keeps is complete here: a wait for it inside the loop would be a wait
+    // for the tile loads requested after it.
+    if constexpr (!QLDS) {
+#pragma unroll
+        for (int rt = 0; rt < RT; ++rt)
+#pragma unroll
+            for (int s = 0; s < KS; ++s)
+#pragma unroll
+                for (int k = 0; k < QP; ++k) hold_operand(qop[rt][s][k]);
+    }
+    // the same slice of a staged K row
+    auto k_operand = [&](const unsigned char *row, int s) {
+        Operand a;
+        if constexpr (W == 16) {
+            a = *reinterpret_cast<const uint2 *>(row + 8 * r);
+        } else if constexpr (CODES) {
+            const uint2 lo = *reinterpret_cast<const uint2 *>(row + 64 * s + 8 * r);
+            const uint2 hi = *reinterpret_cast<const uint2 *>(row + 64 * s + 32 + 8 * r);
+            a = make_uint4(lo.x, lo.y, hi.x, hi.y);
+        } else {
+            a = *reinterpret_cast<const uint4 *>(row + 64 * s + 16 * r);
+        }
+        return a;
+    };
 
     float m[RT], lsum[RT];                  // running max / partial sum of row rt*16 + c
-    f32x4_t oacc[RT][8];                    // oacc[rt][i][x] = O[row rt*16 + 4r + x][d = 8c + i]
+    f32x4_t oacc[RT][SETS];                 // oacc[rt][i][x] = O[row rt*16 + c][out_col(x, i)]
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         m[rt] = -INFINITY;
         lsum[rt] = 0.0f;
 #pragma unroll
-        for (int i = 0; i < 8; ++i) oacc[rt][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+        for (int i = 0; i < SETS; ++i) oacc[rt][i] = f32x4_t{0.f, 0.f, 0.f, 0.f};
     }
 
-    unsigned char *kst = lds_k[wave];
-    unsigned char *pst_hi = lds_p[wave][0];
-    unsigned char *pst_lo = lds_p[wave][1];
+    auto out_col = [&](int x, int i) {
+        const int mm = 4 * r + x;
+        return Row::kPairs ? 2 * (mm & 7) + (mm >> 3) : SETS * mm + i;
+    };
+    const uint32_t pair_sel = c < 8 ? 0x05040100u : 0x03020706u;   // W = 16: low halves, or high halves
 
-    for (; t0 < r1; t0 += kWavesPerBlock * kGqaTile) {
-        const int tnext = t0 + kWavesPerBlock * kGqaTile;
+    unsigned char *kst = lds_k[wave];
+    // The order of a wave's requests is the same on every path - K of the next tile, V of the next
+    // tile, K ... - and no request sits under a condition inside the loop: the wait for a tile's K
+    // is then a wait for those loads alone, with its V still in flight.  (With the two prefetches
+    // under `if (tnext < r1)` the compiler had to allow for K without V and waited for both.)
+    if (t0 < r1) do {
+        const int tnext = t0 + kWavesPerBlock * TILE;
 
         // K rows -> LDS (row-major, padded), then the next tile's K loads reuse the registers
         if constexpr (!KPRE) {
-            // K where it is used: the clamped form for every tile (one code path, no branch
-            // between the loads and their use), with 32-bit byte offsets from the kv head's base
-            // (the host admits this kernel only for less than 4 GiB per kv head of a shard)
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const unsigned row = (unsigned)min(t0 + 8 * r + t, r1 - 1);
-                kr[t] = load16_stream(Kb + (size_t)(row * (unsigned)row_bytes + 16u * (unsigned)c));
-            }
+            load_k(t0);                      // K where it is used
         }
 #pragma unroll
-        for (int t = 0; t < 8; ++t)
-            *reinterpret_cast<uint4 *>(kst + (8 * r + t) * kGqaKPitch + 16 * c) = kr[t];
-        if constexpr (KPRE) {
-            if (tnext < r1) load_tile(kr, Kb, tnext);
-        }
+        for (int t = 0; t < Row::kKLoads; ++t)
+            *reinterpret_cast<uint4 *>(kst + (t * Row::kKRows + k_row) * PITCH + k_col) = kr[t];
+        if constexpr (KPRE) load_k(tnext);   // past the end: the clamped last row once more
         wave_lds_order();
 
 #pragma unroll
         for (int rt = 0; rt < RT; ++rt) {
             if (rt * 16 >= gb) break;        // row tiles past the group (wave-uniform)
-            // S^T = K Q^T for the two 16-entry halves of the tile
-            f32x4_t sc[2];
+            // S^T = K Q^T, 16 entries at a time; sv[8 sub + 4 hb + x] is the score of entry
+            // t0 + 32 sub + 16 hb + 4 r + x
+            float sv[8 * SUBS];
 #pragma unroll
-            for (int hb = 0; hb < 2; ++hb) {
-                sc[hb] = f32x4_t{0.f, 0.f, 0.f, 0.f};
+            for (int hb = 0; hb < 2 * SUBS; ++hb) {
+                f32x4_t sc = f32x4_t{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
-                for (int s = 0; s < 4; ++s) {
-                    const uint4 a = *reinterpret_cast<const uint4 *>(kst + (16 * hb + c) * kGqaKPitch + 64 * s + 16 * r);
-                    bf16x8_t qv;
-                    if constexpr (QLDS)
-                        qv = __builtin_bit_cast(bf16x8_t, *reinterpret_cast<const uint4 *>(
-                                                              lds_q + (rt * 16 + c) * kGqaKPitch + 64 * s + 16 * r));
-                    else
-                        qv = qop[rt][s];
-                    sc[hb] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), qv, sc[hb],
-                                                                    0, 0, 0);
+                for (int s = 0; s < KS; ++s) {
+                    const Operand a = k_operand(kst + (16 * hb + c) * PITCH, s);
+                    if constexpr (QLDS) {
+                        sc = mfma_rows(a, *reinterpret_cast<const uint4 *>(lds_q + (rt * 16 + c) * PITCH + 64 * s + 16 * r),
+                                       sc);
+                    } else {
+#pragma unroll
+                        for (int k = QP - 1; k >= 0; --k) sc = mfma_rows(a, qop[rt][s][k], sc);
+                    }
                 }
-            }
-            // lane (row c, group r): sc[hb][x] is the score of entry t0 + 16 hb + 4 r + x
-            const int row_g = rt * 16 + c;   // row of the group this lane's scores belong to
-            float sv[8];
-#pragma unroll
-            for (int hb = 0; hb < 2; ++hb)
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
                     const int row = t0 + 16 * hb + 4 * r + x;
-                    sv[hb * 4 + x] = row < r1 ? sc[hb][x] * p.scale : -INFINITY;
+                    const float score = CODES ? sc[x] : sc[x] * p.scale;
+                    sv[4 * hb + x] = row < r1 ? score : -INFINITY;
                 }
+            }
+            const int row_g = rt * 16 + c;   // row of the group this lane's scores belong to
             if (SC == kScoresStaged && row_g < gb) {
                 // [row of the group][row of the block]: chunk is a multiple of the tile, so the
                 // float4 stores stay aligned
                 float *dst = gqa_stage + row_g * p.chunk + (t0 - r0) + 4 * r;
 #pragma unroll
-                for (int hb = 0; hb < 2; ++hb)
+                for (int hb = 0; hb < 2 * SUBS; ++hb)
                     *reinterpret_cast<float4 *>(dst + 16 * hb) =
                         make_float4(sv[hb * 4], sv[hb * 4 + 1], sv[hb * 4 + 2], sv[hb * 4 + 3]);
-            } else if (SC == kScoresDirect && row_g < gb) {
-                float *dst = p.scores + (((int64_t)b * p.Hq + h0 + row_g) * p.k + j) * p.S + t0 + 4 * r;
+            } else if (SC == kScoresDirect) {
+                // Whole 128-byte lines: lanes c and c + 8 swap halves, so that one store covers
+                // 32 entries of 8 rows instead of 16 entries of 16.
+                const bool upper = c >= 8;
 #pragma unroll
-                for (int hb = 0; hb < 2; ++hb) {
-                    const int row = t0 + 16 * hb + 4 * r;
-                    if (row + 4 <= r1 && (p.S & 3) == 0) {
-                        *reinterpret_cast<float4 *>(dst + 16 * hb) =
-                            make_float4(sv[hb * 4], sv[hb * 4 + 1], sv[hb * 4 + 2], sv[hb * 4 + 3]);
-                    } else {
+                for (int sub = 0; sub < SUBS; ++sub) {
+                    float va[4], vb[4];
 #pragma unroll
-                        for (int x = 0; x < 4; ++x)
-                            if (row + x < r1) dst[16 * hb + x] = sv[hb * 4 + x];
+                    for (int x = 0; x < 4; ++x) {
+                        const float lo = sv[8 * sub + x], hi = sv[8 * sub + 4 + x];
+                        const float got = __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(upper ? lo : hi), 0x128, 0xf, 0xf, true));
+                        va[x] = upper ? got : lo;
+                        vb[x] = upper ? hi : got;
+                    }
+                    const int first = 32 * sub + (upper ? 16 : 0) + 4 * r;
+                    const int row = t0 + first;
+                    float *dst = p.scores + (((int64_t)b * p.Hq + h0 + rt * 16 + (c & 7)) * p.k + j) * p.S + row;
+#pragma unroll
+                    for (int half = 0; half < 2; ++half) {
+                        const float *v = half ? vb : va;
+                        float *to = dst + (int64_t)half * 8 * p.k * p.S;
+                        if (rt * 16 + half * 8 + (c & 7) < gb) {
+                            if (row + 4 <= r1 && (p.S & 3) == 0) {
+                                *reinterpret_cast<float4 *>(to) = make_float4(v[0], v[1], v[2], v[3]);
+                            } else {
+#pragma unroll
+                                for (int x = 0; x < 4; ++x)
+                                    if (row + x < r1) to[x] = v[x];
+                            }
+                        }
                     }
                 }
             }
 
-            // online softmax for row c of this tile (entries are spread over the 4 lane groups)
+            // online softmax for row c of this tile (its entries are spread over the 4 lane groups)
             float tm = sv[0];
 #pragma unroll
-            for (int x = 1; x < 8; ++x) tm = fmaxf(tm, sv[x]);
-            tm = fmaxf(tm, __shfl_xor(tm, 16, kWave));
-            tm = fmaxf(tm, __shfl_xor(tm, 32, kWave));
-            const float mn = fmaxf(m[rt], tm);
-            const float corr = __expf(m[rt] - mn);
-            m[rt] = mn;
-            lsum[rt] *= corr;
-            float pv[8];
+            for (int x = 1; x < 8 * SUBS; ++x) tm = fmaxf(tm, sv[x]);
+            const float mn = fmaxf(m[rt], group_max(tm));
+            if (__any(mn > m[rt])) {         // else the factor is 1 in every lane
+                const float corr = __expf(m[rt] - mn);
+                m[rt] = mn;
+                lsum[rt] *= corr;
 #pragma unroll
-            for (int x = 0; x < 8; ++x) {
-                pv[x] = __expf(sv[x] - mn);
-                lsum[rt] += pv[x];
+                for (int i = 0; i < SETS; ++i)
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) oacc[rt][i][x] *= corr;
             }
-            // probabilities as bf16 high part + bf16 residual, 4 consecutive entries per store
 #pragma unroll
-            for (int hb = 0; hb < 2; ++hb) {
-                uint32_t hi2[2], lo2[2];
+            for (int x = 0; x < 8 * SUBS; ++x) {
+                sv[x] = __expf(sv[x] - mn);
+                lsum[rt] += sv[x];
+            }
+            // O^T += V^T P^T, output set i takes the i-th value of each of the lane's 8 V rows
 #pragma unroll
-                for (int q2 = 0; q2 < 2; ++q2) {
-                    const f32x2_t v = {pv[hb * 4 + 2 * q2], pv[hb * 4 + 2 * q2 + 1]};
-                    const bf16x2_t hi = __builtin_convertvector(v, bf16x2_t);
-                    const f32x2_t back = {(float)hi[0], (float)hi[1]};
-                    const bf16x2_t lo = __builtin_convertvector(v - back, bf16x2_t);
-                    hi2[q2] = __builtin_bit_cast(uint32_t, hi);
-                    lo2[q2] = __builtin_bit_cast(uint32_t, lo);
+            for (int sub = 0; sub < SUBS; ++sub) {
+                uint4 pop[PP];
+                split_bf16(sv + 8 * sub, pop);
+                const auto &v = vr[sub];
+#pragma unroll
+                for (int i = 0; i < SETS; ++i) {
+                    uint4 vop;
+                    if constexpr (Row::kPairs) {
+                        auto both = [&](uint32_t mine) {
+                            const uint32_t other = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)mine, 0x128, 0xf, 0xf, true);
+                            return __builtin_amdgcn_perm(other, mine, pair_sel);
+                        };
+                        vop = make_uint4(both(v[0][0]), both(v[1][0]), both(v[2][0]), both(v[3][0]));
+                    } else {
+                        const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
+                        vop = make_uint4(__builtin_amdgcn_perm(v[1][i >> 1], v[0][i >> 1], sel),
+                                         __builtin_amdgcn_perm(v[3][i >> 1], v[2][i >> 1], sel),
+                                         __builtin_amdgcn_perm(v[5][i >> 1], v[4][i >> 1], sel),
+                                         __builtin_amdgcn_perm(v[7][i >> 1], v[6][i >> 1], sel));
+                    }
+#pragma unroll
+                    for (int k = PP - 1; k >= 0; --k) oacc[rt][i] = mfma_rows(vop, pop[k], oacc[rt][i]);
                 }
-                const int off = c * kGqaPPitch + (16 * hb + 4 * r) * 2;
-                *reinterpret_cast<uint2 *>(pst_hi + off) = make_uint2(hi2[0], hi2[1]);
-                *reinterpret_cast<uint2 *>(pst_lo + off) = make_uint2(lo2[0], lo2[1]);
-            }
-            if (r == 0) lds_corr[wave][c] = corr;
-            wave_lds_order();
-
-            // row operands P[row c][entries 8r..8r+7] and the rescale factors of rows 4r..4r+3
-            const bf16x8_t p_hi = __builtin_bit_cast(
-                bf16x8_t, *reinterpret_cast<const uint4 *>(pst_hi + c * kGqaPPitch + 16 * r));
-            const bf16x8_t p_lo = __builtin_bit_cast(
-                bf16x8_t, *reinterpret_cast<const uint4 *>(pst_lo + c * kGqaPPitch + 16 * r));
-            const float4 cr = *reinterpret_cast<const float4 *>(&lds_corr[wave][4 * r]);
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                oacc[rt][i][0] *= cr.x;
-                oacc[rt][i][1] *= cr.y;
-                oacc[rt][i][2] *= cr.z;
-                oacc[rt][i][3] *= cr.w;
-            }
-            // O += P V, output column set i takes the i-th value of each of the lane's 8 V rows
-#pragma unroll
-            for (int i = 0; i < 8; ++i) {
-                const uint32_t sel = (i & 1) ? 0x07060302u : 0x05040100u;
-                uint32_t w[8];
-#pragma unroll
-                for (int t = 0; t < 8; ++t) {
-                    const uint4 &v = vr[t];
-                    w[t] = (i >> 1) == 0 ? v.x : (i >> 1) == 1 ? v.y : (i >> 1) == 2 ? v.z : v.w;
-                }
-                const uint4 packed = make_uint4(__builtin_amdgcn_perm(w[1], w[0], sel),
-                                                __builtin_amdgcn_perm(w[3], w[2], sel),
-                                                __builtin_amdgcn_perm(w[5], w[4], sel),
-                                                __builtin_amdgcn_perm(w[7], w[6], sel));
-                const bf16x8_t vop = __builtin_bit_cast(bf16x8_t, packed);
-                oacc[rt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p_hi, vop, oacc[rt][i], 0, 0, 0);
-                oacc[rt][i] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(p_lo, vop, oacc[rt][i], 0, 0, 0);
-            }
-            wave_lds_order();                // the P tiles are rewritten by the next row tile
-        }
-        if constexpr (KPRE) {
-            if (tnext < r1) load_tile(vr, Vb, tnext);
-        } else {
-            // the next tile's V rows, requested on the loop's own path (its exit test comes first)
-            // rather than under a condition inside it
-            if (tnext >= r1) break;
-#pragma unroll
-            for (int t = 0; t < 8; ++t) {
-                const unsigned row = (unsigned)min(tnext + 8 * r + t, r1 - 1);
-                vr[t] = load16_stream(Vb + (size_t)(row * (unsigned)row_bytes + 16u * (unsigned)c));
             }
         }
-    }
+        wave_lds_order();                    // the K tile is rewritten by the next iteration
+        load_v(tnext);
+        t0 = tnext;
+    } while (t0 < r1);
 
     __syncthreads();
     if (SC == kScoresStaged) {   // the block's scores: one burst per row of the group
         const int rows = r1 - r0, rows4 = rows & ~3;
-        for (int g = 0; g < gb; ++g) {
+        for (int g = wave; g < gb; g += kWavesPerBlock) {      // a row per wave
             float *dst = p.scores + (((int64_t)b * p.Hq + h0 + g) * p.k + j) * p.S + r0;
             const float *src = gqa_stage + g * p.chunk;
             if ((p.S & 3) == 0 && (reinterpret_cast<uintptr_t>(p.scores) & 15) == 0) {
-                for (int i = tid * 4; i < rows4; i += blockDim.x * 4)
+                for (int i = lane * 4; i < rows4; i += kWave * 4)
                     *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(src + i);
-                if (tid < rows - rows4) dst[rows4 + tid] = src[rows4 + tid];
+                if (lane < rows - rows4) dst[rows4 + lane] = src[rows4 + lane];
             } else {
-                for (int i = tid; i < rows; i += blockDim.x) dst[i] = src[i];
+                for (int i = lane; i < rows; i += kWave) dst[i] = src[i];
             }
         }
     }
 
     // per row tile: wave results -> LDS (the wave's own K staging area is free now), then merge
-    // the waves and write the block's partial
+    // the waves and write the block's partial.  Rows are padded by 4 floats (banks).
+    constexpr int AP = W + 4;
+    static_assert(16 * AP * 4 <= TILE * PITCH, "the wave's results fit its K staging area");
 #pragma unroll
     for (int rt = 0; rt < RT; ++rt) {
         if (rt * 16 >= gb) break;
@@ -747,16 +925,12 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, GqaShape<RT>::kBlocksPerCU) 
         float ls = lsum[rt];
         ls += __shfl_xor(ls, 16, kWave);
         ls += __shfl_xor(ls, 32, kWave);
-        float *wacc = reinterpret_cast<float *>(kst);          // [16][128] floats = 8 KiB
+        float *wacc = reinterpret_cast<float *>(kst) + c * AP;
+        if (c < rows_here) {
 #pragma unroll
-        for (int x = 0; x < 4; ++x) {
-            const int head = 4 * r + x;
-            if (head < rows_here) {
-                *reinterpret_cast<float4 *>(wacc + head * W + 8 * c) =
-                    make_float4(oacc[rt][0][x], oacc[rt][1][x], oacc[rt][2][x], oacc[rt][3][x]);
-                *reinterpret_cast<float4 *>(wacc + head * W + 8 * c + 4) =
-                    make_float4(oacc[rt][4][x], oacc[rt][5][x], oacc[rt][6][x], oacc[rt][7][x]);
-            }
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int i = 0; i < SETS; ++i) wacc[out_col(x, i)] = oacc[rt][i][x];
         }
         if (r == 0) {
             sm_m[wave][c] = m[rt];
@@ -772,7 +946,7 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, GqaShape<RT>::kBlocksPerCU) 
 #pragma unroll
             for (int w2 = 0; w2 < kWavesPerBlock; ++w2) {
                 const float f = sm_m[w2][g] == -INFINITY ? 0.0f : __expf(sm_m[w2][g] - M);
-                a = fmaf(reinterpret_cast<const float *>(lds_k[w2])[g * W + d], f, a);
+                a = fmaf(reinterpret_cast<const float *>(lds_k[w2])[g * AP + d], f, a);
                 L = fmaf(sm_l[w2][g], f, L);
             }
             const int64_t at = part_base + (rt * 16 + g) * part_head_stride;
@@ -806,6 +980,23 @@ int launch_partial_w(int gb, const AttnParams &p, int blocks, hipStream_t st) {
     return launch_status();
 }
 
+template <int W, bool CODES>
+void launch_gqa(int row_tiles, const AttnParams &p, int64_t blocks, size_t lds, hipStream_t st) {
+    const dim3 grid((unsigned)blocks), block(kWavesPerBlock * kWave);
+    auto launch = [&](auto rt) {
+        constexpr int RT = decltype(rt)::value;
+        if (p.scores == nullptr)
+            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresNone, CODES>), grid, block, lds, st, p);
+        else if (p.stage_scores)
+            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresStaged, CODES>), grid, block, lds, st, p);
+        else
+            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresDirect, CODES>), grid, block, lds, st, p);
+    };
+    if (row_tiles == 1) launch(std::integral_constant<int, 1>{});
+    else if (row_tiles == 2) launch(std::integral_constant<int, 2>{});
+    else launch(std::integral_constant<int, 4>{});
+}
+
 template <typename T>
 int launch_partial(int width, int gb, const AttnParams &p, int blocks, hipStream_t st) {
     switch (width) {
@@ -831,24 +1022,28 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan) {
     const int G = d->Hq / d->Hkv;
     int gb = 1;
     if (d->route_rows_per_seq == 1 && (G == 2 || G == 4 || G == 8)) gb = G;
-    const bool gqa_mfma = d->route_rows_per_seq == 1 && d->dtype == PIKV_BF16 && d->rank == 0 &&
-                          d->D == 128 && G >= 2 && G <= 64 &&
-                          (int64_t)d->S * d->stride_s * 2 < ((int64_t)1 << 32);
+    // The matrix-core kernel takes every group of bf16 rows that shares one routing decision and
+    // addresses a kv head's rows in 32 bits.
+    const bool gqa_mfma = d->route_rows_per_seq == 1 && d->dtype == PIKV_BF16 && G >= 2 && G <= 64 &&
+                          ((int64_t)d->S + kClampRows) * d->stride_s * 2 < ((int64_t)1 << 32);
     if (gqa_mfma) gb = G;
     const int tq = d->tq > 1 ? d->tq : 1;
-    // draft queries are folded into the query group of the matrix-core kernel only
-    if (tq > 1 && (!gqa_mfma || d->Hq % tq != 0 || G % tq != 0)) return PIKV_ERR_UNSUPPORTED;
+    // draft queries are folded into the query group of the matrix-core kernel's 128-value rows only
+    if (tq > 1 && (!gqa_mfma || W != 128 || d->Hq % tq != 0 || G % tq != 0)) return PIKV_ERR_UNSUPPORTED;
     const int row_tiles = !gqa_mfma ? 0 : (G <= 16 ? 1 : (G <= 32 ? 2 : 4));
     const int epl = 16 / elem_bytes(d->dtype);
     const int lpr = W / epl;
     if (lpr < 1 || lpr > 32) return PIKV_ERR_UNSUPPORTED;
     const int row_bytes = W * elem_bytes(d->dtype);
-    const int tile = gqa_mfma ? kGqaTile : (kWave / lpr) * plain_loads_per_tile(row_bytes, gb);
+    const int tile = gqa_mfma ? gqa_tile(W, row_tiles) : (kWave / lpr) * plain_loads_per_tile(row_bytes, gb);
     const int64_t units = (int64_t)d->B * (d->Hq / gb) * k;
     // One round of resident blocks: 256 CUs times the 4-wave blocks a CU holds at this
     // kernel's register footprint.  Fewer, longer blocks keep the per-wave prefetch chain
     // busy and shrink the partials that the combine pass has to merge.
-    int resident = gqa_mfma ? (row_tiles == 1 ? 3 : 2) : plain_blocks_per_cu(row_bytes, gb);
+    int resident = gqa_mfma ? gqa_blocks_per_cu(W, row_tiles, d->rank > 0) : plain_blocks_per_cu(row_bytes, gb);
+    // More than 8 rows per kv head: every split writes and re-reads rows * 128 accumulators, and
+    // two rounds' worth of longer blocks beat three (16 rows, 128 MiB: 36.0 against 40.0 us).
+    if (gqa_mfma && W == 128 && gb > 8 && resident > 2) resident = 2;
     int64_t nsplit = 1;
     int chunk = 0;
     auto split_for = [&](int res) {
@@ -886,19 +1081,19 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan) {
     };
     split_for(resident);
     size_t stage = (size_t)gb * chunk * sizeof(float);      // the block's raw scores, staged in LDS
-    if (gqa_mfma && gb < 8) {
-        // few rows per kv head: the score writes are ~3 % of the bytes and staging them measures
-        // no faster (its LDS stores collide with the tile staging)
+    if (gqa_mfma && W == 128 && gb <= 8) {
+        // few rows per kv head of long entries: writing whole lines from the loop measures faster
+        // than staging them (8 rows, 128 MiB: 31.8 against 32.8 us with the merge, 4 rows even;
+        // 16 rows 37.1 against 36.7, and rank-32 codes at 4 rows 39.5 against 38.0)
         stage = 0;
     } else if (gqa_mfma) {
-        // The matrix-core kernel's tile staging takes kGqaStaticLds per block (plus the query
-        // tile at four row tiles): the score stage must fit beside it as often as a CU holds
+        // The score stage must fit beside the matrix-core kernel's own LDS as often as a CU holds
         // blocks - three times with one row tile, or twice with longer blocks - or is left out.
         const size_t lds_cu = 160 * 1024;
-        const size_t fixed = kGqaStaticLds + (row_tiles == 4 ? (size_t)64 * kGqaKPitch : 0);
+        const size_t fixed = gqa_static_lds(W, tile, row_tiles);
         if ((size_t)resident * (fixed + stage) > lds_cu || stage > 64 * 1024 - 256) {
             bool fits = false;
-            if (resident == 3) {
+            if (resident > 2) {
                 split_for(2);
                 stage = (size_t)gb * chunk * sizeof(float);
                 fits = 2 * (fixed + stage) <= lds_cu && stage <= 64 * 1024 - 256;
@@ -1031,21 +1226,12 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
     if (g_prof_start) (void)hipEventRecord(g_prof_start, st);
     if (plan.gqa_mfma) {
         const size_t lds = p.stage_scores ? plan.score_stage_bytes : 0;
-        const dim3 grid((unsigned)blocks64), block(kWavesPerBlock * kWave);
-        switch (plan.row_tiles) {
-#define PIKV_LAUNCH_GQA(RT)                                                                                 \
-    do {                                                                                                    \
-        if (p.scores == nullptr)                                                                            \
-            hipLaunchKernelGGL((attn_partial_gqa128<RT, kScoresNone>), grid, block, lds, st, p);            \
-        else if (p.stage_scores)                                                                            \
-            hipLaunchKernelGGL((attn_partial_gqa128<RT, kScoresStaged>), grid, block, lds, st, p);          \
-        else                                                                                                \
-            hipLaunchKernelGGL((attn_partial_gqa128<RT, kScoresDirect>), grid, block, lds, st, p);          \
-    } while (0)
-            case 1: PIKV_LAUNCH_GQA(1); break;
-            case 2: PIKV_LAUNCH_GQA(2); break;
-            default: PIKV_LAUNCH_GQA(4); break;
-#undef PIKV_LAUNCH_GQA
+        const bool codes = desc->rank > 0;
+        switch (W) {
+            case 16: codes ? launch_gqa<16, true>(plan.row_tiles, p, blocks64, lds, st) : launch_gqa<16, false>(plan.row_tiles, p, blocks64, lds, st); break;
+            case 32: codes ? launch_gqa<32, true>(plan.row_tiles, p, blocks64, lds, st) : launch_gqa<32, false>(plan.row_tiles, p, blocks64, lds, st); break;
+            case 64: codes ? launch_gqa<64, true>(plan.row_tiles, p, blocks64, lds, st) : launch_gqa<64, false>(plan.row_tiles, p, blocks64, lds, st); break;
+            default: launch_gqa<128, false>(plan.row_tiles, p, blocks64, lds, st); break;
         }
         lrc = launch_status();
     } else {

@@ -137,6 +137,18 @@ __device__ __forceinline__ uint4 load16_stream(const void *p) {
     const u32x4_t v = __builtin_nontemporal_load((global_u32x4_ptr)(uintptr_t)p);
     return make_uint4(v.x, v.y, v.z, v.w);
 }
+// The same for a row slice of WORDS (1, 2 or 4) 32-bit words per lane.
+template <int WORDS>
+__device__ __forceinline__ void load_words_stream(uint32_t (&dst)[WORDS], const void *p) {
+    if constexpr (WORDS == 1) {
+        dst[0] = __builtin_nontemporal_load((const uint32_t __attribute__((address_space(1))) *)(uintptr_t)p);
+    } else {
+        typedef uint32_t words_t __attribute__((ext_vector_type(WORDS)));
+        const words_t v = __builtin_nontemporal_load((const words_t __attribute__((address_space(1))) *)(uintptr_t)p);
+#pragma unroll
+        for (int i = 0; i < WORDS; ++i) dst[i] = v[i];
+    }
+}
 // 16-byte store of data nobody reads back soon (written once, consumed by a later kernel):
 // the non-temporal hint sends it on its way instead of parking a dirty line in L2.
 typedef u32x4_t __attribute__((address_space(1))) *global_u32x4_wptr;
@@ -172,7 +184,7 @@ inline int elem_bytes(int dtype) { return dtype == PIKV_F32 ? 4 : 2; }
 
 // Split geometry of the attention pass (also defines the workspace size).
 struct AttnPlan {
-    bool gqa_mfma;        // matrix-core grouped-query kernel (bf16, D = 128, 2..64 query rows per kv head)
+    bool gqa_mfma;        // matrix-core grouped-query kernel (bf16, 2..64 query rows per kv head)
     int heads_per_block;  // query heads sharing one K/V stream
     int row_tiles;        // matrix-core kernel: 16-row tiles the query group occupies (1, 2 or 4)
     int head_blocks;      // Hq / heads_per_block
