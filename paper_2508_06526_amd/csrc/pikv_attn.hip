@@ -45,7 +45,8 @@ struct AttnParams {
     float *scores;
     int B, Hq, G, D, E, S, k, rr, rank;
     int64_t stride_h, stride_s;
-    int nsplit, chunk;
+    int nsplit, chunk;  // splits per shard, and the most rows one of them takes
+    uint32_t nsplit_rcp;   // 2^32 / nsplit, rounded up (0: nsplit == 1)
     int tq;             // draft queries per sequence: q is [B, tq, Hq / tq, D] (1: plain [B, Hq, D])
     int stage_scores;   // keep the block's scores in LDS, write them in one burst at the end
     int stream_scores;  // ... with non-temporal stores
@@ -79,6 +80,25 @@ __device__ __forceinline__ ShardRef resolve_shard(const AttnParams &p, int b, in
     out.K = reinterpret_cast<const char *>(((uint64_t)khi << 32) | klo);
     out.V = reinterpret_cast<const char *>(((uint64_t)vhi << 32) | vlo);
     return out;
+}
+
+// Rows [r0, r1) of split `split` of a shard that holds n entries.  The split count is planned for
+// full shards; the rows are cut by what the shard holds, so that a young cache - a few hundred
+// entries in shards of thousands - still spreads over the splits instead of leaving all but the
+// first of them empty.  A split takes whole rounds of tiles, one per wave: with uneven waves it
+// runs as long as one of more rows (32 splits of 136 rows in blocks of 160: 23.0 us, of 256: 21.6).  (4 sequences, 8 kv heads, 4 of
+// 16 shards of 8192 slots, 100 - 1000 entries each: pass 17.7 -> YOUNG us.)
+template <int TILE>
+__device__ __forceinline__ void split_rows(const AttnParams &p, int n, int split, int *r0, int *r1) {
+    const int m = min(n, p.S);
+    int per = p.chunk;
+    if (p.nsplit_rcp != 0) {
+        constexpr int ROUND = kWavesPerBlock * TILE;
+        per = (int)__umulhi((uint32_t)(m + p.nsplit - 1), p.nsplit_rcp);
+        per = min((max(per, 1) + ROUND - 1) / ROUND * ROUND, p.chunk);   // chunk: nsplit * chunk >= S
+    }
+    *r0 = split * per;
+    *r1 = min(m, *r0 + per);
 }
 
 // Where the caller keeps the query of internal row h of sequence b, in rows of D values.
@@ -129,9 +149,8 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, plain_blocks_per_cu(W * (int
     const int hk = h0 / p.G;
     const int route_row = b * p.rr + (p.rr == 1 ? 0 : h0);
     const ShardRef sh = resolve_shard(p, b, route_row, j, lane);
-    const int n = sh.n;
-    const int r0 = split * p.chunk;
-    const int r1 = min(n, r0 + p.chunk);
+    int r0, r1;
+    split_rows<TILE>(p, sh.n, split, &r0, &r1);
 
     __shared__ float q_s[GB][W];
     __shared__ float sm_acc[kWavesPerBlock][GB][W];
@@ -612,9 +631,8 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
             for (int s = 0; s < DS; ++s) u_raw[ct][s] = load16(U + (int64_t)16 * ct * p.D + min(32 * s + 8 * r, p.D - 8));
     }
     const ShardRef sh = resolve_shard(p, b, b, j, lane);
-    const int n = sh.n;
-    const int r0 = split * p.chunk;
-    const int r1 = min(n, r0 + p.chunk);
+    int r0, r1;
+    split_rows<TILE>(p, sh.n, split, &r0, &r1);
 
     __shared__ __attribute__((aligned(16))) unsigned char lds_k[kWavesPerBlock][TILE * PITCH];
     __shared__ float sm_m[kWavesPerBlock][16];
@@ -1216,6 +1234,7 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
     p.stride_s = desc->stride_s;
     p.nsplit = plan.nsplit;
     p.chunk = plan.chunk;
+    p.nsplit_rcp = plan.nsplit > 1 ? (uint32_t)(((uint64_t)1 << 32) / plan.nsplit + 1) : 0u;
     p.stage_scores = scores != nullptr && plan.score_stage_bytes > 0;
     p.scale = scale > 0.0f ? scale : 1.0f / sqrtf((float)desc->D);
 

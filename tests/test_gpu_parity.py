@@ -323,7 +323,6 @@ GROUPED_ROWS = [
 ]
 
 
-@pytest.mark.gpu
 @pytest.mark.parametrize("spec", GROUPED_ROWS, ids=lambda s: "D%d_r%d_G%d_S%d" % (s["D"], s.get("rank", 0), s["Hq"] // s["Hkv"], s["S"]))
 @pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "q_off_by_one"])
 def test_grouped_rows_of_every_width_match_oracle(spec, offset):
@@ -349,6 +348,39 @@ def test_grouped_rows_of_every_width_match_oracle(spec, offset):
     with_scores = y
     dc.attend(topk=d_idx, gates=d_gates, want_scores=False)     # the kernel without score output: the same bits
     np.testing.assert_array_equal(t2n(dc.y), with_scores)
+
+
+@pytest.mark.parametrize("spec", [
+    dict(B=1, Hq=8, Hkv=2, D=128, E=12, S=2304, k=12, dtype="bf16"),       # matrix cores, 128 rows a round
+    dict(B=1, Hq=6, Hkv=2, D=64, E=12, S=2051, k=12, dtype="bf16", rank=32),
+    dict(B=1, Hq=2, Hkv=2, D=128, E=12, S=2304, k=12, dtype="bf16"),       # plain ALU
+    dict(B=1, Hq=4, Hkv=2, D=64, E=12, S=1030, k=12, dtype="f32"),
+], ids=lambda s: "G%d_%s_r%d" % (s["Hq"] // s["Hkv"], s["dtype"], s.get("rank", 0)))
+@pytest.mark.parametrize("forced", [0, 5, 64])
+def test_splits_follow_the_entry_count(spec, forced):
+    """Shards that hold from nothing to their capacity, at the edges of a round of tiles and of a split:
+    every split takes its share of the entries that are there, and the merge sees each of them once."""
+    g = wl.Geometry(**spec)
+    nv = np.array([[0, 1, 63, 64, 127, 128, 129, 255, 257, g.S // 2 + 1, g.S - 1, g.S]], np.int32)
+    case = wl.make_host_case(g, seed=3, n_valid=nv, utility0="exp")
+    idx, gates = random_selection(g, 4)
+    u_ref = case.utility.copy()
+    ref = oracle_step(case, idx, gates, orc.COMBINE_LSE, utility=u_ref, decay=0.5)
+    pk.pikv_set_attn_split(forced)
+    try:
+        dc = DeviceCase(case)
+        d_idx, d_gates = torch.from_numpy(idx).to(DEV), torch.from_numpy(gates).to(DEV)
+        dc.attend(topk=d_idx, gates=d_gates)
+        dc.update_utility(0.5, topk=d_idx)
+        y = t2n(dc.y)
+    finally:
+        pk.pikv_set_attn_split(0)
+    assert np.linalg.norm(y - ref["y"]) <= 8e-6 * np.linalg.norm(ref["y"])
+    assert_utility_close(t2n(dc.utility), u_ref)
+    sc = t2n(dc.scores)
+    for j in range(g.k):         # a score row is written up to the shard's count and not past it
+        n = nv[0, idx[0, j]]
+        assert np.isfinite(sc[0, :, j, :n]).all() and np.isnan(sc[0, :, j, n:]).all()
 
 
 def test_attention_is_bitwise_repeatable():
