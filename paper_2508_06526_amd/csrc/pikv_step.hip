@@ -422,6 +422,10 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     for (int a = 0; a < kAhead; ++a) held[a] = load_pass(a);
     fetch(i, p.S, true);
 
+    const int e = __builtin_amdgcn_readlane(sel_of_lane, j);
+    const int n = __builtin_amdgcn_readlane(n_of_lane, e);
+    if (i0 >= n) return;     // block-uniform: no entries in this block's slots
+
     const int passes = (npairs + kPairsPerPass - 1) / kPairsPerPass;
     for (int pass0 = 0; pass0 < passes; pass0 += kAhead) {
 #pragma unroll
@@ -443,9 +447,6 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
             }
         }
     }
-    const int e = __builtin_amdgcn_readlane(sel_of_lane, j);
-    const int n = __builtin_amdgcn_readlane(n_of_lane, e);
-    if (i0 >= n) return;     // block-uniform: no entries in this block's slots
     float *urow = p.utility + ((int64_t)b * p.E + e) * p.S;
     float u_old = (i < n && hg == 0) ? urow[i] : 0.0f;
     if (p.c.gates != nullptr && tid < k) g_s[tid] = gate_of_thread;
