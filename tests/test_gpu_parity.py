@@ -58,6 +58,36 @@ def test_route_matches_oracle(spec, with_bias):
     np.testing.assert_allclose(t2n(dc.probs), probs, rtol=2e-5, atol=1e-7)
 
 
+@pytest.mark.parametrize("rows", [257, 511, 513, 1027, 2051])
+@pytest.mark.parametrize("E,dtype", [(8, "bf16"), (16, "bf16"), (32, "bf16"), (64, "bf16"), (4, "f32"), (8, "f32"),
+                                     (16, "f32"), (64, "f32"), (6, "bf16"), (13, "f32")])
+def test_route_of_many_rows_gives_each_row_its_own_bits(rows, E, dtype):
+    """A prompt's rows share a block's pass over W_r (2, 4 or 8 of them, the last block partly filled);
+    selection, gates and probabilities of a row are those of a call with few rows, bit for bit - in
+    both the aligned and the generic form, every chunk count, with NaN and infinite logits among them."""
+    k, d_r = 3, 520
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(rows + E)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    x = torch.randn((rows, d_r), device=DEV, generator=gen)
+    x[5, 7], x[rows - 1, 0], x[9] = float("nan"), float("inf"), 0.0
+    x = x.to(tdt)
+    W = (torch.randn((d_r, E), device=DEV, generator=gen) * 0.1).to(tdt)
+    bias = torch.randn(E, device=DEV, generator=gen)
+
+    def route(xs):
+        n = xs.shape[0]
+        out = (torch.full((n, k), -1, device=DEV, dtype=torch.int32), torch.zeros((n, k), device=DEV),
+               torch.zeros((n, E), device=DEV))
+        pk.pikv_route(xs, W, bias, n, d_r, E, k, *out)
+        return [t2n(t) for t in out]
+
+    whole = route(x)
+    parts = [route(x[i:i + 200].contiguous()) for i in range(0, rows, 200)]
+    for w, p in zip(whole, zip(*parts)):
+        np.testing.assert_array_equal(w, np.concatenate(p))
+
+
 def test_route_exact_ties_lower_index_first():
     rng = np.random.default_rng(6)
     rows, d_r = 64, 32
