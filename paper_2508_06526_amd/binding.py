@@ -125,6 +125,9 @@ def _dtype_code(t) -> int:
     raise TypeError("storage dtype must be float32 or bfloat16, got %s" % t.dtype)
 
 
+# An eager pass over a small cache is bound by what happens here, once per pointer: addresses and
+# streams go to ctypes as plain integers (its argument types convert them), without a c_void_p or
+# a torch Stream object in between.
 def _p(t):
     """Device address of a tensor (None -> NULL)."""
     if t is None:
@@ -133,14 +136,25 @@ def _p(t):
         raise ValueError("libpikv takes device memory only")
     if not t.is_contiguous():
         raise ValueError("tensor must be contiguous")
-    return C.c_void_p(t.data_ptr())
+    return t.data_ptr()
+
+
+_current_stream = None     # () -> hipStream_t of torch's current stream on the current device
 
 
 def _stream(stream):
-    import torch
-    if stream is None:
-        stream = torch.cuda.current_stream()
-    return C.c_void_p(stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream))
+    global _current_stream
+    if stream is not None:
+        return stream.cuda_stream if hasattr(stream, "cuda_stream") else int(stream)
+    if _current_stream is None:
+        import torch
+        torch.cuda.current_stream()          # initialises the device
+        try:
+            raw, device = torch._C._cuda_getCurrentRawStream, torch._C._cuda_getDevice
+            _current_stream = lambda: raw(device())
+        except AttributeError:
+            _current_stream = lambda: torch.cuda.current_stream().cuda_stream
+    return _current_stream()
 
 
 def _check(status, where):
@@ -323,8 +337,7 @@ def make_policy_args(policy, now, lam=0.0, window=0, protect=0, threshold=0.0, b
     a.policy, a.now, a.lam, a.window, a.protect, a.threshold = int(policy), int(now), float(lam), int(window), \
         int(protect), float(threshold)
     for name, t in (("birth", birth), ("last_access", last_access), ("freq", freq)):
-        ptr = _p(t)
-        setattr(a, name, None if ptr is None else ptr.value)
+        setattr(a, name, _p(t))
     return a
 
 
@@ -337,8 +350,7 @@ def make_router_feedback(mode, coef, load, bias, miss=None):
     f = PikvRouterFeedback()
     f.mode, f.coef = int(mode), float(coef)
     for name, t in (("load", load), ("miss", miss), ("bias", bias)):
-        ptr = _p(t)
-        setattr(f, name, None if ptr is None else ptr.value)
+        setattr(f, name, _p(t))
     return f
 
 
