@@ -152,6 +152,9 @@ __device__ __forceinline__ void load_words_stream(uint32_t (&dst)[WORDS], const 
 // 16-byte store of data nobody reads back soon (written once, consumed by a later kernel):
 // the non-temporal hint sends it on its way instead of parking a dirty line in L2.
 typedef u32x4_t __attribute__((address_space(1))) *global_u32x4_wptr;
+__device__ __forceinline__ void store16(void *p, uint4 v) {
+    *(u32x4_t __attribute__((address_space(1))) *)(uintptr_t)p = u32x4_t{v.x, v.y, v.z, v.w};
+}
 __device__ __forceinline__ void store16_stream(void *p, uint4 v) {
     const u32x4_t x = {v.x, v.y, v.z, v.w};
     __builtin_nontemporal_store(x, (global_u32x4_wptr)(uintptr_t)p);

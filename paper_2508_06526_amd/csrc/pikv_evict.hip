@@ -10,7 +10,7 @@
 //                  then one pass in slot order, driven by a block-wide prefix sum of the
 //                  per-thread counts, emits the evicted slots ascending and (optionally)
 //                  compacts the utilities in place.
-//   evict_move   : one block per (shard, kv head, K or V, row slice) slides the kept rows down,
+//   evict_move   : one block per (shard, kv head, K or V, column slice) slides the kept rows down,
 //                  a pass of rows at a time in ascending order (a destination never lies
 //                  above its source, so holding a pass in registers before writing it is
 //                  enough).
@@ -20,7 +20,7 @@
 namespace pikv {
 namespace {
 
-constexpr int kEvictThreads = 256;   // every kernel of this file
+constexpr int kEvictThreads = 256;   // every kernel of this file but evict_move
 constexpr int kSelWaves = kEvictThreads / kWave;
 constexpr int kSelCache = 128;       // keys a thread can keep in registers (n <= 32768);
                                      // at most 255: the digit counts of a step are bytes
@@ -372,83 +372,131 @@ struct MoveParams {
     const int32_t *evicted_idx;
     const int32_t *evicted_cnt;
     int64_t stride_h_bytes, stride_s_bytes;
-    int row_chunks;      // 16-byte chunks of a row that one block moves, 1..kEvictThreads
+    int row_chunks;      // 16-byte chunks of a row that one block moves, a power of two up to 256
     int max_evict;
 };
 
-constexpr int kMoveRows = 8;                             // rows a thread carries per pass
-constexpr int kMoveFlagWords = kEvictThreads * kMoveRows / 32;
-static_assert(kMoveFlagWords == kWave, "one wave ranks the flag words");
+constexpr int kMoveThreads = 1024;       // at most; 256 for shards of few slots (kMoveFewSlots)
+constexpr int kMoveFewSlots = 1024;
+constexpr int kMoveRows = 4;             // rows a thread carries per pass
+constexpr int kMoveList = 8192;          // evicted slots of a shard kept in LDS (more: read from memory)
+inline __host__ __device__ int move_pass_rows(int threads, int row_chunks) { return threads / row_chunks * kMoveRows; }
+inline size_t move_lds_bytes(int threads, int row_chunks, int max_evict) {
+    return ((size_t)2 * move_pass_rows(threads, row_chunks) + (max_evict < kMoveList ? max_evict : kMoveList)) * sizeof(int);
+}
 
-__global__ __launch_bounds__(kEvictThreads) void evict_move(MoveParams p) {
+// Slides the kept rows of one (shard, kv head, K or V, column slice) down, a pass of destination
+// rows at a time in ascending order.  Destination d takes the d-th kept slot, d + (how many evicted
+// slots lie below it), found by binary search in the ascending list, one thread per row, while the
+// rows of the pass before are on their way.  A pass's sources lie at or above its first destination:
+// the rows of a pass can be requested before those of the pass before are written, so a block
+// always has a pass of loads in flight; only the writes of a pass wait (a barrier) until the whole
+// block holds its rows.  What bounded the form before - 256 threads, every pass a chain of four
+// barriers and a trip to memory - were those chains (5 us per 256 rows).  Measured, 16 shards x 8
+// heads, 8192 -> 6144 rows of 256 bytes: 161 -> 140 us (5.75 TB/s of
+// reads and writes).
+template <bool STREAM>
+__global__ __launch_bounds__(kMoveThreads) void evict_move(MoveParams p) {
     // blockIdx.z: bit 0 picks K or V, the rest picks the column slice of the row
     const int be = blockIdx.x, hk = blockIdx.y;
     const bool is_v = blockIdx.z & 1;
     const int slice = blockIdx.z >> 1;
-    const int tid = threadIdx.x;
+    const int tid = threadIdx.x, threads = blockDim.x;
     const int cnt = p.evicted_cnt[be];
     if (cnt <= 0) return;
-    const int n_old = p.n_valid[be] + cnt;
+    const int n_new = p.n_valid[be];
     const int32_t *gone = p.evicted_idx + (int64_t)be * p.max_evict;
-    const int group_rows = kEvictThreads / p.row_chunks;   // rows covered by one sweep of the block
-    const int pass_rows = group_rows * kMoveRows;
-    const int rsub = tid / p.row_chunks, csub = tid - rsub * p.row_chunks;
-    const bool lane_used = rsub < group_rows;
-    char *Xb = static_cast<char *>(is_v ? p.V[be] : p.K[be]) + hk * p.stride_h_bytes +
-               (slice * p.row_chunks + csub) * 16;
+    const int first = gone[0];               // rows below it stay
+    if (first >= n_new) return;
 
-    // One bit per row of the pass: set = the row is evicted.  The list is ascending, so the
-    // evicted rows of a pass are the next entries after the `run` ones already passed.
-    __shared__ uint32_t flags[kMoveFlagWords];
-    __shared__ int flags_before[kMoveFlagWords + 1];   // set bits in the words below; [last] = all
-    int run = 0;
-    for (int base = gone[0]; base < n_old; base += pass_rows) {
-        if (tid < kMoveFlagWords) flags[tid] = 0u;
+    extern __shared__ int move_lds[];        // two tables of source rows, used in turn, and the list
+    const int pass_rows = move_pass_rows(threads, p.row_chunks);
+    const int list = 2 * pass_rows;
+    const bool cached = cnt <= kMoveList;
+    if (cached) {
+        for (int i = tid; i < cnt; i += threads) move_lds[list + i] = gone[i] - i;   // kept slots below it
         __syncthreads();
-        for (int x = tid; x < pass_rows; x += kEvictThreads) {
-            if (run + x < cnt) {
-                const int off = gone[run + x] - base;
-                if (off < pass_rows) atomicOr(&flags[off >> 5], 1u << (off & 31));
-            }
-        }
-        __syncthreads();
-        if (tid < kWave) {               // the first wave ranks the 64 words
-            const int mine = __popc(flags[tid]);
-            int incl = mine;
-#pragma unroll
-            for (int off = 1; off < kWave; off <<= 1) {
-                const int t = __shfl_up(incl, off, kWave);
-                if (tid >= off) incl += t;
-            }
-            flags_before[tid] = incl - mine;
-            if (tid == kWave - 1) flags_before[kMoveFlagWords] = incl;
-        }
-        __syncthreads();
-        uint4 held[kMoveRows];
-        int dst[kMoveRows];
-#pragma unroll
-        for (int r = 0; r < kMoveRows; ++r) {
-            const int off = r * group_rows + rsub;
-            const int row = base + off;
-            dst[r] = -1;
-            held[r] = make_uint4(0, 0, 0, 0);
-            if (lane_used && row < n_old) {
-                const int word = off >> 5, pos = off & 31;
-                const uint32_t mine = flags[word];
-                const int before = run + flags_before[word] + __popc(mine & ((1u << pos) - 1u));
-                if (!((mine >> pos) & 1u) && before > 0) {
-                    dst[r] = row - before;
-                    held[r] = *reinterpret_cast<const uint4 *>(Xb + row * p.stride_s_bytes);
+    }
+    auto fill = [&](int table, int base) {
+        for (int x = tid; x < pass_rows; x += threads) {
+            const int d = base + x;
+            int lo = 0, hi = cnt;            // evicted slots below the d-th kept one
+            if (cached) {
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (move_lds[list + mid] <= d) lo = mid + 1;
+                    else hi = mid;
+                }
+            } else {
+                while (lo < hi) {
+                    const int mid = (lo + hi) >> 1;
+                    if (gone[mid] - mid <= d) lo = mid + 1;
+                    else hi = mid;
                 }
             }
+            move_lds[table + x] = d < n_new ? d + lo : first;        // every entry is a row of the shard
         }
-        const int passed = flags_before[kMoveFlagWords];
-        __syncthreads();                 // every row of the pass is in registers
+    };
+    const int rsub = tid / p.row_chunks, csub = tid & (p.row_chunks - 1);
+    const int group_rows = threads / p.row_chunks;      // rows covered by one sweep of the block
+    char *Xb = static_cast<char *>(is_v ? p.V[be] : p.K[be]) + hk * p.stride_h_bytes +
+               (slice * p.row_chunks + csub) * 16;
+    struct Rows {
+        uint4 v[kMoveRows];
+    };
+    auto load = [&](Rows &to, int table) {
+        int row[kMoveRows];
+#pragma unroll
+        for (int r = 0; r < kMoveRows; ++r) row[r] = move_lds[table + r * group_rows + rsub];
 #pragma unroll
         for (int r = 0; r < kMoveRows; ++r) {
-            if (dst[r] >= 0) *reinterpret_cast<uint4 *>(Xb + dst[r] * p.stride_s_bytes) = held[r];
+            const char *from = Xb + row[r] * p.stride_s_bytes;
+            to.v[r] = STREAM ? load16_stream(from) : load16(from);
         }
-        run += passed;
+    };
+    auto store = [&](char *to, const uint4 &v) {
+        if (STREAM) store16_stream(to, v);
+        else store16(to, v);
+    };
+    Rows rows[2];
+    int base = first;
+    // one pass: the next pass's rows are requested, this pass's written.  Nothing in it is
+    // conditional, so a wait for rows is never a wait for the writes after them.
+    auto pass = [&](Rows &cur, Rows &next, int next_table) {
+        fill(next_table, base + pass_rows);
+#pragma unroll
+        for (int r = 0; r < kMoveRows; ++r)  // this wave's rows are here ...
+            asm volatile("" : "+v"(cur.v[r].x), "+v"(cur.v[r].y), "+v"(cur.v[r].z), "+v"(cur.v[r].w));
+        __syncthreads();                     // ... and so are the block's
+        load(next, next_table);
+#pragma unroll
+        for (int r = 0; r < kMoveRows; ++r)
+            store(Xb + (base + r * group_rows + rsub) * p.stride_s_bytes, cur.v[r]);
+        base += pass_rows;
+    };
+    auto last = [&](Rows &cur) {             // a partial pass
+#pragma unroll
+        for (int r = 0; r < kMoveRows; ++r)
+            asm volatile("" : "+v"(cur.v[r].x), "+v"(cur.v[r].y), "+v"(cur.v[r].z), "+v"(cur.v[r].w));
+        __syncthreads();
+#pragma unroll
+        for (int r = 0; r < kMoveRows; ++r) {
+            const int d = base + r * group_rows + rsub;
+            if (d < n_new) store(Xb + d * p.stride_s_bytes, cur.v[r]);
+        }
+    };
+    fill(0, base);
+    __syncthreads();
+    load(rows[0], 0);
+    while (base + 2 * pass_rows <= n_new) {
+        pass(rows[0], rows[1], pass_rows);
+        pass(rows[1], rows[0], 0);
+    }
+    if (base + pass_rows <= n_new) {
+        pass(rows[0], rows[1], pass_rows);
+        if (base < n_new) last(rows[1]);
+    } else if (base < n_new) {
+        last(rows[0]);
     }
 }
 
@@ -537,12 +585,21 @@ extern "C" int pikv_evict(const pikv_desc *desc, float *utility, int32_t *n_vali
     const int eb = elem_bytes(desc->dtype);
     m.stride_h_bytes = desc->stride_h * eb;
     m.stride_s_bytes = desc->stride_s * eb;
-    // K and V move in separate blocks; rows of 256 bytes or more are also cut in two slices
-    const int slices = (row_chunks >= 16 && row_chunks % 2 == 0) ? 2 : 1;
+    // K and V move in separate blocks; rows are cut in column slices of at least 64 bytes until there
+    // are two blocks per CU
+    int slices = 1;
+    while ((int64_t)desc->B * desc->E * desc->Hkv * 2 * slices < 512 && row_chunks / slices >= 8) slices *= 2;
     m.row_chunks = row_chunks / slices;
     m.max_evict = max_evict;
-    hipLaunchKernelGGL(evict_move, dim3(desc->B * desc->E, desc->Hkv, 2 * slices),
-                       dim3(kEvictThreads), 0, st, m);
+    // Caches beyond the 256 MiB that the Infinity Cache holds go past it, reads and writes (512 MiB:
+    // 161 us for the whole call against 187, 4 GiB 556 against 639; 33 MiB that are still in it 44
+    // against 33).
+    const int threads = desc->S <= kMoveFewSlots ? 256 : kMoveThreads;
+    const dim3 grid(desc->B * desc->E, desc->Hkv, 2 * slices), block(threads);
+    const size_t lds = move_lds_bytes(threads, m.row_chunks, max_evict);
+    const int64_t cache_bytes = (int64_t)desc->B * desc->E * desc->Hkv * desc->S * row_chunks * 32;
+    if (cache_bytes > ((int64_t)256 << 20)) hipLaunchKernelGGL(evict_move<true>, grid, block, lds, st, m);
+    else hipLaunchKernelGGL(evict_move<false>, grid, block, lds, st, m);
     return launch_status();
 }
 

@@ -557,6 +557,45 @@ def test_evict_with_compaction_moves_rows_like_oracle(spec):
             np.testing.assert_array_equal(dc.shard_host("V", s)[:, :nn], ref.V_shards[s][:, :nn])
 
 
+@pytest.mark.parametrize("S,cap,D,dtype,Hkv,E", [
+    (513, 512, 16, "bf16", 1, 2),           # one row leaves; 256 threads
+    (2048, 1536, 128, "bf16", 2, 3), (2561, 2048, 128, "f32", 1, 2), (4096, 1, 64, "bf16", 1, 2),
+    (3000, 0, 64, "bf16", 2, 2),            # nothing is kept
+    (30000, 10000, 32, "bf16", 1, 2),       # more evicted slots than the mover holds in LDS
+    (40000, 30001, 128, "bf16", 7, 2),      # more than 256 MiB of K and V: the streaming form
+], ids=lambda v: str(v))
+@pytest.mark.parametrize("where", ["mixed", "tail", "head"])
+def test_compaction_slides_rows_at_the_movers_edges(S, cap, D, dtype, Hkv, E, where):
+    """Kept rows of K and V against an indexed copy, bit for bit, and nothing above the kept prefix changes:
+    evicted slots everywhere, only at the end (nothing moves) and only at the start (all rows move)."""
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(S + D)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+    K = torch.empty((1, E, Hkv, S, D), device=DEV, dtype=tdt).normal_(generator=gen)
+    V = torch.empty_like(K).normal_(generator=gen)
+    n = torch.tensor([[S] + [max(1, S - 77)] * (E - 1)], device=DEV, dtype=torch.int32)
+    u = torch.rand((1, E, S), device=DEV, generator=gen) + 0.5
+    if where == "tail":
+        u[:] = torch.arange(S, 0, -1, device=DEV)
+    elif where == "head":
+        u[:] = torch.arange(1, S + 1, device=DEV)
+    wantK, wantV, gone = K.clone(), V.clone(), {}
+    for e in range(E):
+        ne = int(n[0, e])
+        if ne > cap:
+            order = torch.argsort(u[0, e, :ne], descending=True, stable=True)
+            keep, gone[e] = order[:cap].sort().values, order[cap:].sort().values
+            wantK[0, e, :, :cap], wantV[0, e, :, :cap] = K[0, e][:, keep], V[0, e][:, keep]
+    drop = S - cap
+    eidx = torch.full((1, E, drop), -1, device=DEV, dtype=torch.int32)
+    ecnt = torch.zeros((1, E), device=DEV, dtype=torch.int32)
+    desc = pk.make_desc(1, Hkv, Hkv, D, E, S, dtype=pk.binding.F32 if dtype == "f32" else pk.binding.BF16)
+    pk.pikv_evict(desc, u, n, cap, None, 0, eidx, ecnt, drop, True, pk.shard_table(K), pk.shard_table(V))
+    assert torch.equal(K, wantK) and torch.equal(V, wantV)
+    for e, slots in gone.items():
+        assert int(ecnt[0, e]) == slots.numel() and torch.equal(eidx[0, e, :slots.numel()], slots.int())
+
+
 def test_append_matches_oracle_bit_exact():
     g = wl.Geometry(B=3, Hq=4, Hkv=2, D=128, E=4, S=50, k=2, dtype="bf16")
     case = wl.make_host_case(g, seed=22, n_valid="ragged", utility0="exp")
