@@ -298,8 +298,8 @@ struct PostParams {
 // LDS of a utility block: statistics of the Hq * k (head, shard) pairs, the gates, and two
 // buffers of per-(head group, slot) sums used in turn.
 inline __host__ __device__ int post_pairs_pad(int pairs) { return (pairs + 3) & ~3; }
-inline size_t post_smem_bytes(int threads, int np, int pairs) {
-    const size_t util = (size_t)(4 * post_pairs_pad(pairs) + 64 + 2 * threads) * 4;
+inline size_t post_smem_bytes(int threads, int np, int pairs, int slots_per_thread) {
+    const size_t util = (size_t)(4 * post_pairs_pad(pairs) + 64 + 2 * slots_per_thread * threads) * 4;
     const size_t comb = combine_smem_bytes(threads, np);
     return util > comb ? util : comb;
 }
@@ -309,9 +309,17 @@ inline size_t post_smem_bytes(int threads, int np, int pairs) {
 // tiles_per_block tiles of THREADS/4 slots of the j-th selected shard of a sequence.  THREADS
 // is the merge's block size (combine_threads), so that the merge is bit-identical to the
 // stand-alone kernel.
-template <typename T, int THREADS, int MODE>
+//
+// SPT slots per thread: 1, or 4 consecutive ones (16-byte score loads, tiles of THREADS slots) when
+// tiles of THREADS / 4 slots would take more than one round of blocks.  Those blocks were bound by
+// their chain of trips and barriers, not by the score bytes: with four slots per thread a quarter
+// of the blocks (or of the tiles a block walks through) has the same bytes in flight at once, and
+// the statistics are formed a quarter as often.  Measured: 16 sequences x 32 heads x 2 shards of 4096
+// slots 10.0 -> 7.2 us, with access bookkeeping 12.5 -> 8.4; 32 sequences, 2048 slots 11.7 -> 10.8; at
+// one round of blocks or less it is no faster (4 shards of 8192 slots, 1 sequence: +1.5 us).
+template <typename T, int THREADS, int MODE, int SPT>
 __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
-    constexpr int kSlots = THREADS / 4;
+    constexpr int kSlots = THREADS / 4 * SPT;
     const int ntiles = MODE != kPostSingle ? p.tiles_per_block : 1;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // post_smem_bytes()
     const int Hq = p.c.Hq, k = p.c.k, nsplit = p.c.nsplit;
@@ -357,13 +365,21 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     float *g_s = coef_s + pairs;               // [64]
     float *part_s = g_s + 64;                  // [2][4][kSlots]
 
-    // thread = (slot, head group); the heads are cut into 4 consecutive groups, each summed in
+    // thread = (SPT slots, head group); the heads are cut into 4 consecutive groups, each summed in
     // ascending order, the groups joined as (g0 + g1) + (g2 + g3) - the order the stand-alone
     // utility kernel uses too
-    const int slot = tid & (kSlots - 1), hg = tid / kSlots;
+    const int slot = (tid & (THREADS / 4 - 1)) * SPT, hg = tid / (THREADS / 4);
     const int gsize = (Hq + 3) / 4;
     const int h_lo = hg * gsize, h_hi = min(Hq, h_lo + gsize);
-    float sc[kPostPrefetchHeads];
+    float sc[kPostPrefetchHeads][SPT];
+    auto load_scores = [&](float(&to)[SPT], const float *from) {
+        if constexpr (SPT == 4) {
+            const float4 v = *reinterpret_cast<const float4 *>(from);
+            to[0] = v.x, to[1] = v.y, to[2] = v.z, to[3] = v.w;
+        } else {
+            to[0] = *from;
+        }
+    };
     // (unconditional loads from clamped, always valid addresses: heads past the group's end and
     // slots past the limit are masked where the values are used.  Loads under a lane-dependent
     // branch would make every later wait a wait for ALL loads in flight.)
@@ -378,7 +394,7 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     const uint32_t off_first = ((uint32_t)h_first * (uint32_t)k + (uint32_t)j) * (uint32_t)p.S;
     const uint32_t off_last = off_first + (uint32_t)t_last * kS;
     auto fetch = [&](int i, int limit, bool first) {
-        const int ic = min(i, limit - 1);
+        const int ic = min(i, SPT == 4 ? p.S - 4 : limit - 1);      // (SPT = 4: S is a multiple of 4)
         // (the later tiles' requests keep the long form: its bases are set up once, after the
         // first requests have gone out, and a tile then costs one add per head; the shape with
         // several tiles per block keeps it throughout - there both forms side by side measured
@@ -387,13 +403,13 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
 #pragma unroll
             for (int t = 0; t < kPostPrefetchHeads; ++t) {
                 const uint32_t off = (t < t_last ? off_first + (uint32_t)t * kS : off_last) + (uint32_t)ic;
-                sc[t] = seq_scores[off];
+                load_scores(sc[t], seq_scores + off);
             }
         } else {
 #pragma unroll
             for (int t = 0; t < kPostPrefetchHeads; ++t) {
                 const int h = min(h_lo + t, Hq - 1);
-                sc[t] = p.scores[(((int64_t)b * Hq + h) * k + j) * p.S + ic];
+                load_scores(sc[t], p.scores + (((int64_t)b * Hq + h) * k + j) * p.S + ic);
             }
         }
     };
@@ -448,7 +464,11 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
         }
     }
     float *urow = p.utility + ((int64_t)b * p.E + e) * p.S;
-    float u_old = (i < n && hg == 0) ? urow[i] : 0.0f;
+    // the utilities: with one slot per thread by the first head group, with four by every thread
+    const int uslot = SPT == 4 ? tid : slot;
+    const bool updates = SPT == 4 || hg == 0;
+    int ui = i0 + uslot;
+    float u_old = (ui < n && updates) ? urow[ui] : 0.0f;
     if (p.c.gates != nullptr && tid < k) g_s[tid] = gate_of_thread;
     __syncthreads();
     // (shift, coef) of every (head, shard) pair: an aligned group of kp lanes per head
@@ -469,7 +489,9 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     __syncthreads();
     for (int it = 0; it < ntiles; ++it) {
         const bool live = i < n;
-        float a = 0.0f;
+        float a[SPT];
+#pragma unroll
+        for (int x = 0; x < SPT; ++x) a[x] = 0.0f;
         // the prefetched heads, without branches: the group's head range is the same in the whole
         // wave (a scalar compare picks the sum or leaves it), heads past its end read a clamped,
         // valid pair, and lanes past the entry count compute on their clamped scores for nothing
@@ -477,39 +499,50 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
 #pragma unroll
         for (int t = 0; t < kPostPrefetchHeads; ++t) {
             const int h = min(h_lo + t, Hq - 1);
-            const float with = fmaf(coef_s[h * k + j], __expf(sc[t] - shift_s[h * k + j]), a);
-            a = t < held_heads ? with : a;
+            const float coef = coef_s[h * k + j], shift = shift_s[h * k + j];
+#pragma unroll
+            for (int x = 0; x < SPT; ++x) {
+                const float with = fmaf(coef, __expf(sc[t][x] - shift), a[x]);
+                a[x] = t < held_heads ? with : a[x];
+            }
         }
         if (live) {
             // more heads per group than were prefetched: batches of loads, same ascending order
             for (int hb = h_lo + kPostPrefetchHeads; hb < h_hi; hb += kPostPrefetchHeads) {
-                float more[kPostPrefetchHeads];
+                float more[kPostPrefetchHeads][SPT];
 #pragma unroll
                 for (int t = 0; t < kPostPrefetchHeads; ++t)
-                    more[t] = hb + t < h_hi ? p.scores[(((int64_t)b * Hq + hb + t) * k + j) * p.S + i] : 0.0f;
+                    load_scores(more[t], p.scores + (((int64_t)b * Hq + min(hb + t, h_hi - 1)) * k + j) * p.S + i);
 #pragma unroll
                 for (int t = 0; t < kPostPrefetchHeads; ++t) {
                     const int h = hb + t;
-                    if (h < h_hi) a = fmaf(coef_s[h * k + j], __expf(more[t] - shift_s[h * k + j]), a);
+                    if (h < h_hi) {
+#pragma unroll
+                        for (int x = 0; x < SPT; ++x)
+                            a[x] = fmaf(coef_s[h * k + j], __expf(more[t][x] - shift_s[h * k + j]), a[x]);
+                    }
                 }
             }
         }
         // the next tile's loads go out before this tile's sums meet in LDS
         const int i_next = i + kSlots;
+        const int u_at = ui;
         const float u_cur = u_old;
+        ui += kSlots;
         if (it + 1 < ntiles) {
             fetch(i_next, n, false);
-            u_old = (i_next < n && hg == 0) ? urow[i_next] : 0.0f;
+            u_old = (ui < n && updates) ? urow[ui] : 0.0f;
         }
         float *part = part_s + (it & 1) * 4 * kSlots;    // rewritten two tiles later, after a barrier
-        part[hg * kSlots + slot] = a;
+#pragma unroll
+        for (int x = 0; x < SPT; ++x) part[hg * kSlots + slot + x] = a[x];
         __syncthreads();
-        if (hg == 0 && live) {
-            const float total = (part[slot] + part[kSlots + slot]) +
-                                (part[2 * kSlots + slot] + part[3 * kSlots + slot]);
-            urow[i] = fmaf(p.decay, u_cur, total);
+        if (updates && u_at < n) {
+            const float total = (part[uslot] + part[kSlots + uslot]) +
+                                (part[2 * kSlots + uslot] + part[3 * kSlots + uslot]);
+            urow[u_at] = fmaf(p.decay, u_cur, total);
             if (p.track && total > p.pol.threshold) {
-                const int64_t at = ((int64_t)b * p.E + e) * p.S + i;
+                const int64_t at = ((int64_t)b * p.E + e) * p.S + u_at;
                 p.pol.last_access[at] = p.pol.now;
                 p.pol.freq[at] += 1;
             }
@@ -670,16 +703,24 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     // Utility blocks: enough of them to fill the GPU once (256 CUs x the blocks a CU holds),
     // each walking through several slot tiles rather than a new block per tile - the
     // statistics of the sequence's (head, shard) pairs are then computed once per block.
-    const int64_t slot_tiles = (desc->S + threads / 4 - 1) / (threads / 4);
     const int64_t want_blocks = threads == 256 ? 1024 : 256;
-    int64_t tpb = ((int64_t)desc->B * k * slot_tiles + want_blocks - 1) / want_blocks;
-    if (tpb < 1) tpb = 1;
-    if (tpb > kPostMaxTiles) tpb = kPostMaxTiles;
-    pp.tiles_per_block = (int)tpb;
-    pp.tiles = (int)((slot_tiles + tpb - 1) / tpb);
+    auto tiles_of = [&](int slots) { return (int64_t)(desc->S + slots - 1) / slots; };
+    auto tiles_per_block = [&](int64_t tiles) {
+        const int64_t t = ((int64_t)desc->B * k * tiles + want_blocks - 1) / want_blocks;
+        return t < 1 ? 1 : t > kPostMaxTiles ? (int64_t)kPostMaxTiles : t;
+    };
     // many (head, shard) pairs per utility block, or many heads per thread: the kernel shape
     // that keeps several passes of statistics in flight and starts the utility blocks first
     const bool many = desc->Hq * k > 2 * (threads / 8) || (desc->Hq + 3) / 4 > 2 * kPostPrefetchHeads;
+    // four slots per thread as soon as one slot per thread needs more than one round of blocks (in
+    // blocks of 1024 threads only where the loop-free shape takes it: the others would spill)
+    bool wide = (int64_t)desc->B * k * tiles_of(threads / 4) > want_blocks && desc->S % 4 == 0 &&
+                reinterpret_cast<uintptr_t>(scores) % 16 == 0;
+    if (threads == 1024 && (many || tiles_per_block(tiles_of(threads)) > 1)) wide = false;
+    const int64_t slot_tiles = tiles_of(wide ? threads : threads / 4);
+    const int64_t tpb = tiles_per_block(slot_tiles);
+    pp.tiles_per_block = (int)tpb;
+    pp.tiles = (int)((slot_tiles + tpb - 1) / tpb);
     pp.util_first = many ? 1 : 0;
     pp.decay = decay;
     pp.feedback = fb != nullptr;
@@ -688,13 +729,20 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     if (blocks > 0x7fffffff) return PIKV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks);
     const bool f32 = desc->dtype == PIKV_F32;
-    const size_t lds = post_smem_bytes(threads, np, desc->Hq * k);
+    const size_t lds = post_smem_bytes(threads, np, desc->Hq * k, wide ? 4 : 1);
     const bool multi = tpb > 1;
+    // (several tiles of four slots per thread: blocks of 256 threads only, see `wide`)
+#define PIKV_LAUNCH_POST_MODE(T, TH, MODE)                                                               \
+    do {                                                                                                 \
+        constexpr int kWide = TH == 256 || MODE == kPostSingle ? 4 : 1;                                  \
+        if (wide) hipLaunchKernelGGL((step_post<T, TH, MODE, kWide>), grid, dim3(TH), lds, st, pp);      \
+        else hipLaunchKernelGGL((step_post<T, TH, MODE, 1>), grid, dim3(TH), lds, st, pp);               \
+    } while (0)
 #define PIKV_LAUNCH_POST(T, TH)                                                                          \
     do {                                                                                                 \
-        if (many) hipLaunchKernelGGL((step_post<T, TH, kPostMany>), grid, dim3(TH), lds, st, pp);        \
-        else if (multi) hipLaunchKernelGGL((step_post<T, TH, kPostMulti>), grid, dim3(TH), lds, st, pp); \
-        else hipLaunchKernelGGL((step_post<T, TH, kPostSingle>), grid, dim3(TH), lds, st, pp);           \
+        if (many) PIKV_LAUNCH_POST_MODE(T, TH, kPostMany);                                               \
+        else if (multi) PIKV_LAUNCH_POST_MODE(T, TH, kPostMulti);                                        \
+        else PIKV_LAUNCH_POST_MODE(T, TH, kPostSingle);                                                  \
     } while (0)
     if (threads == 256) {
         if (f32) PIKV_LAUNCH_POST(float, 256);
@@ -704,6 +752,7 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
         else PIKV_LAUNCH_POST(bf16, 1024);
     }
 #undef PIKV_LAUNCH_POST
+#undef PIKV_LAUNCH_POST_MODE
     return launch_status();
 }
 

@@ -1184,6 +1184,47 @@ def test_fused_step_with_many_head_shard_pairs_equals_separate_calls(spec, combi
                                           err_msg="%s differs at step %d" % (name, step))
 
 
+@pytest.mark.parametrize("spec", [
+    dict(B=9, Hq=5, Hkv=5, D=16, E=8, S=2052, k=8, dtype="bf16"),       # four slots per thread, one tile per block
+    dict(B=9, Hq=5, Hkv=5, D=16, E=8, S=2051, k=8, dtype="bf16"),       # odd capacity: one slot per thread
+    dict(B=32, Hq=38, Hkv=1, D=16, E=8, S=2500, k=4, dtype="bf16"),     # several tiles of four slots, 10 heads a thread
+    dict(B=4, Hq=80, Hkv=1, D=16, E=8, S=4100, k=4, dtype="f32"),       # many (head, shard) pairs
+    dict(B=4, Hq=2, Hkv=1, D=128, E=8, S=2304, k=8, dtype="bf16"),      # blocks of 1024 threads
+], ids=["wide", "odd", "multi", "many", "threads1024"])
+def test_fused_step_on_many_slots_equals_separate_calls(spec):
+    """More than one round of utility blocks: four slots per thread, against the stand-alone utility
+    kernel with its access bookkeeping, bit for bit; entry counts from a few slots to full."""
+    from gpu_harness import dev_storage
+    g = wl.Geometry(**spec)
+    case = wl.make_host_case(g, seed=5, n_valid="ragged", utility0="exp", w_sigma=0.1)
+    case.n_valid[0, :4] = [3, 255, 257, g.S]
+    dA, dB = DeviceCase(case), DeviceCase(case)
+    for d in (dA, dB):
+        d.last = torch.zeros((g.B, g.E, g.S), device=DEV, dtype=torch.int32)
+        d.freq, d.birth = d.last.clone(), d.last.clone()
+        d.eidx = torch.full((g.B, g.E, 1), -1, device=DEV, dtype=torch.int32)
+        d.ecnt = torch.full((g.B, g.E), -5, device=DEV, dtype=torch.int32)
+    for step in range(2):
+        kn, vn = wl.draw_new_kv(g, 600 + step)
+        dkn, dvn = dev_storage(kn, g.dtype), dev_storage(vn, g.dtype)
+        args = pk.make_policy_args(pk.POLICY_H2O, 7 + step, threshold=2.0 / g.S, birth=dA.birth, last_access=dA.last,
+                                   freq=dA.freq)
+        pk.pikv_decode_step_policy(dA.desc, dA.q, dA.W_r, dA.bias, dkn, dvn, dA.K_tab, dA.V_tab, None, None, dA.n_valid,
+                                   dA.utility, g.k, pk.COMBINE_LSE, 0.0, 0.9, dA.topk, dA.gates, dA.eidx, dA.ecnt, dA.y,
+                                   dA.row_max, dA.row_norm, dA.scores, dA.slot_coef, dA.workspace, args)
+        dB.route()
+        pk.pikv_evict(dB.desc, dB.utility, dB.n_valid, g.S - 1, dB.topk, g.k, dB.eidx, dB.ecnt, 1, False, None, None)
+        pk.pikv_policy_stamp(dB.desc, dB.topk, g.k, dB.eidx, dB.ecnt, 1, dB.n_valid, 7 + step, dB.birth, dB.last, dB.freq)
+        pk.pikv_append(dB.desc, dkn, dvn, dB.topk, g.k, dB.eidx, dB.ecnt, 1, dB.K_tab, dB.V_tab, dB.utility, dB.n_valid)
+        dB.attend()
+        pk.pikv_update_utility_tracked(dB.desc, dB.scores, dB.slot_coef, dB.n_valid, dB.topk, g.k, 0.9, dB.utility,
+                                       2.0 / g.S, 7 + step, dB.last, dB.freq)
+        for name in ("topk", "n_valid", "utility", "y", "row_norm", "last", "freq", "birth"):
+            np.testing.assert_array_equal(t2n(getattr(dA, name)), t2n(getattr(dB, name)),
+                                          err_msg="%s differs at step %d" % (name, step))
+    assert (t2n(dA.freq) > 0).any()
+
+
 def test_fused_step_with_many_heads_times_shards_uses_the_separate_merge():
     """Hq * k beyond what a utility block restages: the step falls back to separate merge and
     utility launches and still equals the separate calls bit for bit."""
