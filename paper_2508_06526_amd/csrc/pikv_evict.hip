@@ -20,22 +20,40 @@
 namespace pikv {
 namespace {
 
-constexpr int kEvictThreads = 256;   // every kernel of this file but evict_move
-constexpr int kSelWaves = kEvictThreads / kWave;
-constexpr int kSelCache = 128;       // keys a thread can keep in registers (n <= 32768);
+constexpr int kAppendThreads = 256;
+// evict_select: 256 threads for shards of up to 2048 slots, 1024 beyond.  A step of the select costs
+// the same vector work on a CU either way; with 1024 threads a thread owns a quarter of the slots,
+// so the lists and the compacted utilities leave as runs of 32 bytes per lane instead of 128, and
+// four waves a SIMD cover each other's latencies.  Measured, graph replay, capacity 3/4:
+// 16 shards of 8192 slots 20.4 -> 18.3 us, 128 of 4096 15.9 -> 14.4; 64 of 1999 slots (rows that are not
+// 16-byte aligned, re-read every step before) with their rows 51.7 -> 33.0, 16 of 20000 162.9 -> 148.
+constexpr int kSelFewSlots = 2048;
+constexpr int kSelCache = 32;        // keys a thread can keep in registers (n <= 32768);
                                      // at most 255: the digit counts of a step are bytes
 
+template <int THREADS>
 struct SelShared {
-    int cnt[2][3 * kSelWaves];       // per-wave digit counts of a select step, two buffers in turn
-    int scan[2][kSelWaves];          // per-wave totals of a block scan, two buffers in turn
-    uint64_t wave_best[kSelWaves];
+    static constexpr int kWaves = THREADS / kWave;
+    int cnt[2][3][16];               // per-wave digit counts of a select step, two buffers in turn
+    int scan[2][16];                 // per-wave totals of a block scan, two buffers in turn
+    uint64_t wave_best[kWaves];
 };
 // Both pairs of buffers are used in turn, which makes one barrier per use enough: a buffer
 // is rewritten two uses later, and every wave has left the reads of use i before any wave
 // passes the barrier of use i+1.
 
+// Sum over the 16 lanes of a DPP row, in every one of them.
+__device__ __forceinline__ int row_sum(int v) {
+    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);    // lane ^ 1
+    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);    // lane ^ 2
+    v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);   // mirror within 8
+    v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);   // mirror within 16
+    return v;
+}
+
 // Exclusive prefix sum of v over the block in thread order.
-__device__ __forceinline__ int block_scan_excl(int v, SelShared &sh, int &turn) {
+template <int THREADS>
+__device__ __forceinline__ int block_scan_excl(int v, SelShared<THREADS> &sh, int &turn) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     int incl = v;
 #pragma unroll
@@ -47,15 +65,13 @@ __device__ __forceinline__ int block_scan_excl(int v, SelShared &sh, int &turn) 
     ++turn;
     if (lane == kWave - 1) slot[wave] = incl;
     __syncthreads();
-    int before = 0;
-#pragma unroll
-    for (int w = 0; w < kSelWaves - 1; ++w)
-        if (w < wave) before += slot[w];
+    const int before = row_sum((lane & 15) < wave ? slot[lane & 15] : 0);
     return before + incl - v;
 }
 
 // Exclusive block-wide rank of a one-bit flag in thread order; *total receives the block sum.
-__device__ __forceinline__ int block_rank_flag(bool flag, SelShared &sh, int &turn, int *total) {
+template <int THREADS>
+__device__ __forceinline__ int block_rank_flag(bool flag, SelShared<THREADS> &sh, int &turn, int *total) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
     const uint64_t votes = __ballot(flag);
     const int in_wave = __popcll(votes & ((1ull << lane) - 1ull));
@@ -63,15 +79,9 @@ __device__ __forceinline__ int block_rank_flag(bool flag, SelShared &sh, int &tu
     ++turn;
     if (lane == 0) slot[wave] = __popcll(votes);
     __syncthreads();
-    int before = 0, all = 0;
-#pragma unroll
-    for (int w = 0; w < kSelWaves; ++w) {
-        const int c = slot[w];
-        if (w < wave) before += c;
-        all += c;
-    }
-    *total = all;
-    return before + in_wave;
+    const int mine = (lane & 15) < SelShared<THREADS>::kWaves ? slot[lane & 15] : 0;
+    *total = row_sum(mine);
+    return row_sum((lane & 15) < wave ? mine : 0) + in_wave;
 }
 
 struct EvictParams {
@@ -90,10 +100,7 @@ __device__ __forceinline__ float key_value(uint32_t key) {
 
 // Sum over the 64 lanes of a wave, returned in every lane.
 __device__ __forceinline__ int wave_sum(int v) {
-    v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);    // lane ^ 1
-    v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);    // lane ^ 2
-    v += __builtin_amdgcn_update_dpp(0, v, 0x141, 0xf, 0xf, true);   // mirror within 8
-    v += __builtin_amdgcn_update_dpp(0, v, 0x140, 0xf, 0xf, true);   // mirror within 16
+    v = row_sum(v);
     v += __shfl_xor(v, 16, kWave);
     v += __shfl_xor(v, 32, kWave);
     return v;
@@ -113,8 +120,8 @@ struct CutSearch {
     // c1..c3: this thread's candidates with digit < 1, < 2, < 3.  With PACKED the caller
     // promises at most 512 per thread, so a wave's totals fit 16 bits and c1, c2 travel
     // through the lane sums as one word.
-    template <bool PACKED>
-    __device__ __forceinline__ void step(int shift, int c1, int c2, int c3, SelShared &sh) {
+    template <bool PACKED, int THREADS>
+    __device__ __forceinline__ void step(int shift, int c1, int c2, int c3, SelShared<THREADS> &sh) {
         const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
         if (PACKED) {
             const int c12 = wave_sum(c1 | (c2 << 16));
@@ -125,22 +132,20 @@ struct CutSearch {
             c2 = wave_sum(c2);
         }
         c3 = wave_sum(c3);
-        int *slot = sh.cnt[turn & 1];
+        int(*slot)[16] = sh.cnt[turn & 1];
         ++turn;
         if (lane == 0) {
-            slot[wave] = c1;
-            slot[kSelWaves + wave] = c2;
-            slot[2 * kSelWaves + wave] = c3;
+            slot[0][wave] = c1;
+            slot[1][wave] = c2;
+            slot[2][wave] = c3;
         }
         __syncthreads();
-        // lanes 0..11 fetch the 3 x 4 counts; quad sums leave the totals in lanes 0, 4, 8
-        int v = lane < 3 * kSelWaves ? slot[lane] : 0;
-        v += __builtin_amdgcn_update_dpp(0, v, 0xB1, 0xf, 0xf, true);
-        v += __builtin_amdgcn_update_dpp(0, v, 0x4E, 0xf, 0xf, true);
-        static_assert(kSelWaves == 4, "quad sums");
+        // row r of 16 lanes fetches the waves' counts for digit < r + 1
+        const int row = lane >> 4, w = lane & 15;
+        const int v = row_sum(row < 3 && w < SelShared<THREADS>::kWaves ? slot[row][w] : 0);
         const int C1 = __builtin_amdgcn_readlane(v, 0);
-        const int C2 = __builtin_amdgcn_readlane(v, 4);
-        const int C3 = __builtin_amdgcn_readlane(v, 8);
+        const int C2 = __builtin_amdgcn_readlane(v, 16);
+        const int C3 = __builtin_amdgcn_readlane(v, 32);
         if (remaining <= C1) {
             cand = C1;
         } else if (remaining <= C2) {
@@ -162,21 +167,23 @@ struct CutSearch {
 // Keys in registers: thread t owns the `per` consecutive slots from t * per (per a multiple
 // of 4, at most NCH), so the 16 steps touch no memory and slot order is thread order.  Slots
 // past n hold the largest key: its digit is always 3, which no cumulative count includes.
-template <int NCH>
+template <int THREADS, int NCH>
 __device__ __forceinline__ void select_cached(const EvictParams &p, int be, float *u, int n,
-                                              int ngone, SelShared &sh) {
+                                              int ngone, bool vec, SelShared<THREADS> &sh) {
     const int tid = threadIdx.x;
-    const int per = (n + kEvictThreads * 4 - 1) / (kEvictThreads * 4) * 4;
+    const int per = (n + THREADS * 4 - 1) / (THREADS * 4) * 4;
     const int first = tid * per;
-    // The row is 16-byte aligned and S is a multiple of 4 (the caller checked), so a group
-    // of four that starts below n lies inside the row; groups past n re-read the first one.
-    // No branch around the loads: all of them are in flight together.
+    // vec: the row is 16-byte aligned and S is a multiple of 4, so a group of four that starts
+    // below n lies inside the row; groups past n re-read the first one.  Otherwise single slots,
+    // clamped onto the last.  No branch around the loads: all of them are in flight together.
     uint32_t keys[NCH];
 #pragma unroll
     for (int j0 = 0; j0 < NCH; j0 += 4) {
         const int i0 = first + j0;
         const bool any = j0 < per && i0 < n;
-        const float4 v = *reinterpret_cast<const float4 *>(u + (any ? i0 : 0));
+        const float4 v = vec ? *reinterpret_cast<const float4 *>(u + (any ? i0 : 0))
+                             : make_float4(u[min(i0, n - 1)], u[min(i0 + 1, n - 1)], u[min(i0 + 2, n - 1)],
+                                           u[min(i0 + 3, n - 1)]);
         keys[j0] = any ? order_key(v.x) : 0xffffffffu;
         keys[j0 + 1] = (any && i0 + 1 < n) ? order_key(v.y) : 0xffffffffu;
         keys[j0 + 2] = (any && i0 + 2 < n) ? order_key(v.z) : 0xffffffffu;
@@ -200,7 +207,7 @@ __device__ __forceinline__ void select_cached(const EvictParams &p, int be, floa
         const int c1 = acc & 0xff;
         const int c2 = c1 + ((acc >> 8) & 0xff);
         const int c3 = c2 + ((acc >> 16) & 0xff);
-        cs.step<true>(shift, c1, c2, c3, sh);
+        cs.template step<true>(shift, c1, c2, c3, sh);
     }
     const uint32_t cut = cs.prefix;               // keys < cut go; of the keys == cut (`cand`
     const int keep_eq = cs.cand - cs.remaining;   // of them) the first keep_eq in slot order stay
@@ -254,30 +261,31 @@ __device__ __forceinline__ void select_cached(const EvictParams &p, int be, floa
     }
 }
 
-// More keys than the registers hold: every step re-reads them (slot i = tid + j * 256).
+// More keys than the registers hold: every step re-reads them (slot i = tid + j * THREADS).
+template <int THREADS>
 __device__ __forceinline__ void select_stream(const EvictParams &p, int be, float *u, int n,
-                                              int ngone, SelShared &sh) {
+                                              int ngone, SelShared<THREADS> &sh) {
     const int tid = threadIdx.x;
-    const int nchunk = (n + kEvictThreads - 1) / kEvictThreads;
+    const int nchunk = (n + THREADS - 1) / THREADS;
     CutSearch cs(n, ngone);
     for (int shift = 30; shift >= 0; shift -= 2) {
         const uint32_t t1 = 1u << shift, t2 = 2u << shift, t3 = 3u << shift;
         int c1 = 0, c2 = 0, c3 = 0;
         for (int j = 0; j < nchunk; ++j) {
-            const int i = tid + j * kEvictThreads;
+            const int i = tid + j * THREADS;
             const uint32_t x = (i < n ? order_key(u[i]) : 0xffffffffu) ^ cs.prefix;
             c1 += x < t1;
             c2 += x < t2;
             c3 += x < t3;
         }
-        cs.step<false>(shift, c1, c2, c3, sh);
+        cs.template step<false>(shift, c1, c2, c3, sh);
     }
     const uint32_t cut = cs.prefix;
     const int keep_eq = cs.cand - cs.remaining;
     int32_t *out = p.evicted_idx + (int64_t)be * p.max_evict;
     int eq_seen = 0, gone_seen = 0;       // running totals over the chunks already done
     for (int j = 0; j < nchunk; ++j) {
-        const int i = tid + j * kEvictThreads;
+        const int i = tid + j * THREADS;
         const bool valid = i < n;
         const float ui = valid ? u[i] : 0.0f;
         const uint32_t key = order_key(ui);
@@ -298,12 +306,13 @@ __device__ __forceinline__ void select_stream(const EvictParams &p, int be, floa
     }
 }
 
-__global__ __launch_bounds__(kEvictThreads) void evict_select(EvictParams p) {
+template <int THREADS>
+__global__ __launch_bounds__(THREADS) void evict_select(EvictParams p) {
     const int be = blockIdx.x;
     const int b = be / p.E, e = be - b * p.E;
     const int tid = threadIdx.x;
 
-    __shared__ SelShared sh;
+    __shared__ SelShared<THREADS> sh;
 
     bool selected = true;
     if (p.sel_idx) {
@@ -323,7 +332,7 @@ __global__ __launch_bounds__(kEvictThreads) void evict_select(EvictParams p) {
         // One composite 64-bit value per entry orders both at once.
         uint64_t best = ~0ull;
         const int n4 = (p.S % 4 == 0) ? (n / 4) * 4 : 0;   // float4 reads need aligned rows
-        for (int i = tid * 4; i < n4; i += kEvictThreads * 4) {
+        for (int i = tid * 4; i < n4; i += THREADS * 4) {
             const float4 v = *reinterpret_cast<const float4 *>(u + i);
             const uint64_t c0 = evict_composite(v.x, i), c1 = evict_composite(v.y, i + 1);
             const uint64_t c2 = evict_composite(v.z, i + 2), c3 = evict_composite(v.w, i + 3);
@@ -331,7 +340,7 @@ __global__ __launch_bounds__(kEvictThreads) void evict_select(EvictParams p) {
             const uint64_t c = a < b2 ? a : b2;
             best = c < best ? c : best;
         }
-        for (int i = n4 + tid; i < n; i += kEvictThreads) {
+        for (int i = n4 + tid; i < n; i += THREADS) {
             const uint64_t c = evict_composite(u[i], i);
             best = c < best ? c : best;
         }
@@ -345,7 +354,7 @@ __global__ __launch_bounds__(kEvictThreads) void evict_select(EvictParams p) {
         if (tid == 0) {
             uint64_t m = sh.wave_best[0];
 #pragma unroll
-            for (int w = 1; w < kSelWaves; ++w) m = sh.wave_best[w] < m ? sh.wave_best[w] : m;
+            for (int w = 1; w < THREADS / kWave; ++w) m = sh.wave_best[w] < m ? sh.wave_best[w] : m;
             p.evicted_idx[(int64_t)be * p.max_evict] = evict_composite_slot(m);
             p.evicted_cnt[be] = 1;
             p.n_valid[be] = p.capacity;
@@ -355,10 +364,9 @@ __global__ __launch_bounds__(kEvictThreads) void evict_select(EvictParams p) {
 
     // keys held per thread: the next size that covers n; beyond the largest, re-read them
     const bool vec = p.S % 4 == 0 && (reinterpret_cast<uintptr_t>(p.utility) & 15) == 0;
-    if (!vec || n > kSelCache * kEvictThreads) select_stream(p, be, u, n, ngone, sh);
-    else if (n <= 8 * kEvictThreads) select_cached<8>(p, be, u, n, ngone, sh);
-    else if (n <= 32 * kEvictThreads) select_cached<32>(p, be, u, n, ngone, sh);
-    else select_cached<kSelCache>(p, be, u, n, ngone, sh);
+    if (n <= 8 * THREADS) select_cached<THREADS, 8>(p, be, u, n, ngone, vec, sh);
+    else if (THREADS == 1024 && n <= kSelCache * THREADS) select_cached<THREADS, kSelCache>(p, be, u, n, ngone, vec, sh);
+    else select_stream<THREADS>(p, be, u, n, ngone, sh);
     if (tid == 0) {
         p.evicted_cnt[be] = ngone;
         p.n_valid[be] = p.capacity;
@@ -376,6 +384,7 @@ struct MoveParams {
     int max_evict;
 };
 
+constexpr int kMaxRowChunks = 256;
 constexpr int kMoveThreads = 1024;       // at most; 256 for shards of few slots (kMoveFewSlots)
 constexpr int kMoveFewSlots = 1024;
 constexpr int kMoveRows = 4;             // rows a thread carries per pass
@@ -514,7 +523,7 @@ struct AppendParams {
     int E, S, Hkv, k, row_chunks, max_evict;
 };
 
-__global__ __launch_bounds__(kEvictThreads) void append_rows(AppendParams p) {
+__global__ __launch_bounds__(kAppendThreads) void append_rows(AppendParams p) {
     const int b = blockIdx.x / p.k, j = blockIdx.x - b * p.k;
     const int e = p.topk[(int64_t)b * p.k + j];
     const int be = b * p.E + e;
@@ -559,7 +568,7 @@ extern "C" int pikv_evict(const pikv_desc *desc, float *utility, int32_t *n_vali
     if (compact && (!K_shards || !V_shards)) return PIKV_ERR_INVALID;
     if (desc->B == 0) return PIKV_OK;
     const int row_chunks = desc_width(desc) * elem_bytes(desc->dtype) / 16;
-    if (compact && (row_chunks < 1 || row_chunks > kEvictThreads)) return PIKV_ERR_UNSUPPORTED;
+    if (compact && (row_chunks < 1 || row_chunks > kMaxRowChunks)) return PIKV_ERR_UNSUPPORTED;
     hipStream_t st = as_stream(stream);
     EvictParams p;
     p.utility = utility;
@@ -573,7 +582,9 @@ extern "C" int pikv_evict(const pikv_desc *desc, float *utility, int32_t *n_vali
     p.sel_k = sel_k;
     p.max_evict = max_evict;
     p.compact = compact ? 1 : 0;
-    hipLaunchKernelGGL(evict_select, dim3(desc->B * desc->E), dim3(kEvictThreads), 0, st, p);
+    const dim3 shards(desc->B * desc->E);
+    if (desc->S <= kSelFewSlots) hipLaunchKernelGGL(evict_select<256>, shards, dim3(256), 0, st, p);
+    else hipLaunchKernelGGL(evict_select<1024>, shards, dim3(1024), 0, st, p);
     int lrc = launch_status();
     if (lrc != PIKV_OK || !compact) return lrc;
     MoveParams m;
@@ -635,7 +646,7 @@ extern "C" int pikv_append(const pikv_desc *desc, const void *K_new, const void 
     p.k = k;
     p.row_chunks = desc_width(desc) * eb / 16;
     p.max_evict = max_evict;
-    hipLaunchKernelGGL(append_rows, dim3(desc->B * k), dim3(kEvictThreads), 0, as_stream(stream),
+    hipLaunchKernelGGL(append_rows, dim3(desc->B * k), dim3(kAppendThreads), 0, as_stream(stream),
                        p);
     return launch_status();
 }

@@ -504,6 +504,13 @@ def test_evict_matches_oracle_bit_exact(S, capacity, ties):
     np.testing.assert_array_equal(t2n(dc.utility), u_ref)
 
 
+@pytest.mark.parametrize("S", [2047, 2048, 2049, 4099, 8192, 8193, 32768, 32771])
+@pytest.mark.parametrize("ties", [False, True], ids=["distinct", "ties"])
+def test_evict_matches_oracle_at_the_edges_of_the_select_shapes(S, ties):
+    """Block sizes, keys per thread and rows that are not 16-byte aligned change at these capacities."""
+    test_evict_matches_oracle_bit_exact(S, S * 3 // 4, ties)
+
+
 def test_evict_special_values_and_selection_list():
     g = wl.Geometry(B=2, Hq=2, Hkv=2, D=16, E=4, S=64, k=2, dtype="bf16")
     rng = np.random.default_rng(3)
