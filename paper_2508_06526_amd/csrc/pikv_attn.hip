@@ -558,7 +558,9 @@ struct GqaShape {
     static constexpr int kQueryParts = CODES ? 3 : 1;
     // Probabilities: 3 parts are the fp32 value, 2 parts differ from it by 2^-17.  Rows of 128
     // values have always used 2 (y is 1.9e-6 off 64 bits); the narrower rows were summed in fp32
-    // on the vector units (2e-7) and keep that.
+    // on the vector units and keep that: y against 64 bits 1.5 - 1.8e-7 (64 values) and 1.8 - 2.5e-7
+    // (codes), from 1.5 - 1.8e-7 and 2.0 - 2.6e-7, with the two small parts summed apart from the
+    // running output (added to it part by part: up to 2.8e-7).
     static constexpr int kProbParts = W == 128 ? 2 : 3;
 };
 
@@ -807,16 +809,19 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
 #pragma unroll
             for (int hb = 0; hb < 2 * SUBS; ++hb) {
                 f32x4_t sc = f32x4_t{0.f, 0.f, 0.f, 0.f};
+                Operand a[KS];
 #pragma unroll
                 for (int s = 0; s < KS; ++s) {
-                    const Operand a = k_operand(kst + (16 * hb + c) * PITCH, s);
-                    if constexpr (QLDS) {
-                        sc = mfma_rows(a, *reinterpret_cast<const uint4 *>(lds_q + (rt * 16 + c) * PITCH + 64 * s + 16 * r),
+                    a[s] = k_operand(kst + (16 * hb + c) * PITCH, s);
+                    if constexpr (QLDS)
+                        sc = mfma_rows(a[s], *reinterpret_cast<const uint4 *>(lds_q + (rt * 16 + c) * PITCH + 64 * s + 16 * r),
                                        sc);
-                    } else {
+                }
+                if constexpr (!QLDS) {       // the small parts first
 #pragma unroll
-                        for (int k = QP - 1; k >= 0; --k) sc = mfma_rows(a, qop[rt][s][k], sc);
-                    }
+                    for (int k = QP - 1; k >= 0; --k)
+#pragma unroll
+                        for (int s = 0; s < KS; ++s) sc = mfma_rows(a[s], qop[rt][s][k], sc);
                 }
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
@@ -909,8 +914,13 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
                                          __builtin_amdgcn_perm(v[5][i >> 1], v[4][i >> 1], sel),
                                          __builtin_amdgcn_perm(v[7][i >> 1], v[6][i >> 1], sel));
                     }
-#pragma unroll
-                    for (int k = PP - 1; k >= 0; --k) oacc[rt][i] = mfma_rows(vop, pop[k], oacc[rt][i]);
+                    if constexpr (PP == 3) {
+                        f32x4_t small = mfma_rows(vop, pop[2], f32x4_t{0.f, 0.f, 0.f, 0.f});
+                        small = mfma_rows(vop, pop[1], small);
+                        oacc[rt][i] = mfma_rows(vop, pop[0], oacc[rt][i]) + small;
+                    } else {
+                        oacc[rt][i] = mfma_rows(vop, pop[0], mfma_rows(vop, pop[1], oacc[rt][i]));
+                    }
                 }
             }
         }
