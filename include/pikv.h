@@ -154,7 +154,8 @@ int pikv_sharded_attn(const pikv_desc *desc, const void *q, const void *const *K
  * different threads) race; serialise them.  The first call on each GPU looks the array's
  * address up (no stream work); make that call outside graph capture.
  * Errors: as pikv_sharded_attn; WORKSPACE when pikv_attn_workspace_bytes(desc, k) exceeds
- * PIKV_NOALLOC_SCRATCH_BYTES (use pikv_sharded_attn with a workspace then); HIP if the array's
+ * PIKV_NOALLOC_SCRATCH_BYTES (use pikv_sharded_attn with a workspace then) - but for groups of
+ * bf16 rows narrower than 128 values, which take fewer splits while those fit; HIP if the array's
  * address cannot be resolved.                                                              */
 #define PIKV_NOALLOC_SCRATCH_BYTES (4u << 20)
 int pikv_sharded_attn_noalloc(const pikv_desc *desc, const void *q, const void *const *K_shards,

@@ -1045,7 +1045,7 @@ static int g_split_override = 0;   // tuning hook, see pikv_set_attn_split
 static hipEvent_t g_prof_start = nullptr, g_prof_stop = nullptr;   // see pikv_set_profile_events
 void g_split_override_set(int v) { g_split_override = v > 0 ? v : 0; }
 
-int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan) {
+int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_limit) {
     const int rc = check_desc(d);
     if (rc != PIKV_OK) return rc;
     if (k < 1 || k > d->E) return PIKV_ERR_INVALID;
@@ -1077,6 +1077,11 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan) {
     if (gqa_mfma && W == 128 && gb > 8 && resident > 2) resident = 2;
     int64_t nsplit = 1;
     int chunk = 0;
+    // Splits whose partials fit the fixed array of the call without a workspace: rows narrower than
+    // 128 values in groups want more of them than the kernel that took these calls before, and are
+    // not refused for it.
+    const size_t split_bytes = (size_t)(d->B > 0 ? d->B : 1) * d->Hq * k * (W + 2) * sizeof(float);
+    const int64_t scratch_splits = scratch_limit == SIZE_MAX || !gqa_mfma || W == 128 ? INT32_MAX : (int64_t)((scratch_limit - 1024) / split_bytes);
     auto split_for = [&](int res) {
         nsplit = units > 0 ? (int64_t)256 * res / units : 1;
         // No finer than two tiles per wave: with one, nothing is in flight while a wave computes,
@@ -1091,6 +1096,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan) {
         if (max_split < 1) max_split = 1;
         if (nsplit > max_split) nsplit = max_split;
         if (nsplit > kMaxPartialsPerHead / k) nsplit = kMaxPartialsPerHead / k;
+        if (nsplit > scratch_splits) nsplit = scratch_splits;
         if (nsplit < 1) nsplit = 1;
         chunk = (int)((d->S + nsplit - 1) / nsplit);
         chunk = (chunk + tile - 1) / tile * tile;
@@ -1104,7 +1110,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan) {
         const int even = 2 * kWavesPerBlock * tile;
         const int64_t fine = d->S / even;
         if (gqa_mfma && g_split_override == 0 && chunk % (kWavesPerBlock * tile) != 0 && d->S % even == 0 &&
-            fine > nsplit && fine * 3 <= nsplit * 4 && fine <= kMaxPartialsPerHead / k &&
+            fine > nsplit && fine * 3 <= nsplit * 4 && fine <= kMaxPartialsPerHead / k && fine <= scratch_splits &&
             (units * fine) % 256 == 0) {
             nsplit = fine;
             chunk = even;
@@ -1170,12 +1176,16 @@ extern "C" void pikv_set_profile_events(void *start, void *stop) {
     pikv::g_profile_events_set(start, stop);
 }
 
-extern "C" size_t pikv_attn_workspace_bytes(const pikv_desc *desc, int32_t k) {
+static size_t workspace_bytes_within(const pikv_desc *desc, int32_t k, size_t scratch_limit) {
     AttnPlan plan;
-    if (make_attn_plan(desc, k, &plan) != PIKV_OK) return 0;
+    if (make_attn_plan(desc, k, &plan, scratch_limit) != PIKV_OK) return 0;
     const size_t acc = (plan.acc_floats * sizeof(float) + 255) / 256 * 256;
     const size_t ml = (plan.ml_floats * sizeof(float) + 255) / 256 * 256;
     return acc + ml + 256;
+}
+
+extern "C" size_t pikv_attn_workspace_bytes(const pikv_desc *desc, int32_t k) {
+    return workspace_bytes_within(desc, k, SIZE_MAX);
 }
 
 namespace pikv {
@@ -1185,9 +1195,9 @@ int check_attn_args(const pikv_desc *desc, const void *q, const void *const *K_s
                     const void *const *V_shards, const void *U_K, const void *U_V,
                     const int32_t *n_valid, const int32_t *topk_idx, int32_t k, int32_t combine,
                     float scale, const float *y, const void *workspace, size_t workspace_bytes,
-                    AttnPlan *plan_out) {
+                    AttnPlan *plan_out, size_t scratch_limit) {
     AttnPlan plan;
-    const int rc = make_attn_plan(desc, k, &plan);
+    const int rc = make_attn_plan(desc, k, &plan, scratch_limit);
     if (rc != PIKV_OK) return rc;
     if (!q || !K_shards || !V_shards || !n_valid || !topk_idx || !y) return PIKV_ERR_INVALID;
     if (desc->rank > 0 && (!U_K || !U_V)) return PIKV_ERR_INVALID;
@@ -1195,7 +1205,7 @@ int check_attn_args(const pikv_desc *desc, const void *q, const void *const *K_s
     if (!(scale == scale)) return PIKV_ERR_INVALID;
     *plan_out = plan;
     if (desc->B == 0) return PIKV_OK;
-    const size_t need = pikv_attn_workspace_bytes(desc, k);
+    const size_t need = workspace_bytes_within(desc, k, scratch_limit);
     if (!workspace || workspace_bytes < need) return PIKV_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return PIKV_ERR_INVALID;
     if ((int64_t)desc->B * plan.head_blocks * k * plan.nsplit > 0x7fffffff) return PIKV_ERR_UNSUPPORTED;
@@ -1211,10 +1221,10 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
                         int32_t k, int32_t combine, float scale, float *y, float *row_max,
                         float *row_norm, float *scores, float *slot_coef, void *workspace,
                         size_t workspace_bytes, void *stream, AttnPlan *plan_out,
-                        CombineParams *c_out) {
+                        CombineParams *c_out, size_t scratch_limit) {
     AttnPlan plan;
     const int rc = check_attn_args(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, k, combine,
-                                   scale, y, workspace, workspace_bytes, &plan);
+                                   scale, y, workspace, workspace_bytes, &plan, scratch_limit);
     if (rc != PIKV_OK) return rc;
     *plan_out = plan;
     if (desc->B == 0) return PIKV_OK;
@@ -1319,6 +1329,20 @@ int pikv_sharded_attn_merge(const pikv_desc *desc, const CombineParams *c, void 
 }
 }  // namespace pikv
 
+static int sharded_attn(const pikv_desc *desc, const void *q, const void *const *K_shards,
+                        const void *const *V_shards, const void *U_K, const void *U_V, const int32_t *n_valid,
+                        const int32_t *topk_idx, const float *gates, int32_t k, int32_t combine, float scale,
+                        float *y, float *row_max, float *row_norm, float *scores, float *slot_coef,
+                        void *workspace, size_t workspace_bytes, void *stream, size_t scratch_limit) {
+    AttnPlan plan;
+    CombineParams c;
+    const int rc = launch_attn_partial(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates,
+                                       k, combine, scale, y, row_max, row_norm, scores, slot_coef,
+                                       workspace, workspace_bytes, stream, &plan, &c, scratch_limit);
+    if (rc != PIKV_OK || desc->B == 0) return rc;
+    return pikv_sharded_attn_merge(desc, &c, stream);
+}
+
 extern "C" int pikv_sharded_attn(const pikv_desc *desc, const void *q, const void *const *K_shards,
                                  const void *const *V_shards, const void *U_K, const void *U_V,
                                  const int32_t *n_valid, const int32_t *topk_idx,
@@ -1326,13 +1350,8 @@ extern "C" int pikv_sharded_attn(const pikv_desc *desc, const void *q, const voi
                                  float *y, float *row_max, float *row_norm, float *scores,
                                  float *slot_coef, void *workspace, size_t workspace_bytes,
                                  void *stream) {
-    AttnPlan plan;
-    CombineParams c;
-    const int rc = launch_attn_partial(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates,
-                                       k, combine, scale, y, row_max, row_norm, scores, slot_coef,
-                                       workspace, workspace_bytes, stream, &plan, &c);
-    if (rc != PIKV_OK || desc->B == 0) return rc;
-    return pikv_sharded_attn_merge(desc, &c, stream);
+    return sharded_attn(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates, k, combine, scale, y,
+                        row_max, row_norm, scores, slot_coef, workspace, workspace_bytes, stream, SIZE_MAX);
 }
 
 // ---------------------------------------------------------------------------------------
@@ -1369,13 +1388,13 @@ extern "C" int pikv_sharded_attn_noalloc(const pikv_desc *desc, const void *q, c
                                          const float *gates, int32_t k, int32_t combine, float scale,
                                          float *y, float *row_max, float *row_norm, float *scores,
                                          float *slot_coef, void *stream) {
-    const size_t need = pikv_attn_workspace_bytes(desc, k);
+    const size_t need = workspace_bytes_within(desc, k, kStaticScratchBytes);
     if (need > kStaticScratchBytes) return PIKV_ERR_WORKSPACE;   // geometry too large for the fixed array
     void *ws = nullptr;
     const int rc = static_scratch(&ws);
     if (rc != PIKV_OK) return rc;
     // Every partial the merge reads is written by the split pass of the same call (empty splits
     // write an empty partial), so nothing in the array has to start at zero.
-    return pikv_sharded_attn(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates, k, combine,
-                             scale, y, row_max, row_norm, scores, slot_coef, ws, kStaticScratchBytes, stream);
+    return sharded_attn(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates, k, combine, scale, y,
+                        row_max, row_norm, scores, slot_coef, ws, kStaticScratchBytes, stream, kStaticScratchBytes);
 }

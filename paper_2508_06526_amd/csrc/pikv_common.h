@@ -199,7 +199,7 @@ struct AttnPlan {
     size_t acc_floats;    // B*Hq*k*nsplit*width
     size_t ml_floats;     // B*Hq*k*nsplit*2
 };
-int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan);
+int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_limit = SIZE_MAX);
 void g_split_override_set(int v);
 void g_profile_events_set(void *start, void *stop);
 

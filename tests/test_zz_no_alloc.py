@@ -64,3 +64,22 @@ def test_no_alloc_attention_rejects_a_geometry_beyond_its_fixed_scratch():
         pk.pikv_sharded_attn_noalloc(desc, fake, fake, fake, None, None, fake, fake, None, g.k, pk.COMBINE_LSE,
                                      0.0, fake, None, None, None, None)
     assert err.value.status == -3
+
+
+def test_no_alloc_attention_takes_fewer_splits_where_the_planned_ones_do_not_fit():
+    """64 heads over one kv head of 64-value rows: the plan's splits want more than the fixed array, the
+    call runs with those that fit (and equals the workspace call with as many)."""
+    spec = dict(B=2, Hq=64, Hkv=1, D=64, E=4, S=8192, k=4, dtype="bf16")
+    g = wl.Geometry(**spec)
+    desc = pk.make_desc(g.B, g.Hq, g.Hkv, g.D, g.E, g.S, dtype=1)
+    assert pk.pikv_attn_workspace_bytes(desc, g.k) > pk.NOALLOC_SCRATCH_BYTES
+    case = wl.make_host_case(g, seed=3, zipf_s=1.1)
+    ensure_route_margin(case, g.k)
+    d = DeviceCase(case)
+    d.route()
+    d.attend()
+    y = t2n(d.y)
+    d.y.zero_()
+    pk.pikv_sharded_attn_noalloc(d.desc, d.q, d.K_tab, d.V_tab, None, None, d.n_valid, d.topk, d.gates, d.k,
+                                 pk.COMBINE_LSE, 0.0, d.y, d.row_max, d.row_norm, d.scores, d.slot_coef)
+    assert np.linalg.norm(t2n(d.y) - y) <= 2e-6 * np.linalg.norm(y)      # fp32 sums in another order
