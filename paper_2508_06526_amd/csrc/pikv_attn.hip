@@ -508,6 +508,30 @@ __device__ __forceinline__ void split_bf16(const float *v, OP (&out)[PARTS]) {
     for (int k = 0; k < PARTS; ++k) out[k] = __builtin_bit_cast(OP, words[k]);
 }
 
+// 8 probabilities as 3 parts, each the leading 8 bits of what is left: all 24 bits, none of the parts
+// negative, and one that would be zero is the smallest normal number.  An infinite value of V then
+// gives the infinity of the unsplit product, where a zero or a negative part would make it NaN.
+// (The lift adds 2^-126 of a value of V.)
+__device__ __forceinline__ void split_bf16_up(const float *v, uint4 (&out)[3]) {
+    typedef uint16_t u16x2_t __attribute__((ext_vector_type(2)));
+    auto upper = [](float hi, float lo) { return __builtin_amdgcn_perm(__float_as_uint(hi), __float_as_uint(lo), 0x07060302u); };
+    auto rest = [](float x) { return x - __uint_as_float(__float_as_uint(x) & 0xffff0000u); };
+    auto lift = [](uint32_t part) {
+        const u16x2_t least = {0x0080, 0x0080};
+        return __builtin_bit_cast(uint32_t, __builtin_elementwise_max(__builtin_bit_cast(u16x2_t, part), least));
+    };
+    uint32_t w[3][4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const float a = v[2 * u], b = v[2 * u + 1], a1 = rest(a), b1 = rest(b);
+        w[0][u] = upper(b, a);
+        w[1][u] = lift(upper(b1, a1));
+        w[2][u] = lift(upper(rest(b1), rest(a1)));
+    }
+#pragma unroll
+    for (int k = 0; k < 3; ++k) out[k] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
+}
+
 __device__ __forceinline__ f32x4_t mfma_rows(uint4 a, uint4 b, f32x4_t acc) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
                                                    acc, 0, 0, 0);
@@ -556,6 +580,9 @@ struct GqaShape {
     // the latency (at four row tiles the kernel is bound by the matrix cores, not by memory).
     static constexpr bool kPrefetchK = !kQueryInLds;
     static constexpr int kQueryParts = CODES ? 3 : 1;
+    // The lane's part of the row addresses is formed again for each tile instead of held (4 registers):
+    // where the shape would spill otherwise.
+    static constexpr bool kLeanAddresses = CODES && ((W == 64 && RT == 1) || (W == 16 && RT == 4));
     // Probabilities: 3 parts are the fp32 value, 2 parts differ from it by 2^-17.  Rows of 128
     // values have always used 2 (y is 1.9e-6 off 64 bits); the narrower rows were summed in fp32
     // on the vector units and keep that: y against 64 bits 1.5 - 1.8e-7 (64 values) and 1.8 - 2.5e-7
@@ -672,8 +699,6 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
     const uint32_t rb = (uint32_t)(p.stride_s * 2);
     const int k_row = lane / Row::kKLanes;
     const uint32_t k_col = 16u * (lane & (Row::kKLanes - 1));
-    const uint32_t v_col = 4u * Row::kVWords * (Row::kPairs ? c & 7 : c);
-    const uint32_t k_lane = (uint32_t)k_row * rb + k_col, v_lane = (uint32_t)(4 * r + (Row::kPairs ? c >> 3 : 0)) * rb + v_col;
     const uint32_t last = (uint32_t)(r1 - 1) * rb;
 
     // (Each tile's offset is hidden from the optimiser: it would otherwise carry one running
@@ -685,19 +710,23 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
     uint4 kr[Row::kKLoads];
     uint32_t vr[SUBS][Row::kVLoads][Row::kVWords];
     auto load_k = [&](int t0) {
-        const uint32_t at = opaque((uint32_t)t0 * rb + k_lane);
+        const uint32_t ln = Shape::kLeanAddresses ? opaque(lane) : lane;
+        const uint32_t col = 16u * (ln & (Row::kKLanes - 1));
+        const uint32_t at = opaque((uint32_t)t0 * rb + ((ln / Row::kKLanes) * rb + col));
 #pragma unroll
         for (int t = 0; t < Row::kKLoads; ++t)
-            kr[t] = load16_stream(Kb + (size_t)min(at + (uint32_t)(t * Row::kKRows) * rb, last + k_col));
+            kr[t] = load16_stream(Kb + (size_t)min(at + (uint32_t)(t * Row::kKRows) * rb, last + col));
     };
     auto load_v = [&](int t0) {
-        const uint32_t at = opaque((uint32_t)t0 * rb + v_lane);
+        const uint32_t ln = Shape::kLeanAddresses ? opaque(lane) : lane;
+        const uint32_t col = 4u * Row::kVWords * (ln & (Row::kPairs ? 7 : 15));
+        const uint32_t at = opaque((uint32_t)t0 * rb + ((4 * (ln >> 4) + (Row::kPairs ? (ln & 15) >> 3 : 0)) * rb + col));
 #pragma unroll
         for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
             for (int t = 0; t < Row::kVLoads; ++t)
                 load_words_stream<Row::kVWords>(
-                    vr[sub][t], Vb + (size_t)min(at + (uint32_t)(sub * kSubTile + Row::v_step(t)) * rb, last + v_col));
+                    vr[sub][t], Vb + (size_t)min(at + (uint32_t)(sub * kSubTile + Row::v_step(t)) * rb, last + col));
     };
     if constexpr (!CODES && !QLDS) {         // ahead of the tile's rows: loads come back in order
         auto load_q = [&](auto aligned) {
@@ -817,11 +846,20 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
                         sc = mfma_rows(a[s], *reinterpret_cast<const uint4 *>(lds_q + (rt * 16 + c) * PITCH + 64 * s + 16 * r),
                                        sc);
                 }
-                if constexpr (!QLDS) {       // the small parts first
+                if constexpr (QP > 1) {
+                    // The small parts first, and kept finite: an infinite code against a part that is zero
+                    // or of the other sign is NaN, where the unsplit query scores an infinity (-Inf: the
+                    // entry drops out of the softmax).  (The median of a NaN and two numbers is a number.)
 #pragma unroll
-                    for (int k = QP - 1; k >= 0; --k)
+                    for (int k = QP - 1; k >= 1; --k)
 #pragma unroll
                         for (int s = 0; s < KS; ++s) sc = mfma_rows(a[s], qop[rt][s][k], sc);
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) sc[x] = __builtin_amdgcn_fmed3f(sc[x], -3e38f, 3e38f);
+                }
+                if constexpr (!QLDS) {
+#pragma unroll
+                    for (int s = 0; s < KS; ++s) sc = mfma_rows(a[s], qop[rt][s][0], sc);
                 }
 #pragma unroll
                 for (int x = 0; x < 4; ++x) {
@@ -896,7 +934,8 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
 #pragma unroll
             for (int sub = 0; sub < SUBS; ++sub) {
                 uint4 pop[PP];
-                split_bf16(sv + 8 * sub, pop);
+                if constexpr (PP == 3) split_bf16_up(sv + 8 * sub, pop);
+                else split_bf16(sv + 8 * sub, pop);
                 const auto &v = vr[sub];
 #pragma unroll
                 for (int i = 0; i < SETS; ++i) {

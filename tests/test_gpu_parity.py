@@ -381,6 +381,43 @@ def test_grouped_rows_of_every_width_match_oracle(spec, offset):
 
 
 @pytest.mark.parametrize("spec", [
+    dict(B=1, Hq=6, Hkv=2, D=16, E=2, S=1024, k=2), dict(B=1, Hq=16, Hkv=2, D=32, E=2, S=1024, k=2),
+    dict(B=16, Hq=14, Hkv=2, D=64, E=4, S=1024, k=4), dict(B=8, Hq=48, Hkv=2, D=64, E=4, S=1024, k=4),
+    dict(B=2, Hq=128, Hkv=2, D=64, E=4, S=4096, k=4), dict(B=4, Hq=16, Hkv=4, D=128, E=4, S=1024, k=4, rank=16),
+    dict(B=8, Hq=20, Hkv=2, D=64, E=4, S=1024, k=4, rank=32), dict(B=4, Hq=32, Hkv=4, D=128, E=2, S=2048, k=2, rank=64),
+    dict(B=8, Hq=64, Hkv=1, D=32, E=4, S=4096, k=4, rank=32),
+], ids=lambda s: "D%d_r%d_G%d" % (s["D"], s.get("rank", 0), s["Hq"] // s["Hkv"]))
+def test_infinite_entries_of_narrow_groups_stay_infinite(spec):
+    """A value of +-Inf with a probability above zero makes its output +-Inf (not NaN: the probability's
+    bf16 parts must not meet it with a zero or a negative one), and an entry whose code is infinite so that it
+    scores -Inf drops out of the softmax; what neither reaches keeps its tolerance."""
+    g = wl.Geometry(dtype="bf16", **spec)
+    case = wl.make_host_case(g, seed=g.S + g.Hq, utility0="exp")
+    inf, ninf = np.uint16(0x7F80), np.uint16(0xFF80)
+    for s, at in ((0, 700), (g.B * g.E - 1, g.S - 300)):      # shards are [Hkv, S, width]
+        case.V_shards[s][0, at, 3], case.V_shards[s][g.Hkv - 1, at + 1, 5] = inf, ninf
+        if g.rank:     # q and the decoder row of one code column are positive: the entry scores -Inf for all heads
+            case.K_shards[s][0, at + 9, 7] = ninf
+            case.V_shards[s][0, at + 9] = 0
+    if g.rank:
+        case.q &= np.uint16(0x7FFF)
+        case.U_K[:, 7] &= np.uint16(0x7FFF)
+    idx, gates = random_selection(g, 2)
+    ref = oracle_step(case, idx, gates, orc.COMBINE_LSE)
+    dc = DeviceCase(case)
+    d_idx, d_gates = torch.from_numpy(idx).to(DEV), torch.from_numpy(gates).to(DEV)
+    for want_scores in (True, False):
+        dc.y.fill_(7.0)
+        dc.attend(topk=d_idx, gates=d_gates, want_scores=want_scores)
+        y = t2n(dc.y)
+        assert np.isinf(ref["y"]).any() and np.isfinite(ref["y"]).any()
+        for kind in (np.isposinf, np.isneginf, np.isnan):
+            np.testing.assert_array_equal(kind(y), kind(ref["y"]), err_msg=kind.__name__)
+        ok = np.isfinite(ref["y"])
+        assert np.linalg.norm(y[ok] - ref["y"][ok]) <= 1e-6 * np.linalg.norm(ref["y"][ok])
+
+
+@pytest.mark.parametrize("spec", [
     dict(B=1, Hq=8, Hkv=2, D=128, E=12, S=2304, k=12, dtype="bf16"),       # matrix cores, 128 rows a round
     dict(B=1, Hq=6, Hkv=2, D=64, E=12, S=2051, k=12, dtype="bf16", rank=32),
     dict(B=1, Hq=2, Hkv=2, D=128, E=12, S=2304, k=12, dtype="bf16"),       # plain ALU
