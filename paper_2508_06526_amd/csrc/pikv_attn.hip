@@ -426,7 +426,6 @@ constexpr int gqa_tile(int width, int row_tiles) {
     if (width == 128 || (width == 64 && row_tiles == 4)) return kSubTile;
     return kSubTile * (width == 16 ? 4 : 2);
 }
-constexpr int kClampRows = 128;   // the loads address at most a tile past a shard's last row before they are clamped
 
 // Bytes per staged K row: the row plus 16 of padding, so that the 16 lanes reading one 16-byte
 // column of 16 different rows do not all start in the same bank.
@@ -692,10 +691,12 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
     const char *Kb = sh.K + (int64_t)hk * p.stride_h * 2;
     const char *Vb = sh.V + (int64_t)hk * p.stride_h * 2;
     // Byte offsets of the lane's rows from the kv head's base, in 32 bits (the host admits this
-    // kernel only where they fit): rows past the end are clamped onto the last valid row - one
-    // minimum per load, no branch around any - and masked out of the softmax.  (Two forms of the
-    // loads, full tiles from a wave-uniform base and clamped ones for the last tile, cost 20
-    // registers more: 124 bytes of spills at one row tile of 128 values.)
+    // kernel only where a shard's fit): rows past the end are clamped onto the last valid row - one
+    // minimum per load, no branch around any - and masked out of the softmax.  The requests run up to
+    // five tiles past the end, so the sums saturate instead of wrapping: with terms of at most the
+    // S - 1 rows below a shard's last, a sum that does not fit lies past it.  (Two forms of the loads, full tiles from
+    // a wave-uniform base and clamped ones for the last tile, cost 20 registers more: 124 bytes of
+    // spills at one row tile of 128 values.)
     const uint32_t rb = (uint32_t)(p.stride_s * 2);
     const int k_row = lane / Row::kKLanes;
     const uint32_t k_col = 16u * (lane & (Row::kKLanes - 1));
@@ -709,24 +710,27 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
     };
     uint4 kr[Row::kKLoads];
     uint32_t vr[SUBS][Row::kVLoads][Row::kVWords];
+    const int row_most = p.S - 1;
+    auto rows_bytes = [&](int rows) { return (uint32_t)min(rows, row_most) * rb; };
+    auto sum = [](uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); };
     auto load_k = [&](int t0) {
-        const uint32_t ln = Shape::kLeanAddresses ? opaque(lane) : lane;
+        const int ln = Shape::kLeanAddresses ? opaque(lane) : lane;
         const uint32_t col = 16u * (ln & (Row::kKLanes - 1));
-        const uint32_t at = opaque((uint32_t)t0 * rb + ((ln / Row::kKLanes) * rb + col));
+        const uint32_t at = opaque(sum(rows_bytes(t0), rows_bytes(ln / Row::kKLanes) + col));
 #pragma unroll
         for (int t = 0; t < Row::kKLoads; ++t)
-            kr[t] = load16_stream(Kb + (size_t)min(at + (uint32_t)(t * Row::kKRows) * rb, last + col));
+            kr[t] = load16_stream(Kb + (size_t)min(sum(at, rows_bytes(t * Row::kKRows)), last + col));
     };
     auto load_v = [&](int t0) {
-        const uint32_t ln = Shape::kLeanAddresses ? opaque(lane) : lane;
+        const int ln = Shape::kLeanAddresses ? opaque(lane) : lane;
         const uint32_t col = 4u * Row::kVWords * (ln & (Row::kPairs ? 7 : 15));
-        const uint32_t at = opaque((uint32_t)t0 * rb + ((4 * (ln >> 4) + (Row::kPairs ? (ln & 15) >> 3 : 0)) * rb + col));
+        const uint32_t at = opaque(sum(rows_bytes(t0), rows_bytes(4 * (ln >> 4) + (Row::kPairs ? (ln & 15) >> 3 : 0)) + col));
 #pragma unroll
         for (int sub = 0; sub < SUBS; ++sub)
 #pragma unroll
             for (int t = 0; t < Row::kVLoads; ++t)
                 load_words_stream<Row::kVWords>(
-                    vr[sub][t], Vb + (size_t)min(at + (uint32_t)(sub * kSubTile + Row::v_step(t)) * rb, last + col));
+                    vr[sub][t], Vb + (size_t)min(sum(at, rows_bytes(sub * kSubTile + Row::v_step(t))), last + col));
     };
     if constexpr (!CODES && !QLDS) {         // ahead of the tile's rows: loads come back in order
         auto load_q = [&](auto aligned) {
@@ -1095,7 +1099,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     // The matrix-core kernel takes every group of bf16 rows that shares one routing decision and
     // addresses a kv head's rows in 32 bits.
     const bool gqa_mfma = d->route_rows_per_seq == 1 && d->dtype == PIKV_BF16 && G >= 2 && G <= 64 &&
-                          ((int64_t)d->S + kClampRows) * d->stride_s * 2 < ((int64_t)1 << 32);
+                          (int64_t)d->S * d->stride_s * 2 < ((int64_t)1 << 32);
     if (gqa_mfma) gb = G;
     const int tq = d->tq > 1 ? d->tq : 1;
     // draft queries are folded into the query group of the matrix-core kernel's 128-value rows only

@@ -58,6 +58,17 @@ def test_workspace_size_is_zero_for_bad_geometry_and_positive_otherwise(lib):
     assert pk.pikv_attn_workspace_bytes(pk.make_desc(1, 32, 8, 128, 16, 8192, rank=24), 4) == 0
 
 
+def test_multi_query_steps_reach_to_the_32_bit_limit_of_a_kv_head(lib):
+    """Draft queries are taken as long as the rows of a kv head span less than 4 GiB, whatever the row
+    stride; from there on no kernel takes them."""
+    for S in (1, 8, 40, 8192):
+        below, at = ((1 << 31) - 8) // S // 8 * 8, -(-(1 << 31) // S // 8) * 8
+        assert S * below * 2 < 1 << 32 <= S * at * 2
+        for G in (2, 16, 32, 64):
+            assert pk.pikv_attn_workspace_bytes(pk.make_desc(1, G, 1, 128, 4, S, stride_s=below, dtype=1, tq=2), 2) > 0
+            assert pk.pikv_attn_workspace_bytes(pk.make_desc(1, G, 1, 128, 4, S, stride_s=at, dtype=1, tq=2), 2) == 0
+
+
 def test_host_side_argument_errors(lib):
     """NULL pointers / out-of-range sizes return PIKV_ERR_INVALID with no GPU present."""
     vp = C.c_void_p

@@ -450,6 +450,48 @@ def test_splits_follow_the_entry_count(spec, forced):
         assert np.isfinite(sc[0, :, j, :n]).all() and np.isnan(sc[0, :, j, n:]).all()
 
 
+@pytest.mark.parametrize("spec,tq", [
+    (dict(Hq=2, D=128, S=40), 2), (dict(Hq=16, D=128, S=300), 2), (dict(Hq=64, D=128, S=9), 4), (dict(Hq=3, D=128, S=33), 1),
+    (dict(Hq=2, D=16, S=40), 1), (dict(Hq=24, D=32, S=130), 1), (dict(Hq=4, D=64, S=700), 1),
+    (dict(Hq=8, D=128, rank=16, S=40), 1), (dict(Hq=5, D=64, rank=64, S=77), 1),
+], ids=lambda v: "tq%d" % v if isinstance(v, int) else "G%d_D%d_r%d_S%d" % (v["Hq"], v["D"], v.get("rank", 0), v["S"]))
+@pytest.mark.parametrize("limit", ["below", "at"])
+def test_rows_spread_over_4_GiB(spec, tq, limit):
+    """A kv head whose rows span nearly 4 GiB (32-bit offsets in the matrix-core kernel, its requests past the
+    end included) and one whose rows span it exactly (the plain kernel, groups of 2, 4 and 8 heads
+    among them) give the bits of densely stored ones, or those of the same kernel's dense form."""
+    g = wl.Geometry(B=1, Hkv=1, E=2, k=2, dtype="bf16", **spec)
+    half = (1 << 31) // g.S // 8 * 8
+    stride = half - 8 if limit == "below" else -(-(1 << 31) // g.S // 8) * 8
+    if limit == "at" and tq > 1:       # no kernel takes draft queries there
+        assert pk.pikv_attn_workspace_bytes(pk.make_desc(1, g.Hq, 1, g.D, 2, g.S, dtype=1, stride_s=stride, tq=tq), g.k) == 0
+        return
+    nv = np.array([[g.S, max(1, g.S - 3)]], np.int32)
+    case = wl.make_host_case(g, seed=g.S, n_valid=nv, utility0="exp")
+    idx, gates = random_selection(g, 1)
+    ref = oracle_step(case, idx, gates, orc.COMBINE_LSE)
+    d = DeviceCase(case)
+    d_idx, d_gates = torch.from_numpy(idx).to(DEV), torch.from_numpy(gates).to(DEV)
+    heap = torch.empty((g.S - 1) * stride + 4 * 1024, device=DEV, dtype=torch.bfloat16)   # all four shards, in each other's gaps
+    # gaps hold what a wrong offset would be punished for
+    heap.fill_(float("nan"))
+    w = g.width
+    shards = [heap[1024 * i:][:(g.S - 1) * stride + w].as_strided((g.S, w), (stride, 1)) for i in range(4)]
+    for e in range(2):
+        shards[e].copy_(d.K[e, 0, :g.S, :w])
+        shards[2 + e].copy_(d.V[e, 0, :g.S, :w])
+    d.K_tab, d.V_tab = pk.shard_table(shards[:2]), pk.shard_table(shards[2:])
+    d.desc = pk.make_desc(1, g.Hq, 1, g.D, 2, g.S, rank=g.rank, dtype=pk.binding.BF16, stride_s=stride, stride_h=0, tq=tq)
+    d.workspace = torch.empty(pk.pikv_attn_workspace_bytes(d.desc, g.k), device=DEV, dtype=torch.uint8)
+    d.attend(topk=d_idx, gates=d_gates)
+    y = t2n(d.y)
+    assert np.linalg.norm(y - ref["y"]) <= (8e-6 if w == 128 else 1e-6) * np.linalg.norm(ref["y"])
+    sc = t2n(d.scores)
+    for j in range(2):
+        n = nv[0, idx[0, j]]
+        assert np.isfinite(sc[0, :, j, :n]).all() and np.isnan(sc[0, :, j, n:]).all()
+
+
 def test_attention_is_bitwise_repeatable():
     spec, nv = ATTN_CASES["c3_scaled"]
     g = wl.Geometry(**spec)
