@@ -120,15 +120,21 @@ constexpr int plain_blocks_per_cu(int row_bytes, int gb) {
     return plain_short_rows(row_bytes, gb) ? 4 : gb == 1 ? 3 : (gb <= 4 ? 2 : 1);
 }
 
+// The most a CU is let hold: over short rows a sixth block fits and costs more than it gives (32 heads
+// over fp32 codes of rank 16, 1 GiB of them: 1646 us with five, 1780 with six).
+constexpr int plain_blocks_most(int row_bytes, int gb) { return plain_short_rows(row_bytes, gb) ? 5 : 8; }
+
 template <typename T, int W, int GB>
-__global__ __launch_bounds__(kWavesPerBlock *kWave, plain_blocks_per_cu(W * (int)sizeof(T), GB)) void attn_partial(
-    AttnParams p) {
+__global__ __launch_bounds__(kWavesPerBlock *kWave)
+__attribute__((amdgpu_waves_per_eu(plain_blocks_per_cu(W * (int)sizeof(T), GB), plain_blocks_most(W * (int)sizeof(T), GB)))) void
+attn_partial(AttnParams p) {
     constexpr int EPL = Pack16<T>::N;        // elements per lane per load
     constexpr int LPR = W / EPL;             // lanes covering one row
     constexpr int RPL = kWave / LPR;         // rows covered by one wave load
     constexpr int NL = plain_loads_per_tile(W * (int)sizeof(T), GB);
     constexpr int TILE = RPL * NL;           // rows per wave iteration
     constexpr int CB = ilog2(LPR);           // lane bits that index the column chunk
+    constexpr bool APART = GB <= 4 && !(EPL == 8 && W == 128);  // a wave's last tile: see the streaming loop
     static_assert(LPR >= 1 && LPR <= 32 && (LPR & (LPR - 1)) == 0, "row must be 16..512 bytes");
 
     const int tid = threadIdx.x;
@@ -194,8 +200,10 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, plain_blocks_per_cu(W * (int
         }
     };
     int t0 = r0 + wave * TILE;
-    load_tile(kr, Kb, t0);                   // (a wave without rows loads the last one)
-    load_tile(vr, Vb, t0);
+    if (!APART || t0 < r1) {                  // (past the end: the last row)
+        load_tile(kr, Kb, t0);
+        load_tile(vr, Vb, t0);
+    }
 
     // Stage the (scaled) query in LDS; for rank-r codes it is the projected query U_K q.
     const T *qp = static_cast<const T *>(p.q) + ((int64_t)b * p.Hq + h0) * p.D;
@@ -245,9 +253,17 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, plain_blocks_per_cu(W * (int
 
     // No request under a condition: with the next tile's K under `if (tnext < r1)` the compiler had
     // to allow for the path without it and waited, before a tile's V was used, for everything in
-    // flight.  (Pass and merge, one head per block: fp32 rows x 4 heads, 512 MiB 104 -> 97 us, x 8 heads
-    // 163 -> 147; bf16 shards a fifth full 44.6 -> 41.4; rank-32 codes 54.4 -> 53.5.)
-    if (t0 < r1) do {
+    // flight.  (Pass and merge: fp32 rows x 4 heads, 512 MiB 104 -> 97 us, x 8 heads 163 -> 147; bf16
+    // shards a fifth full 44.6 -> 41.4; rank-32 codes 54.4 -> 53.5.)  Instead a wave's last tile has a
+    // pass of its own that requests nothing: a tile requested past the end is a trip to memory that the
+    // block's end waits for (32 sequences x 64 heads over 16 kv heads x 3 shards of 64 fp32 codes: 31.8 ->
+    // 28.8 us; the longer code costs 4 heads x 1501 rows 17.2 -> 17.5).  Not with eight heads
+    // per block, which its arithmetic bounds (147 -> 152 us), nor over bf16 rows of 128 values (it spills):
+    // there the request past the end is the last row once more.
+#pragma unroll
+    for (int pass = APART ? 0 : 1; pass < 2; ++pass)
+    while (APART && pass == 0 ? t0 + kWavesPerBlock * TILE < r1 : t0 < r1) {
+        const bool more = !APART || pass == 0;
         const int tnext = t0 + kWavesPerBlock * TILE;
 
         // scores: each lane's partial dot over its EPL columns, summed over the row's lanes
@@ -266,7 +282,7 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, plain_blocks_per_cu(W * (int
                 s[t][g] = valid ? d : -INFINITY;
             }
         }
-        load_tile(kr, Kb, tnext);            // past the end: the clamped last row once more
+        if (more) load_tile(kr, Kb, tnext);
 
         if (p.scores != nullptr) {  // raw scores for the utility pass, one row per lane
 #pragma unroll
@@ -317,9 +333,9 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, plain_blocks_per_cu(W * (int
 #pragma unroll
                 for (int i = 0; i < EPL; ++i) acc[g][i] = fmaf(s[t][g], vf[i], acc[g][i]);
         }
-        load_tile(vr, Vb, tnext);
+        if (more) load_tile(vr, Vb, tnext);
         t0 = tnext;
-    } while (t0 < r1);
+    }
 
     // merge the row groups of the wave (same column chunk c, different r) ...
 #pragma unroll

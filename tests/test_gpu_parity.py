@@ -422,6 +422,10 @@ def test_infinite_entries_of_narrow_groups_stay_infinite(spec):
     dict(B=1, Hq=6, Hkv=2, D=64, E=12, S=2051, k=12, dtype="bf16", rank=32),
     dict(B=1, Hq=2, Hkv=2, D=128, E=12, S=2304, k=12, dtype="bf16"),       # plain ALU
     dict(B=1, Hq=4, Hkv=2, D=64, E=12, S=1030, k=12, dtype="f32"),
+    # a wave's last tile has a pass of its own (one, two and four heads) or none (eight)
+    dict(B=1, Hq=2, Hkv=2, D=128, E=12, S=1030, k=12, dtype="f32"), dict(B=1, Hq=8, Hkv=2, D=64, E=12, S=1031, k=12, dtype="f32"),
+    dict(B=1, Hq=8, Hkv=1, D=32, E=12, S=1030, k=12, dtype="f32"), dict(B=1, Hq=3, Hkv=1, D=128, E=12, S=1030, k=12, dtype="f32", rank=16),
+    dict(B=1, Hq=2, Hkv=2, D=64, E=12, S=2051, k=12, dtype="bf16", rank=32),
 ], ids=lambda s: "G%d_%s_r%d" % (s["Hq"] // s["Hkv"], s["dtype"], s.get("rank", 0)))
 @pytest.mark.parametrize("forced", [0, 5, 64])
 def test_splits_follow_the_entry_count(spec, forced):
