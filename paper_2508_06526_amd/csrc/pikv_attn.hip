@@ -995,8 +995,13 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
             float *dst = p.scores + (((int64_t)b * p.Hq + h0 + g) * p.k + j) * p.S + r0;
             const float *src = gqa_stage + g * p.chunk;
             if ((p.S & 3) == 0 && (reinterpret_cast<uintptr_t>(p.scores) & 15) == 0) {
-                for (int i = lane * 4; i < rows4; i += kWave * 4)
-                    *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(src + i);
+                if (p.stream_scores) {       // as in attn_partial
+                    for (int i = lane * 4; i < rows4; i += kWave * 4)
+                        store16_stream(dst + i, *reinterpret_cast<const uint4 *>(src + i));
+                } else {
+                    for (int i = lane * 4; i < rows4; i += kWave * 4)
+                        *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(src + i);
+                }
                 if (lane < rows - rows4) dst[rows4 + lane] = src[rows4 + lane];
             } else {
                 for (int i = lane; i < rows; i += kWave) dst[i] = src[i];
@@ -1195,10 +1200,25 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
                 fits = 2 * (fixed + stage) <= lds_cu && stage <= 64 * 1024 - 256;
                 if (fits) resident = 2;
             }
-            if (!fits) {
-                split_for(resident);
-                stage = 0;
+            if (!fits) split_for(resident);
+            if (!fits && W < 128 && gb < 8 && g_split_override == 0) {
+                // Rounds of blocks over long shards of narrow rows: cut finer until the stage fits twice,
+                // as long as a block keeps four rounds of tiles.  Scores written from the loop cost
+                // these passes more than the partials of the extra splits (32 sequences x 64 heads over
+                // 16 kv heads x 4 shards of 8832 rows of 32 values 545 -> 485 us, 8 kv heads x 2 heads over rank-32
+                // codes 126 -> 108; without scores 355 -> 358, 92 -> 93).
+                const size_t room = lds_cu / 2 - fixed < 64 * 1024 - 256 ? lds_cu / 2 - fixed : 64 * 1024 - 256;
+                const int round = kWavesPerBlock * tile, rows = (int)(room / (gb * sizeof(float)) / round * round);
+                const int64_t splits = rows > 0 ? (d->S + rows - 1) / rows : INT32_MAX;
+                if (rows >= 4 * round && splits <= kMaxPartialsPerHead / k && splits <= scratch_splits) {
+                    chunk = (int)((d->S + splits - 1) / splits + round - 1) / round * round;
+                    nsplit = (d->S + chunk - 1) / chunk;
+                    stage = (size_t)gb * chunk * sizeof(float);
+                    fits = true;
+                    resident = 2;
+                }
             }
+            if (!fits) stage = 0;
         }
     } else if (stage > (size_t)kScoreStageBytes) {
         stage = 0;

@@ -69,6 +69,20 @@ def test_multi_query_steps_reach_to_the_32_bit_limit_of_a_kv_head(lib):
             assert pk.pikv_attn_workspace_bytes(pk.make_desc(1, G, 1, 128, 4, S, stride_s=at, dtype=1, tq=2), 2) == 0
 
 
+def splits_of(desc, k):
+    """Splits of the attention plan, from the workspace it asks for."""
+    w = desc.rank or desc.D
+    acc = lambda n: -(-desc.B * desc.Hq * k * n * w * 4 // 256) * 256 + -(-desc.B * desc.Hq * k * n * 2 * 4 // 256) * 256 + 256
+    return next(n for n in range(1, 2049) if acc(n) == pk.pikv_attn_workspace_bytes(desc, k))
+
+
+def test_long_narrow_shards_are_cut_until_their_scores_fit_beside_the_tiles(lib):
+    """More units than a round of blocks and shards whose scores of one split do not fit the LDS: the splits
+    go up until they do, for groups of fewer than 8 rows, down to 4 rounds of tiles per block."""
+    assert splits_of(pk.make_desc(32, 64, 16, 32, 8, 8832, dtype=1), 4) == 3               # 4 heads: 47 KiB for 2944 rows
+    assert splits_of(pk.make_desc(32, 128, 16, 32, 8, 8832, dtype=1), 4) == 1              # 8 heads
+
+
 def test_host_side_argument_errors(lib):
     """NULL pointers / out-of-range sizes return PIKV_ERR_INVALID with no GPU present."""
     vp = C.c_void_p
