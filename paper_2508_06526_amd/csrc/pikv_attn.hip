@@ -1139,6 +1139,9 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     // More than 8 rows per kv head: every split writes and re-reads rows * 128 accumulators, and
     // two rounds' worth of longer blocks beat three (16 rows, 128 MiB: 36.0 against 40.0 us).
     if (gqa_mfma && W == 128 && gb > 8 && resident > 2) resident = 2;
+    // Rank-64 codes: forming the query costs a block about as much as a tile (2 sequences x 8 kv heads
+    // x 2 of 10112 rows 30.8 -> 27.5 us, 256 MiB over 256 units even).
+    if (gqa_mfma && W == 64 && d->rank > 0 && resident > 2) resident = 2;
     int64_t nsplit = 1;
     int chunk = 0;
     // Splits whose partials fit the fixed array of the call without a workspace: rows narrower than
