@@ -1109,6 +1109,32 @@ static int g_split_override = 0;   // tuning hook, see pikv_set_attn_split
 static hipEvent_t g_prof_start = nullptr, g_prof_stop = nullptr;   // see pikv_set_profile_events
 void g_split_override_set(int v) { g_split_override = v > 0 ? v : 0; }
 
+// Groups of narrow rows: does the plain kernel do better?  Measured on both sides over 2300 drawn calls
+// (pass and merge; 16 - 64 values or codes, 2 - 64 heads, up to 1 GiB).
+//   - 2 heads over 16 values: 14 of a tile's 16 rows are padding, and from 28 MB of K/V on that bounds the pass
+//     (63 MB 22.8 against 25.6 us; below, the matrix cores are 5 - 15 % ahead).
+//   - Groups of 2, 4 and 8 heads otherwise: never (4 heads 0.77, 8 heads 0.53 of the plain kernel's time).
+//   - Other groups, which the plain kernel takes one head per block, re-reading K/V from the caches for each:
+//     as long as whole groups make few blocks, which then are long (64 heads over 576 rows of rank 16 11
+//     against 30 us), and the heads re-read little.  The lines: 96 blocks of rows of 16 values, 64 of 32, 48 of 64
+//     (64 of one row tile); 64 MiB of re-reading at one row tile, 192 and 512 MiB at two and four, whose
+//     blocks are longer (16 heads, 1664 rows of 64 values, 218 MB re-read 27.5 against 14.6 us).
+// What counts is the capacity: the entry counts are on the device.
+static bool plain_pays(const pikv_desc *d, int k, int row_tiles) {
+    const int W = desc_width(d), G = d->Hq / d->Hkv;
+    const int64_t units = (int64_t)d->B * d->Hkv * k, bytes = units * d->S * W * 4;
+    if (G == 2 && W == 16) return bytes >= 28000000;
+    if (W == 128 || G == 2 || G == 4 || G == 8 || units == 0) return false;
+    int64_t splits = 256 * gqa_blocks_per_cu(W, row_tiles, d->rank > 0) / units;
+    const int64_t most = d->S / (2 * kWavesPerBlock * gqa_tile(W, row_tiles));
+    if (splits > most) splits = most;
+    if (splits < 1) splits = 1;
+    const int64_t few = W == 16 ? 96 : W == 32 || row_tiles == 1 ? 64 : 48;
+    const int64_t mib = row_tiles == 1 ? 64 : row_tiles == 2 ? 192 : 512;
+    if (W == 64 && d->rank > 0 && d->S <= 128 && units * G <= 768) return true;   // forming the query costs more than the rows
+    return units * splits <= few && bytes * G <= mib << 20;
+}
+
 int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_limit) {
     const int rc = check_desc(d);
     if (rc != PIKV_OK) return rc;
@@ -1118,14 +1144,16 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     int gb = 1;
     if (d->route_rows_per_seq == 1 && (G == 2 || G == 4 || G == 8)) gb = G;
     // The matrix-core kernel takes every group of bf16 rows that shares one routing decision and
-    // addresses a kv head's rows in 32 bits.
+    // addresses a kv head's rows in 32 bits - but for narrow ones where the plain kernel does better.
+    const int group_tiles = G <= 16 ? 1 : (G <= 32 ? 2 : 4);
     const bool gqa_mfma = d->route_rows_per_seq == 1 && d->dtype == PIKV_BF16 && G >= 2 && G <= 64 &&
-                          (int64_t)d->S * d->stride_s * 2 < ((int64_t)1 << 32);
+                          (int64_t)d->S * d->stride_s * 2 < ((int64_t)1 << 32) &&
+                          !plain_pays(d, k, group_tiles);
     if (gqa_mfma) gb = G;
     const int tq = d->tq > 1 ? d->tq : 1;
     // draft queries are folded into the query group of the matrix-core kernel's 128-value rows only
     if (tq > 1 && (!gqa_mfma || W != 128 || d->Hq % tq != 0 || G % tq != 0)) return PIKV_ERR_UNSUPPORTED;
-    const int row_tiles = !gqa_mfma ? 0 : (G <= 16 ? 1 : (G <= 32 ? 2 : 4));
+    const int row_tiles = gqa_mfma ? group_tiles : 0;
     const int epl = 16 / elem_bytes(d->dtype);
     const int lpr = W / epl;
     if (lpr < 1 || lpr > 32) return PIKV_ERR_UNSUPPORTED;

@@ -76,6 +76,18 @@ def splits_of(desc, k):
     return next(n for n in range(1, 2049) if acc(n) == pk.pikv_attn_workspace_bytes(desc, k))
 
 
+@pytest.mark.parametrize("rank", [0, 64])
+def test_small_groups_of_narrow_rows_are_planned_one_head_per_block(lib, rank):
+    """A few blocks of whole groups leave the chip empty: small calls with groups of other than 2, 4 or 8
+    heads are cut as the one-head kernel cuts them (256 rows a split at the least; whole groups
+    take 512), calls with blocks enough are not."""
+    few = pk.make_desc(1, 48, 4, 64, 4, 847, rank=rank, dtype=1)
+    assert splits_of(few, 3) == 3
+    many = pk.make_desc(16, 48, 4, 64, 4, 847, rank=rank, dtype=1)
+    assert splits_of(many, 3) == 1
+    assert splits_of(pk.make_desc(1, 32, 4, 64, 4, 1100, rank=rank, dtype=1), 3) == 2      # 8 heads: always whole groups
+
+
 def test_long_narrow_shards_are_cut_until_their_scores_fit_beside_the_tiles(lib):
     """More units than a round of blocks and shards whose scores of one split do not fit the LDS: the splits
     go up until they do, for groups of fewer than 8 rows, down to 4 rounds of tiles per block."""

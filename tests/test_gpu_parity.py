@@ -380,6 +380,59 @@ def test_grouped_rows_of_every_width_match_oracle(spec, offset):
     np.testing.assert_array_equal(t2n(dc.y), with_scores)
 
 
+def check_group(case, want_rel, forced=0):
+    """Attention (with scores) and utility of one call against the fp64 oracle."""
+    g = case.geo
+    idx, gates = random_selection(g, g.S)
+    u_ref = case.utility.copy()
+    ref = oracle_step(case, idx, gates, orc.COMBINE_LSE, utility=u_ref, decay=0.9)
+    d_idx, d_gates = torch.from_numpy(idx).to(DEV), torch.from_numpy(gates).to(DEV)
+    for split in (forced if isinstance(forced, tuple) else (forced,)):
+        pk.pikv_set_attn_split(split)
+        try:
+            d = DeviceCase(case)
+            d.attend(topk=d_idx, gates=d_gates)
+            d.update_utility(0.9, topk=d_idx)
+            y, sc = t2n(d.y), t2n(d.scores)
+        finally:
+            pk.pikv_set_attn_split(0)
+        assert np.linalg.norm(y - ref["y"]) <= want_rel * np.linalg.norm(ref["y"])
+        assert_utility_close(t2n(d.utility), u_ref)
+        n = np.take_along_axis(case.n_valid, idx, axis=1)                       # [B, k]
+        live = np.broadcast_to((np.arange(g.S) < n[:, :, None])[:, None], sc.shape)
+        assert np.isfinite(sc[live]).all() and np.isnan(sc[~live]).all()       # written up to the count, not past it
+
+
+@pytest.mark.parametrize("D,rank", [(16, 0), (32, 0), (64, 0), (128, 16), (64, 32), (128, 64)], ids=lambda v: str(v))
+@pytest.mark.parametrize("G", [16, 31, 64])
+@pytest.mark.parametrize("S", [1100, 1103])
+def test_groups_on_the_matrix_cores_in_both_forms_of_the_score_output(D, rank, G, S):
+    """100 units, more than the one-head kernel is given.  In one split the scores of a block (70 KB at 16 rows)
+    do not fit the LDS and are written from the loop, in sixteen they are staged; whole and
+    ragged counts, score rows that are whole 16-byte chunks and not, all row tiles, widths and decoders.
+    y: 3-part probabilities and fp32 sums, 2.5e-7 measured (a part less gives 2.3e-6)."""
+    g = wl.Geometry(B=25, Hq=G, Hkv=1, D=D, rank=rank, E=4, S=S, k=4, dtype="bf16")
+    case = wl.make_host_case(g, seed=S + G, n_valid="ragged", utility0="exp")
+    case.n_valid[0] = [S, S - 1, 1, 129]
+    check_group(case, 1e-6, forced=(1, 16))
+
+
+@pytest.mark.parametrize("spec", [
+    # either side of: 48, 64 and 96 blocks, the bytes re-read, and 28 MB of K/V for two heads over 16 values
+    dict(B=24, Hq=48, Hkv=2, D=64, S=300, k=1), dict(B=49, Hq=24, Hkv=1, D=64, S=300, k=1),
+    dict(B=32, Hq=10, Hkv=2, D=32, S=257, k=1), dict(B=13, Hq=5, Hkv=1, D=32, S=257, k=5),
+    dict(B=24, Hq=12, Hkv=4, D=128, rank=16, S=130, k=1), dict(B=97, Hq=3, Hkv=1, D=16, S=130, k=1),
+    dict(B=2, Hq=24, Hkv=2, D=64, S=5461, k=2), dict(B=2, Hq=24, Hkv=2, D=64, S=5463, k=2),
+    dict(B=8, Hq=16, Hkv=8, D=16, S=3417, k=2), dict(B=8, Hq=16, Hkv=8, D=16, S=3418, k=2),
+    dict(B=4, Hq=18, Hkv=6, D=64, rank=64, S=128, k=4), dict(B=4, Hq=18, Hkv=6, D=64, rank=64, S=129, k=4),
+    dict(B=64, Hq=64, Hkv=16, D=32, S=1300, k=1),       # finer splits, so that the scores fit the LDS
+], ids=lambda s: "B%d_G%d_D%d_r%d_S%d" % (s["B"], s["Hq"] // s["Hkv"], s["D"], s.get("rank", 0), s["S"]))
+def test_narrow_groups_on_both_sides_of_the_choice_of_kernel(spec):
+    """One head per block of the plain kernel, or whole groups on the matrix cores: the same result."""
+    g = wl.Geometry(E=spec["k"], dtype="bf16", **spec)
+    check_group(wl.make_host_case(g, seed=g.S, n_valid="ragged", utility0="exp"), 1e-6)
+
+
 @pytest.mark.parametrize("spec", [
     dict(B=1, Hq=6, Hkv=2, D=16, E=2, S=1024, k=2), dict(B=1, Hq=16, Hkv=2, D=32, E=2, S=1024, k=2),
     dict(B=16, Hq=14, Hkv=2, D=64, E=4, S=1024, k=4), dict(B=8, Hq=48, Hkv=2, D=64, E=4, S=1024, k=4),
