@@ -364,9 +364,20 @@ __global__ __launch_bounds__(THREADS) void evict_select(EvictParams p) {
 
     // keys held per thread: the next size that covers n; beyond the largest, re-read them
     const bool vec = p.S % 4 == 0 && (reinterpret_cast<uintptr_t>(p.utility) & 15) == 0;
-    if (n <= 8 * THREADS) select_cached<THREADS, 8>(p, be, u, n, ngone, vec, sh);
-    else if (THREADS == 1024 && n <= kSelCache * THREADS) select_cached<THREADS, kSelCache>(p, be, u, n, ngone, vec, sh);
-    else select_stream<THREADS>(p, be, u, n, ngone, sh);
+    if constexpr (THREADS == 256) {
+        select_cached<THREADS, 8>(p, be, u, n, ngone, vec, sh);         // S <= kSelFewSlots
+    } else if (n <= kSelFewSlots) {
+        // Few entries in a large shard: as a small one.  (A barrier waits for the waves that are left.)
+        __shared__ SelShared<256> few;
+        if (tid >= 256) return;
+        select_cached<256, 8>(p, be, u, n, ngone, vec, few);
+    } else if (n <= 8 * THREADS) {
+        select_cached<THREADS, 8>(p, be, u, n, ngone, vec, sh);
+    } else if (n <= kSelCache * THREADS) {
+        select_cached<THREADS, kSelCache>(p, be, u, n, ngone, vec, sh);
+    } else {
+        select_stream<THREADS>(p, be, u, n, ngone, sh);
+    }
     if (tid == 0) {
         p.evicted_cnt[be] = ngone;
         p.n_valid[be] = p.capacity;

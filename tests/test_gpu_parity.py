@@ -647,6 +647,28 @@ def test_evict_matches_oracle_at_the_edges_of_the_select_shapes(S, ties):
     test_evict_matches_oracle_bit_exact(S, S * 3 // 4, ties)
 
 
+@pytest.mark.parametrize("n", [2, 255, 1025, 2047, 2048, 2049])
+@pytest.mark.parametrize("S", [2049, 2052, 9000])
+@pytest.mark.parametrize("compact", [False, True], ids=["list", "compact"])
+def test_evict_few_entries_of_a_large_shard(n, S, compact):
+    """Up to 2048 entries take a quarter of the block, whatever the capacity; shards of both kinds in a call."""
+    g = wl.Geometry(B=1, Hq=2, Hkv=2, D=16, E=4, S=S, k=2, dtype="bf16")
+    rng = np.random.default_rng(n)
+    u = (rng.integers(0, 900, size=(1, 4, S)) / 8 + 1).astype(np.float32)
+    counts = np.array([[n, S, n // 2, max(1, n - 1)]], np.int32)
+    capacity = max(1, n // 2)
+    u_ref, n_ref = u.copy(), counts.copy()
+    ridx, rcnt = orc.evict(u_ref, n_ref, capacity, max_evict=S)
+    dc, eidx, ecnt = run_gpu_evict(g, u, counts, capacity, max_evict=S, compact=compact)
+    np.testing.assert_array_equal(ecnt, rcnt)
+    np.testing.assert_array_equal(t2n(dc.n_valid), n_ref)
+    got_u = t2n(dc.utility)
+    for e in range(4):
+        np.testing.assert_array_equal(eidx[0, e, :rcnt[0, e]], ridx[0, e, :rcnt[0, e]])
+        kept = np.delete(u[0, e, :counts[0, e]], ridx[0, e, :rcnt[0, e]]) if compact else u[0, e]
+        np.testing.assert_array_equal(got_u[0, e, :kept.size], kept)
+
+
 def test_evict_special_values_and_selection_list():
     g = wl.Geometry(B=2, Hq=2, Hkv=2, D=16, E=4, S=64, k=2, dtype="bf16")
     rng = np.random.default_rng(3)
