@@ -396,8 +396,9 @@ struct MoveParams {
 };
 
 constexpr int kMaxRowChunks = 256;
-constexpr int kMoveThreads = 1024;       // at most; 256 for shards of few slots (kMoveFewSlots)
+constexpr int kMoveThreads = 1024;       // at most; 256 for shards of few slots (kMoveFewSlots) ...
 constexpr int kMoveFewSlots = 1024;
+constexpr int kMoveManyBlocks = 2048;    // ... or of one pass in this many blocks
 constexpr int kMoveRows = 4;             // rows a thread carries per pass
 constexpr int kMoveList = 8192;          // evicted slots of a shard kept in LDS (more: read from memory)
 inline __host__ __device__ int move_pass_rows(int threads, int row_chunks) { return threads / row_chunks * kMoveRows; }
@@ -440,7 +441,7 @@ __global__ __launch_bounds__(kMoveThreads) void evict_move(MoveParams p) {
     auto fill = [&](int table, int base) {
         for (int x = tid; x < pass_rows; x += threads) {
             const int d = base + x;
-            int lo = 0, hi = cnt;            // evicted slots below the d-th kept one
+            int lo = 0, hi = d < n_new ? cnt : 0;    // evicted slots below the d-th kept one
             if (cached) {
                 while (lo < hi) {
                     const int mid = (lo + hi) >> 1;
@@ -607,20 +608,30 @@ extern "C" int pikv_evict(const pikv_desc *desc, float *utility, int32_t *n_vali
     const int eb = elem_bytes(desc->dtype);
     m.stride_h_bytes = desc->stride_h * eb;
     m.stride_s_bytes = desc->stride_s * eb;
-    // K and V move in separate blocks; rows are cut in column slices of at least 64 bytes until there
-    // are two blocks per CU
+    // K and V move in separate blocks; rows are cut in column slices of whole 128-byte lines until there
+    // are two blocks per CU (64-byte slices, two blocks on a line, cost 10 shards x 8 heads of 8192 rows
+    // 131 -> 157 us), and of 64 bytes only to reach half the CUs (2 shards x 4 heads of 32768 rows 161 -> 147).
+    const int64_t uncut = (int64_t)desc->B * desc->E * desc->Hkv * 2;
     int slices = 1;
-    while ((int64_t)desc->B * desc->E * desc->Hkv * 2 * slices < 512 && row_chunks / slices >= 8) slices *= 2;
+    while (uncut * slices < 512 && row_chunks / slices >= 16) slices *= 2;
+    while (uncut * slices < 128 && row_chunks / slices >= 8) slices *= 2;
     m.row_chunks = row_chunks / slices;
     m.max_evict = max_evict;
-    // Caches beyond the 256 MiB that the Infinity Cache holds go past it, reads and writes (512 MiB:
-    // 161 us for the whole call against 187, 4 GiB 556 against 639; 33 MiB that are still in it 44
-    // against 33).
-    const int threads = desc->S <= kMoveFewSlots ? 256 : kMoveThreads;
+    // 1024 threads shorten the chain of passes; 256 where there is none: in small shards, and in those of
+    // one pass with blocks enough to fill the chip (512 shards x 8 heads of 1108 rows of 32 bytes, 32 of the
+    // shards selected, 92 -> 52 us: the blocks of the others only start and leave).
+    const bool few = desc->S <= kMoveFewSlots ||
+                     (uncut * slices >= kMoveManyBlocks && desc->S <= move_pass_rows(kMoveThreads, m.row_chunks));
+    const int threads = few ? 256 : kMoveThreads;
     const dim3 grid(desc->B * desc->E, desc->Hkv, 2 * slices), block(threads);
     const size_t lds = move_lds_bytes(threads, m.row_chunks, max_evict);
-    const int64_t cache_bytes = (int64_t)desc->B * desc->E * desc->Hkv * desc->S * row_chunks * 32;
-    if (cache_bytes > ((int64_t)256 << 20)) hipLaunchKernelGGL(evict_move<true>, grid, block, lds, st, m);
+    // From 512 MiB on, twice what the Infinity Cache holds, reads and writes go past it (512 MiB: 161 us
+    // for the whole call against 187, 4 GiB 556 against 639).  Below, what a call moves may still be in it,
+    // and half of it is where one entry leaves each shard (319 MB 61 us against 86, 470 MB 87 against 122).  Only
+    // the shards that the call processes count.
+    const int64_t shards_moved = (int64_t)desc->B * (sel_idx && sel_k < desc->E ? sel_k : desc->E);
+    const int64_t cache_bytes = shards_moved * desc->Hkv * desc->S * row_chunks * 32;
+    if (cache_bytes >= ((int64_t)512 << 20)) hipLaunchKernelGGL(evict_move<true>, grid, block, lds, st, m);
     else hipLaunchKernelGGL(evict_move<false>, grid, block, lds, st, m);
     return launch_status();
 }

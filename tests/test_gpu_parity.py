@@ -727,7 +727,11 @@ def test_evict_with_compaction_moves_rows_like_oracle(spec):
     (2048, 1536, 128, "bf16", 2, 3), (2561, 2048, 128, "f32", 1, 2), (4096, 1, 64, "bf16", 1, 2),
     (3000, 0, 64, "bf16", 2, 2),            # nothing is kept
     (30000, 10000, 32, "bf16", 1, 2),       # more evicted slots than the mover holds in LDS
-    (40000, 30001, 128, "bf16", 7, 2),      # more than 256 MiB of K and V: the streaming form
+    (40000, 30001, 128, "bf16", 7, 2),      # more than the Infinity Cache holds ...
+    (40000, 30001, 128, "bf16", 7, 4),      # ... and past 512 MiB: the streaming form
+    (1100, 300, 16, "bf16", 64, 16),        # 2048 blocks of a single pass: 256 threads
+    (2100, 2099, 16, "bf16", 64, 16),       # as many of more than one pass
+    (3000, 500, 128, "bf16", 2, 2),         # 64-byte column slices
 ], ids=lambda v: str(v))
 @pytest.mark.parametrize("where", ["mixed", "tail", "head"])
 def test_compaction_slides_rows_at_the_movers_edges(S, cap, D, dtype, Hkv, E, where):
