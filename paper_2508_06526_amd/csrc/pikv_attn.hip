@@ -1232,12 +1232,13 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
                 if (fits) resident = 2;
             }
             if (!fits) split_for(resident);
-            if (!fits && W < 128 && gb < 8 && g_split_override == 0) {
+            if (!fits && W < 128 && gb <= 4 && g_split_override == 0) {
                 // Rounds of blocks over long shards of narrow rows: cut finer until the stage fits twice,
                 // as long as a block keeps four rounds of tiles.  Scores written from the loop cost
                 // these passes more than the partials of the extra splits (32 sequences x 64 heads over
-                // 16 kv heads x 4 shards of 8832 rows of 32 values 545 -> 485 us, 8 kv heads x 2 heads over rank-32
-                // codes 126 -> 108; without scores 355 -> 358, 92 -> 93).
+                // 16 kv heads x 4 shards of 8832 rows of 32 values 545 -> 491 us, 16 x 16 over 8 x 4 of 8192 rank-32
+                // codes 126 -> 107; without scores 355 -> 359, 92 -> 93).  Not from 5 rows on, where a store
+                // from the loop fills more of its lines (7 rows of 64 values 434 against 441).
                 const size_t room = lds_cu / 2 - fixed < 64 * 1024 - 256 ? lds_cu / 2 - fixed : 64 * 1024 - 256;
                 const int round = kWavesPerBlock * tile, rows = (int)(room / (gb * sizeof(float)) / round * round);
                 const int64_t splits = rows > 0 ? (d->S + rows - 1) / rows : INT32_MAX;
