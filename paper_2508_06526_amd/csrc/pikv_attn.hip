@@ -995,13 +995,10 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
             float *dst = p.scores + (((int64_t)b * p.Hq + h0 + g) * p.k + j) * p.S + r0;
             const float *src = gqa_stage + g * p.chunk;
             if ((p.S & 3) == 0 && (reinterpret_cast<uintptr_t>(p.scores) & 15) == 0) {
-                if (p.stream_scores) {       // as in attn_partial
-                    for (int i = lane * 4; i < rows4; i += kWave * 4)
-                        store16_stream(dst + i, *reinterpret_cast<const uint4 *>(src + i));
-                } else {
-                    for (int i = lane * 4; i < rows4; i += kWave * 4)
-                        *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(src + i);
-                }
+                // (Non-temporal stores where blocks run in several rounds, as in attn_partial, are 3 %
+                // faster there, 508 -> 491 us, but the second form costs the single round 1 us of 42.)
+                for (int i = lane * 4; i < rows4; i += kWave * 4)
+                    *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(src + i);
                 if (lane < rows - rows4) dst[rows4 + lane] = src[rows4 + lane];
             } else {
                 for (int i = lane; i < rows; i += kWave) dst[i] = src[i];
@@ -1236,8 +1233,8 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
                 // Rounds of blocks over long shards of narrow rows: cut finer until the stage fits twice,
                 // as long as a block keeps four rounds of tiles.  Scores written from the loop cost
                 // these passes more than the partials of the extra splits (32 sequences x 64 heads over
-                // 16 kv heads x 4 shards of 8832 rows of 32 values 545 -> 491 us, 16 x 16 over 8 x 4 of 8192 rank-32
-                // codes 126 -> 107; without scores 355 -> 359, 92 -> 93).  Not from 5 rows on, where a store
+                // 16 kv heads x 4 shards of 8832 rows of 32 values 545 -> 508 us, 16 x 16 over 8 x 4 of 8192 rank-32
+                // codes 126 -> 111; without scores 355 -> 359, 92 -> 93).  Not from 5 rows on, where a store
                 // from the loop fills more of its lines (7 rows of 64 values 434 against 441).
                 const size_t room = lds_cu / 2 - fixed < 64 * 1024 - 256 ? lds_cu / 2 - fixed : 64 * 1024 - 256;
                 const int round = kWavesPerBlock * tile, rows = (int)(room / (gb * sizeof(float)) / round * round);
