@@ -86,8 +86,8 @@ __device__ __forceinline__ ShardRef resolve_shard(const AttnParams &p, int b, in
 // full shards; the rows are cut by what the shard holds, so that a young cache - a few hundred
 // entries in shards of thousands - still spreads over the splits instead of leaving all but the
 // first of them empty.  A split takes whole rounds of tiles, one per wave: with uneven waves it
-// runs as long as one of more rows (32 splits of 136 rows in blocks of 160: 23.0 us, of 256: 21.6).  (4 sequences, 8 kv heads, 4 of
-// 16 shards of 8192 slots, 100 - 1000 entries each: pass 17.7 -> YOUNG us.)
+// runs as long as one of more rows (32 splits of 136 rows in blocks of 160: 23.0 us, of 256: 21.6).
+// (4 sequences, 8 kv heads, 4 of 16 shards of 8192 slots, 573 entries each: pass and merge 20.1 -> 16.3 us.)
 template <int TILE>
 __device__ __forceinline__ void split_rows(const AttnParams &p, int n, int split, int *r0, int *r1) {
     const int m = min(n, p.S);
@@ -113,9 +113,11 @@ __device__ __forceinline__ int64_t query_row(const AttnParams &p, int b, int h) 
     return ((int64_t)b * p.tq + t) * heads + hk * g + gg;
 }
 
-// 4-wave blocks of the plain-ALU kernel that one CU holds: its register footprint grows with the
-// heads per block (about 150 VGPRs at one head, 180-240 at two and four, all 256 at eight).
-// The launch bounds hold the compiler to it and the split plan counts resident blocks with it.
+// 4-wave blocks of the plain-ALU kernel that the split plan counts per CU, and that the launch bounds
+// hold the compiler to at the least.  The registers allow more in places (fp32: 119 registers at one head over
+// rows of 256 bytes and more, 140 at two, 252 - 254 at eight; bf16: 131 at one head over 256 bytes, 154 - 164
+// at two); the counts were measured with the kernel before its loop lost registers, and a plan for
+// more has not been.
 constexpr int plain_blocks_per_cu(int row_bytes, int gb) {
     return plain_short_rows(row_bytes, gb) ? 4 : gb == 1 ? 3 : (gb <= 4 ? 2 : 1);
 }
@@ -578,6 +580,7 @@ __device__ __forceinline__ void hold_operand(uint2 &v) { asm volatile("" : "+v"(
 // staged in LDS and the V rows in registers, so the streamed bytes do not grow with RT; the
 // accumulators do (W/4 registers per row tile), which is why a CU holds 3 blocks at RT = 1 and 2
 // above.  For RT = 4 the query operands live in LDS instead of registers.
+// (The least; rows of 32 values at two row tiles without scores, and at four, have registers for one more.)
 constexpr int gqa_blocks_per_cu(int width, int row_tiles, bool codes) {
     if (codes && width == 64 && row_tiles == 4) return 1;      // 96 registers of query operand
     if (width <= 32) return row_tiles == 1 ? 4 : row_tiles == 2 ? 3 : 2;
@@ -617,7 +620,8 @@ constexpr size_t gqa_static_lds(int width, int tile, int row_tiles) {
 // one burst per row at the block's end) or kScoresDirect (written from the loop).  A template
 // parameter and not a run-time branch: each form costs registers, and a value spilled for one
 // of them is reloaded inside the loop by a scratch load, which the wait counters cannot tell
-// from the tile loads in flight - the wave then waits for all of them.
+// from the tile loads in flight - the wave then waits for all of them.  (One form of the 42 still
+// spills: rank-16 codes at four row tiles with scores written from the loop, 28 bytes.)
 constexpr int kScoresNone = 0, kScoresStaged = 1, kScoresDirect = 2;
 template <int W, int RT, int SC, bool CODES>
 __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, CODES)) void attn_partial_gqa(

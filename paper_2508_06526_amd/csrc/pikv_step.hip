@@ -316,7 +316,11 @@ inline size_t post_smem_bytes(int threads, int np, int pairs, int slots_per_thre
 // of the blocks (or of the tiles a block walks through) has the same bytes in flight at once, and
 // the statistics are formed a quarter as often.  Measured: 16 sequences x 32 heads x 2 shards of 4096
 // slots 10.0 -> 7.2 us, with access bookkeeping 12.5 -> 8.4; 32 sequences, 2048 slots 11.7 -> 10.8; at
-// one round of blocks or less it is no faster (4 shards of 8192 slots, 1 sequence: +1.5 us).
+// one round of blocks or less it is no faster (4 shards of 8192 slots, 1 sequence: +1.5 us).  Several
+// tiles per block take 151 - 159 registers, three blocks per CU instead of the four planned, and gain all
+// the same (whole step, rows of 16 values: 32 sequences x 8 heads x 4 shards of 8192 slots 131.5 with one slot per
+// thread -> 127 us, 64 x 4 x 8 of 8192 283 -> 257, 32 x 32 x 8 of 4096 436 -> 432; planned for three
+// blocks: even).
 template <typename T, int THREADS, int MODE, int SPT>
 __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     constexpr int kSlots = THREADS / 4 * SPT;
@@ -351,8 +355,8 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     // (lane l takes selection l, shard l's count and gate l; the block's own are picked out of
     // the registers after the statistics); then the (max, sum) pairs of the statistics; then
     // the scores - a trip to memory, with the shard's capacity as the bound: slots past the
-    // entry count are masked when they are used, and a block past the shard's end leaves after
-    // the statistics.
+    // entry count are masked when they are used, and a block past the shard's end leaves when
+    // the count is here, before the statistics.
     const int lane_id = tid & (kWave - 1);
     const int sel_of_lane = p.topk[(int64_t)b * k + min(lane_id, k - 1)];
     const int n_of_lane = p.n_valid[(int64_t)b * p.E + min(lane_id, p.E - 1)];

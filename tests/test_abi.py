@@ -90,7 +90,7 @@ def test_small_groups_of_narrow_rows_are_planned_one_head_per_block(lib, rank):
 
 def test_long_narrow_shards_are_cut_until_their_scores_fit_beside_the_tiles(lib):
     """More units than a round of blocks and shards whose scores of one split do not fit the LDS: the splits
-    go up until they do, for groups of fewer than 8 rows, down to 4 rounds of tiles per block."""
+    go up until they do, for groups of up to 4 rows, down to 4 rounds of tiles per block."""
     assert splits_of(pk.make_desc(32, 64, 16, 32, 8, 8832, dtype=1), 4) == 3               # 4 heads: 47 KiB for 2944 rows
     assert splits_of(pk.make_desc(32, 128, 16, 32, 8, 8832, dtype=1), 4) == 1              # 8 heads
 

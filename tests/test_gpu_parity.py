@@ -356,9 +356,9 @@ GROUPED_ROWS = [
 @pytest.mark.parametrize("spec", GROUPED_ROWS, ids=lambda s: "D%d_r%d_G%d_S%d" % (s["D"], s.get("rank", 0), s["Hq"] // s["Hkv"], s["S"]))
 @pytest.mark.parametrize("offset", [0, 1], ids=["aligned", "q_off_by_one"])
 def test_grouped_rows_of_every_width_match_oracle(spec, offset):
-    """y against the fp64 oracle: exact products, fp32 sums over at most 3 * 1028 entries (random
-    signs: about sqrt(n) * 2^-24 = 3e-6 relative at the worst, measured 2e-7) - and for rows of 128
-    values probabilities of 17 bits (2e-6 measured)."""
+    """y against the fp64 oracle: exact products and fp32 sums, 2.5e-7 measured for rows and codes narrower
+    than 128 values (with probabilities of a part less, 2.3e-6) - and for rows of 128 values
+    probabilities of 17 bits (2e-6 measured).  Small calls, which the one-head kernel takes in part."""
     g = wl.Geometry(dtype="bf16", **spec)
     case = wl.make_host_case(g, seed=g.S + g.Hq, kv="lognormal_token", n_valid="ragged", utility0="exp")
     idx, gates = random_selection(g, g.S)
@@ -372,7 +372,7 @@ def test_grouped_rows_of_every_width_match_oracle(spec, offset):
     dc.attend(topk=d_idx, gates=d_gates)
     dc.update_utility(0.9, topk=d_idx)
     y = t2n(dc.y)
-    assert np.linalg.norm(y - ref["y"]) <= (8e-6 if g.width == 128 else 3e-6) * np.linalg.norm(ref["y"])
+    assert np.linalg.norm(y - ref["y"]) <= (8e-6 if g.width == 128 else 1e-6) * np.linalg.norm(ref["y"])
     np.testing.assert_allclose(t2n(dc.row_max), ref["row_max"], rtol=1e-5, atol=1e-6)
     assert_utility_close(t2n(dc.utility), u_ref)
     with_scores = y
