@@ -479,20 +479,9 @@ template <>
 struct OperandOf<16> {
     typedef uint2 type;
 };
-typedef short s16x4_t __attribute__((ext_vector_type(4)));
 
-typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x2_t __attribute__((ext_vector_type(2)));
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
 typedef float f32x2_t __attribute__((ext_vector_type(2)));
-
-__device__ __forceinline__ void wave_lds_order() {
-    // LDS operations of one wave execute in order; this only stops the compiler from moving
-    // them across the point where another lane's data is expected.
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-}
 
 // max over the four lanes c, c + 16, c + 32, c + 48, in all of them, without LDS: the swaps leave
 // the two halves (then the two rows of each half) side by side in two registers.
@@ -549,14 +538,6 @@ __device__ __forceinline__ void split_bf16_up(const float *v, uint4 (&out)[3]) {
     for (int k = 0; k < 3; ++k) out[k] = make_uint4(w[k][0], w[k][1], w[k][2], w[k][3]);
 }
 
-__device__ __forceinline__ f32x4_t mfma_rows(uint4 a, uint4 b, f32x4_t acc) {
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
-                                                   acc, 0, 0, 0);
-}
-__device__ __forceinline__ f32x4_t mfma_rows(uint2 a, uint2 b, f32x4_t acc) {
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a), __builtin_bit_cast(s16x4_t, b),
-                                                     acc, 0, 0, 0);
-}
 
 // Consecutive bf16 query values as an operand; a caller's q need not be 16-byte aligned.
 template <typename OP>

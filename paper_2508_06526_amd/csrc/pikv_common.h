@@ -160,6 +160,29 @@ __device__ __forceinline__ void store16_stream(void *p, uint4 v) {
     __builtin_nontemporal_store(x, (global_u32x4_wptr)(uintptr_t)p);
 }
 
+// One 16x16x32 bf16 matrix-core product: lane (c, r) = (lane % 16, lane / 16) holds A[row c] and
+// B[column c] at the 8 contraction indices of its group r, and gets acc[x] = D[row 4r + x][column c].
+typedef __bf16 bf16x8_t __attribute__((ext_vector_type(8)));
+typedef float f32x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4_t mfma_rows(uint4 a, uint4 b, f32x4_t acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8_t, a), __builtin_bit_cast(bf16x8_t, b),
+                                                   acc, 0, 0, 0);
+}
+// The same over 16 contraction indices, 4 per group.
+typedef short s16x4_t __attribute__((ext_vector_type(4)));
+__device__ __forceinline__ f32x4_t mfma_rows(uint2 a, uint2 b, f32x4_t acc) {
+    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s16x4_t, a), __builtin_bit_cast(s16x4_t, b),
+                                                     acc, 0, 0, 0);
+}
+
+__device__ __forceinline__ void wave_lds_order() {
+    // LDS operations of one wave execute in order; this only stops the compiler from moving
+    // them across the point where another lane's data is expected.
+    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
+
 // fp32 -> uint32 whose unsigned order is the float order (-0 folded onto +0).
 __device__ __forceinline__ uint32_t order_key(float u) {
     uint32_t bits = __float_as_uint(u);

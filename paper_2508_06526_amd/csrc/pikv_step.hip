@@ -45,7 +45,9 @@ struct PreParams {
     int64_t stride_h_bytes, stride_s_bytes;
     int64_t x_stride;    // elements between the routed vectors of consecutive sequences (>= d_r)
     int d_r, E, cpr, k, S, Hkv, row_chunks, do_insert;
-    int EP;              // 0: rows of W_r are aligned 16-byte chunks (cpr of them); else E rounded up to a power of two
+    int flat_threads;    // fp32: 0 where rows of W_r are cpr aligned chunks, else the threads of the flat form
+    bool w_aligned;      // ... and whether W_r is 16-byte aligned
+    bool words;          // bf16: see route_words_ok
     int use_policy;      // the entry to evict is chosen by pol (Table 3) instead of the utility
     PolicyView pol;      // its arrays, when given, are also stamped for the new entry
 };
@@ -73,14 +75,14 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
 // decision (W_r is L2-resident and tiny next to the cache) so that the k evict/insert jobs
 // run on k compute units at once instead of one after the other; block j == 0 publishes the
 // decision.
-template <typename T>
+// MOST: bf16, the router's experts at most (RouteTiles); 0 for fp32.
+template <typename T, int MOST>
 __global__ __launch_bounds__(kRouteThreads) void step_pre(PreParams p) {
     constexpr int kWaves = kRouteThreads / kWave;
     const int b = blockIdx.x / p.k, j = blockIdx.x - b * p.k;
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid >> 6;
 
-    __shared__ float red[kWaves][64];
     __shared__ uint64_t wave_best[kWaves];
 
     // neither the router's additive term, nor the entry counts of the sequence's shards (lane e
@@ -95,23 +97,27 @@ __global__ __launch_bounds__(kRouteThreads) void step_pre(PreParams p) {
         vnew = load16(static_cast<const char *>(p.V_new) + ((int64_t)b * new_chunks + tid) * 16);
     }
 
-    if (p.EP == 0)
-        route_logits_vec<T>(static_cast<const T *>(p.x) + (int64_t)b * p.x_stride,
-                            static_cast<const T *>(p.W_r), p.bias, p.d_r, p.E, p.cpr, red);
-    else      // any E, any alignment: the stand-alone router's generic form, same bits
-        route_logits_generic<T>(static_cast<const T *>(p.x) + (int64_t)b * p.x_stride,
-                                static_cast<const T *>(p.W_r), p.d_r, p.E, p.EP, &red[0][0]);
+    const T *xr = static_cast<const T *>(p.x) + (int64_t)b * p.x_stride;
+    const T *W_r = static_cast<const T *>(p.W_r);
+    float logit = 0.0f;                      // of expert `lane`, in the first wave
+    if constexpr (MOST > 0) {
+        __shared__ RouteShared<MOST, 1> sh;
+        logit = route_logit_mfma<MOST>(xr, W_r, p.d_r, p.E, p.words, bias_e, sh);
+    } else {
+        __shared__ float red[kWaves][64];
+        __shared__ __attribute__((aligned(16))) float flat[kFlatFloats];
+        if (p.flat_threads == 0) route_logits_vec(xr, W_r, p.d_r, p.cpr, red);
+        else route_logits_flat(xr, W_r, p.d_r, p.E, p.flat_threads, p.w_aligned, flat, red);
+        if (wave == 0) logit = route_logit_of_lane(red[0], 64, bias_e, p.E, lane);
+    }
     // The first wave ranks the experts and tells the others which shard is the block's (one LDS
     // word and a barrier): sixteen waves doing it side by side, four to a SIMD, take twice as
     // long as one wave alone plus the barrier.  The ranks come first - the shard to scan hangs
     // off them alone - and the softmax and the gates are formed, by that wave of the sequence's
     // first block, while the scan's requests are in flight.
     __shared__ int block_expert;
-    float logit = 0.0f;
     int rank = 64;
     if (wave == 0) {
-        logit = p.EP == 0 ? route_logit_of_lane(red, bias_e, p.E, lane)
-                          : route_logit_generic_of_lane(&red[0][0], bias_e, p.E, lane);
         rank = route_rank(logit, lane, p.E);
         const uint64_t owner = __ballot(rank == j);      // taken with every lane of the wave active
         if (lane == 0) block_expert = __builtin_ctzll(owner);
@@ -611,11 +617,6 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     if (!(decay >= 0.0f) || decay > 3.0e38f) return PIKV_ERR_INVALID;
     if (combine != PIKV_COMBINE_LSE && combine != PIKV_COMBINE_LOCAL) return PIKV_ERR_INVALID;
     if (desc->route_rows_per_seq != 1) return PIKV_ERR_UNSUPPORTED;
-    int cpr = 0, EP = 0;
-    if (!route_vec_ok(W_r, desc->E, desc->dtype, &cpr)) {
-        EP = 1;
-        while (EP < desc->E) EP <<= 1;
-    }
     // the attention pass's own checks come before the first launch as well: a rejected call
     // leaves the cache (rows, utilities, entry counts, policy arrays) exactly as it was
     AttnPlan checked;
@@ -654,8 +655,10 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     p.d_r = desc->Hq / tq * desc->D;
     p.x_stride = (int64_t)desc->Hq * desc->D;
     p.E = desc->E;
-    p.cpr = cpr;
-    p.EP = EP;
+    p.cpr = 0;
+    p.flat_threads = desc->dtype == PIKV_F32 && !route_vec_ok(W_r, desc->E, &p.cpr) ? route_flat_threads(p.d_r, desc->E) : 0;
+    p.w_aligned = reinterpret_cast<uintptr_t>(W_r) % 16 == 0;
+    p.words = route_words_ok(q, p.x_stride, W_r, p.d_r, desc->E);
     p.k = k;
     p.S = desc->S;
     p.Hkv = desc->Hkv;
@@ -663,10 +666,17 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     p.do_insert = K_new != nullptr;
     p.use_policy = use_policy;
     p.pol = pol;
-    if (desc->dtype == PIKV_F32)
-        hipLaunchKernelGGL(step_pre<float>, dim3(desc->B * k), dim3(kRouteThreads), 0, st, p);
-    else
-        hipLaunchKernelGGL(step_pre<bf16>, dim3(desc->B * k), dim3(kRouteThreads), 0, st, p);
+    const dim3 pre_grid(desc->B * k), pre_block(kRouteThreads);
+    if (desc->dtype == PIKV_F32) {
+        hipLaunchKernelGGL((step_pre<float, 0>), pre_grid, pre_block, 0, st, p);
+    } else {
+        switch (route_experts_most(desc->E)) {
+            case 8: hipLaunchKernelGGL((step_pre<bf16, 8>), pre_grid, pre_block, 0, st, p); break;
+            case 16: hipLaunchKernelGGL((step_pre<bf16, 16>), pre_grid, pre_block, 0, st, p); break;
+            case 32: hipLaunchKernelGGL((step_pre<bf16, 32>), pre_grid, pre_block, 0, st, p); break;
+            default: hipLaunchKernelGGL((step_pre<bf16, 64>), pre_grid, pre_block, 0, st, p); break;
+        }
+    }
     int lrc = launch_status();
     if (lrc != PIKV_OK) return lrc;
     AttnPlan plan;

@@ -88,6 +88,48 @@ def test_route_of_many_rows_gives_each_row_its_own_bits(rows, E, dtype):
         np.testing.assert_array_equal(w, np.concatenate(p))
 
 
+@pytest.mark.parametrize("d_r", [1, 31, 127, 128, 130, 2048, 4104])
+@pytest.mark.parametrize("E,dtype", [(1, "bf16"), (2, "bf16"), (5, "bf16"), (8, "bf16"), (10, "bf16"), (16, "bf16"), (24, "bf16"),
+                                     (32, "bf16"), (33, "bf16"), (36, "bf16"), (62, "bf16"), (64, "bf16"),
+                                     (1, "f32"), (3, "f32"), (6, "f32"), (12, "f32"), (40, "f32"), (63, "f32")])
+def test_route_forms_agree_and_stay_within_their_rounding(E, dtype, d_r):
+    """Whole and partial units of the contraction, every layout of the experts, rows in columns of their own or
+    traded, words or single elements (x or W_r off by one element): the same bits, and within the rounding of
+    the sums - at most a chain of d_r / 512 + 32 fp32 additions, exp to 4e-6 - of 64 bits."""
+    k, rows = min(2, E), 1100
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(1000 * E + d_r)
+    tdt = torch.bfloat16 if dtype == "bf16" else torch.float32
+
+    def at_offset(t, off):               # the same values, `off` elements into their buffer
+        buf = torch.empty(t.numel() + off, device=DEV, dtype=t.dtype)
+        buf[off:].copy_(t.reshape(-1))
+        return buf[off:].view(t.shape)
+
+    x = torch.randn((rows, d_r), device=DEV, generator=gen).to(tdt)
+    W = (torch.randn((d_r, E), device=DEV, generator=gen) * d_r ** -0.5).to(tdt)
+
+    def route(xs, Ws):
+        n = xs.shape[0]
+        out = (torch.full((n, k), -1, device=DEV, dtype=torch.int32), torch.zeros((n, k), device=DEV),
+               torch.zeros((n, E), device=DEV))
+        pk.pikv_route(xs, Ws, None, n, d_r, E, k, *out)
+        return [t2n(t) for t in out]
+
+    whole = route(x, W)
+    logits = x.double() @ W.double()
+    bound = (d_r / 512 + 32) * 2.0 ** -24 * (x.double().abs() @ W.double().abs())
+    ref = torch.softmax(logits, 1)
+    assert ((torch.from_numpy(whole[2]).to(DEV) - ref).abs() <= ref * (2 * bound.amax(1, keepdim=True) + 4e-6)).all()
+    # (fp32 takes another layout where rows of W_r are whole chunks that lose their alignment)
+    moved = E * 4 % 16 != 0 or dtype == "bf16"
+    variants = [(x[:300].contiguous(), W), (x[:3].contiguous(), W), (at_offset(x[:3], 1), W), (at_offset(x[:700], 1), W)]
+    variants += [(x[:3].contiguous(), at_offset(W, 1)), (x, at_offset(W, 1))] if moved else []
+    for xs, Ws in variants:
+        for w, p in zip(whole, route(xs, Ws)):
+            np.testing.assert_array_equal(w[:xs.shape[0]], p)
+
+
 def test_route_exact_ties_lower_index_first():
     rng = np.random.default_rng(6)
     rows, d_r = 64, 32
