@@ -4,7 +4,7 @@
 //   evict_select : one block per (sequence, expert).  The entries to drop are the
 //                  n - capacity smallest under (utility ascending, slot descending), i.e.
 //                  the complement of the `capacity` best under (utility descending, slot
-//                  ascending).  A two-bits-a-step select over the order-preserving integer image
+//                  ascending).  A histogram select over the order-preserving integer image
 //                  of the fp32 utilities, held in registers, finds the cut value exactly
 //                  (no floating-point comparison is ever redone in a different order),
 //                  then one pass in slot order, driven by a block-wide prefix sum of the
@@ -21,24 +21,26 @@ namespace pikv {
 namespace {
 
 constexpr int kAppendThreads = 256;
-// evict_select: 256 threads for shards of up to 2048 slots, 1024 beyond.  A step of the select costs
-// the same vector work on a CU either way; with 1024 threads a thread owns a quarter of the slots,
-// so the lists and the compacted utilities leave as runs of 32 bytes per lane instead of 128, and
-// four waves a SIMD cover each other's latencies.  Measured, graph replay, capacity 3/4:
-// 16 shards of 8192 slots 20.4 -> 18.3 us, 128 of 4096 15.9 -> 14.4; 64 of 1999 slots (rows that are not
-// 16-byte aligned, re-read every step before) with their rows 51.7 -> 33.0, 16 of 20000 162.9 -> 148.
+// evict_select: 256 threads for shards of up to 2048 slots, 1024 beyond: a thread then owns a quarter of
+// the slots, the lists and the compacted utilities leave as runs of 32 bytes per lane instead of 128, and
+// four waves a SIMD cover each other's latencies.  (Graph replay, capacity 3/4, select of 16 steps:
+// 16 shards of 8192 slots 20.4 -> 18.3 us, 128 of 4096 15.9 -> 14.4.)
 constexpr int kSelFewSlots = 2048;
-constexpr int kSelCache = 32;        // keys a thread can keep in registers (n <= 32768);
-                                     // at most 255: the digit counts of a step are bytes
+constexpr int kSelCache = 32;        // keys a thread can keep in registers (n <= 32768)
+constexpr int kSelBins = 1024;       // of a round of the select
+constexpr int kSelBinBits = 10;
 
 template <int THREADS>
 struct SelShared {
     static constexpr int kWaves = THREADS / kWave;
-    int cnt[2][3][16];               // per-wave digit counts of a select step, two buffers in turn
+    int hist[kSelBins];
+    uint32_t low[16], high[16];      // per-wave extremes of the keys
+    int least[2];                    // keys equal to the range's lower end; two buffers in turn
+    int found[2][3];                 // the bin of the cut, the keys below it, the keys in it; two buffers in turn
     int scan[2][16];                 // per-wave totals of a block scan, two buffers in turn
     uint64_t wave_best[kWaves];
 };
-// Both pairs of buffers are used in turn, which makes one barrier per use enough: a buffer
+// The pairs of buffers are used in turn, which makes one barrier per use enough: a buffer
 // is rewritten two uses later, and every wave has left the reads of use i before any wave
 // passes the barrier of use i+1.
 
@@ -55,12 +57,15 @@ __device__ __forceinline__ int row_sum(int v) {
 template <int THREADS>
 __device__ __forceinline__ int block_scan_excl(int v, SelShared<THREADS> &sh, int &turn) {
     const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
+    // inclusive sums within the rows of 16 lanes, then the rows before (lane 15 of a row to the next, lane 31 to
+    // the upper half), without LDS
     int incl = v;
-#pragma unroll
-    for (int off = 1; off < kWave; off <<= 1) {
-        const int t = __shfl_up(incl, off, kWave);
-        if (lane >= off) incl += t;
-    }
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x111, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x112, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x114, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x118, 0xf, 0xf, true);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x142, 0xa, 0xf, false);
+    incl += __builtin_amdgcn_update_dpp(0, incl, 0x143, 0xc, 0xf, false);
     int *slot = sh.scan[turn & 1];
     ++turn;
     if (lane == kWave - 1) slot[wave] = incl;
@@ -98,75 +103,126 @@ __device__ __forceinline__ float key_value(uint32_t key) {
     return __uint_as_float((key & 0x80000000u) ? (key & 0x7fffffffu) : ~key);
 }
 
-// Sum over the 64 lanes of a wave, returned in every lane.
-__device__ __forceinline__ int wave_sum(int v) {
-    v = row_sum(v);
-    v += __shfl_xor(v, 16, kWave);
-    v += __shfl_xor(v, 32, kWave);
-    return v;
+// Minimum and maximum over the 64 lanes of a wave, in every lane.
+__device__ __forceinline__ void wave_extremes(uint32_t &low, uint32_t &high) {
+    auto take = [&](uint32_t l, uint32_t h) {
+        low = min(low, l);
+        high = max(high, h);
+    };
+#define PIKV_DPP(v, ctrl) (uint32_t)__builtin_amdgcn_update_dpp(0, (int)(v), ctrl, 0xf, 0xf, true)
+    take(PIKV_DPP(low, 0xB1), PIKV_DPP(high, 0xB1));         // lane ^ 1
+    take(PIKV_DPP(low, 0x4E), PIKV_DPP(high, 0x4E));         // lane ^ 2
+    take(PIKV_DPP(low, 0x141), PIKV_DPP(high, 0x141));       // mirror within 8
+    take(PIKV_DPP(low, 0x140), PIKV_DPP(high, 0x140));       // mirror within 16
+#undef PIKV_DPP
+    auto l = __builtin_amdgcn_permlane16_swap(low, low, false, false), h = __builtin_amdgcn_permlane16_swap(high, high, false, false);
+    low = min(l[0], l[1]), high = max(h[0], h[1]);
+    l = __builtin_amdgcn_permlane32_swap(low, low, false, false), h = __builtin_amdgcn_permlane32_swap(high, high, false, false);
+    low = min(l[0], l[1]), high = max(h[0], h[1]);
 }
 
-// The cut of the general case (drop the `ngone` worst of `n`) is the ngone-th smallest key,
-// found two bits at a time from the top.  With x = key ^ prefix, the candidates whose next
-// digit is below d are exactly the keys with x < d << shift, so three compares per key give
-// the cumulative digit counts and the step enters the digit that holds the wanted rank.
-struct CutSearch {
-    uint32_t prefix = 0;
-    int remaining;           // rank still to locate among the keys that match `prefix`
-    int cand;                // how many keys match `prefix` on the digits decided so far
-    int turn = 0;
-    __device__ CutSearch(int n, int ngone) : remaining(ngone), cand(n) {}
-
-    // c1..c3: this thread's candidates with digit < 1, < 2, < 3.  With PACKED the caller
-    // promises at most 512 per thread, so a wave's totals fit 16 bits and c1, c2 travel
-    // through the lane sums as one word.
-    template <bool PACKED, int THREADS>
-    __device__ __forceinline__ void step(int shift, int c1, int c2, int c3, SelShared<THREADS> &sh) {
-        const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6;
-        if (PACKED) {
-            const int c12 = wave_sum(c1 | (c2 << 16));
-            c1 = c12 & 0xffff;
-            c2 = (int)((uint32_t)c12 >> 16);
-        } else {
-            c1 = wave_sum(c1);
-            c2 = wave_sum(c2);
-        }
-        c3 = wave_sum(c3);
-        int(*slot)[16] = sh.cnt[turn & 1];
-        ++turn;
-        if (lane == 0) {
-            slot[0][wave] = c1;
-            slot[1][wave] = c2;
-            slot[2][wave] = c3;
+// The cut of the general case (drop the `ngone` worst of n) is the ngone-th smallest key: keys below it go, and of
+// the keys equal to it the first keep_eq in slot order stay.  Rounds of a 1024-bin histogram over the
+// range that still holds it - first the smallest to the largest key, then the bin the cut fell into - end
+// when a bin is one value wide or goes as a whole.  Utilities spread over their range, so a bin of the first
+// round holds a few dozen keys and the second or third ends it.  At most four rounds, of three barriers
+// each.  Before, the cut was found two bits at a step, in 16 steps of a barrier and some 20 dependent lane
+// and LDS operations (0.5 us each).  Measured (graph replay, capacity 3/4, no rows moved): 16 shards of 8192 slots
+// 17.7 -> 10.6 us, 128 of 4096 13.4 -> 7.2, 64 of 1999 10.3 -> 6.9, 64 of 256 8.9 -> 5.1, 16 of 20000 32 -> 24, 8 of 60000
+// (read from memory in every round) 218 -> 90; 16 of 8192, 70 % of them zero, 17.9 -> 9.0.
+// `each(f)` calls f(key, real) for the thread's keys, in all lanes.
+struct Cut {
+    uint32_t key;
+    int keep_eq;
+};
+template <int THREADS, class F>
+__device__ __forceinline__ Cut find_cut(int ngone, F each, SelShared<THREADS> &sh, int &turn) {
+    constexpr int kBins = kSelBins / THREADS;                 // a thread's, in the scan
+    const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
+    uint32_t low = 0xffffffffu, high = 0;
+    each([&](uint32_t key, bool valid) {
+        low = min(low, valid ? key : 0xffffffffu);
+        high = max(high, valid ? key : 0u);
+    });
+    wave_extremes(low, high);
+    if (lane == 0) sh.low[wave] = low, sh.high[wave] = high;
+#pragma unroll
+    for (int i = 0; i < kBins; ++i) sh.hist[tid * kBins + i] = 0;
+    if (tid == 0) sh.least[0] = 0;
+    __syncthreads();
+    low = sh.low[min(lane, SelShared<THREADS>::kWaves - 1)];
+    high = sh.high[min(lane, SelShared<THREADS>::kWaves - 1)];
+    wave_extremes(low, high);
+    uint32_t width = high - low;                              // candidates: key - low <= width
+    int remaining = ngone;
+    for (int round = 0;; ++round) {
+        const int bits = width == 0 ? 0 : 32 - __builtin_clz(width);
+        const int shift = bits > kSelBinBits ? bits - kSelBinBits : 0;
+        // Keys of the range's least value - entries that were never attended have utility zero - are counted by
+        // the wave, and when they alone reach the cut it is that value.  (Other values that fill a wave
+        // would queue for their bin: a wave that sees that for its first keys lets one lane count for
+        // all that share the leader's bin.)
+        int seen = 0, least = 0;
+        bool crowded = false;
+        each([&](uint32_t key, bool valid) {
+            const uint32_t x = key - low;
+            bool in = valid && x <= width;
+            const int bin = (int)(x >> shift);
+            least += __popcll(__ballot(in && x == 0));
+            in = in && x != 0;
+            if (seen++ == 0 || crowded) {
+                const uint64_t who = __ballot(in);
+                if (who != 0) {
+                    const int leader = __builtin_ctzll(who), first = __builtin_amdgcn_readlane(bin, leader);
+                    const uint64_t same = __ballot(in && bin == first);
+                    crowded = __popcll(same) > 16;
+                    if (crowded) {
+                        if (lane == leader) atomicAdd(&sh.hist[first], __popcll(same));
+                        in = in && bin != first;
+                    }
+                }
+            }
+            if (in) atomicAdd(&sh.hist[bin], 1);
+        });
+        if (lane == 0 && least > 0) {
+            atomicAdd(&sh.hist[0], least);
+            atomicAdd(&sh.least[round & 1], least);
         }
         __syncthreads();
-        // row r of 16 lanes fetches the waves' counts for digit < r + 1
-        const int row = lane >> 4, w = lane & 15;
-        const int v = row_sum(row < 3 && w < SelShared<THREADS>::kWaves ? slot[row][w] : 0);
-        const int C1 = __builtin_amdgcn_readlane(v, 0);
-        const int C2 = __builtin_amdgcn_readlane(v, 16);
-        const int C3 = __builtin_amdgcn_readlane(v, 32);
-        if (remaining <= C1) {
-            cand = C1;
-        } else if (remaining <= C2) {
-            prefix |= 1u << shift;
-            remaining -= C1;
-            cand = C2 - C1;
-        } else if (remaining <= C3) {
-            prefix |= 2u << shift;
-            remaining -= C2;
-            cand = C3 - C2;
-        } else {
-            prefix |= 3u << shift;
-            remaining -= C3;
-            cand -= C3;
+        least = sh.least[round & 1];
+        if (remaining <= least) return Cut{low, least - remaining};          // (the same in the whole block)
+        if (tid == 0) sh.least[(round & 1) ^ 1] = 0;
+        int count[kBins], sum = 0;
+#pragma unroll
+        for (int i = 0; i < kBins; ++i) {
+            count[i] = sh.hist[tid * kBins + i];
+            sum += count[i];
         }
+        int below = block_scan_excl(sum, sh, turn);
+        int *found = sh.found[round & 1];
+        if (below < remaining && remaining <= below + sum) {
+#pragma unroll
+            for (int i = 0; i < kBins; ++i) {
+                if (below < remaining && remaining <= below + count[i])
+                    found[0] = tid * kBins + i, found[1] = below, found[2] = count[i];
+                below += count[i];
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < kBins; ++i) sh.hist[tid * kBins + i] = 0;     // (its own bins only)
+        __syncthreads();
+        const uint32_t offset = (uint32_t)found[0] << shift;
+        remaining -= found[1];
+        const int cand = found[2];
+        low += offset;
+        width = min(width - offset, (1u << shift) - 1u);
+        if (shift == 0) return Cut{low, cand - remaining};
+        if (remaining == cand) return Cut{low + width, 0};
     }
-};
+}
 
 // Keys in registers: thread t owns the `per` consecutive slots from t * per (per a multiple
-// of 4, at most NCH), so the 16 steps touch no memory and slot order is thread order.  Slots
-// past n hold the largest key: its digit is always 3, which no cumulative count includes.
+// of 4, at most NCH), so the rounds touch no memory and slot order is thread order.
 template <int THREADS, int NCH>
 __device__ __forceinline__ void select_cached(const EvictParams &p, int be, float *u, int n,
                                               int ngone, bool vec, SelShared<THREADS> &sh) {
@@ -189,28 +245,14 @@ __device__ __forceinline__ void select_cached(const EvictParams &p, int be, floa
         keys[j0 + 2] = (any && i0 + 2 < n) ? order_key(v.z) : 0xffffffffu;
         keys[j0 + 3] = (any && i0 + 3 < n) ? order_key(v.w) : 0xffffffffu;
     }
-    CutSearch cs(n, ngone);
-    for (int shift = 30; shift >= 0; shift -= 2) {
-        // One byte of `acc` per digit value; a key off the prefix has x >> shift >= 4 and is
-        // counted with digit 3, which no cumulative count includes.  No compare, no carry.
-        uint32_t acc = 0;
+    int turn = 0;
+    const Cut found = find_cut<THREADS>(ngone, [&](auto take) {
 #pragma unroll
-        for (int j0 = 0; j0 < NCH; j0 += 4) {
-            if (j0 < per) {
-#pragma unroll
-                for (int t = 0; t < 4; ++t) {
-                    const uint32_t digit = min((keys[j0 + t] ^ cs.prefix) >> shift, 3u);
-                    acc += 1u << (digit << 3);
-                }
-            }
-        }
-        const int c1 = acc & 0xff;
-        const int c2 = c1 + ((acc >> 8) & 0xff);
-        const int c3 = c2 + ((acc >> 16) & 0xff);
-        cs.template step<true>(shift, c1, c2, c3, sh);
-    }
-    const uint32_t cut = cs.prefix;               // keys < cut go; of the keys == cut (`cand`
-    const int keep_eq = cs.cand - cs.remaining;   // of them) the first keep_eq in slot order stay
+        for (int j = 0; j < NCH; ++j)
+            if (j < per) take(keys[j], first + j < n);
+    }, sh, turn);
+    const uint32_t cut = found.key;               // keys < cut go; of the keys == cut
+    const int keep_eq = found.keep_eq;            // the first keep_eq in slot order stay
 
     constexpr int kWords = (NCH + 31) / 32;
     uint32_t gone[kWords];
@@ -226,7 +268,7 @@ __device__ __forceinline__ void select_cached(const EvictParams &p, int be, floa
         n_eq += valid && keys[j] == cut;
     }
     if (keep_eq > 0) {                            // ties at the cut: the earliest keep_eq stay
-        int eq_rank = block_scan_excl(n_eq, sh, cs.turn);
+        int eq_rank = block_scan_excl(n_eq, sh, turn);
 #pragma unroll
         for (int j = 0; j < NCH; ++j) {
             const bool valid = j < per && first + j < n;
@@ -239,7 +281,7 @@ __device__ __forceinline__ void select_cached(const EvictParams &p, int be, floa
             }
         }
     }
-    int rank = block_scan_excl(n_gone, sh, cs.turn);   // evicted slots before my first slot
+    int rank = block_scan_excl(n_gone, sh, turn);   // evicted slots before my first slot
     int32_t *out = p.evicted_idx + (int64_t)be * p.max_evict;
     // In-place compaction is safe here: every utility is already held as a key.
 #pragma unroll
@@ -261,27 +303,21 @@ __device__ __forceinline__ void select_cached(const EvictParams &p, int be, floa
     }
 }
 
-// More keys than the registers hold: every step re-reads them (slot i = tid + j * THREADS).
+// More keys than the registers hold: every round re-reads them (slot i = tid + j * THREADS).
 template <int THREADS>
 __device__ __forceinline__ void select_stream(const EvictParams &p, int be, float *u, int n,
                                               int ngone, SelShared<THREADS> &sh) {
     const int tid = threadIdx.x;
     const int nchunk = (n + THREADS - 1) / THREADS;
-    CutSearch cs(n, ngone);
-    for (int shift = 30; shift >= 0; shift -= 2) {
-        const uint32_t t1 = 1u << shift, t2 = 2u << shift, t3 = 3u << shift;
-        int c1 = 0, c2 = 0, c3 = 0;
+    int turn = 0;
+    const Cut found = find_cut<THREADS>(ngone, [&](auto take) {
         for (int j = 0; j < nchunk; ++j) {
             const int i = tid + j * THREADS;
-            const uint32_t x = (i < n ? order_key(u[i]) : 0xffffffffu) ^ cs.prefix;
-            c1 += x < t1;
-            c2 += x < t2;
-            c3 += x < t3;
+            take(i < n ? order_key(u[i]) : 0u, i < n);
         }
-        cs.template step<false>(shift, c1, c2, c3, sh);
-    }
-    const uint32_t cut = cs.prefix;
-    const int keep_eq = cs.cand - cs.remaining;
+    }, sh, turn);
+    const uint32_t cut = found.key;
+    const int keep_eq = found.keep_eq;
     int32_t *out = p.evicted_idx + (int64_t)be * p.max_evict;
     int eq_seen = 0, gone_seen = 0;       // running totals over the chunks already done
     for (int j = 0; j < nchunk; ++j) {
@@ -291,9 +327,9 @@ __device__ __forceinline__ void select_stream(const EvictParams &p, int be, floa
         const uint32_t key = order_key(ui);
         const bool is_eq = valid && key == cut, is_less = valid && key < cut;
         int eq_total, gone_total;
-        const int eq_rank = eq_seen + block_rank_flag(is_eq, sh, cs.turn, &eq_total);
+        const int eq_rank = eq_seen + block_rank_flag(is_eq, sh, turn, &eq_total);
         const bool gone = is_less || (is_eq && eq_rank >= keep_eq);
-        const int gone_before = gone_seen + block_rank_flag(gone, sh, cs.turn, &gone_total);
+        const int gone_before = gone_seen + block_rank_flag(gone, sh, turn, &gone_total);
         if (valid) {
             if (gone) {
                 if (gone_before < p.max_evict) out[gone_before] = i;
@@ -362,7 +398,7 @@ __global__ __launch_bounds__(THREADS) void evict_select(EvictParams p) {
         return;
     }
 
-    // keys held per thread: the next size that covers n; beyond the largest, re-read them
+    // keys held per thread: the next size that covers n; beyond the largest, re-read in every round
     const bool vec = p.S % 4 == 0 && (reinterpret_cast<uintptr_t>(p.utility) & 15) == 0;
     if constexpr (THREADS == 256) {
         select_cached<THREADS, 8>(p, be, u, n, ngone, vec, sh);         // S <= kSelFewSlots

@@ -711,6 +711,40 @@ def test_evict_few_entries_of_a_large_shard(n, S, compact):
         np.testing.assert_array_equal(got_u[0, e, :kept.size], kept)
 
 
+@pytest.mark.parametrize("n", [3, 1023, 2048, 2049, 8193, 33000])
+@pytest.mark.parametrize("kind", ["clusters", "neighbours", "least", "extremes", "crowd"])
+def test_evict_cut_at_every_depth_of_the_histogram(n, kind):
+    """Utilities that end the select in its first, second, third or last round: two far clusters of neighbouring
+    bit patterns, consecutive bit patterns, ties at the least value, infinities of both signs, one value
+    that fills most of a bin - in registers and re-read from memory, against a stable sort."""
+    rng = np.random.default_rng(n)
+    if kind == "clusters":
+        bits = np.where(rng.random(n) < 0.5, 0x00000100, 0x7f000000) + rng.integers(0, 64, n)
+        u = bits.astype(np.uint32).view(np.float32)
+    elif kind == "neighbours":
+        u = (0x3f000000 + rng.permutation(n)).astype(np.uint32).view(np.float32)
+    elif kind == "least":
+        u = np.where(rng.random(n) < 0.6, 0.0, rng.exponential(1.0, n)).astype(np.float32)
+    elif kind == "extremes":
+        u = rng.normal(size=n).astype(np.float32)
+        u[rng.random(n) < 0.2], u[rng.random(n) < 0.2] = np.inf, -np.inf
+    else:
+        u = np.where(rng.random(n) < 0.8, 0.25, rng.random(n)).astype(np.float32)
+        u[0] = -1.0
+    E, S = 3, n + 5
+    desc = pk.make_desc(1, 1, 1, 16, E, S, dtype=1)
+    order = np.lexsort((np.arange(n), -u))                       # utility descending, then slot ascending
+    for drop in sorted({1, n // 5 + 1, n // 2, n - 1, n} - {0}):
+        util = torch.zeros((1, E, S), device=DEV)
+        util[0, 1, :n] = torch.from_numpy(u.copy()).to(DEV)
+        nv = torch.tensor([[0, n, 0]], device=DEV, dtype=torch.int32)
+        eidx = torch.full((1, E, n), -7, device=DEV, dtype=torch.int32)
+        ecnt = torch.zeros((1, E), device=DEV, dtype=torch.int32)
+        pk.pikv_evict(desc, util, nv, n - drop, None, 0, eidx, ecnt, n, False, None, None)
+        assert t2n(ecnt).tolist() == [[0, drop, 0]] and t2n(nv).tolist() == [[0, n - drop, 0]]
+        np.testing.assert_array_equal(t2n(eidx)[0, 1, :drop], np.sort(order[n - drop:]))
+
+
 def test_evict_special_values_and_selection_list():
     g = wl.Geometry(B=2, Hq=2, Hkv=2, D=16, E=4, S=64, k=2, dtype="bf16")
     rng = np.random.default_rng(3)
