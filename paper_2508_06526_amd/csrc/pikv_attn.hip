@@ -1037,6 +1037,309 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
     }
 }
 
+// ---------------------------------------------------------------------------------------
+// Grouped queries over fp32 rows on the matrix cores: up to 16 heads of a group share every K/V byte as
+// one side of 16x16x4 fp32 products (full fp32 multiply-adds, one routing decision per token).
+//
+// Per wave and 16 entries, lane (c, r) = (lane % 16, lane / 16):
+//   * S^T[entry][head] = K . Q^T.  The order of the contraction is free: product i of step s takes the
+//     dimensions {16 s + 4 r + i}, so that a lane's operands are 16-byte pieces of row c - K is requested in
+//     that form (64 bytes of a row per load, the next load the line's other half) and needs no LDS.  The four i, and
+//     the steps, are summed apart and joined pairwise.
+//   * The lane's scores are those of entries 4r .. 4r+3 and head c, and product i of the second
+//     contraction takes the entries {4 r + i}: its operand is the lane's own i-th probability.  The
+//     operand of V is the i-th of four rows, loaded as such.
+//   * The four products of 16 entries are summed apart, pairwise, and then added to the running output (in one
+//     chain: y 1.89 - 2.42e-7 off 64 bits; so 1.82 - 2.32e-7, the plain kernel 1.83 - 2.39e-7).
+// Codes: the projected query U_K q comes out of the same products in operand form, each wave over a quarter
+// of the head dimension, joined in LDS.
+// The plain kernel above spends 4 multiply-adds and a reduction over 4 - 32 lanes per head and row piece:
+// with 4 and 8 heads it was bound by vector issue, and at 8 it left one wave per SIMD (252 registers);
+// groups of other than 2, 4 and 8 heads streamed K/V once per head.
+// Measured, pass and merge, against the plain kernel: 8 heads over rows of 128 values (512 MiB) 147 -> 102 us, 64 values
+// 129 -> 107, 3 heads 250 -> 92, 6 heads (256 MiB) 166 -> 53, 16 heads 459 -> 63, 32 heads (128 MiB) 392 -> 60; rank-64 codes x 8
+// heads (104 MiB) 46 -> 38; 4 heads 107 -> 100 at 64 values, even at 128; 2 heads stay there (49 -> 51).
+constexpr int gqa32_tile(int width) { return width >= 128 ? 16 : width == 64 ? 32 : 64; }
+constexpr int kGqa32BlocksPerCu = 3;
+// Rows of 4 floats more than W: banks.
+constexpr size_t gqa32_merge_bytes(int width) { return (size_t)kWavesPerBlock * 16 * (width + 4) * sizeof(float); }
+
+template <int W, int SC, bool CODES>
+__global__ __launch_bounds__(kWavesPerBlock *kWave, kGqa32BlocksPerCu) void attn_partial_gqa32(AttnParams p, int gb) {
+    constexpr int TILE = gqa32_tile(W), SUBS = TILE / 16, KS = W / 16, SETS = W / 16;
+    constexpr int VW = SETS < 4 ? SETS : 4, VL = SETS / VW;   // floats of a V load, loads per row
+    const int tid = threadIdx.x;
+    const int lane = tid & (kWave - 1);
+    const int wave = tid >> 6;
+    const int c = lane & 15;
+    const int r = lane >> 4;
+
+    // (ids to work items as in attn_partial_gqa)
+    int bid = blockIdx.x;
+    if (gridDim.x % 8 == 0) bid = (bid % 8) * (gridDim.x / 8) + bid / 8;
+    const int split = bid % p.nsplit;
+    bid /= p.nsplit;
+    const int j = bid % p.k;
+    bid /= p.k;
+    const int hgroups = p.Hq / gb;
+    const int hg = bid % hgroups;
+    const int b = bid / hgroups;
+    const int h0 = hg * gb;
+    const int hk = h0 / p.G;
+
+    // Query operand: q[head c][16 s + 4 r + i]; heads past the group repeat the last one, nothing reads
+    // what they lead to.
+    const float *q = static_cast<const float *>(p.q) + ((int64_t)b * p.Hq + h0 + min(c, gb - 1)) * p.D;
+    const bool q_aligned = (reinterpret_cast<uintptr_t>(p.q) & 15) == 0;
+    auto query = [&](int d) {
+        if (q_aligned) return *reinterpret_cast<const f32x4_t *>(q + d);
+        return f32x4_t{q[d], q[d + 1], q[d + 2], q[d + 3]};
+    };
+    constexpr int US = CODES ? 2 : 1;        // a wave's 16-value pieces of the head dimension (D <= 128)
+    f32x4_t qop[KS], q_raw[US], u_raw[US][KS];
+    if constexpr (CODES) {                   // what the projection reads is requested ahead of everything
+        const float *U = static_cast<const float *>(p.U_K) + ((int64_t)hk * W + c) * p.D;
+#pragma unroll
+        for (int n = 0; n < US; ++n) {
+            const int d = min(16 * (wave + kWavesPerBlock * n), p.D - 16) + 4 * r;
+            q_raw[n] = query(d);
+#pragma unroll
+            for (int s = 0; s < KS; ++s) u_raw[n][s] = __builtin_bit_cast(f32x4_t, load16(U + (int64_t)16 * s * p.D + d));
+        }
+    } else {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) qop[s] = query(16 * s + 4 * r);
+    }
+    const ShardRef sh = resolve_shard(p, b, b, j, lane);
+    int r0, r1;
+    split_rows<TILE>(p, sh.n, split, &r0, &r1);
+
+    __shared__ float sm_m[kWavesPerBlock][16];
+    __shared__ float sm_l[kWavesPerBlock][16];
+    // the waves' parts of the projected query; the raw scores of the block's rows, [head][chunk]; the waves'
+    // outputs (gqa32_merge_bytes)
+    extern __shared__ __attribute__((aligned(16))) float gqa32_lds[];
+
+    const int64_t part_base = (((int64_t)b * p.Hq + h0) * p.k + j) * p.nsplit + split;
+    const int64_t part_head_stride = (int64_t)p.k * p.nsplit;
+    if (r0 >= r1) {
+        for (int idx = tid; idx < gb * W; idx += blockDim.x) {
+            const int g = idx / W, d = idx - g * W;
+            p.part_acc[(part_base + g * part_head_stride) * W + d] = 0.0f;
+            if (d == 0) {
+                p.part_ml[(part_base + g * part_head_stride) * 2 + 0] = -INFINITY;
+                p.part_ml[(part_base + g * part_head_stride) * 2 + 1] = 0.0f;
+            }
+        }
+        return;
+    }
+
+    // Requests as in attn_partial_gqa: 32-bit byte offsets from the kv head's base, rows past the end
+    // clamped onto the last one by a minimum, sums that saturate, each tile's offset hidden from the optimiser.
+    const char *Kb = sh.K + (int64_t)hk * p.stride_h * 4;
+    const char *Vb = sh.V + (int64_t)hk * p.stride_h * 4;
+    const uint32_t rb = (uint32_t)(p.stride_s * 4);
+    const uint32_t last = (uint32_t)(r1 - 1) * rb;
+    auto opaque = [](uint32_t v) {
+        asm volatile("" : "+v"(v));
+        return v;
+    };
+    const int row_most = p.S - 1;
+    auto rows_bytes = [&](int rows) { return (uint32_t)min(rows, row_most) * rb; };
+    auto sum = [](uint32_t a, uint32_t b) { return __builtin_elementwise_add_sat(a, b); };
+    f32x4_t kr[SUBS][KS];
+    uint32_t vr[SUBS][4][VL][VW];
+    auto load_k = [&](int t0) {
+        const uint32_t at = opaque(sum(rows_bytes(t0), rows_bytes(c)));
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) {
+            const char *row = Kb + (size_t)(min(sum(at, rows_bytes(16 * sub)), last) + 16 * r);
+#pragma unroll
+            for (int s = 0; s < KS; ++s) kr[sub][s] = __builtin_bit_cast(f32x4_t, load16_stream(row + 64 * s));
+        }
+    };
+    auto load_v = [&](int t0) {
+        const uint32_t at = opaque(sum(rows_bytes(t0), rows_bytes(4 * r)));
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+            for (int i = 0; i < 4; ++i) {
+                const char *row = Vb + (size_t)(min(sum(at, rows_bytes(16 * sub + i)), last) + 4 * VW * c);
+#pragma unroll
+                for (int l = 0; l < VL; ++l) load_words_stream<VW>(vr[sub][i][l], row + 64 * VW * l);
+            }
+    };
+    auto mfma = [](float a, float b, f32x4_t acc) { return __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc, 0, 0, 0); };
+    const f32x4_t zero = {0.f, 0.f, 0.f, 0.f};
+    int t0 = r0 + __builtin_amdgcn_readfirstlane(wave) * TILE;
+    load_k(t0);                              // (a wave without rows loads the last one)
+    load_v(t0);
+
+    constexpr int AP = W + 4;                // floats of a head's row in LDS (banks)
+    if constexpr (CODES) {
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            f32x4_t proj[4] = {zero, zero, zero, zero};
+#pragma unroll
+            for (int n = 0; n < US; ++n)
+                if (16 * (wave + kWavesPerBlock * n) < p.D)
+#pragma unroll
+                    for (int i = 0; i < 4; ++i) proj[i] = mfma(u_raw[n][s][i], q_raw[n][i], proj[i]);
+            *reinterpret_cast<f32x4_t *>(gqa32_lds + (wave * 16 + c) * AP + 16 * s + 4 * r) =
+                (proj[0] + proj[1]) + (proj[2] + proj[3]);
+        }
+        __syncthreads();
+#pragma unroll
+        for (int s = 0; s < KS; ++s) {
+            f32x4_t of[kWavesPerBlock];
+#pragma unroll
+            for (int w = 0; w < kWavesPerBlock; ++w)
+                of[w] = *reinterpret_cast<const f32x4_t *>(gqa32_lds + (w * 16 + c) * AP + 16 * s + 4 * r);
+            qop[s] = (of[0] + of[1]) + (of[2] + of[3]);
+        }
+        if (SC == kScoresStaged) __syncthreads();            // the area becomes the score stage
+    }
+    // complete before the loop: a wait for it in there would be a wait for the tiles' loads
+#pragma unroll
+    for (int s = 0; s < KS; ++s) asm volatile("" : "+v"(qop[s]));
+
+    float m = -INFINITY, lsum = 0.0f;
+    f32x4_t oacc[SETS];                      // oacc[4 l + i][x] = O[head c][16 VW l + VW (4 r + x) + i]
+#pragma unroll
+    for (int i = 0; i < SETS; ++i) oacc[i] = zero;
+
+    if (t0 < r1) do {
+        const int tnext = t0 + kWavesPerBlock * TILE;
+        float sv[4 * SUBS];                  // sv[4 sub + x]: entry t0 + 16 sub + 4 r + x
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub) {
+            f32x4_t of[4];                   // of[l]: sums of 2^l steps that wait for their partner
+#pragma unroll
+            for (int s = 0; s < KS; ++s) {
+                f32x4_t part[4];
+#pragma unroll
+                for (int i = 0; i < 4; ++i) part[i] = mfma(kr[sub][s][i], qop[s][i], zero);
+                f32x4_t t = (part[0] + part[1]) + (part[2] + part[3]);
+#pragma unroll
+                for (int l = 0; l < 3; ++l) {                // pairwise, like the carry of a counter
+                    if (((s + 1) & ((2 << l) - 1)) == 0) t = of[l] + t;
+                    else if (((s + 1) & ((1 << l) - 1)) == 0) of[l] = t;
+                }
+                of[3] = t;
+                if (W == 128 && (s & 1)) __builtin_amdgcn_sched_barrier(0);      // (registers)
+            }
+#pragma unroll
+            for (int x = 0; x < 4; ++x) sv[4 * sub + x] = t0 + 16 * sub + 4 * r + x < r1 ? of[3][x] * p.scale : -INFINITY;
+        }
+        load_k(tnext);
+
+        if (SC == kScoresStaged && c < gb) {
+            float *dst = gqa32_lds + c * p.chunk + (t0 - r0) + 4 * r;
+#pragma unroll
+            for (int sub = 0; sub < SUBS; ++sub)
+                *reinterpret_cast<float4 *>(dst + 16 * sub) = make_float4(sv[4 * sub], sv[4 * sub + 1], sv[4 * sub + 2], sv[4 * sub + 3]);
+        } else if (SC == kScoresDirect && c < gb) {
+            float *dst = p.scores + (((int64_t)b * p.Hq + h0 + c) * p.k + j) * p.S;
+#pragma unroll
+            for (int sub = 0; sub < SUBS; ++sub) {
+                const int row = t0 + 16 * sub + 4 * r;
+                if (row + 4 <= r1 && (p.S & 3) == 0 && (reinterpret_cast<uintptr_t>(p.scores) & 15) == 0) {
+                    *reinterpret_cast<float4 *>(dst + row) = make_float4(sv[4 * sub], sv[4 * sub + 1], sv[4 * sub + 2], sv[4 * sub + 3]);
+                } else {
+#pragma unroll
+                    for (int x = 0; x < 4; ++x)
+                        if (row + x < r1) dst[row + x] = sv[4 * sub + x];
+                }
+            }
+        }
+
+        // online softmax for head c (its entries are spread over the 4 lane groups)
+        float tm = sv[0];
+#pragma unroll
+        for (int x = 1; x < 4 * SUBS; ++x) tm = fmaxf(tm, sv[x]);
+        const float mn = fmaxf(m, group_max(tm));
+        if (__any(mn > m)) {                 // else the factor is 1 in every lane
+            const float corr = __expf(m - mn);
+            m = mn;
+            lsum *= corr;
+#pragma unroll
+            for (int i = 0; i < SETS; ++i) oacc[i] = oacc[i] * corr;
+        }
+#pragma unroll
+        for (int x = 0; x < 4 * SUBS; ++x) {
+            sv[x] = __expf(sv[x] - mn);
+            lsum += sv[x];
+        }
+#pragma unroll
+        for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+            for (int l = 0; l < VL; ++l)
+#pragma unroll
+                for (int i = 0; i < VW; ++i) {
+                    f32x4_t part[4];
+#pragma unroll
+                    for (int x = 0; x < 4; ++x) part[x] = mfma(__uint_as_float(vr[sub][x][l][i]), sv[4 * sub + x], zero);
+                    oacc[VW * l + i] = oacc[VW * l + i] + ((part[0] + part[1]) + (part[2] + part[3]));
+                }
+        load_v(tnext);
+        t0 = tnext;
+    } while (t0 < r1);
+
+    __syncthreads();
+    if (SC == kScoresStaged) {               // the block's scores: one burst per head, a head per wave
+        const int rows = r1 - r0, rows4 = rows & ~3;
+        for (int g = wave; g < gb; g += kWavesPerBlock) {
+            float *dst = p.scores + (((int64_t)b * p.Hq + h0 + g) * p.k + j) * p.S + r0;
+            const float *src = gqa32_lds + g * p.chunk;
+            if ((p.S & 3) == 0 && (reinterpret_cast<uintptr_t>(p.scores) & 15) == 0) {
+                for (int i = lane * 4; i < rows4; i += kWave * 4)
+                    *reinterpret_cast<float4 *>(dst + i) = *reinterpret_cast<const float4 *>(src + i);
+                if (lane < rows - rows4) dst[rows4 + lane] = src[rows4 + lane];
+            } else {
+                for (int i = lane; i < rows; i += kWave) dst[i] = src[i];
+            }
+        }
+        __syncthreads();                     // the stage becomes the merge area
+    }
+
+    // the waves' results -> LDS, then merge the waves and write the block's partial
+    lsum += __shfl_xor(lsum, 16, kWave);
+    lsum += __shfl_xor(lsum, 32, kWave);
+    if (c < gb) {
+        float *wacc = gqa32_lds + (wave * 16 + c) * AP;
+#pragma unroll
+        for (int l = 0; l < VL; ++l)
+#pragma unroll
+            for (int x = 0; x < 4; ++x)
+#pragma unroll
+                for (int i = 0; i < VW; ++i) wacc[16 * VW * l + VW * (4 * r + x) + i] = oacc[VW * l + i][x];
+    }
+    if (r == 0) {
+        sm_m[wave][c] = m;
+        sm_l[wave][c] = lsum;
+    }
+    __syncthreads();
+    for (int idx = tid; idx < gb * W; idx += blockDim.x) {
+        const int g = idx / W, d = idx - g * W;
+        float M = sm_m[0][g];
+#pragma unroll
+        for (int w2 = 1; w2 < kWavesPerBlock; ++w2) M = fmaxf(M, sm_m[w2][g]);
+        float a = 0.0f, L = 0.0f;
+#pragma unroll
+        for (int w2 = 0; w2 < kWavesPerBlock; ++w2) {
+            const float f = sm_m[w2][g] == -INFINITY ? 0.0f : __expf(sm_m[w2][g] - M);
+            a = fmaf(gqa32_lds[(w2 * 16 + g) * AP + d], f, a);
+            L = fmaf(sm_l[w2][g], f, L);
+        }
+        const int64_t at = part_base + g * part_head_stride;
+        p.part_acc[at * W + d] = a;
+        if (d == 0) {
+            p.part_ml[at * 2 + 0] = M;
+            p.part_ml[at * 2 + 1] = L;
+        }
+    }
+}
+
 template <typename T, int THREADS>
 __global__ __launch_bounds__(THREADS) void attn_combine(CombineParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // combine_smem_bytes()
@@ -1072,6 +1375,19 @@ void launch_gqa(int row_tiles, const AttnParams &p, int64_t blocks, size_t lds, 
     if (row_tiles == 1) launch(std::integral_constant<int, 1>{});
     else if (row_tiles == 2) launch(std::integral_constant<int, 2>{});
     else launch(std::integral_constant<int, 4>{});
+}
+
+template <int W, bool CODES>
+void launch_gqa32(int gb, const AttnParams &p, int64_t blocks, hipStream_t st) {
+    const dim3 grid((unsigned)blocks), block(kWavesPerBlock * kWave);
+    const size_t stage = p.stage_scores ? (size_t)gb * p.chunk * sizeof(float) : 0, merge = gqa32_merge_bytes(W);
+    const size_t lds = stage > merge ? stage : merge;
+    if (p.scores == nullptr)
+        hipLaunchKernelGGL((attn_partial_gqa32<W, kScoresNone, CODES>), grid, block, lds, st, p, gb);
+    else if (p.stage_scores)
+        hipLaunchKernelGGL((attn_partial_gqa32<W, kScoresStaged, CODES>), grid, block, lds, st, p, gb);
+    else
+        hipLaunchKernelGGL((attn_partial_gqa32<W, kScoresDirect, CODES>), grid, block, lds, st, p, gb);
 }
 
 template <typename T>
@@ -1117,6 +1433,10 @@ static bool plain_pays(const pikv_desc *d, int k, int row_tiles) {
     return units * splits <= few && bytes * G <= mib << 20;
 }
 
+// The least heads per block for the fp32 matrix-core kernel: with two, 14 of a product's 16 rows are padding, and the plain
+// kernel is ahead by 1 - 4 % (256 MiB 48.5 against 50.6 us, rank-32 codes 52.9 against 59).
+constexpr int kGqa32Heads = 3;
+
 int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_limit) {
     const int rc = check_desc(d);
     if (rc != PIKV_OK) return rc;
@@ -1132,6 +1452,12 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
                           (int64_t)d->S * d->stride_s * 2 < ((int64_t)1 << 32) &&
                           !plain_pays(d, k, group_tiles);
     if (gqa_mfma) gb = G;
+    // fp32 groups: as many heads per block as divide the group, up to the 16 of a product
+    int gb32 = G < 16 ? G : 16;
+    while (G % gb32 != 0) --gb32;
+    const bool gqa_f32 = d->route_rows_per_seq == 1 && d->dtype == PIKV_F32 && gb32 >= kGqa32Heads &&
+                         (int64_t)d->S * d->stride_s * 4 < ((int64_t)1 << 32);
+    if (gqa_f32) gb = gb32;
     const int tq = d->tq > 1 ? d->tq : 1;
     // draft queries are folded into the query group of the matrix-core kernel's 128-value rows only
     if (tq > 1 && (!gqa_mfma || W != 128 || d->Hq % tq != 0 || G % tq != 0)) return PIKV_ERR_UNSUPPORTED;
@@ -1140,12 +1466,12 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     const int lpr = W / epl;
     if (lpr < 1 || lpr > 32) return PIKV_ERR_UNSUPPORTED;
     const int row_bytes = W * elem_bytes(d->dtype);
-    const int tile = gqa_mfma ? gqa_tile(W, row_tiles) : (kWave / lpr) * plain_loads_per_tile(row_bytes, gb);
+    const int tile = gqa_mfma ? gqa_tile(W, row_tiles) : gqa_f32 ? gqa32_tile(W) : (kWave / lpr) * plain_loads_per_tile(row_bytes, gb);
     const int64_t units = (int64_t)d->B * (d->Hq / gb) * k;
     // One round of resident blocks: 256 CUs times the 4-wave blocks a CU holds at this
     // kernel's register footprint.  Fewer, longer blocks keep the per-wave prefetch chain
     // busy and shrink the partials that the combine pass has to merge.
-    int resident = gqa_mfma ? gqa_blocks_per_cu(W, row_tiles, d->rank > 0) : plain_blocks_per_cu(row_bytes, gb);
+    int resident = gqa_mfma ? gqa_blocks_per_cu(W, row_tiles, d->rank > 0) : gqa_f32 ? kGqa32BlocksPerCu : plain_blocks_per_cu(row_bytes, gb);
     // More than 8 rows per kv head: every split writes and re-reads rows * 128 accumulators, and
     // two rounds' worth of longer blocks beat three (16 rows, 128 MiB: 36.0 against 40.0 us).
     if (gqa_mfma && W == 128 && gb > 8 && resident > 2) resident = 2;
@@ -1158,7 +1484,8 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     // 128 values in groups want more of them than the kernel that took these calls before, and are
     // not refused for it.
     const size_t split_bytes = (size_t)(d->B > 0 ? d->B : 1) * d->Hq * k * (W + 2) * sizeof(float);
-    const int64_t scratch_splits = scratch_limit == SIZE_MAX || !gqa_mfma || W == 128 ? INT32_MAX : (int64_t)((scratch_limit - 1024) / split_bytes);
+    const bool capped = scratch_limit != SIZE_MAX && (gqa_f32 || (gqa_mfma && W != 128));
+    const int64_t scratch_splits = capped ? (int64_t)((scratch_limit - 1024) / split_bytes) : INT32_MAX;
     auto split_for = [&](int res) {
         nsplit = units > 0 ? (int64_t)256 * res / units : 1;
         // No finer than two tiles per wave: with one, nothing is in flight while a wave computes,
@@ -1176,7 +1503,8 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
         if (nsplit > scratch_splits) nsplit = scratch_splits;
         if (nsplit < 1) nsplit = 1;
         chunk = (int)((d->S + nsplit - 1) / nsplit);
-        chunk = (chunk + tile - 1) / tile * tile;
+        const int unit = gqa_f32 ? kWavesPerBlock * tile : tile;      // (fp32 groups: whole rounds, so that a split's scores start a line)
+        chunk = (chunk + unit - 1) / unit * unit;
         nsplit = (d->S + chunk - 1) / chunk;
         // Matrix-core kernel: when that leaves the waves of a block uneven tile counts (c3: 11
         // tiles, 3 + 3 + 3 + 2) and blocks of exactly two tiles per wave are at most a third more
@@ -1186,7 +1514,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
         // measured slower (k = 16: 8 splits of 8 tiles per wave against 6 splits, +3.7 %).
         const int even = 2 * kWavesPerBlock * tile;
         const int64_t fine = d->S / even;
-        if (gqa_mfma && g_split_override == 0 && chunk % (kWavesPerBlock * tile) != 0 && d->S % even == 0 &&
+        if ((gqa_mfma || gqa_f32) && g_split_override == 0 && chunk % (kWavesPerBlock * tile) != 0 && d->S % even == 0 &&
             fine > nsplit && fine * 3 <= nsplit * 4 && fine <= kMaxPartialsPerHead / k && fine <= scratch_splits &&
             (units * fine) % 256 == 0) {
             nsplit = fine;
@@ -1234,11 +1562,41 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
             }
             if (!fits) stage = 0;
         }
+    } else if (gqa_f32) {
+        // The stage shares its LDS with the merge of the waves; 512 bytes of statistics beside it.
+        auto fits = [&](int res) {
+            const size_t merge = gqa32_merge_bytes(W), lds = (stage > merge ? stage : merge) + 1024;
+            return (size_t)res * lds <= 160 * 1024 && stage <= 64 * 1024 - 256;
+        };
+        if (!fits(resident)) {
+            split_for(2);
+            stage = (size_t)gb * chunk * sizeof(float);
+            bool fit = fits(2);
+            if (!fit && g_split_override == 0) {
+                // long shards: cut until the scores fit, as long as a block keeps four rounds of tiles (8 heads x
+                // 8192 rows of 32 values, 512 MiB: 134.8 -> 126.7 us)
+                const int round = kWavesPerBlock * tile, rows = (int)(52 * 1024 / (gb * sizeof(float)) / round * round);
+                const int64_t splits = rows > 0 ? (d->S + rows - 1) / rows : INT32_MAX;
+                if (rows >= 4 * round && splits <= kMaxPartialsPerHead / k && splits <= scratch_splits) {
+                    chunk = (int)((d->S + splits - 1) / splits + round - 1) / round * round;
+                    nsplit = (d->S + chunk - 1) / chunk;
+                    stage = (size_t)gb * chunk * sizeof(float);
+                    fit = fits(resident);
+                }
+            } else if (fit) {
+                resident = 2;
+            }
+            if (!fit) {
+                split_for(resident);
+                stage = 0;
+            }
+        }
     } else if (stage > (size_t)kScoreStageBytes) {
         stage = 0;
     }
     const int64_t target_blocks = 256 * resident;
     plan->gqa_mfma = gqa_mfma;
+    plan->gqa_f32 = gqa_f32;
     plan->heads_per_block = gb;
     plan->row_tiles = row_tiles;
     plan->head_blocks = d->Hq / gb;
@@ -1367,6 +1725,16 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
             case 32: codes ? launch_gqa<32, true>(plan.row_tiles, p, blocks64, lds, st) : launch_gqa<32, false>(plan.row_tiles, p, blocks64, lds, st); break;
             case 64: codes ? launch_gqa<64, true>(plan.row_tiles, p, blocks64, lds, st) : launch_gqa<64, false>(plan.row_tiles, p, blocks64, lds, st); break;
             default: launch_gqa<128, false>(plan.row_tiles, p, blocks64, lds, st); break;
+        }
+        lrc = launch_status();
+    } else if (plan.gqa_f32) {
+        const bool codes = desc->rank > 0;
+        const int gb = plan.heads_per_block;
+        switch (W) {
+            case 16: codes ? launch_gqa32<16, true>(gb, p, blocks64, st) : launch_gqa32<16, false>(gb, p, blocks64, st); break;
+            case 32: codes ? launch_gqa32<32, true>(gb, p, blocks64, st) : launch_gqa32<32, false>(gb, p, blocks64, st); break;
+            case 64: codes ? launch_gqa32<64, true>(gb, p, blocks64, st) : launch_gqa32<64, false>(gb, p, blocks64, st); break;
+            default: launch_gqa32<128, false>(gb, p, blocks64, st); break;
         }
         lrc = launch_status();
     } else {

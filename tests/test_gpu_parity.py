@@ -513,6 +513,46 @@ def test_infinite_entries_of_narrow_groups_stay_infinite(spec):
 
 
 @pytest.mark.parametrize("spec", [
+    dict(B=2, Hq=6, Hkv=2, D=128, S=17), dict(B=1, Hq=8, Hkv=2, D=128, S=1030), dict(B=2, Hq=32, Hkv=2, D=128, S=513),
+    dict(B=1, Hq=64, Hkv=2, D=128, S=300),                      # 32 heads in two blocks of 16
+    dict(B=1, Hq=36, Hkv=2, D=64, S=700), dict(B=3, Hq=10, Hkv=2, D=64, S=129), dict(B=1, Hq=34, Hkv=2, D=64, S=90),
+    dict(B=2, Hq=14, Hkv=2, D=32, S=1025), dict(B=1, Hq=16, Hkv=1, D=16, S=1999), dict(B=2, Hq=8, Hkv=2, D=64, S=1),
+    dict(B=1, Hq=16, Hkv=2, D=32, S=5000),                      # scores that fit the LDS in finer splits only
+    dict(B=2, Hq=12, Hkv=4, D=64, rank=16, S=260), dict(B=1, Hq=30, Hkv=2, D=128, rank=32, S=515),
+    dict(B=2, Hq=16, Hkv=2, D=32, rank=64, S=300), dict(B=1, Hq=16, Hkv=4, D=16, rank=16, S=130),
+    dict(B=1, Hq=16, Hkv=1, D=128, rank=64, S=1100),
+], ids=lambda s: "D%d_r%d_G%d_S%d" % (s["D"], s.get("rank", 0), s["Hq"] // s["Hkv"], s["S"]))
+def test_groups_of_fp32_rows_match_oracle(spec):
+    """Groups of 3 and more heads on the fp32 matrix cores: tiles of 16 to 64 entries and their remainders, scores
+    staged, in finer splits and written from the loop, groups that no number of heads up to 16 but one divides.
+    fp32 sums, 1.7e-7 measured."""
+    g = wl.Geometry(E=3, k=2, dtype="f32", **spec)
+    case = wl.make_host_case(g, seed=g.S, n_valid="ragged", utility0="exp")
+    case.n_valid[0] = [g.S, max(1, g.S - 1), (g.S + 1) // 2]
+    check_group(case, 1e-6, forced=(0, 1, 7))
+
+
+@pytest.mark.parametrize("spec", [dict(B=2, Hq=16, Hkv=2, D=128), dict(B=2, Hq=12, Hkv=2, D=64), dict(B=1, Hq=32, Hkv=2, D=16),
+                                  dict(B=2, Hq=8, Hkv=2, D=64, rank=32)],
+                         ids=lambda s: "D%d_r%d_G%d" % (s["D"], s.get("rank", 0), s["Hq"] // s["Hkv"]))
+def test_infinite_entries_of_fp32_groups_stay_infinite(spec):
+    g = wl.Geometry(E=2, k=2, S=512, dtype="f32", **spec)
+    case = wl.make_host_case(g, seed=g.Hq, utility0="exp")
+    for s, at in ((0, 300), (g.B * g.E - 1, 100)):
+        case.V_shards[s][0, at, 3], case.V_shards[s][g.Hkv - 1, at + 1, 5] = np.inf, -np.inf
+    idx, gates = random_selection(g, 2)
+    ref = oracle_step(case, idx, gates, orc.COMBINE_LSE)
+    dc = DeviceCase(case)
+    dc.attend(topk=torch.from_numpy(idx).to(DEV), gates=torch.from_numpy(gates).to(DEV))
+    y = t2n(dc.y)
+    assert np.isinf(ref["y"]).any()
+    for kind in (np.isposinf, np.isneginf, np.isnan):
+        np.testing.assert_array_equal(kind(y), kind(ref["y"]), err_msg=kind.__name__)
+    ok = np.isfinite(ref["y"])
+    assert np.linalg.norm(y[ok] - ref["y"][ok]) <= 1e-6 * np.linalg.norm(ref["y"][ok])
+
+
+@pytest.mark.parametrize("spec", [
     dict(B=1, Hq=8, Hkv=2, D=128, E=12, S=2304, k=12, dtype="bf16"),       # matrix cores, 128 rows a round
     dict(B=1, Hq=6, Hkv=2, D=64, E=12, S=2051, k=12, dtype="bf16", rank=32),
     dict(B=1, Hq=2, Hkv=2, D=128, E=12, S=2304, k=12, dtype="bf16"),       # plain ALU
