@@ -1434,7 +1434,10 @@ static bool plain_pays(const pikv_desc *d, int k, int row_tiles) {
 }
 
 // The least heads per block for the fp32 matrix-core kernel: with two, 14 of a product's 16 rows are padding, and the plain
-// kernel is ahead by 1 - 4 % (256 MiB 48.5 against 50.6 us, rank-32 codes 52.9 against 59).
+// kernel is ahead by 1 - 4 % (256 MiB 48.5 against 50.6 us, rank-32 codes 52.9 against 59).  Groups of four, which
+// share one stream there too, are as fast or faster there, most of all in shards of uneven fill, its blocks being shorter
+// (fused step, 16 x 8 kv heads x 2 shards of 2048 slots of 64 values: full 59.3 against 61.5 us, 10 - 100 % full 47.6
+// against 51.8; 8 x 8 x 2 of 4096 rank-32 codes 43.2 against 45.3 and 36.9 against 40.6).
 constexpr int kGqa32Heads = 3;
 
 int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_limit) {
@@ -1456,7 +1459,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     int gb32 = G < 16 ? G : 16;
     while (G % gb32 != 0) --gb32;
     const bool gqa_f32 = d->route_rows_per_seq == 1 && d->dtype == PIKV_F32 && gb32 >= kGqa32Heads &&
-                         (int64_t)d->S * d->stride_s * 4 < ((int64_t)1 << 32);
+                         G != 4 && (int64_t)d->S * d->stride_s * 4 < ((int64_t)1 << 32);
     if (gqa_f32) gb = gb32;
     const int tq = d->tq > 1 ? d->tq : 1;
     // draft queries are folded into the query group of the matrix-core kernel's 128-value rows only
