@@ -155,8 +155,9 @@ int pikv_sharded_attn(const pikv_desc *desc, const void *q, const void *const *K
  * address up (no stream work); make that call outside graph capture.
  * Errors: as pikv_sharded_attn; WORKSPACE when pikv_attn_workspace_bytes(desc, k) exceeds
  * PIKV_NOALLOC_SCRATCH_BYTES (use pikv_sharded_attn with a workspace then) - but for groups of
- * bf16 rows narrower than 128 values, which take fewer splits while those fit; HIP if the array's
- * address cannot be resolved.                                                              */
+ * bf16 rows narrower than 128 values, of up to 8 heads over up to 64 units (sequence, kv head,
+ * shard) and of fp32 rows, and for calls of at most 256 rounds of a block's rows in all, which
+ * take fewer splits while those fit; HIP if the array's address cannot be resolved.        */
 #define PIKV_NOALLOC_SCRATCH_BYTES (4u << 20)
 int pikv_sharded_attn_noalloc(const pikv_desc *desc, const void *q, const void *const *K_shards,
                               const void *const *V_shards, const void *U_K, const void *U_V,

@@ -47,6 +47,7 @@ struct AttnParams {
     int64_t stride_h, stride_s;
     int nsplit, chunk;  // splits per shard, and the most rows one of them takes
     uint32_t nsplit_rcp;   // 2^32 / nsplit, rounded up (0: nsplit == 1)
+    int least_splits, long_rows;   // group kernels: see split_rows (long_rows 0: all splits)
     int tq;             // draft queries per sequence: q is [B, tq, Hq / tq, D] (1: plain [B, Hq, D])
     int stage_scores;   // keep the block's scores in LDS, write them in one burst at the end
     int stream_scores;  // ... with non-temporal stores
@@ -88,17 +89,44 @@ __device__ __forceinline__ ShardRef resolve_shard(const AttnParams &p, int b, in
 // first of them empty.  A split takes whole rounds of tiles, one per wave: with uneven waves it
 // runs as long as one of more rows (32 splits of 136 rows in blocks of 160: 23.0 us, of 256: 21.6).
 // (4 sequences, 8 kv heads, 4 of 16 shards of 8192 slots, 573 entries each: pass and merge 20.1 -> 16.3 us.)
+// Groups (long_rows > 0) do not spread over all of them: as many as make a block per CU of the launch
+// (least_splits), more from long_rows rows each on, the rest stays empty (make_attn_plan).
 template <int TILE>
 __device__ __forceinline__ void split_rows(const AttnParams &p, int n, int split, int *r0, int *r1) {
     const int m = min(n, p.S);
     int per = p.chunk;
     if (p.nsplit_rcp != 0) {
         constexpr int ROUND = kWavesPerBlock * TILE;
-        per = (int)__umulhi((uint32_t)(m + p.nsplit - 1), p.nsplit_rcp);
+        if (p.long_rows > 0) {
+            const int wanted = min(max(p.least_splits, (m + p.long_rows - 1) / p.long_rows), p.nsplit);
+            per = (int)((uint32_t)(m + wanted - 1) / (uint32_t)wanted);
+        } else {
+            per = (int)__umulhi((uint32_t)(m + p.nsplit - 1), p.nsplit_rcp);
+        }
         per = min((max(per, 1) + ROUND - 1) / ROUND * ROUND, p.chunk);   // chunk: nsplit * chunk >= S
     }
     *r0 = split * per;
     *r1 = min(m, *r0 + per);
+}
+
+// Work item of a group kernel's block: its unit (sequence, head group, shard) and split.
+// Workgroups go to the 8 XCDs round-robin by id.  Giving each XCD a contiguous range of units, whose splits share
+// score rows and partial lines, measures 1.3 % faster than spreading neighbours over all XCDs.  Where a shard may
+// leave its last splits empty (long_rows > 0) an XCD takes the first split of all its units, then the second: with a
+// unit's splits side by side, the blocks with work landed on few of the CUs
+// (128 units, 2 of 8 splits: 34.3 us, now 26.9).
+__device__ __forceinline__ int group_block(const AttnParams &p, int *split) {
+    const int id = blockIdx.x, grid = gridDim.x;
+    if (p.long_rows > 0) {
+        const int units = grid / p.nsplit;
+        const bool even = units % 8 == 0;
+        const int per = even ? units / 8 : units, at = even ? id / 8 : id;
+        *split = at / per;
+        return (even ? id % 8 * per : 0) + at % per;
+    }
+    const int item = grid % 8 == 0 ? (id % 8) * (grid / 8) + id / 8 : id;
+    *split = item % p.nsplit;
+    return item / p.nsplit;
 }
 
 // Where the caller keeps the query of internal row h of sequence b, in rows of D values.
@@ -621,14 +649,9 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
     const int r = lane >> 4;
     const int gb = p.G;                       // rows per block = the whole query group
 
-    // Workgroups go to the 8 XCDs round-robin by id.  Giving each XCD a contiguous range of
-    // work items - whole (kv head, shard) units, whose splits share score rows and partial
-    // lines - measures 1.3 % faster here than spreading neighbours over all XCDs; the
-    // plain-ALU kernel above measures 2.6 % slower with it and keeps the round-robin order.
-    int bid = blockIdx.x;
-    if (gridDim.x % 8 == 0) bid = (bid % 8) * (gridDim.x / 8) + bid / 8;
-    const int split = bid % p.nsplit;
-    bid /= p.nsplit;
+    // (the plain-ALU kernel above measures 2.6 % slower with a contiguous range per XCD)
+    int split;
+    int bid = group_block(p, &split);
     const int j = bid % p.k;
     bid /= p.k;
     const int hgroups = p.Hq / gb;
@@ -931,10 +954,13 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
                     for (int x = 0; x < 4; ++x) oacc[rt][i][x] *= corr;
             }
 #pragma unroll
-            for (int x = 0; x < 8 * SUBS; ++x) {
-                sv[x] = __expf(sv[x] - mn);
-                lsum[rt] += sv[x];
-            }
+            for (int x = 0; x < 8 * SUBS; ++x) sv[x] = __expf(sv[x] - mn);
+            // The tile's weights and products are summed apart and meet the running sums in one addition: a wave's rows
+            // may be many (blocks of 512 KiB), and each rounding of a running sum is one of the whole sum's size.
+            float tl = 0.f;
+#pragma unroll
+            for (int x = 0; x < 8 * SUBS; x += 4) tl += (sv[x] + sv[x + 1]) + (sv[x + 2] + sv[x + 3]);
+            lsum[rt] += tl;
             // O^T += V^T P^T, output set i takes the i-th value of each of the lane's 8 V rows
 #pragma unroll
             for (int sub = 0; sub < SUBS; ++sub) {
@@ -961,7 +987,7 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
                     if constexpr (PP == 3) {
                         f32x4_t small = mfma_rows(vop, pop[2], f32x4_t{0.f, 0.f, 0.f, 0.f});
                         small = mfma_rows(vop, pop[1], small);
-                        oacc[rt][i] = mfma_rows(vop, pop[0], oacc[rt][i]) + small;
+                        oacc[rt][i] += mfma_rows(vop, pop[0], small);
                     } else {
                         oacc[rt][i] = mfma_rows(vop, pop[0], mfma_rows(vop, pop[1], oacc[rt][i]));
                     }
@@ -1074,11 +1100,8 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, kGqa32BlocksPerCu) void attn
     const int c = lane & 15;
     const int r = lane >> 4;
 
-    // (ids to work items as in attn_partial_gqa)
-    int bid = blockIdx.x;
-    if (gridDim.x % 8 == 0) bid = (bid % 8) * (gridDim.x / 8) + bid / 8;
-    const int split = bid % p.nsplit;
-    bid /= p.nsplit;
+    int split;
+    int bid = group_block(p, &split);
     const int j = bid % p.k;
     bid /= p.k;
     const int hgroups = p.Hq / gb;
@@ -1483,19 +1506,48 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     if (gqa_mfma && W == 64 && d->rank > 0 && resident > 2) resident = 2;
     int64_t nsplit = 1;
     int chunk = 0;
-    // Splits whose partials fit the fixed array of the call without a workspace: rows narrower than
-    // 128 values in groups want more of them than the kernel that took these calls before, and are
-    // not refused for it.
+    // bf16 groups of one row tile whose units (sequence, head group, shard) make 192 to 256 blocks at `least` splits each:
+    // that many, and no block of more than 512 KiB of K and V.  Blocks beyond that cost more - their start, their merge,
+    // the partials that the merge reads - than they hide; and a shard that is not full still makes whole, even
+    // blocks (split_rows takes the same two numbers from its entry count).  Fused step, three or four blocks per CU
+    // before: 128 units of 4096 slots of 64 values 44.6 -> 43.4 us, 55 % full 38.7 -> 33.9; rank-32 codes 49.1 -> 45.7 and
+    // 41.9 -> 35.4; 64 units of 4096 rows of 128 38.0 -> 36.5, 50 % full 30.0 -> 27.7; 40 units 28.9 -> 27.7.  Rows of 128
+    // values over more units keep the old plan (128 units, 10 - 100 % full, 47.5 us against 48.5: their longest blocks end
+    // late), and so do 32 units (1 x 8 x 4 of 8192, 36.4 against 38.5: the merge of 32 partials takes narrower blocks).
+    const int round = kWavesPerBlock * tile;
+    const int long_rows = 512 * 1024 / (2 * W * 2);
+    const int64_t least = units > 0 ? 256 / units : 1;
+    // With few units a block takes fewer than two tiles per wave, down to one, and below 64 blocks to one in all: every
+    // kernel's chain of trips to memory is shorter then.  (7 units of 938 rows of 64 values x 8 heads, pass and
+    // merge 15.1 -> 9.7 us, 6 of 256 rows of 128 9.7 -> 8.5, 16 of 768 rank-32 codes of one head 12.0 -> 9.9, 8 of 256
+    // fp32 rows 9.9 -> 7.9, 4 of 1192 11.5 -> 9.5.)  Not past 128 partials of a head: 256 blocks of one unit 21.8 -> 24.8.  Groups
+    // of narrow bf16 rows, whose tiles are long, only where the old plan had one block per unit.
+    const bool by_unit = gqa_mfma && row_tiles == 1 && (W < 128 || gb <= 8) && units > 32 &&
+                         units <= (W == 128 ? 64 : 256) && least * units >= 192 && g_split_override == 0;
+    const int64_t rounds = (d->S + round - 1) / round;
+    const bool few = units > 0 && g_split_override == 0 && units * rounds <= 256 && k * rounds <= 128 &&
+                     !(gqa_mfma && W < 128 && d->S >= 4 * round);
+    int64_t finest = rounds;
+    for (int part = round; few && part > tile && units * finest * 2 <= 64; part /= 2)
+        finest = (d->S + part / 2 - 1) / (part / 2);
+    // Splits whose partials fit the fixed array of the call without a workspace: where a plan wants more of them than
+    // the one that took these calls before, the call takes fewer and is not refused for it.
     const size_t split_bytes = (size_t)(d->B > 0 ? d->B : 1) * d->Hq * k * (W + 2) * sizeof(float);
-    const bool capped = scratch_limit != SIZE_MAX && (gqa_f32 || (gqa_mfma && W != 128));
+    const bool capped = scratch_limit != SIZE_MAX && (few || by_unit || gqa_f32 || (gqa_mfma && W != 128));
     const int64_t scratch_splits = capped ? (int64_t)((scratch_limit - 1024) / split_bytes) : INT32_MAX;
     auto split_for = [&](int res) {
         nsplit = units > 0 ? (int64_t)256 * res / units : 1;
+        if (by_unit) {
+            const int64_t by_rows = (d->S + long_rows - 1) / long_rows;
+            nsplit = by_rows > least ? by_rows : least;
+        }
         // No finer than two tiles per wave: with one, nothing is in flight while a wave computes,
         // and a block of uneven waves (2, 2, 1, 1 tiles) runs as long as one of twice the rows.
         // (Few units, short passes: 64 MiB over 16 units 14.0 -> 12.8 us, 32 MiB over 8 units
         // 8.6 -> 7.9 us, and fewer partials for the merge.)  A forced count is only held to one tile.
         int64_t max_split = d->S / (2 * kWavesPerBlock * tile);
+        if (few) nsplit = max_split = finest;
+        else if (by_unit) max_split = finest;
         if (g_split_override > 0) {
             nsplit = g_split_override;
             max_split = (d->S + tile - 1) / tile;
@@ -1517,8 +1569,8 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
         // measured slower (k = 16: 8 splits of 8 tiles per wave against 6 splits, +3.7 %).
         const int even = 2 * kWavesPerBlock * tile;
         const int64_t fine = d->S / even;
-        if ((gqa_mfma || gqa_f32) && g_split_override == 0 && chunk % (kWavesPerBlock * tile) != 0 && d->S % even == 0 &&
-            fine > nsplit && fine * 3 <= nsplit * 4 && fine <= kMaxPartialsPerHead / k && fine <= scratch_splits &&
+        if ((gqa_mfma || gqa_f32) && !by_unit && g_split_override == 0 && chunk % (kWavesPerBlock * tile) != 0 &&
+            d->S % even == 0 && fine > nsplit && fine * 3 <= nsplit * 4 && fine <= kMaxPartialsPerHead / k && fine <= scratch_splits &&
             (units * fine) % 256 == 0) {
             nsplit = fine;
             chunk = even;
@@ -1526,6 +1578,12 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     };
     split_for(resident);
     size_t stage = (size_t)gb * chunk * sizeof(float);      // the block's raw scores, staged in LDS
+    size_t stage_most = 64 * 1024 - 256;
+    if (by_unit || few) {                                   // as many blocks as there are: a CU has LDS for larger stages
+        const int64_t per_cu = (units * nsplit + 255) / 256;
+        if (per_cu < resident) resident = per_cu > 0 ? (int)per_cu : 1;
+        stage_most = 96 * 1024;
+    }
     if (gqa_mfma && W == 128 && gb <= 8) {
         // few rows per kv head of long entries: writing whole lines from the loop measures faster
         // than staging them (8 rows, 128 MiB: 31.8 against 32.8 us with the merge, 4 rows even;
@@ -1536,7 +1594,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
         // blocks - three times with one row tile, or twice with longer blocks - or is left out.
         const size_t lds_cu = 160 * 1024;
         const size_t fixed = gqa_static_lds(W, tile, row_tiles);
-        if ((size_t)resident * (fixed + stage) > lds_cu || stage > 64 * 1024 - 256) {
+        if ((size_t)resident * (fixed + stage) > lds_cu || stage > stage_most) {
             bool fits = false;
             if (resident > 2) {
                 split_for(2);
@@ -1569,7 +1627,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
         // The stage shares its LDS with the merge of the waves; 512 bytes of statistics beside it.
         auto fits = [&](int res) {
             const size_t merge = gqa32_merge_bytes(W), lds = (stage > merge ? stage : merge) + 1024;
-            return (size_t)res * lds <= 160 * 1024 && stage <= 64 * 1024 - 256;
+            return (size_t)res * lds <= 160 * 1024 && stage <= stage_most;
         };
         if (!fits(resident)) {
             split_for(2);
@@ -1600,6 +1658,8 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     const int64_t target_blocks = 256 * resident;
     plan->gqa_mfma = gqa_mfma;
     plan->gqa_f32 = gqa_f32;
+    plan->least_splits = (int)least;
+    plan->long_rows = by_unit && !few ? long_rows : 0;
     plan->heads_per_block = gb;
     plan->row_tiles = row_tiles;
     plan->head_blocks = d->Hq / gb;
@@ -1711,6 +1771,8 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
     p.stride_s = desc->stride_s;
     p.nsplit = plan.nsplit;
     p.chunk = plan.chunk;
+    p.least_splits = plan.least_splits;
+    p.long_rows = plan.long_rows;
     p.nsplit_rcp = plan.nsplit > 1 ? (uint32_t)(((uint64_t)1 << 32) / plan.nsplit + 1) : 0u;
     p.stage_scores = scores != nullptr && plan.score_stage_bytes > 0;
     p.scale = scale > 0.0f ? scale : 1.0f / sqrtf((float)desc->D);

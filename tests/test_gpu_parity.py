@@ -589,6 +589,21 @@ def test_splits_follow_the_entry_count(spec, forced):
         assert np.isfinite(sc[0, :, j, :n]).all() and np.isnan(sc[0, :, j, n:]).all()
 
 
+@pytest.mark.parametrize("spec", [
+    # a block per CU: 60, 192, 204 (not spread over XCDs in whole units) and 192 units, of them some with one split
+    dict(Hq=20, Hkv=5, D=128, S=4111, k=12), dict(Hq=32, Hkv=16, D=64, S=2304, k=12), dict(Hq=51, Hkv=17, D=64, S=2050, k=12),
+    dict(Hq=48, Hkv=16, D=64, S=4500, k=12, rank=32), dict(Hq=64, Hkv=16, D=16, S=8200, k=12),
+    # few units: a tile per wave, and blocks of fewer waves with rows than waves
+    dict(Hq=8, Hkv=1, D=128, S=1030, k=2), dict(Hq=8, Hkv=1, D=64, S=938, k=7), dict(Hq=3, Hkv=3, D=128, S=600, k=3),
+    dict(Hq=4, Hkv=1, D=128, S=258, k=1, rank=16), dict(Hq=20, Hkv=1, D=128, S=1000, k=1),
+    dict(Hq=2, Hkv=2, D=64, S=700, k=2, dtype="f32"), dict(Hq=8, Hkv=1, D=128, S=300, k=1, dtype="f32"),
+    dict(Hq=6, Hkv=2, D=64, S=515, k=2, rank=32, dtype="f32"),
+], ids=lambda s: "%s_G%d_u%d_D%d_r%d" % (s.get("dtype", "bf16"), s["Hq"] // s["Hkv"], s["Hkv"] * s["k"], s["D"], s.get("rank", 0)))
+def test_few_and_whole_blocks_follow_the_entry_count(spec):
+    """The same for the plans of few units (down to a tile per block) and of one block per CU."""
+    test_splits_follow_the_entry_count(dict(dict(B=1, E=12, dtype="bf16"), **spec), 0)
+
+
 @pytest.mark.parametrize("spec,tq", [
     (dict(Hq=2, D=128, S=40), 2), (dict(Hq=16, D=128, S=300), 2), (dict(Hq=64, D=128, S=9), 4), (dict(Hq=3, D=128, S=33), 1),
     (dict(Hq=2, D=16, S=40), 1), (dict(Hq=24, D=32, S=130), 1), (dict(Hq=4, D=64, S=700), 1),
