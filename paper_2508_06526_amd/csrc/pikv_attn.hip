@@ -1281,8 +1281,9 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, kGqa32BlocksPerCu) void attn
 #pragma unroll
         for (int x = 1; x < 4 * SUBS; ++x) tm = fmaxf(tm, sv[x]);
         const float mn = fmaxf(m, group_max(tm));
+        const float base = mn == -INFINITY ? 0.0f : mn;      // (nothing but -Inf so far: weights of zero, not NaN)
         if (__any(mn > m)) {                 // else the factor is 1 in every lane
-            const float corr = __expf(m - mn);
+            const float corr = __expf(m - base);
             m = mn;
             lsum *= corr;
 #pragma unroll
@@ -1290,8 +1291,18 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, kGqa32BlocksPerCu) void attn
         }
 #pragma unroll
         for (int x = 0; x < 4 * SUBS; ++x) {
-            sv[x] = __expf(sv[x] - mn);
+            sv[x] = __expf(sv[x] - base);
             lsum += sv[x];
+        }
+        if (t0 + TILE > r1) {                // rows past the end repeat the last one: a weight of zero times Inf is NaN
+#pragma unroll
+            for (int sub = 0; sub < SUBS; ++sub)
+#pragma unroll
+                for (int x = 0; x < 4; ++x)
+#pragma unroll
+                    for (int l = 0; l < VL; ++l)
+#pragma unroll
+                        for (int i = 0; i < VW; ++i) vr[sub][x][l][i] = t0 + 16 * sub + 4 * r + x < r1 ? vr[sub][x][l][i] : 0u;
         }
 #pragma unroll
         for (int sub = 0; sub < SUBS; ++sub)

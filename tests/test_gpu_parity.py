@@ -552,6 +552,36 @@ def test_infinite_entries_of_fp32_groups_stay_infinite(spec):
     assert np.linalg.norm(y[ok] - ref["y"][ok]) <= 1e-6 * np.linalg.norm(ref["y"][ok])
 
 
+@pytest.mark.parametrize("spec", [dict(Hq=16, D=128, S=17), dict(Hq=6, D=64, S=33), dict(Hq=16, D=32, S=65), dict(Hq=12, D=16, S=200),
+                                  dict(Hq=16, D=64, S=41, rank=32)],
+                         ids=lambda s: "D%d_r%d_G%d" % (s["D"], s.get("rank", 0), s["Hq"] // 2))
+def test_infinities_in_the_last_entry_of_fp32_groups(spec):
+    """A shard's last tile is partly past its entries, and may be its wave's first: an infinite value in the last entry
+    is no NaN of the rows behind it, and a last entry that scores -Inf drops out of the softmax."""
+    g = wl.Geometry(B=1, Hkv=2, E=2, k=2, dtype="f32", **spec)
+    idx, gates = random_selection(g, 2)
+    for kind in ("value", "score"):
+        case = wl.make_host_case(g, seed=g.Hq, utility0="exp")
+        if kind == "value":
+            for s, sign in ((0, 1.0), (1, -1.0)):
+                case.V_shards[s][s, g.S - 1, 3] = sign * np.inf
+        elif g.rank:                     # q and the decoder row of one code column positive: -Inf for all heads
+            case.q, case.U_K[:, 7] = np.abs(case.q), np.abs(case.U_K[:, 7])
+            case.K_shards[1][:, g.S - 1, 7] = -np.inf
+        else:
+            case.q[..., 5] = np.abs(case.q[..., 5])
+            case.K_shards[1][:, g.S - 1, 5] = -np.inf
+        ref = oracle_step(case, idx, gates, orc.COMBINE_LSE)["y"]
+        assert np.isinf(ref).any() == (kind == "value") and not np.isnan(ref).any()
+        dc = DeviceCase(case)
+        dc.attend(topk=torch.from_numpy(idx).to(DEV), gates=torch.from_numpy(gates).to(DEV))
+        y = t2n(dc.y)
+        for what in (np.isposinf, np.isneginf, np.isnan):
+            np.testing.assert_array_equal(what(y), what(ref), err_msg=kind)
+        ok = np.isfinite(ref)
+        assert np.linalg.norm(y[ok] - ref[ok]) <= 1e-6 * np.linalg.norm(ref[ok])
+
+
 @pytest.mark.parametrize("spec", [
     dict(B=1, Hq=8, Hkv=2, D=128, E=12, S=2304, k=12, dtype="bf16"),       # matrix cores, 128 rows a round
     dict(B=1, Hq=6, Hkv=2, D=64, E=12, S=2051, k=12, dtype="bf16", rank=32),
