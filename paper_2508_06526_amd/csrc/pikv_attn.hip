@@ -630,7 +630,7 @@ constexpr size_t gqa_static_lds(int width, int tile, int row_tiles) {
 // parameter and not a run-time branch: each form costs registers, and a value spilled for one
 // of them is reloaded inside the loop by a scratch load, which the wait counters cannot tell
 // from the tile loads in flight - the wave then waits for all of them.  (One form of the 42 still
-// spills: rank-16 codes at four row tiles with scores written from the loop, 28 bytes.)
+// spills: rank-16 codes at four row tiles with scores written from the loop, 24 bytes.)
 constexpr int kScoresNone = 0, kScoresStaged = 1, kScoresDirect = 2;
 template <int W, int RT, int SC, bool CODES>
 __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, CODES)) void attn_partial_gqa(
@@ -955,12 +955,20 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
             }
 #pragma unroll
             for (int x = 0; x < 8 * SUBS; ++x) sv[x] = __expf(sv[x] - mn);
-            // The tile's weights and products are summed apart and meet the running sums in one addition: a wave's rows
-            // may be many (blocks of 512 KiB), and each rounding of a running sum is one of the whole sum's size.
-            float tl = 0.f;
+            // At one row tile the tile's weights and products are summed apart and meet the running sums in one addition: a
+            // wave's rows may be many (blocks of 512 KiB, which are planned for one row tile alone), and each rounding of a
+            // running sum is one of the whole sum's size.  At two and four the temporaries cost registers: rows of 16 values
+            // x 64 heads 57.7 us, apart 80.8 (224 bytes of scratch), rank-32 codes 74.7 and 99.7.  (Rows of 128 values have
+            // them for the weights.)
+            if constexpr (RT == 1 || W == 128) {
+                float tl = 0.f;
 #pragma unroll
-            for (int x = 0; x < 8 * SUBS; x += 4) tl += (sv[x] + sv[x + 1]) + (sv[x + 2] + sv[x + 3]);
-            lsum[rt] += tl;
+                for (int x = 0; x < 8 * SUBS; x += 4) tl += (sv[x] + sv[x + 1]) + (sv[x + 2] + sv[x + 3]);
+                lsum[rt] += tl;
+            } else {
+#pragma unroll
+                for (int x = 0; x < 8 * SUBS; ++x) lsum[rt] += sv[x];
+            }
             // O^T += V^T P^T, output set i takes the i-th value of each of the lane's 8 V rows
 #pragma unroll
             for (int sub = 0; sub < SUBS; ++sub) {
@@ -987,7 +995,8 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, COD
                     if constexpr (PP == 3) {
                         f32x4_t small = mfma_rows(vop, pop[2], f32x4_t{0.f, 0.f, 0.f, 0.f});
                         small = mfma_rows(vop, pop[1], small);
-                        oacc[rt][i] += mfma_rows(vop, pop[0], small);
+                        if constexpr (RT == 1) oacc[rt][i] += mfma_rows(vop, pop[0], small);
+                        else oacc[rt][i] = mfma_rows(vop, pop[0], oacc[rt][i]) + small;
                     } else {
                         oacc[rt][i] = mfma_rows(vop, pop[0], mfma_rows(vop, pop[1], oacc[rt][i]));
                     }
