@@ -87,15 +87,19 @@ __global__ __launch_bounds__(kRouteThreads) void step_pre(PreParams p) {
 
     // neither the router's additive term, nor the entry counts of the sequence's shards (lane e
     // takes shard e's; the selected one is picked out of the register once the router has
-    // spoken), nor the new rows depend on anything: requested now
+    // spoken), nor the new rows depend on anything: requested now (the rows behind the router's sums for more than
+    // 32 experts, which leave no registers for them: 20 bytes of scratch a lane)
     const float bias_e = route_bias_of_lane(p.bias, p.E, lane);
     const int n_of_lane = p.n_valid[(int64_t)b * p.E + min(lane, p.E - 1)];
     const int new_chunks = p.Hkv * p.row_chunks;
     uint4 knew = make_uint4(0, 0, 0, 0), vnew = knew;
-    if (p.do_insert && tid < new_chunks) {
-        knew = load16(static_cast<const char *>(p.K_new) + ((int64_t)b * new_chunks + tid) * 16);
-        vnew = load16(static_cast<const char *>(p.V_new) + ((int64_t)b * new_chunks + tid) * 16);
-    }
+    auto request_new = [&]() {
+        if (p.do_insert && tid < new_chunks) {
+            knew = load16(static_cast<const char *>(p.K_new) + ((int64_t)b * new_chunks + tid) * 16);
+            vnew = load16(static_cast<const char *>(p.V_new) + ((int64_t)b * new_chunks + tid) * 16);
+        }
+    };
+    if constexpr (MOST < 64) request_new();
 
     const T *xr = static_cast<const T *>(p.x) + (int64_t)b * p.x_stride;
     const T *W_r = static_cast<const T *>(p.W_r);
@@ -103,6 +107,7 @@ __global__ __launch_bounds__(kRouteThreads) void step_pre(PreParams p) {
     if constexpr (MOST > 0) {
         __shared__ RouteShared<MOST, 1> sh;
         logit = route_logit_mfma<MOST>(xr, W_r, p.d_r, p.E, p.words, bias_e, sh);
+        if constexpr (MOST == 64) request_new();
     } else {
         __shared__ float red[kWaves][64];
         __shared__ __attribute__((aligned(16))) float flat[kFlatFloats];

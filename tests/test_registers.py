@@ -45,7 +45,7 @@ def scratch_bytes(image):
                 yield name[:-3], struct.unpack_from("<I", image, start + value - address + 4)[0]
 
 
-@pytest.mark.parametrize("family", ["attn_partial"])
+@pytest.mark.parametrize("family", ["attn_partial", "attn_combine", "step_", "route_", "evict_"])
 def test_kernels_use_no_scratch_memory(family):
     if not os.path.exists(pk.library_path()):
         from paper_2508_06526_amd import build
