@@ -459,6 +459,16 @@ def test_groups_on_the_matrix_cores_in_both_forms_of_the_score_output(D, rank, G
     check_group(case, 1e-6, forced=(1, 16))
 
 
+@pytest.mark.parametrize("spec,most", [(dict(Hq=64, D=64), 1.9e-7), (dict(Hq=16, D=64), 1.9e-7), (dict(Hq=32, D=128, rank=32), 2.3e-7),
+                                       (dict(Hq=32, D=128, rank=16), 2.15e-7), (dict(Hq=64, D=128, rank=64), 2.5e-7)],
+                         ids=lambda v: "" if isinstance(v, float) else "D%d_r%d_G%d" % (v["D"], v.get("rank", 0), v["Hq"] // 8))
+def test_long_blocks_of_narrow_groups_keep_the_precision_of_short_ones(spec, most):
+    """48 units: blocks of 512 KiB, in which a wave adds up to 8 tiles to its running sums.  The bounds lie between
+    the error with a tile's products summed apart and the error with products that accumulate."""
+    g = wl.Geometry(B=1, Hkv=8, E=6, S=8192, k=6, dtype="bf16", **spec)
+    check_group(wl.make_host_case(g, seed=1, utility0="exp"), most)
+
+
 @pytest.mark.parametrize("spec", [
     # either side of: 48, 64 and 96 blocks, the bytes re-read, and 28 MB of K/V for two heads over 16 values
     dict(B=24, Hq=48, Hkv=2, D=64, S=300, k=1), dict(B=49, Hq=24, Hkv=1, D=64, S=300, k=1),
