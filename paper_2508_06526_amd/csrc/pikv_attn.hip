@@ -595,11 +595,17 @@ constexpr int gqa_blocks_per_cu(int width, int row_tiles, bool codes) {
     if (width <= 32) return row_tiles == 1 ? 4 : row_tiles == 2 ? 3 : 2;
     return row_tiles == 1 ? 3 : 2;
 }
+// LONG: rows of 128 values in the plan of a block per CU.  A wave takes up to 256 rows in a row, fewer of its weights are its
+// running maximum - which is 1, and exact in any number of parts - and with two parts y would be further off 64 bits than in
+// short blocks (64 units of 4096 slots 2.0e-6 against 1.8e-6).  A third part makes it 2.0e-7; its registers are there
+// where a CU holds two blocks.  (Fused step 37.0 us in short blocks, 36.2 in long ones, so 36.6; half full 29.4, 27.4, 27.9.
+// For every plan of these rows it would cost 1 - 2 %: 1 x 8 x 4 units of 8192 slots 36.4 -> 36.9.)
+constexpr int kGqaLongBlocksPerCu = 2;
 // CODES: the rows are rank-W codes.  Their query is U_K q, formed in fp32 by MFMAs in the kernel's
 // prologue - W/16 tiles of (code column, query row), whose result layout is again the operand
 // layout up to the order of the contraction index - and split into 3 bf16 parts, so that its
 // products with the codes stay exact to 24 bits.
-template <int W, int RT, bool CODES>
+template <int W, int RT, bool CODES, bool LONG>
 struct GqaShape {
     static constexpr bool kQueryInLds = W == 128 && RT > 2;
     // W = 128, RT = 4: the 128 accumulator registers leave no room to hold the next K tile across
@@ -611,13 +617,13 @@ struct GqaShape {
     // where the shape would spill otherwise.
     static constexpr bool kLeanAddresses = CODES && ((W == 64 && RT == 1) || (W == 16 && RT == 4));
     // Probabilities: 3 parts are the fp32 value, 2 parts differ from it by 2^-17.  Rows of 128
-    // values have always used 2 (y is 1.9e-6 off 64 bits); the narrower rows were summed in fp32
+    // values have always used 2 (y is 1.8e-6 off 64 bits), but for LONG blocks; the narrower rows were summed in fp32
     // on the vector units and keep that: y against 64 bits 1.5 - 1.8e-7 (64 values) and 1.8 - 2.5e-7
     // (codes), from 1.5 - 1.8e-7 and 2.0 - 2.6e-7, with the two small parts summed apart from the
     // running output (added to it part by part: up to 2.8e-7).  At one row tile, whose waves take up to 8 tiles
     // in a row, the large part is summed apart too: 128 units of 4096 slots of 64 values 1.76e-7, accumulated onto the
     // small parts 2.02e-7, onto the running output 2.16e-7; rank-16 codes 2.00, 2.22 and 2.36e-7, rank 64 2.39, 2.61, 2.68e-7.
-    static constexpr int kProbParts = W == 128 ? 2 : 3;
+    static constexpr int kProbParts = W == 128 && !LONG ? 2 : 3;
 };
 
 // LDS a block holds besides the score stage: a K tile per wave and the wave statistics, and the
@@ -634,12 +640,12 @@ constexpr size_t gqa_static_lds(int width, int tile, int row_tiles) {
 // from the tile loads in flight - the wave then waits for all of them.  (One form of the 42 still
 // spills: rank-16 codes at four row tiles with scores written from the loop, 24 bytes.)
 constexpr int kScoresNone = 0, kScoresStaged = 1, kScoresDirect = 2;
-template <int W, int RT, int SC, bool CODES>
-__global__ __launch_bounds__(kWavesPerBlock *kWave, gqa_blocks_per_cu(W, RT, CODES)) void attn_partial_gqa(
+template <int W, int RT, int SC, bool CODES, bool LONG>
+__global__ __launch_bounds__(kWavesPerBlock *kWave, LONG ? kGqaLongBlocksPerCu : gqa_blocks_per_cu(W, RT, CODES)) void attn_partial_gqa(
     AttnParams p) {
     using Row = RowShape<W, RT>;
     constexpr int TILE = Row::kTile, SUBS = Row::kSubs, SETS = Row::kSets, PITCH = Row::kPitch;
-    using Shape = GqaShape<W, RT, CODES>;
+    using Shape = GqaShape<W, RT, CODES, LONG>;
     typedef typename OperandOf<W>::type Operand;
     constexpr bool QLDS = Shape::kQueryInLds;
     constexpr bool KPRE = Shape::kPrefetchK;
@@ -1407,20 +1413,22 @@ int launch_partial_w(int gb, const AttnParams &p, int blocks, hipStream_t st) {
 }
 
 template <int W, bool CODES>
-void launch_gqa(int row_tiles, const AttnParams &p, int64_t blocks, size_t lds, hipStream_t st) {
+void launch_gqa(int row_tiles, bool long_blocks, const AttnParams &p, int64_t blocks, size_t lds, hipStream_t st) {
     const dim3 grid((unsigned)blocks), block(kWavesPerBlock * kWave);
-    auto launch = [&](auto rt) {
+    auto launch = [&](auto rt, auto longs) {
         constexpr int RT = decltype(rt)::value;
+        constexpr bool LONG = decltype(longs)::value;
         if (p.scores == nullptr)
-            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresNone, CODES>), grid, block, lds, st, p);
+            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresNone, CODES, LONG>), grid, block, lds, st, p);
         else if (p.stage_scores)
-            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresStaged, CODES>), grid, block, lds, st, p);
+            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresStaged, CODES, LONG>), grid, block, lds, st, p);
         else
-            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresDirect, CODES>), grid, block, lds, st, p);
+            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresDirect, CODES, LONG>), grid, block, lds, st, p);
     };
-    if (row_tiles == 1) launch(std::integral_constant<int, 1>{});
-    else if (row_tiles == 2) launch(std::integral_constant<int, 2>{});
-    else launch(std::integral_constant<int, 4>{});
+    if (row_tiles == 2) launch(std::integral_constant<int, 2>{}, std::false_type{});
+    else if (row_tiles == 4) launch(std::integral_constant<int, 4>{}, std::false_type{});
+    else if (long_blocks) launch(std::integral_constant<int, 1>{}, std::bool_constant<W == 128>{});
+    else launch(std::integral_constant<int, 1>{}, std::false_type{});
 }
 
 template <int W, bool CODES>
@@ -1683,6 +1691,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     plan->gqa_f32 = gqa_f32;
     plan->least_splits = (int)least;
     plan->long_rows = by_unit && !few ? long_rows : 0;
+    plan->long_blocks = W == 128 && by_unit && !few;
     plan->heads_per_block = gb;
     plan->row_tiles = row_tiles;
     plan->head_blocks = d->Hq / gb;
@@ -1809,10 +1818,10 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
         const size_t lds = p.stage_scores ? plan.score_stage_bytes : 0;
         const bool codes = desc->rank > 0;
         switch (W) {
-            case 16: codes ? launch_gqa<16, true>(plan.row_tiles, p, blocks64, lds, st) : launch_gqa<16, false>(plan.row_tiles, p, blocks64, lds, st); break;
-            case 32: codes ? launch_gqa<32, true>(plan.row_tiles, p, blocks64, lds, st) : launch_gqa<32, false>(plan.row_tiles, p, blocks64, lds, st); break;
-            case 64: codes ? launch_gqa<64, true>(plan.row_tiles, p, blocks64, lds, st) : launch_gqa<64, false>(plan.row_tiles, p, blocks64, lds, st); break;
-            default: launch_gqa<128, false>(plan.row_tiles, p, blocks64, lds, st); break;
+            case 16: codes ? launch_gqa<16, true>(plan.row_tiles, plan.long_blocks, p, blocks64, lds, st) : launch_gqa<16, false>(plan.row_tiles, plan.long_blocks, p, blocks64, lds, st); break;
+            case 32: codes ? launch_gqa<32, true>(plan.row_tiles, plan.long_blocks, p, blocks64, lds, st) : launch_gqa<32, false>(plan.row_tiles, plan.long_blocks, p, blocks64, lds, st); break;
+            case 64: codes ? launch_gqa<64, true>(plan.row_tiles, plan.long_blocks, p, blocks64, lds, st) : launch_gqa<64, false>(plan.row_tiles, plan.long_blocks, p, blocks64, lds, st); break;
+            default: launch_gqa<128, false>(plan.row_tiles, plan.long_blocks, p, blocks64, lds, st); break;
         }
         lrc = launch_status();
     } else if (plan.gqa_f32) {

@@ -459,13 +459,16 @@ def test_groups_on_the_matrix_cores_in_both_forms_of_the_score_output(D, rank, G
     check_group(case, 1e-6, forced=(1, 16))
 
 
-@pytest.mark.parametrize("spec,most", [(dict(Hq=64, D=64), 1.9e-7), (dict(Hq=16, D=64), 1.9e-7), (dict(Hq=32, D=128, rank=32), 2.3e-7),
-                                       (dict(Hq=32, D=128, rank=16), 2.15e-7), (dict(Hq=64, D=128, rank=64), 2.5e-7)],
+@pytest.mark.parametrize("spec,most", [(dict(Hq=64, D=64), 2.1e-7), (dict(Hq=16, D=64), 2.1e-7), (dict(Hq=32, D=128, rank=32), 2.35e-7),
+                                       (dict(Hq=32, D=128, rank=16), 2.4e-7), (dict(Hq=64, D=128, rank=64), 2.7e-7),
+                                       (dict(Hq=32, D=128, S=5000), 1e-6), (dict(Hq=64, D=128, S=5000), 1e-6)],
                          ids=lambda v: "" if isinstance(v, float) else "D%d_r%d_G%d" % (v["D"], v.get("rank", 0), v["Hq"] // 8))
-def test_long_blocks_of_narrow_groups_keep_the_precision_of_short_ones(spec, most):
-    """48 units: blocks of 512 KiB, in which a wave adds up to 8 tiles to its running sums.  The bounds lie between
-    the error with a tile's products summed apart and the error with products that accumulate."""
-    g = wl.Geometry(B=1, Hkv=8, E=6, S=8192, k=6, dtype="bf16", **spec)
+def test_long_blocks_of_groups_keep_the_precision_of_short_ones(spec, most):
+    """48 units: blocks of up to 512 KiB, in which a wave adds 8 tiles to its running sums.  Error of y with the products of
+    a tile summed apart 1.78, 1.73, 2.09, 2.18 and 2.41e-7 (short blocks 1.76, 1.77, 2.03, 2.26, 2.47), with products that
+    accumulate 2.52, 2.45, 2.64, 2.72 and 2.98; rows of 128 values 2.0e-7 with probabilities of three
+    parts, 2.0e-6 with two (short blocks 1.83e-6).  The bounds lie between."""
+    g = wl.Geometry(**dict(dict(B=2, Hkv=8, E=3, S=8192, k=3, dtype="bf16"), **spec))
     check_group(wl.make_host_case(g, seed=1, utility0="exp"), most)
 
 
