@@ -47,7 +47,6 @@ struct AttnParams {
     int64_t stride_h, stride_s;
     int nsplit, chunk;  // splits per shard, and the most rows one of them takes
     uint32_t nsplit_rcp;   // 2^32 / nsplit, rounded up (0: nsplit == 1)
-    int least_splits, long_rows;   // group kernels: see split_rows (long_rows 0: all splits)
     int tq;             // draft queries per sequence: q is [B, tq, Hq / tq, D] (1: plain [B, Hq, D])
     int stage_scores;   // keep the block's scores in LDS, write them in one burst at the end
     int stream_scores;  // ... with non-temporal stores
@@ -89,20 +88,13 @@ __device__ __forceinline__ ShardRef resolve_shard(const AttnParams &p, int b, in
 // first of them empty.  A split takes whole rounds of tiles, one per wave: with uneven waves it
 // runs as long as one of more rows (32 splits of 136 rows in blocks of 160: 23.0 us, of 256: 21.6).
 // (4 sequences, 8 kv heads, 4 of 16 shards of 8192 slots, 573 entries each: pass and merge 20.1 -> 16.3 us.)
-// Groups (long_rows > 0) do not spread over all of them: as many as make a block per CU of the launch
-// (least_splits), more from long_rows rows each on, the rest stays empty (make_attn_plan).
 template <int TILE>
 __device__ __forceinline__ void split_rows(const AttnParams &p, int n, int split, int *r0, int *r1) {
     const int m = min(n, p.S);
     int per = p.chunk;
     if (p.nsplit_rcp != 0) {
         constexpr int ROUND = kWavesPerBlock * TILE;
-        if (p.long_rows > 0) {
-            const int wanted = min(max(p.least_splits, (m + p.long_rows - 1) / p.long_rows), p.nsplit);
-            per = (int)((uint32_t)(m + wanted - 1) / (uint32_t)wanted);
-        } else {
-            per = (int)__umulhi((uint32_t)(m + p.nsplit - 1), p.nsplit_rcp);
-        }
+        per = (int)__umulhi((uint32_t)(m + p.nsplit - 1), p.nsplit_rcp);
         per = min((max(per, 1) + ROUND - 1) / ROUND * ROUND, p.chunk);   // chunk: nsplit * chunk >= S
     }
     *r0 = split * per;
@@ -111,19 +103,9 @@ __device__ __forceinline__ void split_rows(const AttnParams &p, int n, int split
 
 // Work item of a group kernel's block: its unit (sequence, head group, shard) and split.
 // Workgroups go to the 8 XCDs round-robin by id.  Giving each XCD a contiguous range of units, whose splits share
-// score rows and partial lines, measures 1.3 % faster than spreading neighbours over all XCDs.  Where a shard may
-// leave its last splits empty (long_rows > 0) an XCD takes the first split of all its units, then the second: with a
-// unit's splits side by side, the blocks with work landed on few of the CUs
-// (128 units, 2 of 8 splits: 34.3 us, now 26.9).
+// score rows and partial lines, measures 1.3 % faster than spreading neighbours over all XCDs.
 __device__ __forceinline__ int group_block(const AttnParams &p, int *split) {
     const int id = blockIdx.x, grid = gridDim.x;
-    if (p.long_rows > 0) {
-        const int units = grid / p.nsplit;
-        const bool even = units % 8 == 0;
-        const int per = even ? units / 8 : units, at = even ? id / 8 : id;
-        *split = at / per;
-        return (even ? id % 8 * per : 0) + at % per;
-    }
     const int item = grid % 8 == 0 ? (id % 8) * (grid / 8) + id / 8 : id;
     *split = item % p.nsplit;
     return item / p.nsplit;
@@ -1537,24 +1519,35 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     if (gqa_mfma && W == 64 && d->rank > 0 && resident > 2) resident = 2;
     int64_t nsplit = 1;
     int chunk = 0;
-    // bf16 groups of one row tile whose units (sequence, head group, shard) make 192 to 256 blocks at `least` splits each:
-    // that many, and no block of more than 512 KiB of K and V.  Blocks beyond that cost more - their start, their merge,
-    // the partials that the merge reads - than they hide; and a shard that is not full still makes whole, even
-    // blocks (split_rows takes the same two numbers from its entry count).  Fused step, three or four blocks per CU
-    // before: 128 units of 4096 slots of 64 values 44.6 -> 43.4 us, 55 % full 38.7 -> 33.9; rank-32 codes 49.1 -> 45.7 and
-    // 41.9 -> 35.4; 64 units of 4096 rows of 128 38.0 -> 36.5, 50 % full 30.0 -> 27.7; 40 units 28.9 -> 27.7.  Rows of 128
-    // values over more units keep the old plan (128 units, 10 - 100 % full, 47.5 us against 48.5: their longest blocks end
-    // late), and so do 32 units (1 x 8 x 4 of 8192, 36.4 against 38.5: the merge of 32 partials takes narrower blocks).
+    // A block per CU, or nearly, for bf16 groups of one row tile: `least` splits of every unit (sequence, head group, shard),
+    // instead of three or four blocks per CU.  Blocks beyond one per CU cost more - their
+    // start, their merge, the partials that the merge reads - than they hide, and a shard that is not full still
+    // makes whole, even blocks.  Where the line lies, from fused steps of 16 - 512 units x 1024 - 8192 slots, full / 55 % /
+    // 10 - 100 % full, time against the other plan's:
+    //   - at most 512 KiB of K and V (128 units x 64 values, 4096 slots 0.94 / 0.89 / 0.89, 8192 0.95 / 1.05 / 1.03; 80 units
+    //     0.95 / 0.86 / 0.93 and 1.10 / 0.98 / 1.13), rows of 16 values 128 KiB (64 units, 6000 slots 0.88 / 0.89 / 0.89; 224
+    //     units, 6000 slots 1.12 / 1.01 / 1.13): beyond, shards of uneven fill leave CUs waiting for the longest block;
+    //   - at least 200 blocks (68 units x 3 0.90 / 0.89 / 0.96, 192 x 1 0.97 / 0.93 / 1.02, 96 x 2 of rank-32 codes 1.02 / 0.93 / 1.05),
+    //     or 192 of at most 256 KiB (0.96 / 0.94 / 0.99 and 0.97 / 0.94 / 0.98);
+    //   - at most 24 partials of a head (7 x 2 x 3 units, 18 partials 0.93 / 0.90 / 0.96, 10 x 5, 25 partials 1.07 / 1.02 / 1.09, 8 x 8,
+    //     32 partials 1.09 / 1.04 / 1.10): the merge of up to 32 takes narrow blocks, where the other plan's many more
+    //     take wide ones.  Narrow rows in blocks of up to two rounds of tiles have no more splits by the other plan:
+    //     up to 32 (8 x 8 units of 1024 slots 0.98 / 0.95 / 0.96; 5 x 4, 48 partials, a tenth full 1.06);
+    //   - rows of 128 values only beyond two rounds, where the other plan cuts alike (64 units of 1024 slots 1.02).
+    // Fewer than 16 units are left to that plan, unmeasured.
     const int round = kWavesPerBlock * tile;
-    const int long_rows = 512 * 1024 / (2 * W * 2);
     const int64_t least = units > 0 ? 256 / units : 1;
+    const int64_t block_rows = least > 0 ? (d->S + least - 1) / least : d->S;
+    const bool two_rounds = block_rows <= 2 * round;
+    const int64_t long_block = least * units >= 200 ? 128 * 1024 : least * units >= 192 ? 64 * 1024 : 0;     // values of K
+    const bool by_unit = gqa_mfma && row_tiles == 1 && (W < 128 || (gb <= 8 && !two_rounds)) && units >= 16 &&
+                         block_rows * W <= (W == 16 ? long_block / 4 : long_block) && k * least <= (W < 128 && two_rounds ? 32 : 24) &&
+                         g_split_override == 0;
     // With few units a block takes fewer than two tiles per wave, down to one, and below 64 blocks to one in all: every
     // kernel's chain of trips to memory is shorter then.  (7 units of 938 rows of 64 values x 8 heads, pass and
     // merge 15.1 -> 9.7 us, 6 of 256 rows of 128 9.7 -> 8.5, 16 of 768 rank-32 codes of one head 12.0 -> 9.9, 8 of 256
     // fp32 rows 9.9 -> 7.9, 4 of 1192 11.5 -> 9.5.)  Not past 128 partials of a head: 256 blocks of one unit 21.8 -> 24.8.  Groups
     // of narrow bf16 rows, whose tiles are long, only where the old plan had one block per unit.
-    const bool by_unit = gqa_mfma && row_tiles == 1 && (W < 128 || gb <= 8) && units > 32 &&
-                         units <= (W == 128 ? 64 : 256) && least * units >= 192 && g_split_override == 0;
     const int64_t rounds = (d->S + round - 1) / round;
     const bool few = units > 0 && g_split_override == 0 && units * rounds <= 256 && k * rounds <= 128 &&
                      !(gqa_mfma && W < 128 && d->S >= 4 * round);
@@ -1568,10 +1561,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     const int64_t scratch_splits = capped ? (int64_t)((scratch_limit - 1024) / split_bytes) : INT32_MAX;
     auto split_for = [&](int res) {
         nsplit = units > 0 ? (int64_t)256 * res / units : 1;
-        if (by_unit) {
-            const int64_t by_rows = (d->S + long_rows - 1) / long_rows;
-            nsplit = by_rows > least ? by_rows : least;
-        }
+        if (by_unit) nsplit = least;
         // No finer than two tiles per wave: with one, nothing is in flight while a wave computes,
         // and a block of uneven waves (2, 2, 1, 1 tiles) runs as long as one of twice the rows.
         // (Few units, short passes: 64 MiB over 16 units 14.0 -> 12.8 us, 32 MiB over 8 units
@@ -1689,8 +1679,6 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     const int64_t target_blocks = 256 * resident;
     plan->gqa_mfma = gqa_mfma;
     plan->gqa_f32 = gqa_f32;
-    plan->least_splits = (int)least;
-    plan->long_rows = by_unit && !few ? long_rows : 0;
     plan->long_blocks = W == 128 && by_unit && !few;
     plan->heads_per_block = gb;
     plan->row_tiles = row_tiles;
@@ -1803,8 +1791,6 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
     p.stride_s = desc->stride_s;
     p.nsplit = plan.nsplit;
     p.chunk = plan.chunk;
-    p.least_splits = plan.least_splits;
-    p.long_rows = plan.long_rows;
     p.nsplit_rcp = plan.nsplit > 1 ? (uint32_t)(((uint64_t)1 << 32) / plan.nsplit + 1) : 0u;
     p.stage_scores = scores != nullptr && plan.score_stage_bytes > 0;
     p.scale = scale > 0.0f ? scale : 1.0f / sqrtf((float)desc->D);

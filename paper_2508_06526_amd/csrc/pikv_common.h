@@ -218,7 +218,6 @@ struct AttnPlan {
     int tile_rows;        // rows one wave consumes per iteration
     int chunk;            // rows per split (multiple of tile_rows)
     int nsplit;
-    int least_splits, long_rows;  // of them a shard uses, by its entry count (long_rows 0: all)
     bool long_blocks;     // 128-value rows in blocks of up to 512 KiB (attn_partial_gqa<.., LONG>)
     int resident_blocks;  // blocks of the split pass the GPU holds at once
     size_t score_stage_bytes;  // LDS per block for the raw scores (0: written straight to memory)

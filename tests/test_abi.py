@@ -95,6 +95,22 @@ def test_long_narrow_shards_are_cut_until_their_scores_fit_beside_the_tiles(lib)
     assert splits_of(pk.make_desc(32, 128, 16, 32, 8, 8832, dtype=1), 4) == 1              # 8 heads
 
 
+@pytest.mark.parametrize("B,Hkv,k,S,group,splits", [
+    (16, 4, 2, 4096, dict(D=64, G=8), 2), (16, 4, 2, 4097, dict(D=64, G=8), 4),          # 512 KiB of a block, 128 units
+    (16, 8, 2, 4096, dict(D=128, G=4, rank=32), 1), (16, 8, 2, 4097, dict(D=128, G=4, rank=32), 4),
+    (16, 8, 2, 2048, dict(D=128, G=4, rank=16), 1), (16, 8, 2, 2049, dict(D=128, G=4, rank=16), 2),   # 128 KiB
+    (4, 8, 2, 4096, dict(D=128, G=4), 4), (4, 8, 2, 4097, dict(D=128, G=4), 12),
+    (17, 4, 1, 4096, dict(D=64, G=8), 3), (8, 8, 3, 1024, dict(D=64, G=8), 1), (8, 8, 3, 1025, dict(D=64, G=8), 2),   # 204 blocks, 192
+    (1, 8, 3, 8192, dict(D=128, G=4), 32), (3, 8, 1, 8192, dict(D=128, G=4), 10),        # 30 and 10 partials of a head
+    (1, 8, 8, 4096, dict(D=64, G=8), 8), (1, 8, 8, 1024, dict(D=64, G=8), 4),            # 32 partials, short blocks
+    (4, 8, 2, 1024, dict(D=128, G=4), 4), (4, 8, 2, 4096, dict(D=128, G=16), 8),         # two rounds; 16 rows
+])
+def test_groups_whose_units_make_a_block_per_cu(lib, B, Hkv, k, S, group, splits):
+    """256 / units splits on one side of each line of the rule, the plan of several blocks per CU on the other."""
+    desc = pk.make_desc(B, Hkv * group["G"], Hkv, group["D"], 16, S, rank=group.get("rank", 0), dtype=1)
+    assert splits_of(desc, k) == splits
+
+
 def test_host_side_argument_errors(lib):
     """NULL pointers / out-of-range sizes return PIKV_ERR_INVALID with no GPU present."""
     vp = C.c_void_p

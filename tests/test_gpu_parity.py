@@ -633,9 +633,9 @@ def test_splits_follow_the_entry_count(spec, forced):
 
 
 @pytest.mark.parametrize("spec", [
-    # a block per CU: 60, 192, 204 (not spread over XCDs in whole units) and 192 units, of them some with one split
-    dict(Hq=20, Hkv=5, D=128, S=4111, k=12), dict(Hq=32, Hkv=16, D=64, S=2304, k=12), dict(Hq=51, Hkv=17, D=64, S=2050, k=12),
-    dict(Hq=48, Hkv=16, D=64, S=4500, k=12, rank=32), dict(Hq=64, Hkv=16, D=16, S=8200, k=12),
+    # a block per CU: 108 units with two splits, 204 and 252 with one
+    dict(Hq=36, Hkv=9, D=128, S=2003, k=12), dict(Hq=72, Hkv=9, D=128, S=2048, k=12), dict(Hq=18, Hkv=9, D=64, S=4091, k=12),
+    dict(Hq=51, Hkv=17, D=64, S=2045, k=12), dict(Hq=63, Hkv=21, D=64, S=4001, k=12, rank=32), dict(Hq=84, Hkv=21, D=16, S=2040, k=12),
     # few units: a tile per wave, and blocks of fewer waves with rows than waves
     dict(Hq=8, Hkv=1, D=128, S=1030, k=2), dict(Hq=8, Hkv=1, D=64, S=938, k=7), dict(Hq=3, Hkv=3, D=128, S=600, k=3),
     dict(Hq=4, Hkv=1, D=128, S=258, k=1, rank=16), dict(Hq=20, Hkv=1, D=128, S=1000, k=1),
