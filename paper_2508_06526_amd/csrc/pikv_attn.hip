@@ -1557,7 +1557,8 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     // Splits whose partials fit the fixed array of the call without a workspace: where a plan wants more of them than
     // the one that took these calls before, the call takes fewer and is not refused for it.
     const size_t split_bytes = (size_t)(d->B > 0 ? d->B : 1) * d->Hq * k * (W + 2) * sizeof(float);
-    const bool capped = scratch_limit != SIZE_MAX && (few || by_unit || gqa_f32 || (gqa_mfma && W != 128));
+    const bool capped = scratch_limit != SIZE_MAX &&
+                        (few || gqa_f32 || (gqa_mfma && (W != 128 || (row_tiles == 1 && gb <= 8 && units <= 64))));
     const int64_t scratch_splits = capped ? (int64_t)((scratch_limit - 1024) / split_bytes) : INT32_MAX;
     auto split_for = [&](int res) {
         nsplit = units > 0 ? (int64_t)256 * res / units : 1;
