@@ -1543,16 +1543,16 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     const bool by_unit = gqa_mfma && row_tiles == 1 && (W < 128 || (gb <= 8 && !two_rounds)) && units >= 16 &&
                          block_rows * W <= (W == 16 ? long_block / 4 : long_block) && k * least <= (W < 128 && two_rounds ? 32 : 24) &&
                          g_split_override == 0;
-    // With few units a block takes fewer than two tiles per wave, down to one, and below 64 blocks to one in all: every
-    // kernel's chain of trips to memory is shorter then.  (7 units of 938 rows of 64 values x 8 heads, pass and
+    // With few units a block takes fewer than two tiles per wave, down to one, and below 64 blocks to one in all (fp32
+    // groups on the matrix cores take whole rounds): every kernel's chain of trips to memory is shorter then.  (7 units of 938 rows of 64 values x 8 heads, pass and
     // merge 15.1 -> 9.7 us, 6 of 256 rows of 128 9.7 -> 8.5, 16 of 768 rank-32 codes of one head 12.0 -> 9.9, 8 of 256
     // fp32 rows 9.9 -> 7.9, 4 of 1192 11.5 -> 9.5.)  Not past 128 partials of a head: 256 blocks of one unit 21.8 -> 24.8.  Groups
-    // of narrow bf16 rows, whose tiles are long, only where the old plan had one block per unit.
+    // of narrow bf16 rows, whose tiles are long, only in shards below four rounds.
     const int64_t rounds = (d->S + round - 1) / round;
     const bool few = units > 0 && g_split_override == 0 && units * rounds <= 256 && k * rounds <= 128 &&
                      !(gqa_mfma && W < 128 && d->S >= 4 * round);
     int64_t finest = rounds;
-    for (int part = round; few && part > tile && units * finest * 2 <= 64; part /= 2)
+    for (int part = round; few && !gqa_f32 && part > tile && units * finest * 2 <= 64; part /= 2)
         finest = (d->S + part / 2 - 1) / (part / 2);
     // Splits whose partials fit the fixed array of the call without a workspace: where a plan wants more of them than
     // the one that took these calls before, the call takes fewer and is not refused for it.
@@ -1591,7 +1591,7 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
         // measured slower (k = 16: 8 splits of 8 tiles per wave against 6 splits, +3.7 %).
         const int even = 2 * kWavesPerBlock * tile;
         const int64_t fine = d->S / even;
-        if ((gqa_mfma || gqa_f32) && !by_unit && g_split_override == 0 && chunk % (kWavesPerBlock * tile) != 0 &&
+        if (gqa_mfma && !by_unit && g_split_override == 0 && chunk % (kWavesPerBlock * tile) != 0 &&
             d->S % even == 0 && fine > nsplit && fine * 3 <= nsplit * 4 && fine <= kMaxPartialsPerHead / k && fine <= scratch_splits &&
             (units * fine) % 256 == 0) {
             nsplit = fine;
