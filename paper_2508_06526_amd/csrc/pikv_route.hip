@@ -10,8 +10,9 @@
 //   route_mfma_rows_kernel : bf16, one row, a few or up to 16, on the matrix cores.
 //   route_vec_kernel,
 //   route_rows_kernel : fp32, W_r rows that are a power-of-two number of 16-byte chunks.
+//   route_single_kernel : fp32, any other E and alignment, few elements.
 //   route_flat_kernel,
-//   route_flat_rows_kernel : fp32, any other E and alignment.
+//   route_flat_rows_kernel : the rest of fp32.
 // The sums are described in pikv_route_dev.h.  Selection
 // is by rank counting: expert e's rank is the number of experts that beat it under (logit
 // descending, index ascending), so the output order and the tie-break need no sorting network.
@@ -94,8 +95,24 @@ __global__ __launch_bounds__(kRouteThreads) void route_vec_kernel(const float *x
                     probs);
 }
 
-// fp32, any E and alignment, one row (4096 values x 12 experts 9.4 -> 5.3 us, x 24 16.4 -> 7.4; several rows, below:
-// 1024 rows 28 -> 9.9 and 53 -> 14.1, 4096 rows 52 -> 36 and 88 -> 50; 4096 short rows, 1024 values x 6 experts, 11.7 -> 12.4).
+// fp32, few elements, R rows.
+template <int R>
+__global__ __launch_bounds__(kRouteThreads) void route_single_kernel(const float *x, const float *W_r, const float *bias,
+                                                                     int rows, int d_r, int E, int EP, int k, int32_t *topk_idx,
+                                                                     float *gates, float *probs) {
+    __shared__ float red[R * kRouteThreads];
+    const int lane = threadIdx.x & (kWave - 1), wave = threadIdx.x >> 6, row0 = blockIdx.x * R;
+    const float bias_e = route_bias_of_lane(bias, E, lane);
+    const float *xr[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) xr[q] = x + (int64_t)min(row0 + q, rows - 1) * d_r;
+    route_logits_single<R>(xr, W_r, d_r, E, EP, red);
+    if (wave < R && row0 + wave < rows)      // a row per wave
+        select_topk(route_logit_single_of_lane(red + wave * kRouteThreads, bias_e, E, lane), lane, row0 + wave, E, k, topk_idx, gates, probs);
+}
+
+// fp32, any E and alignment, one row (4096 values x 12 experts, against single elements 9.2 -> 5.1 us, x 24 16.3 -> 7.3;
+// several rows, below: 1024 rows 22 -> 9.2 and 40 -> 12.6, 4096 rows 51 -> 29 and 87 -> 43).
 __global__ __launch_bounds__(kRouteThreads) void route_flat_kernel(const float *x, const float *W_r, const float *bias,
                                                                    int d_r, int E, int T, bool aligned, int k,
                                                                    int32_t *topk_idx, float *gates, float *probs) {
@@ -107,9 +124,10 @@ __global__ __launch_bounds__(kRouteThreads) void route_flat_kernel(const float *
     if (threadIdx.x < kWave) select_topk(route_logit_of_lane(red[0], 64, bias_e, E, lane), lane, row, E, k, topk_idx, gates, probs);
 }
 
-// ... several rows: a set of T threads takes RT rows, a block up to 4 sets.
+// ... several rows: a set of T threads takes RT rows, a block up to 4 sets.  Held to 64 registers, a CU takes two blocks,
+// and one's loads cover the other's sums (4096 rows: 2048 values x 6 17.6 -> 13.2 us, 4096 x 24 49.8 -> 43.0).
 template <int RT>
-__global__ __launch_bounds__(kRouteThreads) void route_flat_rows_kernel(const float *x, const float *W_r, const float *bias,
+__global__ __launch_bounds__(kRouteThreads, RT == 1 ? 4 : 8) void route_flat_rows_kernel(const float *x, const float *W_r, const float *bias,
                                                                         int rows, int sets, int d_r, int E, int EP, int T,
                                                                         bool aligned, int k, int32_t *topk_idx, float *gates,
                                                                         float *probs) {
@@ -117,7 +135,6 @@ __global__ __launch_bounds__(kRouteThreads) void route_flat_rows_kernel(const fl
     extern __shared__ __attribute__((aligned(16))) float flat_sums[];     // [row of the block][4 T], [row][wave][EP]
     const int tid = threadIdx.x, lane = tid & (kWave - 1), wave = tid >> 6;
     const int row0 = blockIdx.x * sets * RT;
-    const float bias_e = route_bias_of_lane(bias, E, lane);
     const int set = tid / T, t = tid - set * T;
     if (set < sets) {
         const float *xr[RT];
@@ -129,6 +146,7 @@ __global__ __launch_bounds__(kRouteThreads) void route_flat_rows_kernel(const fl
         for (int q = 0; q < RT; ++q)
             *reinterpret_cast<float4 *>(flat_sums + (set * RT + q) * 4 * T + 4 * t) = make_float4(acc[q][0], acc[q][1], acc[q][2], acc[q][3]);
     }
+    const float bias_e = route_bias_of_lane(bias, E, lane);   // (not across the sums: registers)
     __syncthreads();
     float *red = flat_sums + sets * RT * 4 * T;
     for (int q = 0; q < sets * RT; ++q) {
@@ -264,26 +282,42 @@ int route_f32(const float *x, const float *W_r, const float *bias, int rows, int
         }
         return launch_status();
     }
+    if (route_single_ok(d_r, E)) {           // a block per CU as long as that takes the rows, then 2, 4 and 8 of them
+        auto go = [&](auto r) {
+            constexpr int R = decltype(r)::value;
+            hipLaunchKernelGGL((route_single_kernel<R>), dim3((rows + R - 1) / R), block, 0, st, x, W_r, bias, rows, d_r, E,
+                               route_flat_pow2(E), k, topk_idx, gates, probs);
+        };
+        if (rows <= 256) go(std::integral_constant<int, 1>{});
+        else if (rows <= 512) go(std::integral_constant<int, 2>{});
+        else if (rows <= 1024) go(std::integral_constant<int, 4>{});
+        else go(std::integral_constant<int, 8>{});
+        return launch_status();
+    }
     const int T = route_flat_threads(d_r, E);
     const bool aligned = reinterpret_cast<uintptr_t>(W_r) % 16 == 0;
     if (rows <= 256) {
         hipLaunchKernelGGL(route_flat_kernel, dim3(rows), block, 0, st, x, W_r, bias, d_r, E, T, aligned, k, topk_idx, gates, probs);
         return launch_status();
     }
-    // One block per CU as long as a block can take the rows: sets of threads first, then rows of a thread.
+    // One block per CU as long as a block can take the rows: sets of threads first, then rows of a thread - no more sets than
+    // those need, and not three where they cannot take the rows: at 12 rows a block 4096 leave some CUs two blocks and
+    // others one (4096 rows x 1024 values x 10 experts 20.0 -> 16.2 us, 1024 rows in blocks of 6 7.4 -> 6.2).
     const int EP = route_flat_pow2(E), want = rows < 16 * 256 ? (rows + 255) / 256 : 16;
     int sets = kRouteThreads / T < 4 ? kRouteThreads / T : 4;
     if (EP == 64 && sets > 2) sets = 2;                       // LDS: at most 96 KiB
-    if (sets > want) sets = want;
+    const int RT = sets >= want ? 1 : 2 * sets >= want ? 2 : 4;
+    if (sets > (want + RT - 1) / RT) sets = (want + RT - 1) / RT;
+    if (sets == 3 && 3 * RT < want) sets = 2;
     auto go = [&](auto rt) {
-        constexpr int RT = decltype(rt)::value;
-        const int per_block = sets * RT;
-        hipLaunchKernelGGL((route_flat_rows_kernel<RT>), dim3((rows + per_block - 1) / per_block), block,
+        constexpr int R = decltype(rt)::value;
+        const int per_block = sets * R;
+        hipLaunchKernelGGL((route_flat_rows_kernel<R>), dim3((rows + per_block - 1) / per_block), block,
                            (size_t)per_block * (4 * T + kRouteThreads / kWave * EP) * sizeof(float), st, x, W_r, bias, rows, sets,
                            d_r, E, EP, T, aligned, k, topk_idx, gates, probs);
     };
-    if (sets >= want) go(std::integral_constant<int, 1>{});
-    else if (2 * sets >= want) go(std::integral_constant<int, 2>{});
+    if (RT == 1) go(std::integral_constant<int, 1>{});
+    else if (RT == 2) go(std::integral_constant<int, 2>{});
     else go(std::integral_constant<int, 4>{});
     return launch_status();
 }

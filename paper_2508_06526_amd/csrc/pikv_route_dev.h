@@ -78,7 +78,7 @@ __device__ __forceinline__ int select_topk(float mine, int lane, int row, int E,
     return rank;
 }
 
-// The logits, three forms.  Each ends with partial sums in LDS that route_logit_of_lane joins, and none depends on scheduling or on how many rows share a block: a row's
+// The logits, four forms.  Each ends with partial sums in LDS that route_logit_of_lane joins, and none depends on scheduling or on how many rows share a block: a row's
 // logits are the same bits in a decode step, in a call of a few rows and in a prompt.
 //
 // (1) bf16 on the matrix cores, any E and d_r.  The block's 16 waves cut the contraction into units of
@@ -631,12 +631,54 @@ __device__ __forceinline__ void route_logits_vec(const float *xr, const float *W
     __syncthreads();
 }
 
-// (3) fp32, any other E and any alignment: W_r as one flat array, cut into chunks of 4 elements.
+// (3) fp32, any other E and any alignment, few elements: threads as (row slice, expert), an element of W_r each, and a
+// pairwise tree over the slices.  A thread has less to set up than in the next form, which pays from about 8
+// elements a thread on, and sooner where its chunks are of one row of W_r (E a multiple of 4); with up to 3 experts a
+// chunk of that form spans rows, and it never pays.  This form against the next, us: 1 row x 64 values x 6 experts
+// 2.9 and 3.6, x 512 3.43 and 3.58, x 2048 4.5 and 3.9; 1024 rows x 1024 x 6 5.5 and 6.0, 4096 rows 10.9 and 11.8;
+// 512 rows x 512 x 12 4.5 and 4.8, 1 row 3.7 and 3.3; 3 experts, 1 row x 8192 6.2 and 6.7, 4096 rows x 4096 22 and 44.
+// (Row counts do not enter: a row's bits are the same whatever their number.)
+inline bool route_single_ok(int d_r, int E) {
+    int EP = 1;
+    while (EP < E) EP <<= 1;
+    return E <= 3 || (int64_t)d_r * EP <= (E % 4 == 0 ? 4096 : 8192);
+}
+// The logits of R rows: row q's are the first E floats of red + 1024 q, of R * 1024.
+template <int R>
+__device__ __forceinline__ void route_logits_single(const float *const (&xr)[R], const float *W_r, int d_r, int E, int EP, float *red) {
+    const int tid = threadIdx.x, e = tid & (EP - 1), slice = tid / EP, slices = kRouteThreads / EP;
+    float acc[R];
+#pragma unroll
+    for (int q = 0; q < R; ++q) acc[q] = 0.0f;
+    if (e < E) {
+        for (int j = slice; j < d_r; j += slices) {
+            const float w = W_r[(int64_t)j * E + e];
+#pragma unroll
+            for (int q = 0; q < R; ++q) acc[q] = fmaf(xr[q][j], w, acc[q]);
+        }
+    }
+#pragma unroll
+    for (int q = 0; q < R; ++q) red[q * kRouteThreads + tid] = acc[q];
+    __syncthreads();
+    for (int half = slices >> 1; half >= 1; half >>= 1) {
+        if (slice < half)
+#pragma unroll
+            for (int q = 0; q < R; ++q) red[q * kRouteThreads + tid] += red[q * kRouteThreads + tid + half * EP];
+        __syncthreads();
+    }
+}
+// Expert `lane`'s logit of a row (experts >= E: -inf; a NaN logit ranks last).
+__device__ __forceinline__ float route_logit_single_of_lane(const float *red, float bias_of_lane, int E, int lane) {
+    if (lane >= E) return -INFINITY;
+    const float v = red[lane] + bias_of_lane;
+    return v != v ? -INFINITY : v;
+}
+
+// (4) fp32, the rest: W_r as one flat array, cut into chunks of 4 elements.
 // A row of E elements repeats its place in the chunks every E / gcd(E, 4) of them, so with the
 // block's threads cut down to a multiple of that, T, thread t's chunks t, t + T, ... hold the same
 // 4 experts each, and it sums them in registers; the 4 T sums (element g belongs to expert g % E)
-// meet in LDS.  Before, a thread read single elements, and a tree over the row slices followed,
-// a barrier per level.
+// meet in LDS.
 // Several rows: route_flat_rows_kernel, R rows to a thread, and as many sets of T threads as a block holds.
 constexpr int kFlatFloats = 4 * kRouteThreads;
 // T: as many threads as have about 8 chunks each - the sums that meet in LDS are few then, and 8 loads
@@ -647,7 +689,7 @@ inline int route_flat_threads(int d_r, int E) {
     const int T = eighth < kRouteThreads ? (int)eighth : kRouteThreads;
     return T < period ? period : T / period * period;
 }
-// XJ: values of x that a chunk meets - 1 (E a multiple of 4), 2 (at most two rows of W_r) or 4 (E < 4).
+// XJ: values of x that a chunk meets - 1 (E a multiple of 4) or 2 (at most two rows of W_r: E > 4).
 template <int R, int XJ>
 __device__ __forceinline__ void route_flat_sums(int tid, const float *const (&xr)[R], const float *W_r, int d_r, int E, int T,
                                                 bool aligned, float (&acc)[R][4]) {
@@ -659,8 +701,7 @@ __device__ __forceinline__ void route_flat_sums(int tid, const float *const (&xr
     int j[XJ];                              // rows of W_r (past the last one: the last)
     j[0] = 4 * tid / E;
     const int second = (j[0] + 1) * E - 4 * tid;              // XJ == 2: the chunk's first element of the second row
-#pragma unroll
-    for (int i = 1; i < XJ; ++i) j[i] = XJ == 2 ? j[0] + 1 : (4 * tid + i) / E;
+    if (XJ == 2) j[XJ - 1] = j[0] + 1;
     const int dj = 4 * T / E;               // rows from one chunk of the thread to the next
     const int64_t whole = (int64_t)d_r * E / 4;
     auto batch = [&](int64_t c, auto count) {
@@ -678,7 +719,7 @@ __device__ __forceinline__ void route_flat_sums(int tid, const float *const (&xr
 #pragma unroll
             for (int r = 0; r < R; ++r)
 #pragma unroll
-                for (int i = 0; i < XJ; ++i) x[u][r][i] = xr[r][XJ == 2 && i == 1 ? min(j[i] + u * dj, d_r - 1) : j[i] + u * dj];
+                for (int i = 0; i < XJ; ++i) x[u][r][i] = xr[r][i == 1 ? min(j[i] + u * dj, d_r - 1) : j[0] + u * dj];
         }
 #pragma unroll
         for (int u = 0; u < N; ++u)
@@ -686,13 +727,13 @@ __device__ __forceinline__ void route_flat_sums(int tid, const float *const (&xr
             for (int r = 0; r < R; ++r)
 #pragma unroll
                 for (int i = 0; i < 4; ++i) {
-                    const float xi = XJ == 4 ? x[u][r][i % XJ] : XJ == 1 || i < second ? x[u][r][0] : x[u][r][XJ - 1];
+                    const float xi = XJ == 1 || i < second ? x[u][r][0] : x[u][r][XJ - 1];
                     acc[r][i] = fmaf(xi, w[u][i], acc[r][i]);
                 }
 #pragma unroll
         for (int i = 0; i < XJ; ++i) j[i] += N * dj;
     };
-    constexpr int MOST = R > 1 ? 2 : XJ < 4 ? 8 : 4;
+    constexpr int MOST = R > 1 ? 2 : 8;
     int64_t c = tid;
     for (; c + (MOST - 1) * T < whole; c += MOST * T) batch(c, std::integral_constant<int, MOST>{});
     for (; c < whole; c += T) batch(c, std::integral_constant<int, 1>{});
@@ -703,15 +744,14 @@ __device__ __forceinline__ void route_flat_sums(int tid, const float *const (&xr
             if (i < left)
 #pragma unroll
                 for (int r = 0; r < R; ++r)
-                    acc[r][i] = fmaf(xr[r][XJ == 4 ? j[i % XJ] : i < second ? j[0] : j[XJ - 1]], W_r[whole * 4 + i], acc[r][i]);
+                    acc[r][i] = fmaf(xr[r][i < second ? j[0] : j[XJ - 1]], W_r[whole * 4 + i], acc[r][i]);
     }
 }
 template <int R>
 __device__ __forceinline__ void route_flat_sums(int tid, const float *const (&xr)[R], const float *W_r, int d_r, int E, int T,
                                                 bool aligned, float (&acc)[R][4]) {
     if (E % 4 == 0) route_flat_sums<R, 1>(tid, xr, W_r, d_r, E, T, aligned, acc);
-    else if (E > 4) route_flat_sums<R, 2>(tid, xr, W_r, d_r, E, T, aligned, acc);
-    else route_flat_sums<R, 4>(tid, xr, W_r, d_r, E, T, aligned, acc);
+    else route_flat_sums<R, 2>(tid, xr, W_r, d_r, E, T, aligned, acc);
 }
 // A wave's share of the 4 T sums of expert lane % EP: every (1024 / EP)-th from wave * (64 / EP) + lane / EP on.
 __device__ __forceinline__ float route_flat_share(const float *buf, int E, int EP, int T, int wave, int lane) {
@@ -719,8 +759,6 @@ __device__ __forceinline__ float route_flat_share(const float *buf, int E, int E
     float s = 0.0f;
     if (e < E)
         for (int m = wave * (kWave / EP) + lane / EP; m < sums; m += kRouteThreads / EP) s += buf[m * E + e];
-    if (EP <= 1) s += lane_xor<0>(s);
-    if (EP <= 2) s += lane_xor<1>(s);
     if (EP <= 4) s += lane_xor<2>(s);
     if (EP <= 8) s += lane_xor<3>(s);
     if (EP <= 16) s = route_sum_rows(s);

@@ -45,7 +45,7 @@ struct PreParams {
     int64_t stride_h_bytes, stride_s_bytes;
     int64_t x_stride;    // elements between the routed vectors of consecutive sequences (>= d_r)
     int d_r, E, cpr, k, S, Hkv, row_chunks, do_insert;
-    int flat_threads;    // fp32: 0 where rows of W_r are cpr aligned chunks, else the threads of the flat form
+    int flat_threads;    // fp32: 0 where rows of W_r are cpr aligned chunks, < 0 for single elements, else the threads of the flat form
     bool w_aligned;      // ... and whether W_r is 16-byte aligned
     bool words;          // bf16: see route_words_ok
     int use_policy;      // the entry to evict is chosen by pol (Table 3) instead of the utility
@@ -112,8 +112,10 @@ __global__ __launch_bounds__(kRouteThreads) void step_pre(PreParams p) {
         __shared__ float red[kWaves][64];
         __shared__ __attribute__((aligned(16))) float flat[kFlatFloats];
         if (p.flat_threads == 0) route_logits_vec(xr, W_r, p.d_r, p.cpr, red);
+        else if (p.flat_threads < 0) route_logits_single<1>({xr}, W_r, p.d_r, p.E, route_flat_pow2(p.E), flat);
         else route_logits_flat(xr, W_r, p.d_r, p.E, p.flat_threads, p.w_aligned, flat, red);
-        if (wave == 0) logit = route_logit_of_lane(red[0], 64, bias_e, p.E, lane);
+        if (wave == 0)
+            logit = p.flat_threads < 0 ? route_logit_single_of_lane(flat, bias_e, p.E, lane) : route_logit_of_lane(red[0], 64, bias_e, p.E, lane);
     }
     // The first wave ranks the experts and tells the others which shard is the block's (one LDS
     // word and a barrier): sixteen waves doing it side by side, four to a SIMD, take twice as
@@ -661,7 +663,9 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     p.x_stride = (int64_t)desc->Hq * desc->D;
     p.E = desc->E;
     p.cpr = 0;
-    p.flat_threads = desc->dtype == PIKV_F32 && !route_vec_ok(W_r, desc->E, &p.cpr) ? route_flat_threads(p.d_r, desc->E) : 0;
+    p.flat_threads = 0;
+    if (desc->dtype == PIKV_F32 && !route_vec_ok(W_r, desc->E, &p.cpr))
+        p.flat_threads = route_single_ok(p.d_r, desc->E) ? -1 : route_flat_threads(p.d_r, desc->E);
     p.w_aligned = reinterpret_cast<uintptr_t>(W_r) % 16 == 0;
     p.words = route_words_ok(q, p.x_stride, W_r, p.d_r, desc->E);
     p.k = k;

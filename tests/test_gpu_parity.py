@@ -130,6 +130,11 @@ def test_route_forms_agree_and_stay_within_their_rounding(E, dtype, d_r):
             np.testing.assert_array_equal(w[:xs.shape[0]], p)
 
 
+@pytest.mark.parametrize("E,d_r", [(3, 9000), (6, 1024), (6, 1025), (13, 512), (13, 513), (12, 256), (12, 257), (63, 128), (63, 129)])
+def test_route_forms_on_both_sides_of_the_line_between_single_elements_and_chunks(E, d_r):
+    test_route_forms_agree_and_stay_within_their_rounding(E, "f32", d_r)
+
+
 def test_route_exact_ties_lower_index_first():
     rng = np.random.default_rng(6)
     rows, d_r = 64, 32
