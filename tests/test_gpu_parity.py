@@ -58,13 +58,13 @@ def test_route_matches_oracle(spec, with_bias):
     np.testing.assert_allclose(t2n(dc.probs), probs, rtol=2e-5, atol=1e-7)
 
 
-@pytest.mark.parametrize("rows", [257, 511, 513, 1027, 2051])
-@pytest.mark.parametrize("E,dtype", [(8, "bf16"), (16, "bf16"), (32, "bf16"), (64, "bf16"), (4, "f32"), (8, "f32"),
-                                     (16, "f32"), (64, "f32"), (6, "bf16"), (13, "f32")])
+@pytest.mark.parametrize("rows", [257, 511, 513, 1027, 2051, 3000, 4096, 4099])
+@pytest.mark.parametrize("E,dtype", [(8, "bf16"), (16, "bf16"), (24, "bf16"), (32, "bf16"), (36, "bf16"), (64, "bf16"), (4, "f32"),
+                                     (8, "f32"), (16, "f32"), (64, "f32"), (6, "bf16"), (6, "f32"), (13, "f32"), (63, "f32")])
 def test_route_of_many_rows_gives_each_row_its_own_bits(rows, E, dtype):
-    """A prompt's rows share a block's pass over W_r (2, 4 or 8 of them, the last block partly filled);
-    selection, gates and probabilities of a row are those of a call with few rows, bit for bit - in
-    both the aligned and the generic form, every chunk count, with NaN and infinite logits among them."""
+    """A prompt's rows share a block's pass over W_r, ceil(rows / 256) of them up to 16 in bf16, 2, 4 or 8 in fp32 or up
+    to 16 in chunks of W_r, the last block partly filled; selection, gates and probabilities of a row are those
+    of a call with few rows, bit for bit - every layout of the experts, with NaN and infinite logits among them."""
     k, d_r = 3, 520
     gen = torch.Generator(device=DEV)
     gen.manual_seed(rows + E)
@@ -91,7 +91,8 @@ def test_route_of_many_rows_gives_each_row_its_own_bits(rows, E, dtype):
 @pytest.mark.parametrize("d_r", [1, 31, 127, 128, 130, 2048, 4104])
 @pytest.mark.parametrize("E,dtype", [(1, "bf16"), (2, "bf16"), (5, "bf16"), (8, "bf16"), (10, "bf16"), (16, "bf16"), (24, "bf16"),
                                      (32, "bf16"), (33, "bf16"), (36, "bf16"), (62, "bf16"), (64, "bf16"),
-                                     (1, "f32"), (3, "f32"), (6, "f32"), (12, "f32"), (40, "f32"), (63, "f32")])
+                                     (1, "f32"), (3, "f32"), (6, "f32"), (12, "f32"), (40, "f32"), (63, "f32"), (4, "f32"), (8, "f32"),
+                                     (16, "f32"), (64, "f32")])
 def test_route_forms_agree_and_stay_within_their_rounding(E, dtype, d_r):
     """Whole and partial units of the contraction, every layout of the experts, rows in columns of their own or
     traded, words or single elements (x or W_r off by one element): the same bits, and within the rounding of
@@ -120,14 +121,22 @@ def test_route_forms_agree_and_stay_within_their_rounding(E, dtype, d_r):
     logits = x.double() @ W.double()
     bound = (d_r / 512 + 32) * 2.0 ** -24 * (x.double().abs() @ W.double().abs())
     ref = torch.softmax(logits, 1)
-    assert ((torch.from_numpy(whole[2]).to(DEV) - ref).abs() <= ref * (2 * bound.amax(1, keepdim=True) + 4e-6)).all()
-    # (fp32 takes another layout where rows of W_r are whole chunks that lose their alignment)
-    moved = E * 4 % 16 != 0 or dtype == "bf16"
-    variants = [(x[:300].contiguous(), W), (x[:3].contiguous(), W), (at_offset(x[:3], 1), W), (at_offset(x[:700], 1), W)]
-    variants += [(x[:3].contiguous(), at_offset(W, 1)), (x, at_offset(W, 1))] if moved else []
-    for xs, Ws in variants:
-        for w, p in zip(whole, route(xs, Ws)):
-            np.testing.assert_array_equal(w[:xs.shape[0]], p)
+
+    def assert_close(probs):
+        assert ((torch.from_numpy(probs).to(DEV) - ref).abs() <= ref * (2 * bound.amax(1, keepdim=True) + 4e-6)).all()
+
+    def assert_same(whole, variants):
+        for xs, Ws in variants:
+            for w, p in zip(whole, route(xs, Ws)):
+                np.testing.assert_array_equal(w[:xs.shape[0]], p)
+
+    assert_close(whole[2])
+    moved = at_offset(W, 1)
+    assert_same(whole, [(x[:300].contiguous(), W), (x[:3].contiguous(), W), (at_offset(x[:3], 1), W), (at_offset(x[:700], 1), W)])
+    if dtype == "f32" and E in (4, 8, 16, 32, 64):           # rows of W_r that are whole chunks lose their layout
+        whole = route(x, moved)
+        assert_close(whole[2])
+    assert_same(whole, [(x[:3].contiguous(), moved), (x[:300].contiguous(), moved), (x, moved)])
 
 
 @pytest.mark.parametrize("E,d_r", [(3, 9000), (6, 1024), (6, 1025), (13, 512), (13, 513), (12, 256), (12, 257), (63, 128), (63, 129)])
@@ -531,17 +540,19 @@ def test_infinite_entries_of_narrow_groups_stay_infinite(spec):
 
 
 @pytest.mark.parametrize("spec", [
-    dict(B=2, Hq=6, Hkv=2, D=128, S=17), dict(B=1, Hq=8, Hkv=2, D=128, S=1030), dict(B=2, Hq=32, Hkv=2, D=128, S=513),
+    dict(B=2, Hq=6, Hkv=2, D=128, S=17), dict(B=1, Hq=10, Hkv=2, D=128, S=1030), dict(B=2, Hq=32, Hkv=2, D=128, S=513),
+    # groups of four: the plain kernel's
+    dict(B=1, Hq=8, Hkv=2, D=128, S=1030), dict(B=2, Hq=8, Hkv=2, D=64, S=1), dict(B=1, Hq=16, Hkv=4, D=16, rank=16, S=130),
     dict(B=1, Hq=64, Hkv=2, D=128, S=300),                      # 32 heads in two blocks of 16
     dict(B=1, Hq=36, Hkv=2, D=64, S=700), dict(B=3, Hq=10, Hkv=2, D=64, S=129), dict(B=1, Hq=34, Hkv=2, D=64, S=90),
-    dict(B=2, Hq=14, Hkv=2, D=32, S=1025), dict(B=1, Hq=16, Hkv=1, D=16, S=1999), dict(B=2, Hq=8, Hkv=2, D=64, S=1),
+    dict(B=2, Hq=14, Hkv=2, D=32, S=1025), dict(B=1, Hq=16, Hkv=1, D=16, S=1999), dict(B=2, Hq=6, Hkv=2, D=64, S=1),
     dict(B=1, Hq=16, Hkv=2, D=32, S=5000),                      # scores that fit the LDS in finer splits only
     dict(B=2, Hq=12, Hkv=4, D=64, rank=16, S=260), dict(B=1, Hq=30, Hkv=2, D=128, rank=32, S=515),
-    dict(B=2, Hq=16, Hkv=2, D=32, rank=64, S=300), dict(B=1, Hq=16, Hkv=4, D=16, rank=16, S=130),
+    dict(B=2, Hq=16, Hkv=2, D=32, rank=64, S=300), dict(B=1, Hq=24, Hkv=4, D=16, rank=16, S=130),
     dict(B=1, Hq=16, Hkv=1, D=128, rank=64, S=1100),
 ], ids=lambda s: "D%d_r%d_G%d_S%d" % (s["D"], s.get("rank", 0), s["Hq"] // s["Hkv"], s["S"]))
 def test_groups_of_fp32_rows_match_oracle(spec):
-    """Groups of 3 and more heads on the fp32 matrix cores: tiles of 16 to 64 entries and their remainders, scores
+    """Groups of 3 and of 5 and more heads on the fp32 matrix cores: tiles of 16 to 64 entries and their remainders, scores
     staged, in finer splits and written from the loop, groups that no number of heads up to 16 but one divides.
     fp32 sums, 1.7e-7 measured."""
     g = wl.Geometry(E=3, k=2, dtype="f32", **spec)
@@ -551,7 +562,7 @@ def test_groups_of_fp32_rows_match_oracle(spec):
 
 
 @pytest.mark.parametrize("spec", [dict(B=2, Hq=16, Hkv=2, D=128), dict(B=2, Hq=12, Hkv=2, D=64), dict(B=1, Hq=32, Hkv=2, D=16),
-                                  dict(B=2, Hq=8, Hkv=2, D=64, rank=32)],
+                                  dict(B=2, Hq=16, Hkv=2, D=64, rank=32), dict(B=2, Hq=8, Hkv=2, D=64, rank=32)],
                          ids=lambda s: "D%d_r%d_G%d" % (s["D"], s.get("rank", 0), s["Hq"] // s["Hkv"]))
 def test_infinite_entries_of_fp32_groups_stay_infinite(spec):
     g = wl.Geometry(E=2, k=2, S=512, dtype="f32", **spec)
@@ -638,6 +649,9 @@ def test_splits_follow_the_entry_count(spec, forced):
 
 
 @pytest.mark.parametrize("spec", [
+    # nearly the units for a block per CU, but many partials or long blocks: 60, 192 and 204 units
+    dict(Hq=20, Hkv=5, D=128, S=4111, k=12), dict(Hq=32, Hkv=16, D=64, S=2304, k=12), dict(Hq=51, Hkv=17, D=64, S=2050, k=12),
+    dict(Hq=48, Hkv=16, D=64, S=4500, k=12, rank=32), dict(Hq=64, Hkv=16, D=16, S=8200, k=12),
     # a block per CU: 108 units with two splits, 204 and 252 with one
     dict(Hq=36, Hkv=9, D=128, S=2003, k=12), dict(Hq=72, Hkv=9, D=128, S=2048, k=12), dict(Hq=18, Hkv=9, D=64, S=4091, k=12),
     dict(Hq=51, Hkv=17, D=64, S=2045, k=12), dict(Hq=63, Hkv=21, D=64, S=4001, k=12, rank=32), dict(Hq=84, Hkv=21, D=16, S=2040, k=12),
@@ -646,7 +660,7 @@ def test_splits_follow_the_entry_count(spec, forced):
     dict(Hq=4, Hkv=1, D=128, S=258, k=1, rank=16), dict(Hq=20, Hkv=1, D=128, S=1000, k=1),
     dict(Hq=2, Hkv=2, D=64, S=700, k=2, dtype="f32"), dict(Hq=8, Hkv=1, D=128, S=300, k=1, dtype="f32"),
     dict(Hq=6, Hkv=2, D=64, S=515, k=2, rank=32, dtype="f32"),
-], ids=lambda s: "%s_G%d_u%d_D%d_r%d" % (s.get("dtype", "bf16"), s["Hq"] // s["Hkv"], s["Hkv"] * s["k"], s["D"], s.get("rank", 0)))
+], ids=lambda s: "%s_G%d_u%d_D%d_r%d_S%d" % (s.get("dtype", "bf16"), s["Hq"] // s["Hkv"], s["Hkv"] * s["k"], s["D"], s.get("rank", 0), s["S"]))
 def test_few_and_whole_blocks_follow_the_entry_count(spec):
     """The same for the plans of few units (down to a tile per block) and of one block per CU."""
     test_splits_follow_the_entry_count(dict(dict(B=1, E=12, dtype="bf16"), **spec), 0)
