@@ -632,16 +632,16 @@ __device__ __forceinline__ void route_logits_vec(const float *xr, const float *W
 }
 
 // (3) fp32, any other E and any alignment, few elements: threads as (row slice, expert), an element of W_r each, and a
-// pairwise tree over the slices.  A thread has less to set up than in the next form, which pays from about 8
+// pairwise tree over the slices.  A thread has less to set up than in the next form, which pays from 6 to 8
 // elements a thread on, and sooner where its chunks are of one row of W_r (E a multiple of 4); with up to 3 experts a
-// chunk of that form spans rows, and it never pays.  This form against the next, us: 1 row x 64 values x 6 experts
-// 2.9 and 3.6, x 512 3.43 and 3.58, x 2048 4.5 and 3.9; 1024 rows x 1024 x 6 5.5 and 6.0, 4096 rows 10.9 and 11.8;
-// 512 rows x 512 x 12 4.5 and 4.8, 1 row 3.7 and 3.3; 3 experts, 1 row x 8192 6.2 and 6.7, 4096 rows x 4096 22 and 44.
+// chunk of that form spans rows, and it never pays.  This form against the next, us, 1 row, 500 and 4096 rows: 600 values x 6
+// experts 3.38, 4.19, 8.7 and 3.60, 4.93, 10.3, 768 x 6 3.59, 4.39, 9.7 and 3.36, 4.81, 10.1; 512 x 13 3.6, 4.5, 10.3 and
+// 3.7, 5.0, 11.2; 512 x 12 3.6, 4.5, 10.3 and 3.3, 4.6, 9.9; 3 experts, 1 row x 8192 6.2 and 6.7, 4096 x 4096 22 and 44.
 // (Row counts do not enter: a row's bits are the same whatever their number.)
 inline bool route_single_ok(int d_r, int E) {
     int EP = 1;
     while (EP < E) EP <<= 1;
-    return E <= 3 || (int64_t)d_r * EP <= (E % 4 == 0 ? 4096 : 8192);
+    return E <= 3 || (int64_t)d_r * EP <= (E % 4 == 0 ? 4096 : EP <= 8 ? 6000 : 8192);
 }
 // The logits of R rows: row q's are the first E floats of red + 1024 q, of R * 1024.
 template <int R>

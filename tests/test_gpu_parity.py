@@ -139,7 +139,7 @@ def test_route_forms_agree_and_stay_within_their_rounding(E, dtype, d_r):
     assert_same(whole, [(x[:3].contiguous(), moved), (x[:300].contiguous(), moved), (x, moved)])
 
 
-@pytest.mark.parametrize("E,d_r", [(3, 9000), (6, 1024), (6, 1025), (13, 512), (13, 513), (12, 256), (12, 257), (63, 128), (63, 129)])
+@pytest.mark.parametrize("E,d_r", [(3, 9000), (6, 750), (6, 751), (13, 512), (13, 513), (12, 256), (12, 257), (63, 128), (63, 129)])
 def test_route_forms_on_both_sides_of_the_line_between_single_elements_and_chunks(E, d_r):
     test_route_forms_agree_and_stay_within_their_rounding(E, "f32", d_r)
 
