@@ -619,7 +619,7 @@ constexpr size_t gqa_static_lds(int width, int tile, int row_tiles) {
 // one burst per row at the block's end) or kScoresDirect (written from the loop).  A template
 // parameter and not a run-time branch: each form costs registers, and a value spilled for one
 // of them is reloaded inside the loop by a scratch load, which the wait counters cannot tell
-// from the tile loads in flight - the wave then waits for all of them.  (One form of the 42 still
+// from the tile loads in flight - the wave then waits for all of them.  (One form of the 45 still
 // spills: rank-16 codes at four row tiles with scores written from the loop, 24 bytes.)
 constexpr int kScoresNone = 0, kScoresStaged = 1, kScoresDirect = 2;
 template <int W, int RT, int SC, bool CODES, bool LONG>
@@ -1082,9 +1082,9 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, LONG ? kGqaLongBlocksPerCu :
 // The plain kernel above spends 4 multiply-adds and a reduction over 4 - 32 lanes per head and row piece:
 // with 4 and 8 heads it was bound by vector issue, and at 8 it left one wave per SIMD (252 registers);
 // groups of other than 2, 4 and 8 heads streamed K/V once per head.
-// Measured, pass and merge, against the plain kernel: 8 heads over rows of 128 values (512 MiB) 147 -> 102 us, 64 values
-// 129 -> 107, 3 heads 250 -> 92, 6 heads (256 MiB) 166 -> 53, 16 heads 459 -> 63, 32 heads (128 MiB) 392 -> 60; rank-64 codes x 8
-// heads (104 MiB) 46 -> 38; 4 heads 107 -> 100 at 64 values, even at 128; 2 heads stay there (49 -> 51).
+// Measured, pass and merge with scores, against the plain kernel: 8 heads over rows of 128 values (512 MiB) 146 -> 107 us,
+// of 64 127 -> 110, 3 heads of 128 169 -> 97, 16 heads 1030 -> 115, 6 heads (256 MiB) 134 -> 59, 32 heads (128 MiB) 387 -> 62;
+// rank-64 codes x 8 heads (100 MiB) 51 -> 39.  Groups of two and four stay there, see kGqa32Heads.
 constexpr int gqa32_tile(int width) { return width >= 128 ? 16 : width == 64 ? 32 : 64; }
 constexpr int kGqa32BlocksPerCu = 3;
 // Rows of 4 floats more than W: banks.

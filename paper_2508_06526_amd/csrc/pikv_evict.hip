@@ -23,8 +23,9 @@ namespace {
 constexpr int kAppendThreads = 256;
 // evict_select: 256 threads for shards of up to 2048 slots, 1024 beyond: a thread then owns a quarter of
 // the slots, the lists and the compacted utilities leave as runs of 32 bytes per lane instead of 128, and
-// four waves a SIMD cover each other's latencies.  (Graph replay, capacity 3/4, select of 16 steps:
-// 16 shards of 8192 slots 20.4 -> 18.3 us, 128 of 4096 15.9 -> 14.4.)
+// four waves a SIMD cover each other's latencies; but a CU holds two such blocks, not eight.  Graph replay, capacity
+// 3/4, with a copy of 3 us, 256 and 1024 threads: 64 shards of 1000 slots 8.3 and 8.9 us, of 2000 9.9 and 9.1, of 4096 14.8
+// and 10.1; 1024 shards of 1000 10.1 and 25.1, of 2000 14.6 and 26.8, of 4096 24.0 and 29.6.
 constexpr int kSelFewSlots = 2048;
 constexpr int kSelCache = 32;        // keys a thread can keep in registers (n <= 32768)
 constexpr int kSelBins = 1024;       // of a round of the select
