@@ -619,7 +619,7 @@ constexpr size_t gqa_static_lds(int width, int tile, int row_tiles) {
 // one burst per row at the block's end) or kScoresDirect (written from the loop).  A template
 // parameter and not a run-time branch: each form costs registers, and a value spilled for one
 // of them is reloaded inside the loop by a scratch load, which the wait counters cannot tell
-// from the tile loads in flight - the wave then waits for all of them.  (One form of the 45 still
+// from the tile loads in flight - the wave then waits for all of them.  (One form of the 44 still
 // spills: rank-16 codes at four row tiles with scores written from the loop, 24 bytes.)
 constexpr int kScoresNone = 0, kScoresStaged = 1, kScoresDirect = 2;
 template <int W, int RT, int SC, bool CODES, bool LONG>
@@ -1400,10 +1400,11 @@ void launch_gqa(int row_tiles, bool long_blocks, const AttnParams &p, int64_t bl
     auto launch = [&](auto rt, auto longs) {
         constexpr int RT = decltype(rt)::value;
         constexpr bool LONG = decltype(longs)::value;
+        constexpr int kStaged = LONG ? kScoresDirect : kScoresStaged;      // (no long block of 128-value rows stages its scores)
         if (p.scores == nullptr)
             hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresNone, CODES, LONG>), grid, block, lds, st, p);
         else if (p.stage_scores)
-            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresStaged, CODES, LONG>), grid, block, lds, st, p);
+            hipLaunchKernelGGL((attn_partial_gqa<W, RT, kStaged, CODES, LONG>), grid, block, lds, st, p);
         else
             hipLaunchKernelGGL((attn_partial_gqa<W, RT, kScoresDirect, CODES, LONG>), grid, block, lds, st, p);
     };

@@ -483,7 +483,15 @@ def test_long_blocks_of_groups_keep_the_precision_of_short_ones(spec, most):
     accumulate 2.52, 2.45, 2.64, 2.72 and 2.98; rows of 128 values 2.0e-7 with probabilities of three
     parts, 2.0e-6 with two (short blocks 1.83e-6).  The bounds lie between."""
     g = wl.Geometry(**dict(dict(B=2, Hkv=8, E=3, S=8192, k=3, dtype="bf16"), **spec))
-    check_group(wl.make_host_case(g, seed=1, utility0="exp"), most)
+    case = wl.make_host_case(g, seed=1, utility0="exp")
+    check_group(case, most)
+    idx, gates = (torch.from_numpy(a).to(DEV) for a in random_selection(g, g.S))
+    y = []
+    for want_scores in (True, False):
+        d = DeviceCase(case)
+        d.attend(topk=idx, gates=gates, want_scores=want_scores)
+        y.append(t2n(d.y))
+    np.testing.assert_array_equal(*y)
 
 
 @pytest.mark.parametrize("spec", [
