@@ -45,6 +45,7 @@ struct AttnParams {
     float *scores;
     int B, Hq, G, D, E, S, k, rr, rank;
     int64_t stride_h, stride_s;
+    FastDiv by_nsplit, by_k, by_groups, by_G;   // head groups (Hq / the heads of a block), heads of a group
     int nsplit, chunk;  // splits per shard, and the most rows one of them takes
     uint32_t nsplit_rcp;   // 2^32 / nsplit, rounded up (0: nsplit == 1)
     int tq;             // draft queries per sequence: q is [B, tq, Hq / tq, D] (1: plain [B, Hq, D])
@@ -106,9 +107,8 @@ __device__ __forceinline__ void split_rows(const AttnParams &p, int n, int split
 // score rows and partial lines, measures 1.3 % faster than spreading neighbours over all XCDs.
 __device__ __forceinline__ int group_block(const AttnParams &p, int *split) {
     const int id = blockIdx.x, grid = gridDim.x;
-    const int item = grid % 8 == 0 ? (id % 8) * (grid / 8) + id / 8 : id;
-    *split = item % p.nsplit;
-    return item / p.nsplit;
+    const int item = (grid & 7) == 0 ? (id & 7) * (grid >> 3) + (id >> 3) : id;
+    return fast_divide(p.by_nsplit, item, split);
 }
 
 // Where the caller keeps the query of internal row h of sequence b, in rows of D values.
@@ -155,16 +155,12 @@ attn_partial(AttnParams p) {
     const int c = lane & (LPR - 1);
     const int r = lane >> CB;
 
-    int bid = blockIdx.x;
-    const int split = bid % p.nsplit;
-    bid /= p.nsplit;
-    const int j = bid % p.k;
-    bid /= p.k;
-    const int hgroups = p.Hq / GB;
-    const int hg = bid % hgroups;
-    const int b = bid / hgroups;
+    int split, j, hg, group_head;
+    int bid = fast_divide(p.by_nsplit, blockIdx.x, &split);
+    bid = fast_divide(p.by_k, bid, &j);
+    const int b = fast_divide(p.by_groups, bid, &hg);
     const int h0 = hg * GB;
-    const int hk = h0 / p.G;
+    const int hk = fast_divide(p.by_G, h0, &group_head);
     const int route_row = b * p.rr + (p.rr == 1 ? 0 : h0);
     const ShardRef sh = resolve_shard(p, b, route_row, j, lane);
     int r0, r1;
@@ -640,13 +636,19 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, LONG ? kGqaLongBlocksPerCu :
     const int gb = p.G;                       // rows per block = the whole query group
 
     // (the plain-ALU kernel above measures 2.6 % slower with a contiguous range per XCD)
-    int split;
+    int split, j, hk;
     int bid = group_block(p, &split);
-    const int j = bid % p.k;
-    bid /= p.k;
-    const int hgroups = p.Hq / gb;
-    const int hk = bid % hgroups;
-    const int b = bid / hgroups;
+    int b;
+    if constexpr (RT < 4) {
+        bid = fast_divide(p.by_k, bid, &j);
+        b = fast_divide(p.by_groups, bid, &hk);
+    } else {                                  // (two registers spill here with fast_divide)
+        j = bid % p.k;
+        bid /= p.k;
+        const int hgroups = p.Hq / gb;
+        hk = bid % hgroups;
+        b = bid / hgroups;
+    }
     const int h0 = hk * gb;
 
     // Query operand of row tile rt: lane (row c, group r) holds Q[row rt*16 + c][32 s + 8 r .. +7]
@@ -1100,15 +1102,12 @@ __global__ __launch_bounds__(kWavesPerBlock *kWave, kGqa32BlocksPerCu) void attn
     const int c = lane & 15;
     const int r = lane >> 4;
 
-    int split;
+    int split, j, hg, group_head;
     int bid = group_block(p, &split);
-    const int j = bid % p.k;
-    bid /= p.k;
-    const int hgroups = p.Hq / gb;
-    const int hg = bid % hgroups;
-    const int b = bid / hgroups;
+    bid = fast_divide(p.by_k, bid, &j);
+    const int b = fast_divide(p.by_groups, bid, &hg);
     const int h0 = hg * gb;
-    const int hk = h0 / p.G;
+    const int hk = fast_divide(p.by_G, h0, &group_head);
 
     // Query operand: q[head c][16 s + 4 r + i]; heads past the group repeat the last one, nothing reads
     // what they lead to.
@@ -1791,6 +1790,10 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
     p.tq = desc->tq > 1 ? desc->tq : 1;
     p.stride_h = desc->stride_h;
     p.stride_s = desc->stride_s;
+    p.by_nsplit = fast_div(plan.nsplit);
+    p.by_k = fast_div(k);
+    p.by_groups = fast_div(plan.head_blocks);
+    p.by_G = fast_div(p.G);
     p.nsplit = plan.nsplit;
     p.chunk = plan.chunk;
     p.nsplit_rcp = plan.nsplit > 1 ? (uint32_t)(((uint64_t)1 << 32) / plan.nsplit + 1) : 0u;
@@ -1841,6 +1844,8 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
     c.slot_coef = slot_coef;
     c.Hq = desc->Hq;
     c.G = p.G;
+    c.by_Hq = fast_div(c.Hq);
+    c.by_G = fast_div(c.G);
     c.D = desc->D;
     c.W = W;
     c.k = k;

@@ -20,6 +20,7 @@ struct CombineParams {
     float *slot_coef;
     int Hq, G, D, W, k, rr, rank, nsplit, combine;
     int value_bias;   // U_V holds rank + 1 rows per kv head, the last one the decoder's additive term
+    FastDiv by_Hq, by_G;
     int tq;           // draft queries per sequence: y and the row statistics are [B, tq, Hq / tq, ...]
 };
 
@@ -148,8 +149,9 @@ __device__ __forceinline__ int64_t caller_row(const CombineParams &p, int b, int
 
 template <typename T, int THREADS>
 __device__ __forceinline__ void combine_head(const CombineParams &p, int bh, unsigned char *smem) {
-    const int b = bh / p.Hq, h = bh - b * p.Hq;
-    const int hk = h / p.G;
+    int h, group_head;
+    const int b = fast_divide(p.by_Hq, bh, &h);
+    const int hk = fast_divide(p.by_G, h, &group_head);
     const int64_t out = caller_row(p, b, h);
     const int tid = threadIdx.x;
     const int np = p.k * p.nsplit;
@@ -162,9 +164,10 @@ __device__ __forceinline__ void combine_head(const CombineParams &p, int bh, uns
     float *ycode = g_s + 64;                                         // [128]
     float *live_s = ycode + 128;                                     // [1] 1 if any selected shard holds entries
 
-    const int cgroups = p.W / 4;                 // float4 column groups: 4..32
-    const int slices = THREADS / cgroups;        // partial slices
-    const int cg = tid % cgroups, sl = tid / cgroups;
+    const int cbits = __builtin_ctz(p.W) - 2;    // float4 column groups: 4..32, a power of two
+    const int cgroups = 1 << cbits;
+    const int slices = THREADS >> cbits;         // partial slices
+    const int cg = tid & (cgroups - 1), sl = tid >> cbits;
     const float *acc = p.part_acc + (int64_t)bh * np * p.W + cg * 4;
     float4 pre[kCombinePrefetch];
 #pragma unroll

@@ -199,6 +199,25 @@ __device__ __forceinline__ int evict_composite_slot(uint64_t c) {
     return 0x7fffffff - (int)(uint32_t)(c & 0xffffffffu);
 }
 
+// Division of a block id, 0 <= n < 2^31, by a number that is the same in the whole launch: the host forms the
+// reciprocal.  The compiler's own division is some 30 dependent scalar instructions, and a block that takes its
+// id apart runs two to four of them in front of its first request (kernel trace: attention over 64 fp32
+// rows x 4 heads 4.55 -> 4.40 us, 1 x 8 x 4 of 8192 x 128 24.45 -> 24.25, 16 x 8 x 2 of 4096 rank-32 codes, step_post 7.5 ->
+// 7.1; step_pre 6.45 -> 6.35).
+struct FastDiv {
+    uint32_t d, rcp;
+};
+inline FastDiv fast_div(int d) { return FastDiv{(uint32_t)d, d > 0 ? 0xffffffffu / (uint32_t)d : 0u}; }
+__device__ __forceinline__ int fast_divide(FastDiv f, int n, int *rest) {
+    uint32_t q = __umulhi((uint32_t)n, f.rcp), r = (uint32_t)n - q * f.d;      // q: the quotient or one less
+    if (r >= f.d) {
+        ++q;
+        r -= f.d;
+    }
+    *rest = __builtin_amdgcn_readfirstlane((int)r);
+    return __builtin_amdgcn_readfirstlane((int)q);
+}
+
 inline hipStream_t as_stream(void *s) { return reinterpret_cast<hipStream_t>(s); }
 
 inline int launch_status() { return hipGetLastError() == hipSuccess ? PIKV_OK : PIKV_ERR_HIP; }

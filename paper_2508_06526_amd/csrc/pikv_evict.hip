@@ -569,11 +569,13 @@ struct AppendParams {
     float *utility;
     int32_t *n_valid;
     int64_t stride_h_bytes, stride_s_bytes;
-    int E, S, Hkv, k, row_chunks, max_evict;
+    FastDiv by_k;
+    int E, S, Hkv, k, row_chunks, row_bits, max_evict;      // chunks of a row: a power of two
 };
 
 __global__ __launch_bounds__(kAppendThreads) void append_rows(AppendParams p) {
-    const int b = blockIdx.x / p.k, j = blockIdx.x - b * p.k;
+    int j;
+    const int b = fast_divide(p.by_k, blockIdx.x, &j);
     const int e = p.topk[(int64_t)b * p.k + j];
     const int be = b * p.E + e;
     const int n = p.n_valid[be];
@@ -587,7 +589,7 @@ __global__ __launch_bounds__(kAppendThreads) void append_rows(AppendParams p) {
     const char *Ks = static_cast<const char *>(p.K_new) + (int64_t)b * total * 16;
     const char *Vs = static_cast<const char *>(p.V_new) + (int64_t)b * total * 16;
     for (int idx = threadIdx.x; idx < total; idx += blockDim.x) {
-        const int hk = idx / p.row_chunks, cc = idx - hk * p.row_chunks;
+        const int hk = idx >> p.row_bits, cc = idx & (p.row_chunks - 1);
         *reinterpret_cast<uint4 *>(Kd + hk * p.stride_h_bytes + cc * 16) =
             *reinterpret_cast<const uint4 *>(Ks + (int64_t)idx * 16);
         *reinterpret_cast<uint4 *>(Vd + hk * p.stride_h_bytes + cc * 16) =
@@ -703,7 +705,9 @@ extern "C" int pikv_append(const pikv_desc *desc, const void *K_new, const void 
     p.S = desc->S;
     p.Hkv = desc->Hkv;
     p.k = k;
+    p.by_k = fast_div(k);
     p.row_chunks = desc_width(desc) * eb / 16;
+    p.row_bits = __builtin_ctz(p.row_chunks);
     p.max_evict = max_evict;
     hipLaunchKernelGGL(append_rows, dim3(desc->B * k), dim3(kAppendThreads), 0, as_stream(stream),
                        p);

@@ -44,10 +44,11 @@ struct PreParams {
     int32_t *evicted_cnt;
     int64_t stride_h_bytes, stride_s_bytes;
     int64_t x_stride;    // elements between the routed vectors of consecutive sequences (>= d_r)
-    int d_r, E, cpr, k, S, Hkv, row_chunks, do_insert;
+    int d_r, E, cpr, k, S, Hkv, row_chunks, row_bits, do_insert;   // chunks of a row: a power of two
     int flat_threads;    // fp32: 0 where rows of W_r are cpr aligned chunks, < 0 for single elements, else the threads of the flat form
     bool w_aligned;      // ... and whether W_r is 16-byte aligned
     bool words;          // bf16: see route_words_ok
+    FastDiv by_k;
     int use_policy;      // the entry to evict is chosen by pol (Table 3) instead of the utility
     PolicyView pol;      // its arrays, when given, are also stamped for the new entry
 };
@@ -79,7 +80,8 @@ __device__ __forceinline__ uint64_t wave_min_u64(uint64_t v) {
 template <typename T, int MOST>
 __global__ __launch_bounds__(kRouteThreads) void step_pre(PreParams p) {
     constexpr int kWaves = kRouteThreads / kWave;
-    const int b = blockIdx.x / p.k, j = blockIdx.x - b * p.k;
+    int j;
+    const int b = fast_divide(p.by_k, blockIdx.x, &j);
     const int tid = threadIdx.x;
     const int lane = tid & (kWave - 1), wave = tid >> 6;
 
@@ -252,7 +254,7 @@ __global__ __launch_bounds__(kRouteThreads) void step_pre(PreParams p) {
             kv = load16(static_cast<const char *>(p.K_new) + ((int64_t)b * new_chunks + idx) * 16);
             vv = load16(static_cast<const char *>(p.V_new) + ((int64_t)b * new_chunks + idx) * 16);
         }
-        const int hk = idx / p.row_chunks, cc = idx - hk * p.row_chunks;
+        const int hk = idx >> p.row_bits, cc = idx & (p.row_chunks - 1);
         *reinterpret_cast<uint4 *>(Kd + hk * p.stride_h_bytes + cc * 16) = kv;
         *reinterpret_cast<uint4 *>(Vd + hk * p.stride_h_bytes + cc * 16) = vv;
     }
@@ -298,6 +300,7 @@ struct PostParams {
     float *utility;
     int B, E, S;
     int tiles;            // utility blocks per selected shard
+    FastDiv by_tiles, by_k;
     int tiles_per_block;  // consecutive slot tiles each of them covers
     int util_first;       // the utility blocks take the grid's first block ids (they start first)
     float decay;
@@ -356,10 +359,9 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     }
     const int np = k * nsplit;
     int bid = util_first ? (int)blockIdx.x : (int)blockIdx.x - ncomb;
-    const int tile = bid % p.tiles;
-    bid /= p.tiles;
-    const int j = bid % k;
-    const int b = bid / k;
+    int tile, j;
+    bid = fast_divide(p.by_tiles, bid, &tile);
+    const int b = fast_divide(p.by_k, bid, &j);
     const int tid = threadIdx.x;
     // Order of the requests: loads come back in the order they were issued, a value the
     // compiler knows to be the same in all lanes is waited for where it is loaded (it goes to a
@@ -672,6 +674,8 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     p.S = desc->S;
     p.Hkv = desc->Hkv;
     p.row_chunks = desc_width(desc) * eb / 16;
+    p.row_bits = __builtin_ctz(p.row_chunks);
+    p.by_k = fast_div(k);
     p.do_insert = K_new != nullptr;
     p.use_policy = use_policy;
     p.pol = pol;
@@ -744,6 +748,8 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     const int64_t tpb = tiles_per_block(slot_tiles);
     pp.tiles_per_block = (int)tpb;
     pp.tiles = (int)((slot_tiles + tpb - 1) / tpb);
+    pp.by_tiles = fast_div(pp.tiles);
+    pp.by_k = fast_div(k);
     pp.util_first = many ? 1 : 0;
     pp.decay = decay;
     pp.feedback = fb != nullptr;

@@ -33,7 +33,8 @@ struct UtilParams {
     const int32_t *n_valid;
     const int32_t *topk;
     float *utility;      // may be null in the tracked form
-    int Hq, E, S, k, rr, tiles;
+    FastDiv by_tiles, by_E;
+    int Hq, E, S, k, rr;
     float decay;
     // access bookkeeping (Table 3 rows LRU / LRU+): an entry whose attention mass of this
     // step exceeds `threshold` is accessed at step `now`
@@ -46,11 +47,9 @@ struct UtilParams {
 template <bool TRACK, bool SPREAD>
 __global__ __launch_bounds__(kUtilThreads) void utility_kernel(UtilParams p) {
     constexpr int kUtilTile = SPREAD ? kUtilThreads / 4 : kUtilThreads;
-    int bid = blockIdx.x;
-    const int tile = bid % p.tiles;
-    bid /= p.tiles;
-    const int e = bid % p.E;
-    const int b = bid / p.E;
+    int tile, e;
+    const int shard = fast_divide(p.by_tiles, blockIdx.x, &tile);
+    const int b = fast_divide(p.by_E, shard, &e);
     const int n = p.n_valid[(int64_t)b * p.E + e];
     const int i0 = tile * kUtilTile;
     if (i0 >= n) return;
@@ -173,13 +172,15 @@ int launch_utility(const pikv_desc *desc, const float *scores, const float *slot
     p.rr = desc->route_rows_per_seq;
     const bool spread = desc->Hq >= kUtilManyHeads;
     const int tile_slots = spread ? kUtilThreads / 4 : kUtilThreads;
-    p.tiles = (desc->S + tile_slots - 1) / tile_slots;
+    const int tiles = (desc->S + tile_slots - 1) / tile_slots;
+    p.by_tiles = fast_div(tiles);
+    p.by_E = fast_div(desc->E);
     p.decay = decay;
     p.last_access = last_access;
     p.freq = freq;
     p.threshold = threshold;
     p.now = now;
-    const int64_t blocks = (int64_t)desc->B * desc->E * p.tiles;
+    const int64_t blocks = (int64_t)desc->B * desc->E * tiles;
     if (blocks > 0x7fffffff) return PIKV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks), block(kUtilThreads);
     hipStream_t st = as_stream(stream);
