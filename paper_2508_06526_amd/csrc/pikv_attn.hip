@@ -1855,6 +1855,7 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
     c.tq = p.tq;
     c.nsplit = plan.nsplit;
     c.combine = combine;
+    c.decoder_bytes = reinterpret_cast<uintptr_t>(U_V) % 16 == 0 ? combine_decoder_bytes(c.rank, c.value_bias, c.D, elem_bytes(desc->dtype)) : 0;
     *c_out = c;
     return PIKV_OK;
 }
@@ -1868,11 +1869,11 @@ int pikv_sharded_attn_merge(const pikv_desc *desc, const CombineParams *c, void 
     const bool f32 = desc->dtype == PIKV_F32;
     const int np = c->k * c->nsplit;
     if (combine_threads(np) == 256) {
-        const size_t lds = combine_smem_bytes(256, np);
+        const size_t lds = combine_smem_bytes(256, np, c->decoder_bytes);
         if (f32) hipLaunchKernelGGL((attn_combine<float, 256>), cgrid, dim3(256), lds, st, *c);
         else hipLaunchKernelGGL((attn_combine<bf16, 256>), cgrid, dim3(256), lds, st, *c);
     } else {
-        const size_t lds = combine_smem_bytes(1024, np);
+        const size_t lds = combine_smem_bytes(1024, np, c->decoder_bytes);
         if (f32) hipLaunchKernelGGL((attn_combine<float, 1024>), cgrid, dim3(1024), lds, st, *c);
         else hipLaunchKernelGGL((attn_combine<bf16, 1024>), cgrid, dim3(1024), lds, st, *c);
     }

@@ -20,8 +20,9 @@ struct CombineParams {
     float *slot_coef;
     int Hq, G, D, W, k, rr, rank, nsplit, combine;
     int value_bias;   // U_V holds rank + 1 rows per kv head, the last one the decoder's additive term
-    FastDiv by_Hq, by_G;
     int tq;           // draft queries per sequence: y and the row statistics are [B, tq, Hq / tq, ...]
+    FastDiv by_Hq, by_G;
+    int decoder_bytes;   // of a kv head's rows of U_V that the merge brings into LDS ahead of its sums; 0: it reads them where they are
 };
 
 constexpr int kCombinePrefetch = 4;         // partial rows each thread loads before the weights exist
@@ -109,6 +110,42 @@ __device__ __forceinline__ HeadWeights head_weights(int kp, float Mj, float Zj, 
     }
     return out;
 }
+// The same from a wave whose 8-lane groups hold the statistics: lanes 8 g .. 8 g + 7 those of shard g % kp of a
+// head, kp <= 8.  The joins run over the lane bits 3 .. 5, by moves inside the vector unit - no LDS, no
+// barrier - and pair the same values in the same order as head_weights does.
+constexpr int kWaveShards = 8;
+template <class F>
+__device__ __forceinline__ float groups_join(int kp, float x, F op) {
+    if (kp > 1) x = op(x, lane_xchg<3>(x));      // (the same value in the 8 lanes of a group)
+    if (kp > 2) {
+        const auto q = __builtin_amdgcn_permlane16_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+    }
+    if (kp > 4) {
+        const auto h = __builtin_amdgcn_permlane32_swap(__float_as_uint(x), __float_as_uint(x), false, false);
+        x = op(__uint_as_float(h[0]), __uint_as_float(h[1]));
+    }
+    return x;
+}
+__device__ __forceinline__ HeadWeights head_weights_of_groups(int kp, float Mj, float Zj, float gj, int combine) {
+    const bool live = Zj > 0.0f;
+    HeadWeights out;
+    out.M = groups_join(kp, live ? Mj : -INFINITY, [](float a, float b) { return fmaxf(a, b); });
+    auto add = [](float a, float b) { return a + b; };
+    if (combine == PIKV_COMBINE_LSE) {
+        const float e = __expf(Mj - out.M);
+        out.norm = groups_join(kp, live ? gj * Zj * e : 0.0f, add);
+        out.w = live ? gj * e / out.norm : 0.0f;
+        out.shift = live ? out.M : 0.0f;
+        out.coef = live ? gj / out.norm : 0.0f;
+    } else {
+        out.norm = groups_join(kp, live ? gj : 0.0f, add);
+        out.w = live ? gj / (out.norm * Zj) : 0.0f;
+        out.shift = live ? Mj : 0.0f;
+        out.coef = out.w;
+    }
+    return out;
+}
 inline __host__ __device__ int pow2_at_least(int v) {
     int p = 1;
     while (p < v) p <<= 1;
@@ -119,17 +156,32 @@ inline __host__ __device__ int pow2_at_least(int v) {
 // accumulators do not depend on the weights, so their loads are issued first and overlap the
 // whole weight computation:
 //   phase 0: every thread = (slice of partials, float4 column group) issues its first
-//            accumulator loads; (max, sum) of every partial goes to LDS.
-//   phase 1: 8 lanes per selected shard reduce its splits to (max, normaliser).
-//   phase 2: k lanes form the k gate-weighted shard weights in either combine mode.
-//   phase 3: weighted sum of the accumulators, slices reduced through LDS in fixed order,
-//            then (rank > 0) the value decoder y = ycode U_V[h'].
+//            accumulator loads; the rows of the value decoder are requested as well.
+//   phase 1: 8 lanes per selected shard reduce its splits to (max, normaliser), the shards' are joined to
+//            the k gate-weighted shard weights in either combine mode, and every partial gets its
+//            weight.  Up to kWaveShards shards that is one wave's work from end to end, without a
+//            barrier: in blocks of four waves each does it for itself (a SIMD has one of them), in
+//            larger ones the first for all.  More shards take the block and its barriers (combine_weights_block).
+//   phase 2: weighted sum of the accumulators, slices reduced in a fixed order - across the waves by the
+//            block's first wave, inside it lane to lane - then (rank > 0) the value decoder
+//            y = ycode U_V[h'], by the same wave.
+// The merge is bound by its chain of phases: with a barrier behind each of them (nine in all) the same sums took, as a kernel
+// of its own, 4.0 us against 3.3 (4 heads x 16 partials of 64 values) and 5.4 against 4.8 (256 heads x 64 partials of 128).
 // Bytes of LDS combine_head<., threads> carves from the buffer it is given (np = k * nsplit
 // partials per head).  Sized by the real np, not by its maximum: the blocks are short and
 // many, and the LDS they reserve decides how many of them a CU holds at once.
 inline __host__ __device__ int combine_np_pad(int np) { return (np + 3) & ~3; }
-inline size_t combine_smem_bytes(int threads, int np) {
-    return (size_t)(2 * combine_np_pad(np) + 6 * 64 + 128 + 4) * 4 + (size_t)threads * 16;
+// rows of [np] floats: a wave's own weights each, or the weights and the sums they come from
+inline __host__ __device__ constexpr int combine_weight_copies(int threads) { return threads == 256 ? 4 : 2; }
+// The value decoder's rows of a kv head go to LDS with the block's first requests where they are at most this many bytes -
+// every bf16 decoder, fp32 ones up to rank 32; read column by column behind the sums they are a trip of their own.
+constexpr int kDecoderBytesMost = 65 * 128 * 2;
+inline int combine_decoder_bytes(int rank, int value_bias, int D, int elem) {
+    const int bytes = (rank + value_bias) * D * elem;
+    return rank > 0 && bytes <= kDecoderBytesMost ? bytes : 0;
+}
+inline size_t combine_smem_bytes(int threads, int np, int decoder_bytes) {
+    return (size_t)(combine_weight_copies(threads) * combine_np_pad(np) + 4 * 64 + 128 + 4) * 4 + (size_t)threads * 16 + decoder_bytes;
 }
 
 // Block size of the merge: one query head rarely has more than a few dozen partials; a small
@@ -147,40 +199,13 @@ __device__ __forceinline__ int64_t caller_row(const CombineParams &p, int b, int
     return ((int64_t)b * p.tq + t) * heads + hk * g + gg;
 }
 
-template <typename T, int THREADS>
-__device__ __forceinline__ void combine_head(const CombineParams &p, int bh, unsigned char *smem) {
-    int h, group_head;
-    const int b = fast_divide(p.by_Hq, bh, &h);
-    const int hk = fast_divide(p.by_G, h, &group_head);
-    const int64_t out = caller_row(p, b, h);
-    const int tid = threadIdx.x;
-    const int np = p.k * p.nsplit;
-
-    float4 *red = reinterpret_cast<float4 *>(smem);                  // [THREADS]
-    float *wt = reinterpret_cast<float *>(smem + THREADS * 16);     // max of every partial, later its weight
-    float *ls = wt + combine_np_pad(np);
-    float *Mj = ls + combine_np_pad(np), *Zj = Mj + 64, *shard_w = Zj + 64;
-    float *g_s = shard_w + 3 * 64;
-    float *ycode = g_s + 64;                                         // [128]
-    float *live_s = ycode + 128;                                     // [1] 1 if any selected shard holds entries
-
-    const int cbits = __builtin_ctz(p.W) - 2;    // float4 column groups: 4..32, a power of two
-    const int cgroups = 1 << cbits;
-    const int slices = THREADS >> cbits;         // partial slices
-    const int cg = tid & (cgroups - 1), sl = tid >> cbits;
-    const float *acc = p.part_acc + (int64_t)bh * np * p.W + cg * 4;
-    float4 pre[kCombinePrefetch];
-#pragma unroll
-    for (int u = 0; u < kCombinePrefetch; ++u) {
-        const int i = sl + u * slices;
-        pre[u] = i < np ? *reinterpret_cast<const float4 *>(acc + (int64_t)i * p.W)
-                        : make_float4(0.f, 0.f, 0.f, 0.f);
-    }
-
-    // the gates are read once into LDS: head_weights walks them several times
-    if (p.gates != nullptr && tid < p.k)
-        g_s[tid] = p.gates[(int64_t)(b * p.rr + (p.rr == 1 ? 0 : h)) * p.k + tid];
-    const float *ml = p.part_ml + (int64_t)bh * np * 2;
+// Weights of all partials of a head by the whole block: any k.
+template <int THREADS>
+__device__ __forceinline__ void combine_weights_block(const CombineParams &p, int bh, int64_t out, const float *ml, float gate,
+                                                      float *wt, float *ls, float *scratch, float *live_s) {
+    const int tid = threadIdx.x, np = p.k * p.nsplit;
+    float *Mj = scratch, *Zj = Mj + 64, *shard_w = Zj + 64, *g_s = shard_w + 64;
+    if (tid < p.k) g_s[tid] = gate;
     for (int i = tid; i < np; i += THREADS) {
         const float2 v = *reinterpret_cast<const float2 *>(ml + 2 * i);
         wt[i] = v.x;
@@ -221,6 +246,112 @@ __device__ __forceinline__ void combine_head(const CombineParams &p, int bh, uns
         wt[i] = ls[i] > 0.0f ? shard_w[j] * __expf(wt[i] - Mj[j]) : 0.0f;
     }
     __syncthreads();
+}
+
+// The same by one wave, k <= kWaveShards: 8 lanes per shard.  `sp`: the pairs of the lane's first splits.
+__device__ __forceinline__ void combine_weights_wave(const CombineParams &p, int bh, int64_t out, const float *ml, float gate,
+                                                     const ShardPairs &sp, float *wt, bool writes, float *live_s) {
+    const int lane = threadIdx.x & (kWave - 1), j = lane >> 3, sub = lane & 7;
+    const int nsplit = j < p.k ? p.nsplit : 0;
+    const float *mine = ml + 2 * (int64_t)j * p.nsplit;
+    auto pair = [&](int s) { return *reinterpret_cast<const float2 *>(mine + 2 * s); };
+    float M, Z;
+    shard_stats8(sp, nsplit, sub, pair, &M, &Z);
+    const HeadWeights hw = head_weights_of_groups(pow2_at_least(p.k), M, Z, gate, p.combine);
+    auto weight = [&](float2 v) { return v.y > 0.0f ? hw.w * __expf(v.x - M) : 0.0f; };
+#pragma unroll
+    for (int u = 0; u < kShardPairsHeld; ++u)
+        if (sub + 8 * u < nsplit) wt[j * p.nsplit + sub + 8 * u] = weight(sp.v[u]);
+    for (int s = sub + 8 * kShardPairsHeld; s < nsplit; s += 8) wt[j * p.nsplit + s] = weight(pair(s));
+    if (writes) {
+        if (p.slot_coef && j < p.k && sub == 0)
+            *reinterpret_cast<float2 *>(p.slot_coef + ((int64_t)bh * p.k + j) * 2) = make_float2(hw.shift, hw.coef);
+        if (lane == 0) {
+            if (p.row_max) p.row_max[out] = hw.M;
+            if (p.row_norm) p.row_norm[out] = hw.norm;
+            *live_s = hw.M > -INFINITY ? 1.0f : 0.0f;
+        }
+    }
+}
+
+__device__ __forceinline__ float4 add4(float4 a, float4 b) { return make_float4(a.x + b.x, a.y + b.y, a.z + b.z, a.w + b.w); }
+// N values at a stride of kWave float4, joined as the fixed tree does: i with i + N / 2, down to one.
+template <int N>
+__device__ __forceinline__ float4 tree_of_waves(const float4 *red) {
+    if constexpr (N == 1) return red[0];
+    else {
+        float4 v[N];
+#pragma unroll
+        for (int i = 0; i < N; ++i) v[i] = red[i * kWave];
+#pragma unroll
+        for (int half = N / 2; half >= 1; half /= 2)
+#pragma unroll
+            for (int i = 0; i < half; ++i) v[i] = add4(v[i], v[i + half]);
+        return v[0];
+    }
+}
+
+template <typename T, int THREADS>
+__device__ __forceinline__ void combine_head(const CombineParams &p, int bh, unsigned char *smem) {
+    int h, group_head;
+    const int b = fast_divide(p.by_Hq, bh, &h);
+    const int hk = fast_divide(p.by_G, h, &group_head);
+    const int64_t out = caller_row(p, b, h);
+    const int tid = threadIdx.x;
+    const int np = p.k * p.nsplit;
+    constexpr int kWaves = THREADS / kWave;
+    constexpr bool kEachWave = kWaves <= 4;      // every wave weighs for itself, a SIMD each
+
+    float4 *red = reinterpret_cast<float4 *>(smem);                  // [THREADS]
+    float *wts = reinterpret_cast<float *>(smem + THREADS * 16);    // weights of the partials
+    float *scratch = wts + combine_weight_copies(THREADS) * combine_np_pad(np);      // [4 * 64]
+    float *ycode = scratch + 4 * 64;                                 // [128]
+    float *live_s = ycode + 128;                                     // [1] 1 if any selected shard holds entries
+    T *decoder = reinterpret_cast<T *>(live_s + 4);                 // [decoder_bytes]
+
+    const int cbits = __builtin_ctz(p.W) - 2;    // float4 column groups: 4..32, a power of two
+    const int cgroups = 1 << cbits;
+    const int slices = THREADS >> cbits;         // partial slices
+    const int cg = tid & (cgroups - 1), sl = tid >> cbits;
+    const float *acc = p.part_acc + (int64_t)bh * np * p.W + cg * 4;
+    const float *ml = p.part_ml + (int64_t)bh * np * 2;
+    const float *gates = p.gates != nullptr ? p.gates + (int64_t)(b * p.rr + (p.rr == 1 ? 0 : h)) * p.k : nullptr;
+    const bool by_wave = p.k <= kWaveShards;
+    const int lane = tid & (kWave - 1), wave = tid / kWave;
+    const int shard = by_wave ? lane >> 3 : tid;
+    // the pairs and gates first: the weights hang off them, the sums off the weights
+    ShardPairs sp;
+    if (by_wave) {
+        const float *mine = ml + 2 * (int64_t)min(shard, p.k - 1) * p.nsplit;
+        sp = shard_pairs_load(shard < p.k ? p.nsplit : 0, lane & 7,
+                              [&](int s) { return *reinterpret_cast<const float2 *>(mine + 2 * s); });
+    }
+    const float gate = gates != nullptr && shard < p.k ? gates[shard] : 1.0f;
+    float4 pre[kCombinePrefetch];
+#pragma unroll
+    for (int u = 0; u < kCombinePrefetch; ++u) {
+        const int i = sl + u * slices;
+        pre[u] = i < np ? *reinterpret_cast<const float4 *>(acc + (int64_t)i * p.W)
+                        : make_float4(0.f, 0.f, 0.f, 0.f);
+    }
+    const T *U = static_cast<const T *>(p.U_V) + (int64_t)hk * (p.rank + p.value_bias) * p.D;
+    if (p.decoder_bytes != 0) {
+        const int chunks = (p.rank + p.value_bias) * p.D * (int)sizeof(T) / 16;
+        for (int i = tid; i < chunks; i += THREADS)
+            reinterpret_cast<uint4 *>(decoder)[i] = load16(reinterpret_cast<const uint4 *>(U) + i);
+    }
+
+    float *wt = wts;
+    if (!by_wave) {
+        combine_weights_block<THREADS>(p, bh, out, ml, gate, wts, wts + combine_np_pad(np), scratch, live_s);
+    } else if constexpr (kEachWave) {
+        wt = wts + wave * combine_np_pad(np);
+        combine_weights_wave(p, bh, out, ml, gate, sp, wt, wave == 0, live_s);
+        wave_lds_order();
+    } else {
+        if (wave == 0) combine_weights_wave(p, bh, out, ml, gate, sp, wt, true, live_s);
+        __syncthreads();
+    }
 
     float4 a = make_float4(0.f, 0.f, 0.f, 0.f);
 #pragma unroll
@@ -242,40 +373,52 @@ __device__ __forceinline__ void combine_head(const CombineParams &p, int bh, uns
     }
     red[tid] = a;
     __syncthreads();
-    // fixed-order tree over the slices (slices is a power of two)
-    for (int half = slices >> 1; half >= 1; half >>= 1) {
-        if (sl < half) {
-            const float4 v = red[tid + half * cgroups];
-            float4 t = red[tid];
-            t.x += v.x;
-            t.y += v.y;
-            t.z += v.z;
-            t.w += v.w;
-            red[tid] = t;
-        }
-        __syncthreads();
-    }
-    if (tid < cgroups) {
-        const float4 t = red[tid];
+    // Fixed-order tree over the slices (a power of two of them): slice s with s + half, half = slices / 2 .. 1.  A
+    // wave holds 64 / cgroups slices, so the first steps join the waves and the last ones lanes of the first wave.
+    if (wave != 0 && (p.rank == 0 || p.decoder_bytes != 0)) return;
+    float4 t = a;
+    if (wave == 0) {
+        t = tree_of_waves<kWaves>(red + lane);
+        auto other = [](float4 v, auto bit) {
+            constexpr int BIT = decltype(bit)::value;
+            return make_float4(lane_xor<BIT>(v.x), lane_xor<BIT>(v.y), lane_xor<BIT>(v.z), lane_xor<BIT>(v.w));
+        };
+        t = add4(t, other(t, std::integral_constant<int, 5>{}));
+        if (cgroups <= 16) t = add4(t, other(t, std::integral_constant<int, 4>{}));
+        if (cgroups <= 8) t = add4(t, other(t, std::integral_constant<int, 3>{}));
+        if (cgroups <= 4) t = add4(t, other(t, std::integral_constant<int, 2>{}));
         if (p.rank == 0) {
-            *reinterpret_cast<float4 *>(p.y + out * p.D + tid * 4) = t;
-        } else {
-            ycode[tid * 4 + 0] = t.x;
-            ycode[tid * 4 + 1] = t.y;
-            ycode[tid * 4 + 2] = t.z;
-            ycode[tid * 4 + 3] = t.w;
+            if (lane < cgroups) *reinterpret_cast<float4 *>(p.y + out * p.D + lane * 4) = t;
+            return;
         }
+        if (lane < cgroups) *reinterpret_cast<float4 *>(ycode + lane * 4) = t;
     }
-    if (p.rank != 0) {  // value decoder: y = ycode U_V[h'] (+ b[h'], the weights of a row sum to one)
-        __syncthreads();
-        const T *U = static_cast<const T *>(p.U_V) + (int64_t)hk * (p.rank + p.value_bias) * p.D;
-        for (int d = tid; d < p.D; d += THREADS) {
-            float a2 = 0.0f;
-            for (int cidx = 0; cidx < p.rank; ++cidx)
-                a2 = fmaf(ycode[cidx], load_scalar<T>(U, (int64_t)cidx * p.D + d), a2);
-            if (p.value_bias && *live_s != 0.0f) a2 += load_scalar<T>(U, (int64_t)p.rank * p.D + d);
-            p.y[out * p.D + d] = a2;
+    // value decoder: y = ycode U_V[h'] (+ b[h'], the weights of a row sum to one)
+    if (p.decoder_bytes != 0) {
+        wave_lds_order();
+        for (int d = 2 * lane; d < p.D; d += 2 * kWave) {
+            float y0 = 0.0f, y1 = 0.0f;
+#pragma unroll 8
+            for (int c = 0; c < p.rank; ++c) {
+                y0 = fmaf(ycode[c], load_scalar<T>(decoder, c * p.D + d), y0);
+                y1 = fmaf(ycode[c], load_scalar<T>(decoder, c * p.D + d + 1), y1);
+            }
+            if (p.value_bias && *live_s != 0.0f) {
+                y0 += load_scalar<T>(decoder, p.rank * p.D + d);
+                y1 += load_scalar<T>(decoder, p.rank * p.D + d + 1);
+            }
+            p.y[out * p.D + d] = y0;              // (y need not be 8-byte aligned)
+            p.y[out * p.D + d + 1] = y1;
         }
+        return;
+    }
+    __syncthreads();
+    for (int d = tid; d < p.D; d += THREADS) {
+        float a2 = 0.0f;
+        for (int cidx = 0; cidx < p.rank; ++cidx)
+            a2 = fmaf(ycode[cidx], load_scalar<T>(U, (int64_t)cidx * p.D + d), a2);
+        if (p.value_bias && *live_s != 0.0f) a2 += load_scalar<T>(U, (int64_t)p.rank * p.D + d);
+        p.y[out * p.D + d] = a2;
     }
 }
 

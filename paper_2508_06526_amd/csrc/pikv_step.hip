@@ -314,9 +314,9 @@ struct PostParams {
 // LDS of a utility block: statistics of the Hq * k (head, shard) pairs, the gates, and two
 // buffers of per-(head group, slot) sums used in turn.
 inline __host__ __device__ int post_pairs_pad(int pairs) { return (pairs + 3) & ~3; }
-inline size_t post_smem_bytes(int threads, int np, int pairs, int slots_per_thread) {
+inline size_t post_smem_bytes(int threads, int np, int pairs, int slots_per_thread, int decoder_bytes) {
     const size_t util = (size_t)(4 * post_pairs_pad(pairs) + 64 + 2 * slots_per_thread * threads) * 4;
-    const size_t comb = combine_smem_bytes(threads, np);
+    const size_t comb = combine_smem_bytes(threads, np, decoder_bytes);
     return util > comb ? util : comb;
 }
 
@@ -337,8 +337,17 @@ inline size_t post_smem_bytes(int threads, int np, int pairs, int slots_per_thre
 // the same (whole step, rows of 16 values: 32 sequences x 8 heads x 4 shards of 8192 slots 131.5 with one slot per
 // thread -> 127 us, 64 x 4 x 8 of 8192 283 -> 257, 32 x 32 x 8 of 4096 436 -> 432; planned for three
 // blocks: even).
-template <typename T, int THREADS, int MODE, int SPT>
+//
+// LANES: up to kWaveShards selected shards.  The (shift, coef) pair of a head comes out of the lanes that reduced its
+// partials, without a trip through LDS between the statistics and the weights; in blocks of 256 threads, where a wave
+// is a head group, each wave forms those of its own heads and no barrier stands before the scores' exponentials: the
+// other waves' statistics are nothing it waits for.  What bounds these blocks is the chain of phases and, with the chip full of
+// them, the instructions of a phase.  Kernel trace, with the merge's change below: 32 sequences x 32 heads x 2 shards of 2048
+// slots 10.6 -> 8.2 us, 4 x 32 x 4 of 8192 a fourteenth full 6.5 -> 5.2, 8 x 32 x 2 of 4096 half full 5.7 -> 5.4, 1 x 32 x 4 of
+// 8192 (blocks of 1024) 5.1 -> 4.8, 16 x 32 x 2 of 4096 codes of rank 32 8.3 -> 7.1.
+template <typename T, int THREADS, int MODE, int SPT, bool LANES>
 __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
+    constexpr bool kOwnHeads = LANES && THREADS == 256;
     constexpr int kSlots = THREADS / 4 * SPT;
     const int ntiles = MODE != kPostSingle ? p.tiles_per_block : 1;
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // post_smem_bytes()
@@ -347,7 +356,7 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     // Blocks are dispatched in id order.  With hundreds of query rows the utility blocks are
     // the long ones and a CU holds one block of either kind: they then take the first ids,
     // so that they do not queue behind the merge blocks (kPostMany only).
-    const bool util_first = MODE == kPostMany && p.util_first;
+    const bool util_first = (MODE == kPostMany || kOwnHeads) && p.util_first;
     const int mb = util_first ? (int)blockIdx.x - p.B * k * p.tiles : (int)blockIdx.x;
     if (mb >= 0 && mb < ncomb) {
         combine_head<T, THREADS>(p.c, mb, smem);
@@ -367,15 +376,18 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     // compiler knows to be the same in all lanes is waited for where it is loaded (it goes to a
     // scalar register at once), and nothing that is needed early may queue behind something
     // slow.  So the sequence's selections, entry counts and gates are read one per lane, first
-    // (lane l takes selection l, shard l's count and gate l; the block's own are picked out of
-    // the registers after the statistics); then the (max, sum) pairs of the statistics; then
-    // the scores - a trip to memory, with the shard's capacity as the bound: slots past the
-    // entry count are masked when they are used, and a block past the shard's end leaves when
-    // the count is here, before the statistics.
+    // (lane l takes selection l, shard l's count; the block's own are picked out of the registers when the pairs are
+    // on their way); then the (max, sum) pairs of the statistics; then, once the count is here and the block
+    // has not left for lack of entries, the scores, which come in while the statistics are formed.  (Requested with the
+    // pairs, up to the shard's capacity, they gain nothing in full shards and cost nearly empty ones 5.3 -> 6.4 us: 4
+    // sequences x 32 heads x 4 shards of 8192 slots, 573 entries each.)
     const int lane_id = tid & (kWave - 1);
     const int sel_of_lane = p.topk[(int64_t)b * k + min(lane_id, k - 1)];
     const int n_of_lane = p.n_valid[(int64_t)b * p.E + min(lane_id, p.E - 1)];
-    const float gate_of_thread = (p.c.gates != nullptr && tid < k) ? p.c.gates[(int64_t)b * k + tid] : 1.0f;
+    // LANES: kp groups of 8 lanes per head, one for each shard (padded to a power of two)
+    const int kp = pow2_at_least(k), kp_log2 = 31 - __builtin_clz(kp);
+    const int gj = LANES ? min((tid >> 3) & (kp - 1), k - 1) : tid;
+    const float gate_of_thread = (p.c.gates != nullptr && gj < k) ? p.c.gates[(int64_t)b * k + gj] : 1.0f;
     const int i0 = tile * kSlots * ntiles;
 
     const int pairs = post_pairs_pad(Hq * k);
@@ -383,6 +395,7 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     float *shift_s = Zj_s + pairs, *coef_s = shift_s + pairs;
     float *g_s = coef_s + pairs;               // [64]
     float *part_s = g_s + 64;                  // [2][4][kSlots]
+    float2 *pc_s = reinterpret_cast<float2 *>(smem);       // LANES: [Hq] (shift, coef) for the block's shard
 
     // thread = (SPT slots, head group); the heads are cut into 4 consecutive groups, each summed in
     // ascending order, the groups joined as (g0 + g1) + (g2 + g3) - the order the stand-alone
@@ -447,34 +460,91 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     // those of the pass kPostStatsAhead later.
     constexpr int kAhead = MODE == kPostMany ? kPostStatsAhead : 1;
     constexpr int kPairsPerPass = THREADS / 8;
-    const int npairs = Hq * k;
+    const int npairs = LANES ? Hq << kp_log2 : Hq * k;
+    // pair t: of head t / k and shard t % k, or by kp
+    auto row_of = [&](int t) { return LANES ? (t >> kp_log2) * k + min(t & (kp - 1), k - 1) : t; };
+    auto is_real = [&](int t) { return t < npairs && (!LANES || (t & (kp - 1)) < k); };
     auto load_pass = [&](int pass) {
         const int t = pass * kPairsPerPass + pair0;
-        return shard_pairs_load(t < npairs ? nsplit : 0, tid & 7, pair_of(min(t, npairs - 1)));
+        return shard_pairs_load(is_real(t) ? nsplit : 0, tid & 7, pair_of(row_of(min(t, npairs - 1))));
     };
     ShardPairs held[kAhead];
+    // A wave's own heads: 8 >> kp_log2 of them per pass, each lane `per` pairs of a pass (1, 2 or 4: blocks of 256 threads
+    // have at most 32 partials per head).  Four pairs are requested ahead: passes x per of them up to 32 heads.
+    const int per_log2 = nsplit > 16 ? 2 : nsplit > 8 ? 1 : 0;
+    const int own_head = lane_id >> (3 + kp_log2), own_shard = (lane_id >> 3) & (kp - 1);
+    const uint32_t own_first = __umul24((uint32_t)min(own_shard, k - 1), (uint32_t)nsplit);
+    float2 own[4];
+    auto load_own = [&](int first) {         // pairs first .. first + 3 of the lane
 #pragma unroll
-    for (int a = 0; a < kAhead; ++a) held[a] = load_pass(a);
-    fetch(i, p.S, true);
-
+        for (int x = 0; x < 4; ++x) {
+            const int pass = (first + x) >> per_log2, sp = (lane_id & 7) + 8 * ((first + x) & ((1 << per_log2) - 1));
+            const int h = h_lo + (pass << (3 - kp_log2)) + own_head;
+            const uint32_t at = __umul24((uint32_t)min(h, Hq - 1), (uint32_t)np) + own_first + (uint32_t)min(sp, nsplit - 1);
+            const float2 v = reinterpret_cast<const float2 *>(ml)[at];
+            const bool real = h < h_hi && own_shard < k && sp < nsplit;
+            own[x].x = real ? v.x : -INFINITY;
+            own[x].y = real ? v.y : 0.0f;
+        }
+    };
+    if constexpr (kOwnHeads) {
+        load_own(0);
+    } else {
+#pragma unroll
+        for (int a = 0; a < kAhead; ++a) held[a] = load_pass(a);
+    }
     const int e = __builtin_amdgcn_readlane(sel_of_lane, j);
     const int n = __builtin_amdgcn_readlane(n_of_lane, e);
     if (i0 >= n) return;     // block-uniform: no entries in this block's slots
+    fetch(i, n, true);
 
-    const int passes = (npairs + kPairsPerPass - 1) / kPairsPerPass;
+    if constexpr (kOwnHeads) {
+        const int pairs_own = __builtin_amdgcn_readfirstlane(((h_hi - h_lo + (8 >> kp_log2) - 1) >> (3 - kp_log2)) << per_log2);
+        auto weigh = [&](int pass, float M, float Z) {
+            const HeadWeights hw = head_weights_of_groups(kp, M, Z, gate_of_thread, p.c.combine);
+            const int h = h_lo + (pass << (3 - kp_log2)) + own_head;
+            if (own_shard == j && h < h_hi && (lane_id & 7) == 0) pc_s[h] = make_float2(hw.shift, hw.coef);
+        };
+        // (shard_stats8 over the `PER` pairs a lane has of a shard)
+        auto pass_of = [&](auto per, int at) {
+            constexpr int PER = decltype(per)::value;
+#pragma unroll
+            for (int x = 0; x < 4; x += PER) {
+                if (at + x >= pairs_own) break;          // wave-uniform
+                float M = -INFINITY, Z = 0.0f;
+#pragma unroll
+                for (int u = 0; u < PER; ++u) M = own[x + u].y > 0.0f ? fmaxf(M, own[x + u].x) : M;
+                M = bits_max<0, 3>(M);
+#pragma unroll
+                for (int u = 0; u < PER; ++u) Z += own[x + u].y > 0.0f ? own[x + u].y * __expf(own[x + u].x - M) : 0.0f;
+                weigh((at + x) >> per_log2, M, bits_sum<0, 3>(Z));
+            }
+        };
+        for (int at = 0; at < pairs_own; at += 4) {      // wave-uniform
+            if (at > 0) load_own(at);
+            if (per_log2 == 0) pass_of(std::integral_constant<int, 1>{}, at);
+            else if (per_log2 == 1) pass_of(std::integral_constant<int, 2>{}, at);
+            else pass_of(std::integral_constant<int, 4>{}, at);
+        }
+        wave_lds_order();
+    }
+    const int passes = kOwnHeads ? 0 : (npairs + kPairsPerPass - 1) / kPairsPerPass;
     for (int pass0 = 0; pass0 < passes; pass0 += kAhead) {
 #pragma unroll
         for (int a = 0; a < kAhead; ++a) {
             const int pass = pass0 + a;
             if (pass < passes) {                 // block-uniform
                 const int t = pass * kPairsPerPass + pair0;
-                const bool real = t < npairs;
+                const bool real = is_real(t);
                 float M, Z;
                 if (MODE == kPostMany || pass == 0)
-                    shard_stats8(held[a], real ? nsplit : 0, tid & 7, pair_of(t), &M, &Z);
+                    shard_stats8(held[a], real ? nsplit : 0, tid & 7, pair_of(row_of(t)), &M, &Z);
                 else
-                    shard_stats8(real ? nsplit : 0, tid & 7, pair_of(t), &M, &Z);
-                if (real && (tid & 7) == 0) {
+                    shard_stats8(real ? nsplit : 0, tid & 7, pair_of(row_of(t)), &M, &Z);
+                if constexpr (LANES) {
+                    const HeadWeights hw = head_weights_of_groups(kp, M, Z, gate_of_thread, p.c.combine);
+                    if (real && (tid & 7) == 0 && (t & (kp - 1)) == j) pc_s[t >> kp_log2] = make_float2(hw.shift, hw.coef);
+                } else if (real && (tid & 7) == 0) {
                     Mj_s[t] = M;
                     Zj_s[t] = Z;
                 }
@@ -488,24 +558,28 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     const bool updates = SPT == 4 || hg == 0;
     int ui = i0 + uslot;
     float u_old = (ui < n && updates) ? urow[ui] : 0.0f;
-    if (p.c.gates != nullptr && tid < k) g_s[tid] = gate_of_thread;
-    __syncthreads();
-    // (shift, coef) of every (head, shard) pair: an aligned group of kp lanes per head
-    const int kp = pow2_at_least(k);
-    for (int h0 = 0; h0 < Hq; h0 += THREADS / kp) {
-        const int h = h0 + tid / kp, jj = tid & (kp - 1);
-        // a wave holds 64 / kp whole heads: one whose first head is past the end has nothing to
-        // do and leaves the SIMD to the waves that have (wave-uniform branch)
-        if (__builtin_amdgcn_readfirstlane(h) >= Hq) break;
-        const bool mine = h < Hq && jj < k;
-        const HeadWeights hw = head_weights(kp, mine ? Mj_s[h * k + jj] : 0.0f, mine ? Zj_s[h * k + jj] : 0.0f,
-                                            (mine && p.c.gates) ? g_s[jj] : 1.0f, p.c.combine);
-        if (mine) {
-            shift_s[h * k + jj] = hw.shift;
-            coef_s[h * k + jj] = hw.coef;
+    if constexpr (LANES) {
+        if constexpr (!kOwnHeads) __syncthreads();
+    } else {
+        if (p.c.gates != nullptr && tid < k) g_s[tid] = gate_of_thread;
+        __syncthreads();
+        // (shift, coef) of every (head, shard) pair: an aligned group of kp lanes per head
+        for (int h0 = 0; h0 < Hq; h0 += THREADS / kp) {
+            const int h = h0 + tid / kp, jj = tid & (kp - 1);
+            // a wave holds 64 / kp whole heads: one whose first head is past the end has nothing to
+            // do and leaves the SIMD to the waves that have (wave-uniform branch)
+            if (__builtin_amdgcn_readfirstlane(h) >= Hq) break;
+            const bool mine = h < Hq && jj < k;
+            const HeadWeights hw = head_weights(kp, mine ? Mj_s[h * k + jj] : 0.0f, mine ? Zj_s[h * k + jj] : 0.0f,
+                                                (mine && p.c.gates) ? g_s[jj] : 1.0f, p.c.combine);
+            if (mine) {
+                shift_s[h * k + jj] = hw.shift;
+                coef_s[h * k + jj] = hw.coef;
+            }
         }
+        __syncthreads();
     }
-    __syncthreads();
+    auto weight_of = [&](int h) { return LANES ? pc_s[h] : make_float2(shift_s[h * k + j], coef_s[h * k + j]); };
     for (int it = 0; it < ntiles; ++it) {
         const bool live = i < n;
         float a[SPT];
@@ -518,10 +592,10 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
 #pragma unroll
         for (int t = 0; t < kPostPrefetchHeads; ++t) {
             const int h = min(h_lo + t, Hq - 1);
-            const float coef = coef_s[h * k + j], shift = shift_s[h * k + j];
+            const float2 w = weight_of(h);
 #pragma unroll
             for (int x = 0; x < SPT; ++x) {
-                const float with = fmaf(coef, __expf(sc[t][x] - shift), a[x]);
+                const float with = fmaf(w.y, __expf(sc[t][x] - w.x), a[x]);
                 a[x] = t < held_heads ? with : a[x];
             }
         }
@@ -536,9 +610,9 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
                 for (int t = 0; t < kPostPrefetchHeads; ++t) {
                     const int h = hb + t;
                     if (h < h_hi) {
+                        const float2 w = weight_of(h);
 #pragma unroll
-                        for (int x = 0; x < SPT; ++x)
-                            a[x] = fmaf(coef_s[h * k + j], __expf(more[t][x] - shift_s[h * k + j]), a[x]);
+                        for (int x = 0; x < SPT; ++x) a[x] = fmaf(w.y, __expf(more[t][x] - w.x), a[x]);
                     }
                 }
             }
@@ -758,20 +832,26 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     if (blocks > 0x7fffffff) return PIKV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks);
     const bool f32 = desc->dtype == PIKV_F32;
-    const size_t lds = post_smem_bytes(threads, np, desc->Hq * k, wide ? 4 : 1);
+    const size_t lds = post_smem_bytes(threads, np, desc->Hq * k, wide ? 4 : 1, c.decoder_bytes);
     const bool multi = tpb > 1;
     // (several tiles of four slots per thread: blocks of 256 threads only, see `wide`)
-#define PIKV_LAUNCH_POST_MODE(T, TH, MODE)                                                               \
-    do {                                                                                                 \
-        constexpr int kWide = TH == 256 || MODE == kPostSingle ? 4 : 1;                                  \
-        if (wide) hipLaunchKernelGGL((step_post<T, TH, MODE, kWide>), grid, dim3(TH), lds, st, pp);      \
-        else hipLaunchKernelGGL((step_post<T, TH, MODE, 1>), grid, dim3(TH), lds, st, pp);               \
+    const bool lanes = k <= kWaveShards;
+#define PIKV_LAUNCH_POST_MODE(T, TH, MODE, LANES)                                                               \
+    do {                                                                                                        \
+        constexpr int kWide = TH == 256 || MODE == kPostSingle ? 4 : 1;                                         \
+        if (wide) hipLaunchKernelGGL((step_post<T, TH, MODE, kWide, LANES>), grid, dim3(TH), lds, st, pp);      \
+        else hipLaunchKernelGGL((step_post<T, TH, MODE, 1, LANES>), grid, dim3(TH), lds, st, pp);               \
     } while (0)
-#define PIKV_LAUNCH_POST(T, TH)                                                                          \
-    do {                                                                                                 \
-        if (many) PIKV_LAUNCH_POST_MODE(T, TH, kPostMany);                                               \
-        else if (multi) PIKV_LAUNCH_POST_MODE(T, TH, kPostMulti);                                        \
-        else PIKV_LAUNCH_POST_MODE(T, TH, kPostSingle);                                                  \
+#define PIKV_LAUNCH_POST_LANES(T, TH, LANES)                                                                    \
+    do {                                                                                                        \
+        if (many && !(LANES && TH == 256)) PIKV_LAUNCH_POST_MODE(T, TH, (LANES && TH == 256 ? kPostSingle : kPostMany), LANES); \
+        else if (multi) PIKV_LAUNCH_POST_MODE(T, TH, kPostMulti, LANES);                                        \
+        else PIKV_LAUNCH_POST_MODE(T, TH, kPostSingle, LANES);                                                  \
+    } while (0)
+#define PIKV_LAUNCH_POST(T, TH)                                                                                 \
+    do {                                                                                                        \
+        if (lanes) PIKV_LAUNCH_POST_LANES(T, TH, true);                                                         \
+        else PIKV_LAUNCH_POST_LANES(T, TH, false);                                                              \
     } while (0)
     if (threads == 256) {
         if (f32) PIKV_LAUNCH_POST(float, 256);
@@ -781,6 +861,7 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
         else PIKV_LAUNCH_POST(bf16, 1024);
     }
 #undef PIKV_LAUNCH_POST
+#undef PIKV_LAUNCH_POST_LANES
 #undef PIKV_LAUNCH_POST_MODE
     return launch_status();
 }

@@ -1727,3 +1727,50 @@ def test_stream_read_probe_folds_every_word_once():
             for pt in range(parts):
                 want = np.bitwise_xor.reduce(host[i, pt * span:(pt + 1) * span]) if pt * span < words else 0
                 assert got[i, pt] == want, (n, words, parts, i, pt)
+
+
+@pytest.mark.parametrize("spec,splits,shift", [
+    (dict(B=2, Hq=7, Hkv=7, D=64, E=8, S=288, k=1, dtype="f32"), (1, 9, 32), 0),
+    (dict(B=1, Hq=6, Hkv=2, D=128, E=8, S=288, k=3, dtype="bf16"), (1, 8, 9), 0),
+    (dict(B=2, Hq=33, Hkv=11, D=16, E=8, S=160, k=5, dtype="f32"), (1, 5, 7), 0),
+    (dict(B=1, Hq=40, Hkv=8, D=64, E=9, S=160, k=8, dtype="bf16"), (2, 4, 5), 0),
+    (dict(B=1, Hq=5, Hkv=5, D=32, E=12, S=160, k=9, dtype="f32"), (1, 3, 5), 0),
+    (dict(B=2, Hq=3, Hkv=3, D=128, E=4, S=1200, k=2, dtype="f32"), (33, 40), 0),
+    (dict(B=2, Hq=8, Hkv=2, D=128, E=8, S=160, k=4, dtype="bf16", rank=32), (1, 3, 9), 0),
+    (dict(B=2, Hq=8, Hkv=2, D=128, E=8, S=160, k=4, dtype="bf16", rank=64), (2,), 3),
+    (dict(B=1, Hq=4, Hkv=4, D=32, E=8, S=160, k=2, dtype="bf16", rank=16), (2,), 0),
+    (dict(B=1, Hq=4, Hkv=4, D=128, E=8, S=160, k=2, dtype="f32", rank=64), (2,), 0),
+    (dict(B=1, Hq=4, Hkv=4, D=128, E=8, S=160, k=2, dtype="f32", rank=32), (2, 17), 1),
+], ids=["k1", "k3", "k5", "k8", "k9", "long", "r32", "r64_shifted", "r16", "f32_r64", "f32_r32_shifted"])
+def test_merge_of_every_count_of_shards_and_partials(spec, splits, shift):
+    """The merge by single waves (up to eight shards) and by the block, one to four pairs a lane and more, decoders in LDS,
+    too large for it and not aligned for it; y and utilities against the oracle, the fused step bit for bit
+    against the separate calls."""
+    from gpu_harness import dev_storage
+    g = wl.Geometry(**spec)
+    case = wl.make_host_case(g, seed=31, n_valid="ragged", utility0="exp", w_sigma=0.05)
+    case.n_valid[0, :2] = [0, g.S]
+    ensure_route_margin(case, g.k)
+    for n in splits:
+        pk.pikv_set_attn_split(n)
+        try:
+            dA, dB = DeviceCase(case), DeviceCase(case)
+            if shift:                # the decoder some values into its buffer
+                for d in (dA, dB):
+                    d.U_V = torch.cat([d.U_V.new_zeros(shift), d.U_V.flatten()])[shift:].view(d.U_V.shape)
+                    assert d.U_V.data_ptr() % 16
+            idx, gates = (lambda d: (d.route(), (t2n(d.topk), t2n(d.gates)))[1])(dB)
+            u_ref = case.utility.copy()
+            ref = oracle_step(case, idx, gates, orc.COMBINE_LSE, utility=u_ref, decay=0.9)
+            pk.pikv_decode_step(dA.desc, dA.q, dA.W_r, dA.bias, None, None, dA.K_tab, dA.V_tab, dA.U_K, dA.U_V, dA.n_valid,
+                                dA.utility, g.k, pk.COMBINE_LSE, 0.0, 0.9, dA.topk, dA.gates, None, None, dA.y, dA.row_max,
+                                dA.row_norm, dA.scores, dA.slot_coef, dA.workspace)
+            dB.attend()
+            dB.update_utility(0.9)
+        finally:
+            pk.pikv_set_attn_split(0)
+        ok, emax, l2 = y_tolerance_ok(t2n(dB.y), ref["y"], g.dtype)
+        assert ok, (n, emax, l2)
+        assert_utility_close(t2n(dB.utility), u_ref)
+        for name in ("topk", "gates", "utility", "y", "row_max", "row_norm", "slot_coef"):
+            np.testing.assert_array_equal(t2n(getattr(dA, name)), t2n(getattr(dB, name)), err_msg="%s, %d splits" % (name, n))
