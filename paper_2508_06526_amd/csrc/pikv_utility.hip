@@ -4,8 +4,9 @@
 // The attention pass left the raw scores s_{h,i} of every visited entry and, per (query
 // head, selected shard), a pair (shift, coef) with p_{h,i} = coef * exp(s_{h,i} - shift).
 // This pass turns them into probabilities and sums them over the heads that read the
-// entry, in fixed head order (no atomics, bit-reproducible).  Grid: (sequence, expert,
-// slot tile); blocks of shards nobody selected exit at once and leave u untouched.
+// entry, in fixed head order (no atomics, bit-reproducible).  Grid: (sequence, selected shard,
+// slot tile) under per-token routing, (sequence, expert, slot tile) where the heads are routed one by one;
+// blocks of shards nobody selected exit at once and leave u untouched.
 //
 // The tracked form also keeps the per-entry bookkeeping of Table 3's LRU / LRU+ rows in the
 // same pass: an entry whose attention mass of this step exceeds a threshold has its
@@ -17,15 +18,20 @@
 namespace pikv {
 namespace {
 
+// Thread = (SPT slots, quarter of the heads): 64 * SPT slots per block, a wave per quarter, kUtilBatch heads' scores
+// of each slot in flight per thread, the quarters' sums joined in LDS as (g0 + g1) + (g2 + g3).  Two trips to memory:
+// selections and counts, then pairs, scores and old utilities together.  Bound by those trips, or by the score bytes once
+// there are many.  With the counts, the selections, the pairs and each group's scores requested one after the other - up to
+// seven trips - kernel trace: 10 sequences x 64 heads x 2 of 6 shards of 2560 slots 9.4 -> 4.8 us, 4 x 16 x 3 of 6
+// ragged ones of 1501 4.8 -> 3.2, 1 x 256 x 4 of 8192 9.6 -> 8.1; heads routed one by one: 23 x 128 x 2 of 32 of 1536
+// 27.2 -> 16.0, 1 x 4 x 2 of 4 of 256 3.1 -> 3.0, 24 x 32 x 2 of 16 of 2047 (unaligned rows) 10.1 -> 10.2.
 constexpr int kUtilThreads = 256;
-// Two block shapes.  One slot per thread (256 slots per block, a wave reads 256 contiguous
-// bytes, every thread walks through all the heads): few heads per entry.  Or one (slot, quarter
-// of the heads) per thread (64 slots per block, one wave per quarter): with hundreds of query
-// rows per entry - a multi-query step - the walk through the heads is four times shorter, four
-// times as many blocks share the score bytes, and each thread keeps 8 loads in flight.  The
-// heads are summed in the same four ascending groups joined as (g0 + g1) + (g2 + g3) either way.
-constexpr int kUtilManyHeads = 128;     // from this many query rows per sequence on: the second shape
-constexpr int kUtilBatch = 8;           // loads in flight per thread in the second shape
+constexpr int kUtilBatch = 8;           // heads whose scores are in flight per thread ...
+constexpr int kUtilFewBatch = 2;        // ... of up to kUtilFewHeads in all
+constexpr int kUtilFewHeads = 4 * kUtilFewBatch;
+// Four slots per thread once one slot per thread makes more blocks than this (24 sequences x 32 heads x 2 of 16 shards of 2048
+// slots, routed head by head, 17.4 us with one; the form before 13.6; now 9.4).
+constexpr int kUtilManyBlocks = 1024;
 
 struct UtilParams {
     const float *scores;
@@ -33,7 +39,7 @@ struct UtilParams {
     const int32_t *n_valid;
     const int32_t *topk;
     float *utility;      // may be null in the tracked form
-    FastDiv by_tiles, by_E;
+    FastDiv by_tiles, by_shards;     // selected shards of a sequence, or all
     int Hq, E, S, k, rr;
     float decay;
     // access bookkeeping (Table 3 rows LRU / LRU+): an entry whose attention mass of this
@@ -44,111 +50,115 @@ struct UtilParams {
     int now;
 };
 
-template <bool TRACK, bool SPREAD>
+// TOKEN: one routing decision per sequence - every head reads the selected shards.
+// A thread's slots are consecutive (LINE: 16-byte loads of aligned rows) or 64 apart.
+template <bool TRACK, int SPT, bool LINE, bool TOKEN, int BATCH>
 __global__ __launch_bounds__(kUtilThreads) void utility_kernel(UtilParams p) {
-    constexpr int kUtilTile = SPREAD ? kUtilThreads / 4 : kUtilThreads;
-    int tile, e;
-    const int shard = fast_divide(p.by_tiles, blockIdx.x, &tile);
-    const int b = fast_divide(p.by_E, shard, &e);
-    const int n = p.n_valid[(int64_t)b * p.E + e];
-    const int i0 = tile * kUtilTile;
-    if (i0 >= n) return;
-
-    // heads that selected expert e, compacted in ascending head order (fixed summation order)
-    __shared__ int head_off[256];       // offset of the head's score row for this shard
-    __shared__ float head_shift[256];
-    __shared__ float head_coef[256];
-    __shared__ int wave_cnt[kUtilThreads / kWave];
+    constexpr int kSlots = kUtilThreads / 4 * SPT;
     const int tid = threadIdx.x;
-    const int lane = tid & (kWave - 1), wave = tid >> 6;
+    const int lane = tid & (kWave - 1), wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+    int tile, x;
+    const int rest = fast_divide(p.by_tiles, blockIdx.x, &tile);
+    const int b = fast_divide(p.by_shards, rest, &x);
+    const int i0 = tile * kSlots;
 
-    int jj = -1;
-    if (tid < p.Hq) {
-        const int row = b * p.rr + (p.rr == 1 ? 0 : tid);
-        for (int j = 0; j < p.k; ++j)
-            if (p.topk[(int64_t)row * p.k + j] == e) jj = j;
-    }
-    const uint64_t mask = __ballot(jj >= 0);
-    if (lane == 0) wave_cnt[wave] = __popcll(mask);
-    __syncthreads();
-    int before = 0, nact = 0;
-#pragma unroll
-    for (int w = 0; w < kUtilThreads / kWave; ++w) {
-        if (w < wave) before += wave_cnt[w];
-        nact += wave_cnt[w];
-    }
-    if (nact == 0) return;
-    if (jj >= 0) {
-        const int pos = before + __popcll(mask & ((1ull << lane) - 1ull));
-        const int hrow = (b * p.Hq + tid) * p.k + jj;
-        head_off[pos] = hrow;
-        head_shift[pos] = p.slot_coef[(int64_t)hrow * 2 + 0];
-        head_coef[pos] = p.slot_coef[(int64_t)hrow * 2 + 1];
-    }
-    __syncthreads();
+    __shared__ int head_row[TOKEN ? 1 : 256];       // heads that selected the shard, ascending: (sequence, head, selection)
+    __shared__ float2 head_w[256];      // their (shift, coef)
+    __shared__ int wave_cnt[kUtilThreads / kWave];
+    __shared__ float part_s[4][kSlots];
 
-    const int gsize = (nact + 3) / 4;
-    if constexpr (SPREAD) {
-        // thread = (slot, group): wave g walks through group g's heads, kUtilBatch loads at a time
-        // from clamped addresses (no load under a lane-dependent condition), the sums meet in LDS
-        __shared__ float part_s[4][kUtilTile];
-        const int slot = tid & (kUtilTile - 1), g = tid / kUtilTile;
-        const int i = i0 + slot, ic = min(i, n - 1);
-        const int lo = g * gsize, hi = min(nact, lo + gsize);
-        float a = 0.0f;
-        for (int t0 = lo; t0 < hi; t0 += kUtilBatch) {
-            float sc[kUtilBatch];
+    // (one count per lane, the shard's own picked when it is needed: a load that is the same in all lanes is waited
+    // for where it stands)
+    const int n_of_lane = p.n_valid[(int64_t)b * p.E + min(lane, p.E - 1)];
+    int e = x, n, nact = p.Hq;
+    if constexpr (TOKEN) {
+        const int sel = p.topk[(int64_t)b * p.k + min(lane, p.k - 1)];
+        e = __builtin_amdgcn_readlane(sel, x);
+        // (of a shard selected twice the last selection counts)
+        if (e < 0 || e >= p.E || __ballot(sel == e && lane > x && lane < p.k) != 0) return;
+        n = __builtin_amdgcn_readlane(n_of_lane, e);
+        if (i0 >= n) return;
+    } else {
+        constexpr int kSel = 4;          // selections requested at a time
+        const int32_t *row = p.topk + ((int64_t)b * p.rr + min(tid, p.Hq - 1)) * p.k;
+        int jj = -1;
+        for (int j0 = 0; j0 < p.k; j0 += kSel) {
+            int sel[kSel];
 #pragma unroll
-            for (int u = 0; u < kUtilBatch; ++u)
-                sc[u] = p.scores[(int64_t)head_off[min(t0 + u, hi - 1)] * p.S + ic];
-            const int left = __builtin_amdgcn_readfirstlane(hi - t0);   // the group is the wave's
+            for (int t = 0; t < kSel; ++t) sel[t] = row[min(j0 + t, p.k - 1)];
 #pragma unroll
-            for (int u = 0; u < kUtilBatch; ++u) {
-                const int t = min(t0 + u, hi - 1);
-                const float with = fmaf(head_coef[t], __expf(sc[u] - head_shift[t]), a);
-                a = u < left ? with : a;
+            for (int t = 0; t < kSel; ++t) jj = sel[t] == e ? min(j0 + t, p.k - 1) : jj;
+        }
+        n = __builtin_amdgcn_readlane(n_of_lane, e);
+        if (i0 >= n) return;
+        const bool active = tid < p.Hq && jj >= 0;
+        const uint64_t mask = __ballot(active);
+        if (lane == 0) wave_cnt[wave] = __popcll(mask);
+        __syncthreads();
+        int before = 0;
+        nact = 0;
+#pragma unroll
+        for (int w = 0; w < kUtilThreads / kWave; ++w) {
+            if (w < wave) before += wave_cnt[w];
+            nact += wave_cnt[w];
+        }
+        if (nact == 0) return;
+        if (active) head_row[before + __popcll(mask & ((1ull << lane) - 1ull))] = (b * p.Hq + tid) * p.k + jj;
+        __syncthreads();
+    }
+    auto row_of = [&](int t) { return TOKEN ? (b * p.Hq + t) * p.k + x : head_row[t]; };
+
+    // the pairs, the scores, the old utilities: requested together, in this order (loads come back in order)
+    const int64_t pair_at = (int64_t)row_of(min(tid, nact - 1)) * 2;
+    const float shift = p.slot_coef[pair_at], coef = p.slot_coef[pair_at + 1];
+    const int gsize = (nact + 3) / 4, lo = wave * gsize, hi = min(nact, lo + gsize);
+    const int slot = LINE ? lane * SPT : lane;
+    float sc[BATCH][SPT];
+    auto fetch = [&](int t0) {           // (heads past the group's end and slots past the count are masked where they are used)
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const int row = __builtin_amdgcn_readfirstlane(row_of(min(t0 + u, nact - 1)));
+            const float *from = p.scores + (int64_t)row * p.S;
+            if constexpr (LINE) {
+                const float4 v = *reinterpret_cast<const float4 *>(from + min(i0 + slot, p.S - 4));
+                sc[u][0] = v.x, sc[u][1] = v.y, sc[u][2] = v.z, sc[u][3] = v.w;
+            } else {
+#pragma unroll
+                for (int s = 0; s < SPT; ++s) sc[u][s] = from[min(i0 + slot + s * kWave, n - 1)];
             }
         }
-        part_s[g][slot] = a;
-        __syncthreads();
-        if (g != 0 || i >= n) return;
-        const float mass = (part_s[0][slot] + part_s[1][slot]) + (part_s[2][slot] + part_s[3][slot]);
-        const int64_t at = ((int64_t)b * p.E + e) * p.S + i;
-        if (!TRACK || p.utility) p.utility[at] = fmaf(p.decay, p.utility[at], mass);
-        if (TRACK && mass > p.threshold) {
-            p.last_access[at] = p.now;
-            p.freq[at] += 1;
-        }
-        return;
-    }
+    };
+    fetch(lo);
+    // the block's slots are written by the first wave, or a slot by every thread
     const int i = i0 + tid;
-    if (i >= n) return;
-    // the active heads are cut into 4 consecutive groups, each summed in ascending order, the
-    // groups joined as (g0 + g1) + (g2 + g3): the fused step kernel spreads the groups over
-    // threads and must reproduce these bits
-    float part[4];
-#pragma unroll
-    for (int g = 0; g < 4; ++g) {
-        const int lo = g * gsize, hi = min(nact, lo + gsize);
-        float a = 0.0f;
-        int t = lo;
-        for (; t + 4 <= hi; t += 4) {   // four independent loads in flight per thread
-            const float s0 = p.scores[(int64_t)head_off[t + 0] * p.S + i];
-            const float s1 = p.scores[(int64_t)head_off[t + 1] * p.S + i];
-            const float s2 = p.scores[(int64_t)head_off[t + 2] * p.S + i];
-            const float s3 = p.scores[(int64_t)head_off[t + 3] * p.S + i];
-            a = fmaf(head_coef[t + 0], __expf(s0 - head_shift[t + 0]), a);
-            a = fmaf(head_coef[t + 1], __expf(s1 - head_shift[t + 1]), a);
-            a = fmaf(head_coef[t + 2], __expf(s2 - head_shift[t + 2]), a);
-            a = fmaf(head_coef[t + 3], __expf(s3 - head_shift[t + 3]), a);
-        }
-        for (; t < hi; ++t)
-            a = fmaf(head_coef[t], __expf(p.scores[(int64_t)head_off[t] * p.S + i] - head_shift[t]), a);
-        part[g] = a;
-    }
-    const float mass = (part[0] + part[1]) + (part[2] + part[3]);
+    const bool writes = (SPT == 4 || wave == 0) && i < n;
     const int64_t at = ((int64_t)b * p.E + e) * p.S + i;
-    if (!TRACK || p.utility) p.utility[at] = fmaf(p.decay, p.utility[at], mass);
+    const bool scored = !TRACK || p.utility != nullptr;
+    const float old = writes && scored ? p.utility[at] : 0.0f;
+    if (tid < nact) head_w[tid] = make_float2(shift, coef);
+    __syncthreads();
+
+    float a[SPT];
+#pragma unroll
+    for (int s = 0; s < SPT; ++s) a[s] = 0.0f;
+    for (int t0 = lo; t0 < hi; t0 += BATCH) {
+        if (t0 != lo) fetch(t0);
+#pragma unroll
+        for (int u = 0; u < BATCH; ++u) {
+            const float2 w = head_w[min(t0 + u, nact - 1)];
+#pragma unroll
+            for (int s = 0; s < SPT; ++s) {
+                const float with = fmaf(w.y, __expf(sc[u][s] - w.x), a[s]);
+                a[s] = t0 + u < hi ? with : a[s];
+            }
+        }
+    }
+#pragma unroll
+    for (int s = 0; s < SPT; ++s) part_s[wave][slot + (LINE ? s : s * kWave)] = a[s];
+    __syncthreads();
+    if (!writes) return;
+    const float mass = (part_s[0][tid] + part_s[1][tid]) + (part_s[2][tid] + part_s[3][tid]);
+    if (scored) p.utility[at] = fmaf(p.decay, old, mass);
     if (TRACK && mass > p.threshold) {
         p.last_access[at] = p.now;
         p.freq[at] += 1;
@@ -170,24 +180,40 @@ int launch_utility(const pikv_desc *desc, const float *scores, const float *slot
     p.S = desc->S;
     p.k = k;
     p.rr = desc->route_rows_per_seq;
-    const bool spread = desc->Hq >= kUtilManyHeads;
-    const int tile_slots = spread ? kUtilThreads / 4 : kUtilThreads;
-    const int tiles = (desc->S + tile_slots - 1) / tile_slots;
-    p.by_tiles = fast_div(tiles);
-    p.by_E = fast_div(desc->E);
+    const int shards = p.rr == 1 ? k : desc->E;
+    auto blocks_of = [&](int slots) { return (int64_t)desc->B * shards * ((desc->S + slots - 1) / slots); };
+    const bool wide = blocks_of(kUtilThreads / 4) > kUtilManyBlocks;
+    const bool line = desc->S % 4 == 0 && reinterpret_cast<uintptr_t>(scores) % 16 == 0;
+    const int tile_slots = wide ? kUtilThreads : kUtilThreads / 4;
+    p.by_tiles = fast_div((desc->S + tile_slots - 1) / tile_slots);
+    p.by_shards = fast_div(shards);
     p.decay = decay;
     p.last_access = last_access;
     p.freq = freq;
     p.threshold = threshold;
     p.now = now;
-    const int64_t blocks = (int64_t)desc->B * desc->E * tiles;
+    const int64_t blocks = blocks_of(tile_slots);
     if (blocks > 0x7fffffff) return PIKV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks), block(kUtilThreads);
     hipStream_t st = as_stream(stream);
-    if (track && spread) hipLaunchKernelGGL((utility_kernel<true, true>), grid, block, 0, st, p);
-    else if (track) hipLaunchKernelGGL((utility_kernel<true, false>), grid, block, 0, st, p);
-    else if (spread) hipLaunchKernelGGL((utility_kernel<false, true>), grid, block, 0, st, p);
-    else hipLaunchKernelGGL((utility_kernel<false, false>), grid, block, 0, st, p);
+    auto launch = [&](auto tracks, auto spt, auto lines, auto batch) {
+        constexpr bool TRACK = decltype(tracks)::value, LINE = decltype(lines)::value;
+        constexpr int SPT = decltype(spt)::value, BATCH = decltype(batch)::value;
+        if (p.rr == 1) hipLaunchKernelGGL((utility_kernel<TRACK, SPT, LINE, true, BATCH>), grid, block, 0, st, p);
+        else hipLaunchKernelGGL((utility_kernel<TRACK, SPT, LINE, false, BATCH>), grid, block, 0, st, p);
+    };
+    auto launch_wide = [&](auto tracks, auto batch) {
+        const std::integral_constant<int, 4> four{};
+        if (wide && line) launch(tracks, four, std::true_type{}, batch);
+        else if (wide) launch(tracks, four, std::false_type{}, batch);
+        else launch(tracks, std::integral_constant<int, 1>{}, std::false_type{}, batch);
+    };
+    auto launch_batch = [&](auto tracks) {
+        if (desc->Hq <= kUtilFewHeads) launch_wide(tracks, std::integral_constant<int, kUtilFewBatch>{});
+        else launch_wide(tracks, std::integral_constant<int, kUtilBatch>{});
+    };
+    if (track) launch_batch(std::true_type{});
+    else launch_batch(std::false_type{});
     return launch_status();
 }
 

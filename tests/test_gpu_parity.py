@@ -1774,3 +1774,44 @@ def test_merge_of_every_count_of_shards_and_partials(spec, splits, shift):
         assert_utility_close(t2n(dB.utility), u_ref)
         for name in ("topk", "gates", "utility", "y", "row_max", "row_norm", "slot_coef"):
             np.testing.assert_array_equal(t2n(getattr(dA, name)), t2n(getattr(dB, name)), err_msg="%s, %d splits" % (name, n))
+
+
+@pytest.mark.parametrize("spec", [
+    dict(B=1, Hq=3, Hkv=3, D=16, E=4, S=63, k=2, dtype="f32", per_head_routing=True),       # fewer heads than quarters
+    dict(B=2, Hq=9, Hkv=9, D=16, E=8, S=65, k=5, dtype="f32", per_head_routing=True),
+    dict(B=6, Hq=9, Hkv=9, D=16, E=8, S=2051, k=3, dtype="bf16", per_head_routing=True),     # four slots, 64 apart
+    dict(B=6, Hq=5, Hkv=5, D=16, E=8, S=2052, k=3, dtype="bf16", per_head_routing=True),     # four slots in a line
+    dict(B=1, Hq=70, Hkv=10, D=16, E=6, S=300, k=1, dtype="f32"),                            # several batches of heads
+    dict(B=12, Hq=8, Hkv=8, D=16, E=4, S=3001, k=2, dtype="bf16"),
+    dict(B=12, Hq=40, Hkv=8, D=16, E=4, S=3004, k=2, dtype="bf16"),
+], ids=["ph3", "ph9", "ph_apart", "ph_line", "heads70", "apart", "line"])
+def test_utility_update_of_every_form(spec):
+    """Per-token and head-by-head selections, one slot per thread and four, aligned rows and others, with and without the access
+    bookkeeping: utilities against the oracle, slots past the count and shards nobody selected untouched."""
+    g = wl.Geometry(**spec)
+    case = wl.make_host_case(g, seed=8, n_valid="ragged", utility0="exp", w_sigma=0.4)
+    case.n_valid[0, :2] = [1, g.S]
+    ensure_route_margin(case, g.k)
+    dc = DeviceCase(case)
+    dc.route()
+    dc.attend()
+    u_ref = case.utility.copy()
+    ref = oracle_step(case, t2n(dc.topk), t2n(dc.gates), orc.COMBINE_LSE, utility=u_ref, decay=0.9)
+    assert y_tolerance_ok(t2n(dc.y), ref["y"], g.dtype)[0]
+    before = dc.utility.clone()
+    dc.update_utility(0.9)
+    got = t2n(dc.utility)
+    assert_utility_close(got, u_ref)
+    np.testing.assert_array_equal(got[u_ref == case.utility], case.utility[u_ref == case.utility])
+    last, freq = (torch.zeros((g.B, g.E, g.S), device=DEV, dtype=torch.int32) for _ in range(2))
+    threshold = 2.0 / g.S
+    pk.pikv_update_utility_tracked(dc.desc, dc.scores, dc.slot_coef, dc.n_valid, dc.topk, g.k, 0.9, before, threshold, 7, last, freq)
+    np.testing.assert_array_equal(t2n(before), got)
+    mass = u_ref - 0.9 * case.utility * (u_ref != case.utility)      # only clear cases: the sum is rounded differently here
+    touched = u_ref != case.utility
+    assert (t2n(freq)[touched & (mass > 1.01 * threshold)] == 1).all()
+    assert (t2n(freq)[~touched | (mass < 0.99 * threshold)] == 0).all()
+    np.testing.assert_array_equal(t2n(last), 7 * t2n(freq))
+    only = (torch.zeros_like(last), torch.zeros_like(freq))
+    pk.pikv_update_utility_tracked(dc.desc, dc.scores, dc.slot_coef, dc.n_valid, dc.topk, g.k, 0.9, None, threshold, 7, *only)
+    np.testing.assert_array_equal(t2n(only[1]), t2n(freq))
