@@ -1,7 +1,7 @@
 """MI355X (gfx950) implementation of PiKV's routed sharded-KV decode path.
 
 The work is done by hand-written HIP kernels in ``libpikv.so`` behind the C ABI declared
-in ``include/pikv.h``; this package is the thin ctypes binding (argument marshalling only).
+in ``include/pikv.h``; this package is the thin binding (argument marshalling only).
 There is no CPU or eager fallback: if the library is missing, calls raise.
 """
 from .binding import (  # noqa: F401

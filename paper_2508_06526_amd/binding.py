@@ -1,16 +1,23 @@
-"""ctypes binding of libpikv.so: same names and argument order as include/pikv.h.
+"""Binding of libpikv.so: same names and argument order as include/pikv.h.
 
 Every function takes torch tensors that already live in device memory (or None for
 optional pointers), passes their addresses and the current HIP stream through the C ABI,
 and returns nothing but the status check.  No arithmetic happens here.
+
+The calls of a step are made by the extension _pikv_native (csrc/pikv_binding.cpp): eager passes over small caches are bound
+by their calls, and ctypes with its attribute lookups took 4 - 5 us of each.  Arguments that are not of the ordinary kind -
+tensor subclasses, numpy numbers, what has to be refused - come back from it as None with nothing launched and take the
+ctypes path below.
 """
 from __future__ import annotations
 
 import ctypes as C
+import importlib.util
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libpikv.so")
+_NATIVE_PATH = os.path.join(_HERE, "_pikv_native.so")
 
 F32, BF16 = 0, 1
 COMBINE_LSE, COMBINE_LOCAL = 0, 1
@@ -45,6 +52,7 @@ class PikvDesc(C.Structure):
 
 
 _lib = None
+_native = None
 
 
 def library_path() -> str:
@@ -53,7 +61,7 @@ def library_path() -> str:
 
 def load_library():
     """dlopen libpikv.so (built by ``python -m paper_2508_06526_amd.build``).  Raises if absent."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -112,7 +120,14 @@ def load_library():
     lib.pikv_set_attn_split.restype = None
     lib.pikv_version.argtypes = []
     lib.pikv_version.restype = C.c_int
-    _lib = lib
+    if not os.path.exists(_NATIVE_PATH):
+        raise OSError("_pikv_native.so is not built: run `python -m paper_2508_06526_amd.build`")
+    spec = importlib.util.spec_from_file_location("_pikv_native", _NATIVE_PATH)
+    native = importlib.util.module_from_spec(spec)
+    spec.loader.exec_module(native)
+    native.setup(PikvDesc, PikvPolicyArgs, PikvRouterFeedback,
+                 {name: C.cast(getattr(lib, name), C.c_void_p).value for name in EXPORTS})
+    _lib, _native = lib, native
     return lib
 
 
@@ -125,9 +140,13 @@ def _dtype_code(t) -> int:
     raise TypeError("storage dtype must be float32 or bfloat16, got %s" % t.dtype)
 
 
-# An eager pass over a small cache is bound by what happens here, once per pointer: addresses and
-# streams go to ctypes as plain integers (its argument types convert them), without a c_void_p or
-# a torch Stream object in between.
+def _calls():
+    """The extension that makes the calls; loads the library if nothing has."""
+    if _native is None:
+        load_library()
+    return _native
+
+
 def _p(t):
     """Device address of a tensor (None -> NULL)."""
     if t is None:
@@ -155,6 +174,11 @@ def _stream(stream):
         except AttributeError:
             _current_stream = lambda: torch.cuda.current_stream().cuda_stream
     return _current_stream()
+
+
+def _raw(stream):
+    """A stream as the extension takes it: None (torch's current one) or an integer."""
+    return None if stream is None else _stream(stream)
 
 
 def _check(status, where):
@@ -210,9 +234,12 @@ def pikv_set_profile_events(start, stop) -> None:
 
 
 def pikv_route(x, W_r, bias, rows, d_r, E, k, topk_idx, gates, probs=None, stream=None):
-    st = load_library().pikv_route(_p(x), _p(W_r), _p(bias), rows, d_r, E, k, _dtype_code(x),
-                                   _p(topk_idx), _p(gates), _p(probs), _stream(stream))
-    _check(st, "pikv_route")
+    st = _calls().pikv_route(x, W_r, bias, rows, d_r, E, k, topk_idx, gates, probs, _raw(stream))
+    if st is None:
+        st = load_library().pikv_route(_p(x), _p(W_r), _p(bias), rows, d_r, E, k, _dtype_code(x),
+                                       _p(topk_idx), _p(gates), _p(probs), _stream(stream))
+    if st != 0:
+        _check(st, "pikv_route")
 
 
 def pikv_attn_workspace_bytes(desc: PikvDesc, k: int) -> int:
@@ -221,12 +248,16 @@ def pikv_attn_workspace_bytes(desc: PikvDesc, k: int) -> int:
 
 def pikv_sharded_attn(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates, k, combine,
                       scale, y, row_max, row_norm, scores, slot_coef, workspace, stream=None):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = load_library().pikv_sharded_attn(
-        C.byref(desc), _p(q), _p(K_shards), _p(V_shards), _p(U_K), _p(U_V), _p(n_valid),
-        _p(topk_idx), _p(gates), k, combine, float(scale), _p(y), _p(row_max), _p(row_norm),
-        _p(scores), _p(slot_coef), _p(workspace), ws_bytes, _stream(stream))
-    _check(st, "pikv_sharded_attn")
+    st = _calls().pikv_sharded_attn(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates, k, combine, scale, y,
+                                    row_max, row_norm, scores, slot_coef, workspace, _raw(stream))
+    if st is None:
+        ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+        st = load_library().pikv_sharded_attn(
+            C.byref(desc), _p(q), _p(K_shards), _p(V_shards), _p(U_K), _p(U_V), _p(n_valid),
+            _p(topk_idx), _p(gates), k, combine, float(scale), _p(y), _p(row_max), _p(row_norm),
+            _p(scores), _p(slot_coef), _p(workspace), ws_bytes, _stream(stream))
+    if st != 0:
+        _check(st, "pikv_sharded_attn")
 
 
 NOALLOC_SCRATCH_BYTES = 4 << 20
@@ -234,46 +265,66 @@ NOALLOC_SCRATCH_BYTES = 4 << 20
 
 def pikv_sharded_attn_noalloc(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates, k, combine,
                               scale, y, row_max, row_norm, scores, slot_coef, stream=None):
-    st = load_library().pikv_sharded_attn_noalloc(
-        C.byref(desc), _p(q), _p(K_shards), _p(V_shards), _p(U_K), _p(U_V), _p(n_valid),
-        _p(topk_idx), _p(gates), k, combine, float(scale), _p(y), _p(row_max), _p(row_norm),
-        _p(scores), _p(slot_coef), _stream(stream))
-    _check(st, "pikv_sharded_attn_noalloc")
+    st = _calls().pikv_sharded_attn_noalloc(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates, k, combine, scale,
+                                            y, row_max, row_norm, scores, slot_coef, _raw(stream))
+    if st is None:
+        st = load_library().pikv_sharded_attn_noalloc(
+            C.byref(desc), _p(q), _p(K_shards), _p(V_shards), _p(U_K), _p(U_V), _p(n_valid),
+            _p(topk_idx), _p(gates), k, combine, float(scale), _p(y), _p(row_max), _p(row_norm),
+            _p(scores), _p(slot_coef), _stream(stream))
+    if st != 0:
+        _check(st, "pikv_sharded_attn_noalloc")
 
 
 def pikv_update_utility(desc, scores, slot_coef, n_valid, topk_idx, k, decay, utility, stream=None):
-    st = load_library().pikv_update_utility(C.byref(desc), _p(scores), _p(slot_coef), _p(n_valid),
-                                            _p(topk_idx), k, float(decay), _p(utility),
-                                            _stream(stream))
-    _check(st, "pikv_update_utility")
+    st = _calls().pikv_update_utility(desc, scores, slot_coef, n_valid, topk_idx, k, decay, utility, _raw(stream))
+    if st is None:
+        st = load_library().pikv_update_utility(C.byref(desc), _p(scores), _p(slot_coef), _p(n_valid),
+                                                _p(topk_idx), k, float(decay), _p(utility),
+                                                _stream(stream))
+    if st != 0:
+        _check(st, "pikv_update_utility")
 
 
 def pikv_evict(desc, utility, n_valid, capacity, sel_idx, sel_k, evicted_idx, evicted_cnt,
                max_evict, compact, K_shards, V_shards, stream=None):
-    st = load_library().pikv_evict(C.byref(desc), _p(utility), _p(n_valid), capacity, _p(sel_idx),
-                                   sel_k, _p(evicted_idx), _p(evicted_cnt), max_evict,
-                                   1 if compact else 0, _p(K_shards), _p(V_shards), _stream(stream))
-    _check(st, "pikv_evict")
+    st = _calls().pikv_evict(desc, utility, n_valid, capacity, sel_idx, sel_k, evicted_idx, evicted_cnt, max_evict,
+                             1 if compact else 0, K_shards, V_shards, _raw(stream))
+    if st is None:
+        st = load_library().pikv_evict(C.byref(desc), _p(utility), _p(n_valid), capacity, _p(sel_idx),
+                                       sel_k, _p(evicted_idx), _p(evicted_cnt), max_evict,
+                                       1 if compact else 0, _p(K_shards), _p(V_shards), _stream(stream))
+    if st != 0:
+        _check(st, "pikv_evict")
 
 
 def pikv_append(desc, K_new, V_new, topk_idx, k, reuse_idx, reuse_cnt, max_evict, K_shards,
                 V_shards, utility, n_valid, stream=None):
-    st = load_library().pikv_append(C.byref(desc), _p(K_new), _p(V_new), _p(topk_idx), k,
-                                    _p(reuse_idx), _p(reuse_cnt), max_evict, _p(K_shards),
-                                    _p(V_shards), _p(utility), _p(n_valid), _stream(stream))
-    _check(st, "pikv_append")
+    st = _calls().pikv_append(desc, K_new, V_new, topk_idx, k, reuse_idx, reuse_cnt, max_evict, K_shards, V_shards,
+                              utility, n_valid, _raw(stream))
+    if st is None:
+        st = load_library().pikv_append(C.byref(desc), _p(K_new), _p(V_new), _p(topk_idx), k,
+                                        _p(reuse_idx), _p(reuse_cnt), max_evict, _p(K_shards),
+                                        _p(V_shards), _p(utility), _p(n_valid), _stream(stream))
+    if st != 0:
+        _check(st, "pikv_append")
 
 
 def pikv_decode_step(desc, q, W_r, bias, K_new, V_new, K_shards, V_shards, U_K, U_V, n_valid, utility,
                      k, combine, scale, decay, topk_idx, gates, evicted_idx, evicted_cnt, y, row_max,
                      row_norm, scores, slot_coef, workspace, stream=None):
-    ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
-    st = load_library().pikv_decode_step(
-        C.byref(desc), _p(q), _p(W_r), _p(bias), _p(K_new), _p(V_new), _p(K_shards), _p(V_shards),
-        _p(U_K), _p(U_V), _p(n_valid), _p(utility), k, combine, float(scale), float(decay),
-        _p(topk_idx), _p(gates), _p(evicted_idx), _p(evicted_cnt), _p(y), _p(row_max), _p(row_norm),
-        _p(scores), _p(slot_coef), _p(workspace), ws_bytes, _stream(stream))
-    _check(st, "pikv_decode_step")
+    st = _calls().pikv_decode_step(desc, q, W_r, bias, K_new, V_new, K_shards, V_shards, U_K, U_V, n_valid, utility, k,
+                                   combine, scale, decay, topk_idx, gates, evicted_idx, evicted_cnt, y, row_max,
+                                   row_norm, scores, slot_coef, workspace, _raw(stream))
+    if st is None:
+        ws_bytes = 0 if workspace is None else workspace.numel() * workspace.element_size()
+        st = load_library().pikv_decode_step(
+            C.byref(desc), _p(q), _p(W_r), _p(bias), _p(K_new), _p(V_new), _p(K_shards), _p(V_shards),
+            _p(U_K), _p(U_V), _p(n_valid), _p(utility), k, combine, float(scale), float(decay),
+            _p(topk_idx), _p(gates), _p(evicted_idx), _p(evicted_cnt), _p(y), _p(row_max), _p(row_norm),
+            _p(scores), _p(slot_coef), _p(workspace), ws_bytes, _stream(stream))
+    if st != 0:
+        _check(st, "pikv_decode_step")
 
 
 def pikv_stream_read_probe(bufs, n, bytes_each, parts, out, stream=None):
@@ -282,47 +333,67 @@ def pikv_stream_read_probe(bufs, n, bytes_each, parts, out, stream=None):
 
 
 def pikv_router_penalty(mode, topk_idx, rows, k, E, load, miss, coef, bias, stream=None):
-    st = load_library().pikv_router_penalty(mode, _p(topk_idx), rows, k, E, _p(load), _p(miss),
-                                            float(coef), _p(bias), _stream(stream))
-    _check(st, "pikv_router_penalty")
+    st = _calls().pikv_router_penalty(mode, topk_idx, rows, k, E, load, miss, coef, bias, _raw(stream))
+    if st is None:
+        st = load_library().pikv_router_penalty(mode, _p(topk_idx), rows, k, E, _p(load), _p(miss),
+                                                float(coef), _p(bias), _stream(stream))
+    if st != 0:
+        _check(st, "pikv_router_penalty")
 
 
 def pikv_compress(desc, K_full, Wenc_K, K_codes, V_full=None, Wenc_V=None, V_codes=None, stream=None):
-    st = load_library().pikv_compress(C.byref(desc), _p(K_full), _p(Wenc_K), _p(K_codes), _p(V_full),
-                                      _p(Wenc_V), _p(V_codes), _stream(stream))
-    _check(st, "pikv_compress")
+    st = _calls().pikv_compress(desc, K_full, Wenc_K, K_codes, V_full, Wenc_V, V_codes, _raw(stream))
+    if st is None:
+        st = load_library().pikv_compress(C.byref(desc), _p(K_full), _p(Wenc_K), _p(K_codes), _p(V_full),
+                                          _p(Wenc_V), _p(V_codes), _stream(stream))
+    if st != 0:
+        _check(st, "pikv_compress")
 
 
 def pikv_policy_stamp(desc, topk_idx, k, reuse_idx, reuse_cnt, max_evict, n_valid, now, birth,
                       last_access, freq, stream=None):
-    st = load_library().pikv_policy_stamp(C.byref(desc), _p(topk_idx), k, _p(reuse_idx), _p(reuse_cnt),
-                                          max_evict, _p(n_valid), int(now), _p(birth), _p(last_access),
-                                          _p(freq), _stream(stream))
-    _check(st, "pikv_policy_stamp")
+    st = _calls().pikv_policy_stamp(desc, topk_idx, k, reuse_idx, reuse_cnt, max_evict, n_valid, now, birth,
+                                    last_access, freq, _raw(stream))
+    if st is None:
+        st = load_library().pikv_policy_stamp(C.byref(desc), _p(topk_idx), k, _p(reuse_idx), _p(reuse_cnt),
+                                              max_evict, _p(n_valid), int(now), _p(birth), _p(last_access),
+                                              _p(freq), _stream(stream))
+    if st != 0:
+        _check(st, "pikv_policy_stamp")
 
 
 def pikv_update_utility_tracked(desc, scores, slot_coef, n_valid, topk_idx, k, decay, utility, threshold,
                                 now, last_access, freq, stream=None):
-    st = load_library().pikv_update_utility_tracked(C.byref(desc), _p(scores), _p(slot_coef), _p(n_valid),
-                                                    _p(topk_idx), k, float(decay), _p(utility),
-                                                    float(threshold), int(now), _p(last_access), _p(freq),
-                                                    _stream(stream))
-    _check(st, "pikv_update_utility_tracked")
+    st = _calls().pikv_update_utility_tracked(desc, scores, slot_coef, n_valid, topk_idx, k, decay, utility, threshold,
+                                              now, last_access, freq, _raw(stream))
+    if st is None:
+        st = load_library().pikv_update_utility_tracked(C.byref(desc), _p(scores), _p(slot_coef), _p(n_valid),
+                                                        _p(topk_idx), k, float(decay), _p(utility),
+                                                        float(threshold), int(now), _p(last_access), _p(freq),
+                                                        _stream(stream))
+    if st != 0:
+        _check(st, "pikv_update_utility_tracked")
 
 
 def pikv_policy_utility(desc, policy, n_valid, now, lam, window, protect, birth, last_access, freq, h2o,
                         out, stream=None):
-    st = load_library().pikv_policy_utility(C.byref(desc), int(policy), _p(n_valid), int(now), float(lam),
-                                            int(window), int(protect), _p(birth), _p(last_access),
-                                            _p(freq), _p(h2o), _p(out), _stream(stream))
-    _check(st, "pikv_policy_utility")
+    st = _calls().pikv_policy_utility(desc, policy, n_valid, now, lam, window, protect, birth, last_access, freq, h2o, out, _raw(stream))
+    if st is None:
+        st = load_library().pikv_policy_utility(C.byref(desc), int(policy), _p(n_valid), int(now), float(lam),
+                                                int(window), int(protect), _p(birth), _p(last_access),
+                                                _p(freq), _p(h2o), _p(out), _stream(stream))
+    if st != 0:
+        _check(st, "pikv_policy_utility")
 
 
 def pikv_policy_compact(desc, evicted_idx, evicted_cnt, max_evict, n_valid, birth, last_access, freq,
                         stream=None):
-    st = load_library().pikv_policy_compact(C.byref(desc), _p(evicted_idx), _p(evicted_cnt), max_evict,
-                                            _p(n_valid), _p(birth), _p(last_access), _p(freq), _stream(stream))
-    _check(st, "pikv_policy_compact")
+    st = _calls().pikv_policy_compact(desc, evicted_idx, evicted_cnt, max_evict, n_valid, birth, last_access, freq, _raw(stream))
+    if st is None:
+        st = load_library().pikv_policy_compact(C.byref(desc), _p(evicted_idx), _p(evicted_cnt), max_evict,
+                                                _p(n_valid), _p(birth), _p(last_access), _p(freq), _stream(stream))
+    if st != 0:
+        _check(st, "pikv_policy_compact")
 
 
 class PikvPolicyArgs(C.Structure):
@@ -333,12 +404,8 @@ class PikvPolicyArgs(C.Structure):
 
 def make_policy_args(policy, now, lam=0.0, window=0, protect=0, threshold=0.0, birth=None, last_access=None,
                      freq=None):
-    a = PikvPolicyArgs()
-    a.policy, a.now, a.lam, a.window, a.protect, a.threshold = int(policy), int(now), float(lam), int(window), \
-        int(protect), float(threshold)
-    for name, t in (("birth", birth), ("last_access", last_access), ("freq", freq)):
-        setattr(a, name, _p(t))
-    return a
+    return PikvPolicyArgs(int(policy), int(now), float(lam), int(window), int(protect), float(threshold), _p(birth),
+                          _p(last_access), _p(freq))
 
 
 class PikvRouterFeedback(C.Structure):
@@ -347,24 +414,25 @@ class PikvRouterFeedback(C.Structure):
 
 
 def make_router_feedback(mode, coef, load, bias, miss=None):
-    f = PikvRouterFeedback()
-    f.mode, f.coef = int(mode), float(coef)
-    for name, t in (("load", load), ("miss", miss), ("bias", bias)):
-        setattr(f, name, _p(t))
-    return f
+    return PikvRouterFeedback(int(mode), float(coef), _p(load), _p(miss), _p(bias))
 
 
 def pikv_decode_step_policy(desc, q, W_r, bias, K_new, V_new, K_shards, V_shards, U_K, U_V, n_valid, utility, k,
                             combine, scale, decay, topk_idx, gates, evicted_idx, evicted_cnt, y, row_max,
                             row_norm, scores, slot_coef, workspace, policy_args, feedback=None, stream=None):
-    st = load_library().pikv_decode_step_policy(
-        C.byref(desc), _p(q), _p(W_r), _p(bias), _p(K_new), _p(V_new), _p(K_shards), _p(V_shards), _p(U_K),
-        _p(U_V), _p(n_valid), _p(utility), k, combine, float(scale), float(decay), _p(topk_idx), _p(gates),
-        _p(evicted_idx), _p(evicted_cnt), _p(y), _p(row_max), _p(row_norm), _p(scores), _p(slot_coef),
-        _p(workspace), workspace.numel() * workspace.element_size(), _stream(stream),
-        None if policy_args is None else C.cast(C.pointer(policy_args), C.c_void_p),
-        None if feedback is None else C.cast(C.pointer(feedback), C.c_void_p))
-    _check(st, "pikv_decode_step_policy")
+    st = _calls().pikv_decode_step_policy(desc, q, W_r, bias, K_new, V_new, K_shards, V_shards, U_K, U_V, n_valid, utility, k,
+                                          combine, scale, decay, topk_idx, gates, evicted_idx, evicted_cnt, y, row_max,
+                                          row_norm, scores, slot_coef, workspace, _raw(stream), policy_args, feedback)
+    if st is None:
+        st = load_library().pikv_decode_step_policy(
+            C.byref(desc), _p(q), _p(W_r), _p(bias), _p(K_new), _p(V_new), _p(K_shards), _p(V_shards), _p(U_K),
+            _p(U_V), _p(n_valid), _p(utility), k, combine, float(scale), float(decay), _p(topk_idx), _p(gates),
+            _p(evicted_idx), _p(evicted_cnt), _p(y), _p(row_max), _p(row_norm), _p(scores), _p(slot_coef),
+            _p(workspace), workspace.numel() * workspace.element_size(), _stream(stream),
+            None if policy_args is None else C.cast(C.pointer(policy_args), C.c_void_p),
+            None if feedback is None else C.cast(C.pointer(feedback), C.c_void_p))
+    if st != 0:
+        _check(st, "pikv_decode_step_policy")
 
 
 def pikv_route_round_robin(rows, E, k, step, topk_idx, gates, stream=None):

@@ -1711,12 +1711,14 @@ extern "C" void pikv_set_profile_events(void *start, void *stop) {
     pikv::g_profile_events_set(start, stop);
 }
 
-static size_t workspace_bytes_within(const pikv_desc *desc, int32_t k, size_t scratch_limit) {
-    AttnPlan plan;
-    if (make_attn_plan(desc, k, &plan, scratch_limit) != PIKV_OK) return 0;
+static size_t workspace_bytes_of(const AttnPlan &plan) {
     const size_t acc = (plan.acc_floats * sizeof(float) + 255) / 256 * 256;
     const size_t ml = (plan.ml_floats * sizeof(float) + 255) / 256 * 256;
     return acc + ml + 256;
+}
+static size_t workspace_bytes_within(const pikv_desc *desc, int32_t k, size_t scratch_limit) {
+    AttnPlan plan;
+    return make_attn_plan(desc, k, &plan, scratch_limit) == PIKV_OK ? workspace_bytes_of(plan) : 0;
 }
 
 extern "C" size_t pikv_attn_workspace_bytes(const pikv_desc *desc, int32_t k) {
@@ -1740,8 +1742,7 @@ int check_attn_args(const pikv_desc *desc, const void *q, const void *const *K_s
     if (!(scale == scale)) return PIKV_ERR_INVALID;
     *plan_out = plan;
     if (desc->B == 0) return PIKV_OK;
-    const size_t need = workspace_bytes_within(desc, k, scratch_limit);
-    if (!workspace || workspace_bytes < need) return PIKV_ERR_WORKSPACE;
+    if (!workspace || workspace_bytes < workspace_bytes_of(plan)) return PIKV_ERR_WORKSPACE;
     if (reinterpret_cast<uintptr_t>(workspace) % 256 != 0) return PIKV_ERR_INVALID;
     if ((int64_t)desc->B * plan.head_blocks * k * plan.nsplit > 0x7fffffff) return PIKV_ERR_UNSUPPORTED;
     return PIKV_OK;
@@ -1749,18 +1750,22 @@ int check_attn_args(const pikv_desc *desc, const void *q, const void *const *K_s
 
 bool profile_events_set() { return g_prof_start != nullptr || g_prof_stop != nullptr; }
 
-// Validate, plan and launch the split pass only; fills the parameters of the merge pass.
+// Validate and plan (unless the caller has), launch the split pass only and fill the parameters of the merge pass.
 int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const *K_shards,
                         const void *const *V_shards, const void *U_K, const void *U_V,
                         const int32_t *n_valid, const int32_t *topk_idx, const float *gates,
                         int32_t k, int32_t combine, float scale, float *y, float *row_max,
                         float *row_norm, float *scores, float *slot_coef, void *workspace,
-                        size_t workspace_bytes, void *stream, AttnPlan *plan_out,
+                        size_t workspace_bytes, void *stream, const AttnPlan *checked, AttnPlan *plan_out,
                         CombineParams *c_out, size_t scratch_limit) {
     AttnPlan plan;
-    const int rc = check_attn_args(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, k, combine,
-                                   scale, y, workspace, workspace_bytes, &plan, scratch_limit);
-    if (rc != PIKV_OK) return rc;
+    if (checked != nullptr) {
+        plan = *checked;
+    } else {
+        const int rc = check_attn_args(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, k, combine,
+                                       scale, y, workspace, workspace_bytes, &plan, scratch_limit);
+        if (rc != PIKV_OK) return rc;
+    }
     *plan_out = plan;
     if (desc->B == 0) return PIKV_OK;
 
@@ -1890,7 +1895,7 @@ static int sharded_attn(const pikv_desc *desc, const void *q, const void *const 
     CombineParams c;
     const int rc = launch_attn_partial(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates,
                                        k, combine, scale, y, row_max, row_norm, scores, slot_coef,
-                                       workspace, workspace_bytes, stream, &plan, &c, scratch_limit);
+                                       workspace, workspace_bytes, stream, nullptr, &plan, &c, scratch_limit);
     if (rc != PIKV_OK || desc->B == 0) return rc;
     return pikv_sharded_attn_merge(desc, &c, stream);
 }

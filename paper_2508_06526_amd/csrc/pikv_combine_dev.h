@@ -433,14 +433,14 @@ int check_attn_args(const pikv_desc *desc, const void *q, const void *const *K_s
 // True while a profiling event pair is installed (pikv_set_profile_events).
 bool profile_events_set();
 
-// launch_attn_partial: validate, plan and launch the split pass only, and fill the parameters
-// of the merge pass.
+// launch_attn_partial: validate and plan - or take the plan that check_attn_args made for the same arguments -, launch the
+// split pass only, and fill the parameters of the merge pass.
 int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const *K_shards,
                         const void *const *V_shards, const void *U_K, const void *U_V,
                         const int32_t *n_valid, const int32_t *topk_idx, const float *gates,
                         int32_t k, int32_t combine, float scale, float *y, float *row_max,
                         float *row_norm, float *scores, float *slot_coef, void *workspace,
-                        size_t workspace_bytes, void *stream, AttnPlan *plan_out,
+                        size_t workspace_bytes, void *stream, const AttnPlan *checked, AttnPlan *plan_out,
                         CombineParams *c_out, size_t scratch_limit = SIZE_MAX);
 
 int pikv_sharded_attn_merge(const pikv_desc *desc, const CombineParams *c, void *stream);

@@ -770,7 +770,7 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     CombineParams c;
     lrc = launch_attn_partial(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates, k,
                               combine, scale, y, row_max, row_norm, scores, slot_coef, workspace,
-                              workspace_bytes, stream, &plan, &c);
+                              workspace_bytes, stream, &checked, &plan, &c);
     if (lrc != PIKV_OK) return lrc;
     if ((int64_t)desc->Hq * k > kPostMaxShards || desc->Hq >= kPostSplitRows) {
         // too many partials to restage per utility block: separate merge and utility launches

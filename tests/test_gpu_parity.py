@@ -1815,3 +1815,55 @@ def test_utility_update_of_every_form(spec):
     only = (torch.zeros_like(last), torch.zeros_like(freq))
     pk.pikv_update_utility_tracked(dc.desc, dc.scores, dc.slot_coef, dc.n_valid, dc.topk, g.k, 0.9, None, threshold, 7, *only)
     np.testing.assert_array_equal(t2n(only[1]), t2n(freq))
+
+
+def test_the_binding_takes_what_it_took_and_refuses_what_it_refused():
+    """Ordinary arguments go through the extension; numbers of other types, parameters and other streams give the same; tensors on the host,
+    strided tensors and wrong types are refused as before."""
+    g = wl.Geometry(B=2, Hq=4, Hkv=2, D=32, E=4, S=64, k=2, dtype="f32")
+    case = wl.make_host_case(g, seed=4, w_sigma=0.3)
+    dc = DeviceCase(case)
+    out = []
+
+    def route(x, W, rows=g.B, k=g.k, stream=None):
+        topk, gates = torch.zeros((g.B, g.k), device=DEV, dtype=torch.int32), torch.zeros((g.B, g.k), device=DEV)
+        pk.pikv_route(x, W, None, rows, g.d_r, g.E, k, topk, gates, stream=stream)
+        out.append((t2n(topk), t2n(gates)))
+
+    x = dc.q.reshape(g.B, -1)
+    assert pk.binding._calls().pikv_route(x, dc.W_r, None, g.B, g.d_r, g.E, g.k, dc.topk, dc.gates, None, None) == 0
+    route(x, dc.W_r)
+    route(torch.nn.Parameter(x), dc.W_r)
+    assert pk.binding._calls().pikv_route(x, dc.W_r, None, g.B, g.d_r, g.E, 2.0, dc.topk, dc.gates, None, None) is None
+
+    class Marked(torch.Tensor):
+        pass
+
+    route(x.as_subclass(Marked), dc.W_r)
+    other = torch.cuda.Stream()
+    other.wait_stream(torch.cuda.current_stream())
+    route(x, dc.W_r, stream=other)
+    with torch.cuda.stream(other):
+        route(x, dc.W_r)
+        torch.cuda.current_stream().synchronize()
+    other.synchronize()
+    route(x, dc.W_r, k=True + 1)
+    route(x, dc.W_r, rows=g.B + (1 << 32))                    # ctypes keeps the low 32 bits
+    for topk, gates in out[1:]:
+        np.testing.assert_array_equal(topk, out[0][0])
+        np.testing.assert_array_equal(gates, out[0][1])
+    with pytest.raises(ValueError, match="device memory"):
+        route(x.cpu(), dc.W_r)
+    with pytest.raises(ValueError, match="contiguous"):
+        route(x, dc.W_r.t().contiguous().t())
+    with pytest.raises(TypeError, match="storage dtype"):
+        route(x.double(), dc.W_r)
+    with pytest.raises(AttributeError):
+        route(None, dc.W_r)
+    with pytest.raises(Exception):
+        route(x, dc.W_r, k=2.0)
+    with pytest.raises(pk.PikvError):
+        route(x, dc.W_r, k=g.E + 1)
+    with pytest.raises(pk.PikvError):                         # no workspace
+        pk.pikv_sharded_attn(dc.desc, dc.q, dc.K_tab, dc.V_tab, None, None, dc.n_valid, dc.topk, dc.gates, g.k, 0, 0.0, dc.y,
+                             None, None, None, None, None)
