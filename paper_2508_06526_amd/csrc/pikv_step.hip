@@ -272,19 +272,36 @@ __global__ __launch_bounds__(kRouteThreads) void step_pre(PreParams p) {
     if (j == 0 && tid < p.E && rank >= p.k) p.evicted_cnt[(int64_t)b * p.E + tid] = 0;
 }
 
+// The merge as a launch of its own with one block more, for the router's penalty update.
+template <typename T, int THREADS>
+__global__ __launch_bounds__(THREADS) void merge_with_penalty(CombineParams c, PenaltyParams fb) {
+    extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // combine_smem_bytes()
+    if (blockIdx.x == gridDim.x - 1) {
+        if (threadIdx.x < kWave) penalty_wave(fb, threadIdx.x);
+        return;
+    }
+    combine_head<T, THREADS>(c, blockIdx.x, smem);
+}
+
 // Post-attention stage of the fused step: the merge of the split partials (one block per
 // query head, as in the stand-alone combine kernel) and the utility update in ONE launch.
 // A utility block (256 slots of a visited shard x 4 groups of heads) cannot wait for the merge
 // blocks, so it recomputes the per-head softmax statistics itself from the (max, sum) pairs of
 // the partials - a few KiB from L2 and the same arithmetic, hence the same bits - while its
 // score loads are already in flight.
-constexpr int kPostMaxShards = 2048;   // Hq * k
-// From this many query rows per sequence on (a multi-query step of 8 drafts x 32 heads) the merge
-// and the utility update run as two launches: every utility block of the single launch re-derives
-// the statistics of all Hq * k (head, shard) pairs from their partials - 128 KiB per block at 256
-// rows and 4 shards - while the stand-alone utility kernel reads the merge's (shift, coef) pairs.
-// Measured, 256 rows: 18.2 us in one launch, 5.3 + 9.4 us in two; 128 rows: 11.4 us either way.
-constexpr int kPostSplitRows = 256;
+// Beyond this many (head, shard) pairs - or heads, where the merge takes blocks of 1024 threads - the merge and the
+// utility update run as two launches: every utility block of the single launch re-derives the statistics of all
+// pairs from their partials, while the stand-alone kernel reads the merge's (shift, coef) pairs.  Kernel trace, one launch
+// against both of the others (which are 0.7 us apart as well): 128 heads x 4 shards 13.9 against 4.7 + 5.2 us, in
+// blocks of 256 threads 13.7 against 4.1 + 4.7, 16 sequences of them 18.4 against 5.8 + 7.5; 96 x 4 10.9 against 4.1 + 4.1, 96 x 2
+// in blocks of 1024 9.9 and 4.1 + 4.2; the other side of the line: 64 x 4 7.1 against 4.0 + 3.7, 16 sequences 10.4 against
+// 4.7 + 4.8, 128 x 2 in blocks of 256 9.5 against 4.6 + 4.2, 32 sequences 12.9 against 8.5 + 5.3, 16 x 16 5.6 against 4.4 + 3.1.
+constexpr int kPostMostPairs = 256;
+constexpr int kPostMostHeads = 64;
+inline bool post_separate(int Hq, int k, int np) {
+    return (int64_t)Hq * k > kPostMostPairs || Hq >= kPostMostPairs || (combine_threads(np) == 1024 && Hq > kPostMostHeads);
+}
+
 constexpr int kPostPrefetchHeads = 8;  // score loads each thread issues before the statistics
 constexpr int kPostMaxTiles = 8;       // slot tiles one utility block walks through
 constexpr int kPostStatsAhead = 4;     // many-pairs shape: passes of statistics whose loads are in flight
@@ -355,7 +372,7 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     const int ncomb = p.B * Hq;
     // Blocks are dispatched in id order.  With hundreds of query rows the utility blocks are
     // the long ones and a CU holds one block of either kind: they then take the first ids,
-    // so that they do not queue behind the merge blocks (kPostMany only).
+    // so that they do not queue behind the merge blocks.
     const bool util_first = (MODE == kPostMany || kOwnHeads) && p.util_first;
     const int mb = util_first ? (int)blockIdx.x - p.B * k * p.tiles : (int)blockIdx.x;
     if (mb >= 0 && mb < ncomb) {
@@ -772,20 +789,27 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
                               combine, scale, y, row_max, row_norm, scores, slot_coef, workspace,
                               workspace_bytes, stream, &checked, &plan, &c);
     if (lrc != PIKV_OK) return lrc;
-    if ((int64_t)desc->Hq * k > kPostMaxShards || desc->Hq >= kPostSplitRows) {
-        // too many partials to restage per utility block: separate merge and utility launches
-        lrc = pikv_sharded_attn_merge(desc, &c, stream);
+    const int np = k * plan.nsplit;
+    const int threads = combine_threads(np);
+    const bool f32 = desc->dtype == PIKV_F32;
+    if (post_separate(desc->Hq, k, np)) {
+        if (fb == nullptr) {
+            lrc = pikv_sharded_attn_merge(desc, &c, stream);
+        } else {
+            const dim3 mgrid(desc->B * desc->Hq + 1);
+            const size_t mlds = combine_smem_bytes(threads, np, c.decoder_bytes);
+            if (threads == 256 && f32) hipLaunchKernelGGL((merge_with_penalty<float, 256>), mgrid, dim3(256), mlds, st, c, pen);
+            else if (threads == 256) hipLaunchKernelGGL((merge_with_penalty<bf16, 256>), mgrid, dim3(256), mlds, st, c, pen);
+            else if (f32) hipLaunchKernelGGL((merge_with_penalty<float, 1024>), mgrid, dim3(1024), mlds, st, c, pen);
+            else hipLaunchKernelGGL((merge_with_penalty<bf16, 1024>), mgrid, dim3(1024), mlds, st, c, pen);
+            lrc = launch_status();
+        }
         if (lrc != PIKV_OK) return lrc;
         if (track)
-            lrc = pikv_update_utility_tracked(desc, scores, slot_coef, n_valid, topk_idx, k, decay,
-                                              utility, pol.threshold, pol.now, pol.last_access,
-                                              pol.freq, stream);
-        else
-            lrc = pikv_update_utility(desc, scores, slot_coef, n_valid, topk_idx, k, decay, utility,
-                                      stream);
-        if (lrc != PIKV_OK || fb == nullptr) return lrc;
-        return pikv_router_penalty(fb->mode, topk_idx, desc->B, k, desc->E, fb->load, fb->miss, fb->coef,
-                                   fb->bias, stream);
+            return pikv_update_utility_tracked(desc, scores, slot_coef, n_valid, topk_idx, k, decay,
+                                               utility, pol.threshold, pol.now, pol.last_access,
+                                               pol.freq, stream);
+        return pikv_update_utility(desc, scores, slot_coef, n_valid, topk_idx, k, decay, utility, stream);
     }
     PostParams pp;
     pp.c = c;
@@ -799,8 +823,6 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     pp.B = desc->B;
     pp.E = desc->E;
     pp.S = desc->S;
-    const int np = k * plan.nsplit;
-    const int threads = combine_threads(np);
     // Utility blocks: enough of them to fill the GPU once (256 CUs x the blocks a CU holds),
     // each walking through several slot tiles rather than a new block per tile - the
     // statistics of the sequence's (head, shard) pairs are then computed once per block.
@@ -810,8 +832,9 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
         const int64_t t = ((int64_t)desc->B * k * tiles + want_blocks - 1) / want_blocks;
         return t < 1 ? 1 : t > kPostMaxTiles ? (int64_t)kPostMaxTiles : t;
     };
-    // many (head, shard) pairs per utility block, or many heads per thread: the kernel shape
-    // that keeps several passes of statistics in flight and starts the utility blocks first
+    const bool lanes = k <= kWaveShards;
+    // more (head, shard) pairs than a pass takes, or many heads per thread: the utility blocks start first, and without
+    // lane statistics (blocks of 256 threads) it takes the shape that keeps several passes of them in flight
     const bool many = desc->Hq * k > 2 * (threads / 8) || (desc->Hq + 3) / 4 > 2 * kPostPrefetchHeads;
     // four slots per thread as soon as one slot per thread needs more than one round of blocks (in
     // blocks of 1024 threads only where the loop-free shape takes it: the others would spill)
@@ -831,38 +854,33 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     const int64_t blocks = (int64_t)desc->B * desc->Hq + (int64_t)desc->B * k * pp.tiles + (fb ? 1 : 0);
     if (blocks > 0x7fffffff) return PIKV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks);
-    const bool f32 = desc->dtype == PIKV_F32;
     const size_t lds = post_smem_bytes(threads, np, desc->Hq * k, wide ? 4 : 1, c.decoder_bytes);
     const bool multi = tpb > 1;
     // (several tiles of four slots per thread: blocks of 256 threads only, see `wide`)
-    const bool lanes = k <= kWaveShards;
-#define PIKV_LAUNCH_POST_MODE(T, TH, MODE, LANES)                                                               \
-    do {                                                                                                        \
-        constexpr int kWide = TH == 256 || MODE == kPostSingle ? 4 : 1;                                         \
-        if (wide) hipLaunchKernelGGL((step_post<T, TH, MODE, kWide, LANES>), grid, dim3(TH), lds, st, pp);      \
-        else hipLaunchKernelGGL((step_post<T, TH, MODE, 1, LANES>), grid, dim3(TH), lds, st, pp);               \
-    } while (0)
-#define PIKV_LAUNCH_POST_LANES(T, TH, LANES)                                                                    \
-    do {                                                                                                        \
-        if (many && !(LANES && TH == 256)) PIKV_LAUNCH_POST_MODE(T, TH, (LANES && TH == 256 ? kPostSingle : kPostMany), LANES); \
-        else if (multi) PIKV_LAUNCH_POST_MODE(T, TH, kPostMulti, LANES);                                        \
-        else PIKV_LAUNCH_POST_MODE(T, TH, kPostSingle, LANES);                                                  \
-    } while (0)
-#define PIKV_LAUNCH_POST(T, TH)                                                                                 \
-    do {                                                                                                        \
-        if (lanes) PIKV_LAUNCH_POST_LANES(T, TH, true);                                                         \
-        else PIKV_LAUNCH_POST_LANES(T, TH, false);                                                              \
-    } while (0)
-    if (threads == 256) {
-        if (f32) PIKV_LAUNCH_POST(float, 256);
-        else PIKV_LAUNCH_POST(bf16, 256);
-    } else {
-        if (f32) PIKV_LAUNCH_POST(float, 1024);
-        else PIKV_LAUNCH_POST(bf16, 1024);
-    }
-#undef PIKV_LAUNCH_POST
-#undef PIKV_LAUNCH_POST_LANES
-#undef PIKV_LAUNCH_POST_MODE
+    auto launch = [&](auto type, auto th, auto mode, auto with_lanes) {
+        typedef decltype(type) T;
+        constexpr int TH = decltype(th)::value, MODE = decltype(mode)::value;
+        constexpr bool LANES = decltype(with_lanes)::value;
+        constexpr int kWide = TH == 256 || MODE == kPostSingle ? 4 : 1;
+        if (wide) hipLaunchKernelGGL((step_post<T, TH, MODE, kWide, LANES>), grid, dim3(TH), lds, st, pp);
+        else hipLaunchKernelGGL((step_post<T, TH, MODE, 1, LANES>), grid, dim3(TH), lds, st, pp);
+    };
+    auto launch_mode = [&](auto type, auto th, auto with_lanes) {
+        constexpr bool kHasMany = decltype(th)::value == 256 && !decltype(with_lanes)::value;
+        if constexpr (kHasMany) {
+            if (many) return launch(type, th, std::integral_constant<int, kPostMany>{}, with_lanes);
+        }
+        if (multi) launch(type, th, std::integral_constant<int, kPostMulti>{}, with_lanes);
+        else launch(type, th, std::integral_constant<int, kPostSingle>{}, with_lanes);
+    };
+    auto launch_type = [&](auto type) {
+        const std::integral_constant<int, 256> small{};
+        const std::integral_constant<int, 1024> large{};
+        if (threads == 256) lanes ? launch_mode(type, small, std::true_type{}) : launch_mode(type, small, std::false_type{});
+        else lanes ? launch_mode(type, large, std::true_type{}) : launch_mode(type, large, std::false_type{});
+    };
+    if (f32) launch_type(float{});
+    else launch_type(bf16{});
     return launch_status();
 }
 

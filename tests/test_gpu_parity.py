@@ -1867,3 +1867,31 @@ def test_the_binding_takes_what_it_took_and_refuses_what_it_refused():
     with pytest.raises(pk.PikvError):                         # no workspace
         pk.pikv_sharded_attn(dc.desc, dc.q, dc.K_tab, dc.V_tab, None, None, dc.n_valid, dc.topk, dc.gates, g.k, 0, 0.0, dc.y,
                              None, None, None, None, None)
+
+
+@pytest.mark.parametrize("spec", [
+    dict(B=2, Hq=128, Hkv=8, D=128, E=8, S=300, k=3, dtype="bf16"),      # merge by 256 threads
+    dict(B=1, Hq=96, Hkv=8, D=128, E=8, S=2100, k=2, dtype="bf16"),      # by 1024, for its heads
+    dict(B=3, Hq=64, Hkv=8, D=64, E=8, S=300, k=4, dtype="f32"),         # at the line: one launch
+    dict(B=3, Hq=65, Hkv=5, D=64, E=8, S=300, k=4, dtype="f32"),         # past it
+], ids=["256", "1024", "line", "past"])
+def test_fused_step_with_feedback_on_both_sides_of_the_separate_merge(spec):
+    """The router's penalty update rides with the merge where that is a launch of its own; the same bits as the separate calls."""
+    g = wl.Geometry(**spec)
+    case = wl.make_host_case(g, seed=12, n_valid="ragged", utility0="exp", w_sigma=0.05)
+    ensure_route_margin(case, g.k)
+    dA, dB = DeviceCase(case), DeviceCase(case)
+    for d in (dA, dB):
+        d.load = torch.arange(g.E, device=DEV, dtype=torch.int32)
+        d.after = torch.zeros(g.E, device=DEV)
+    feedback = pk.make_router_feedback(pk.PENALTY_LOAD_BALANCE, 0.01, dA.load, dA.after)
+    pk.pikv_decode_step_policy(dA.desc, dA.q, dA.W_r, dA.bias, None, None, dA.K_tab, dA.V_tab, None, None, dA.n_valid, dA.utility,
+                               g.k, pk.COMBINE_LSE, 0.0, 0.9, dA.topk, dA.gates, None, None, dA.y, dA.row_max, dA.row_norm,
+                               dA.scores, dA.slot_coef, dA.workspace, None, feedback=feedback)
+    dB.route()
+    dB.attend()
+    dB.update_utility(0.9)
+    pk.pikv_router_penalty(pk.PENALTY_LOAD_BALANCE, dB.topk, g.B, g.k, g.E, dB.load, None, 0.01, dB.after)
+    for name in ("topk", "gates", "utility", "y", "row_max", "row_norm", "slot_coef", "load", "after"):
+        np.testing.assert_array_equal(t2n(getattr(dA, name)), t2n(getattr(dB, name)), err_msg=name)
+    assert t2n(dA.load).sum() == g.E * (g.E - 1) // 2 + g.B * g.k
