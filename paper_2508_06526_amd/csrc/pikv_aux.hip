@@ -82,36 +82,52 @@ __device__ __forceinline__ void store_elem<bf16>(bf16 *p, int64_t i, float v) {
     p[i].bits = (uint16_t)(__builtin_bit_cast(uint32_t, r) & 0xffffu);
 }
 
+// A block's 256 threads take 32 code elements a pass, at most two passes; what both read is requested before either is
+// summed (no request under a lane's condition), so that a block is one trip to memory: with a trip per 64 values of
+// the head dimension and pass it was two (bf16, rank 32) to eight (kernel trace: 15 x 4 kv heads, rank 64, 3.3 -> 2.6 us, 5 x 2 in
+// fp32, rank 16, 2.85 -> 2.5; right behind another kernel's writes 4.6 either way).
 template <typename T>
 __global__ __launch_bounds__(256) void compress_rows(const T *xK, const T *WK, T *codesK, const T *xV,
-                                                     const T *WV, T *codesV, int Hkv, int D, int rank) {
+                                                     const T *WV, T *codesV, FastDiv by_Hkv, int D, int rank) {
     constexpr int EPL = Pack16<T>::N;
+    constexpr int kChunks = 128 / EPL / 8;     // of a lane, D <= 128
+    constexpr int kPasses = 2;                 // rank <= 64
     const T *x = blockIdx.y == 0 ? xK : xV;    // grid.y: 0 = keys, 1 = values
     const T *W_enc = blockIdx.y == 0 ? WK : WV;
     T *codes = blockIdx.y == 0 ? codesK : codesV;
     const int bh = blockIdx.x;                 // b * Hkv + h
-    const int h = bh % Hkv;
+    int h;
+    fast_divide(by_Hkv, bh, &h);
     const int tid = threadIdx.x, sub = tid & 7;
     const int chunks = D / EPL;
     const T *xv = x + (int64_t)bh * D;
     const T *W = W_enc + (int64_t)h * rank * D;
-    for (int c0 = 0; c0 < rank; c0 += 256 / 8) {
-        const int c = c0 + (tid >> 3);
-        const bool real = c < rank;
-        float a = 0.0f;
-        if (real) {
-            for (int ch = sub; ch < chunks; ch += 8) {
-                float wf[EPL], xf[EPL];
-                Pack16<T>::widen(load16(W + (int64_t)c * D + ch * EPL), wf);
-                Pack16<T>::widen(load16(xv + ch * EPL), xf);
+    uint4 xr[kChunks], wr[kPasses][kChunks];
 #pragma unroll
-                for (int i = 0; i < EPL; ++i) a = fmaf(wf[i], xf[i], a);
-            }
+    for (int u = 0; u < kChunks; ++u) xr[u] = load16(xv + min(sub + 8 * u, chunks - 1) * EPL);
+#pragma unroll
+    for (int pass = 0; pass < kPasses; ++pass)
+#pragma unroll
+        for (int u = 0; u < kChunks; ++u)
+            wr[pass][u] = load16(W + min(32 * pass + (tid >> 3), rank - 1) * D + min(sub + 8 * u, chunks - 1) * EPL);
+#pragma unroll
+    for (int pass = 0; pass < kPasses; ++pass) {
+        const int c = 32 * pass + (tid >> 3);
+        if (32 * pass >= rank) break;          // block-uniform
+        float a = 0.0f;
+#pragma unroll
+        for (int u = 0; u < kChunks; ++u) {
+            float wf[EPL], xf[EPL], with = a;
+            Pack16<T>::widen(wr[pass][u], wf);
+            Pack16<T>::widen(xr[u], xf);
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) with = fmaf(wf[i], xf[i], with);
+            a = sub + 8 * u < chunks ? with : a;
         }
-        a += __shfl_xor(a, 1, kWave);
-        a += __shfl_xor(a, 2, kWave);
-        a += __shfl_xor(a, 4, kWave);
-        if (real && sub == 0) store_elem<T>(codes, (int64_t)bh * rank + c, a);
+        a += lane_xor<0>(a);
+        a += lane_xor<1>(a);
+        a += lane_xor<2>(a);
+        if (c < rank && sub == 0) store_elem<T>(codes, (int64_t)bh * rank + c, a);
     }
 }
 
@@ -156,12 +172,12 @@ extern "C" int pikv_compress(const pikv_desc *desc, const void *K_full, const vo
         hipLaunchKernelGGL(compress_rows<float>, grid, block, 0, st, static_cast<const float *>(K_full),
                            static_cast<const float *>(Wenc_K), static_cast<float *>(K_codes),
                            static_cast<const float *>(V_full), static_cast<const float *>(Wenc_V),
-                           static_cast<float *>(V_codes), desc->Hkv, desc->D, desc->rank);
+                           static_cast<float *>(V_codes), fast_div(desc->Hkv), desc->D, desc->rank);
     else
         hipLaunchKernelGGL(compress_rows<bf16>, grid, block, 0, st, static_cast<const bf16 *>(K_full),
                            static_cast<const bf16 *>(Wenc_K), static_cast<bf16 *>(K_codes),
                            static_cast<const bf16 *>(V_full), static_cast<const bf16 *>(Wenc_V),
-                           static_cast<bf16 *>(V_codes), desc->Hkv, desc->D, desc->rank);
+                           static_cast<bf16 *>(V_codes), fast_div(desc->Hkv), desc->D, desc->rank);
     return launch_status();
 }
 
