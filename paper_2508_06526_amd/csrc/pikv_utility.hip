@@ -29,6 +29,9 @@ constexpr int kUtilThreads = 256;
 constexpr int kUtilBatch = 8;           // heads whose scores are in flight per thread ...
 constexpr int kUtilFewBatch = 2;        // ... of up to kUtilFewHeads in all
 constexpr int kUtilFewHeads = 4 * kUtilFewBatch;
+// Many heads in few blocks: a batch is a trip and what a CU has in flight bounds the rate (256 heads x 4 of 8192 slots, 32 MiB,
+// batches of 8 8.1 us, 16 7.3, 32 7.1; 128 heads 5.1, 4.85, 4.9).
+constexpr int kUtilManyHeads = 64, kUtilManyBatch = 16;
 // Four slots per thread once one slot per thread makes more blocks than this (24 sequences x 32 heads x 2 of 16 shards of 2048
 // slots, routed head by head, 17.4 us with one; the form before 13.6; now 9.4).
 constexpr int kUtilManyBlocks = 1024;
@@ -210,6 +213,7 @@ int launch_utility(const pikv_desc *desc, const float *scores, const float *slot
     };
     auto launch_batch = [&](auto tracks) {
         if (desc->Hq <= kUtilFewHeads) launch_wide(tracks, std::integral_constant<int, kUtilFewBatch>{});
+        else if (desc->Hq > kUtilManyHeads && !wide && p.rr == 1) launch(tracks, std::integral_constant<int, 1>{}, std::false_type{}, std::integral_constant<int, kUtilManyBatch>{});
         else launch_wide(tracks, std::integral_constant<int, kUtilBatch>{});
     };
     if (track) launch_batch(std::true_type{});
