@@ -311,6 +311,17 @@ def test_multi_query_step_in_token_major_layout(spec, combine):
     assert_utility_close(t2n(dc.utility), u_ref)
 
 
+@pytest.mark.parametrize("spec", [
+    dict(B=2, Hq=34, Hkv=2, D=128, E=3, S=200, k=2, dtype="bf16", tq=17),     # one head per draft; a second row tile of one row
+    dict(B=1, Hq=45, Hkv=3, D=128, E=4, S=700, k=4, dtype="bf16", tq=5),      # three heads per draft, 15 rows, empty splits
+    dict(B=1, Hq=99, Hkv=3, D=128, E=3, S=257, k=2, dtype="bf16", tq=3),      # 33 rows: the third row tile of one row
+], ids=["tq17_g1", "tq5_g3", "tq3_g11"])
+def test_draft_rows_of_odd_groups(spec):
+    """The caller's rows of a group (the quotient by the heads of a draft) and the merge of a block's waves, four
+    values per thread, at row tiles that end in one row."""
+    test_multi_query_step_in_token_major_layout(spec, orc.COMBINE_LSE)
+
+
 def test_library_opened_before_torch_still_launches():
     """A caller may load the binding's library before it ever imports torch; both must end up on
     one HIP runtime (a kernel launched through a second copy fails on torch's streams).  Runs in
