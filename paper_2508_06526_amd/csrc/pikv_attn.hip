@@ -1383,6 +1383,140 @@ __global__ __launch_bounds__(THREADS) void attn_combine(CombineParams p) {
     combine_head<T, THREADS>(p, blockIdx.x, smem);
 }
 
+// The smallest calls of one head per block in one launch: where the plan gives every split one tile and a head has at most
+// kSmallWaves of them, a block takes a whole head, a wave a split.  The partials stay in LDS and the same block merges
+// them - same rows per split, same sums in the same order, same bits as attn_partial and attn_combine, whose blocks here
+// hold one busy wave of four.  What bounds such a call are launches and trips to memory: the merge's launch and its
+// trip go.  (Pass and merge in a graph: 4 heads x 2 shards of 256 fp32 rows of 64 values 7.9 -> 7.25 us, of 128 x 2 sequences 8.0 ->
+// 6.2, 4 heads x 2 of 128 bf16 rows of 128 8.5 -> 6.7, 63 heads x 3 of 128 rows of 16 values 8.45 -> 6.05; a launch less of host
+// time.)  More tiles than a block has waves would be a second trip: those calls stay with the two kernels.
+constexpr int kSmallWaves = 16;
+inline size_t small_lds_bytes(int W, int np) { return (size_t)np * (W + 2) * sizeof(float) + 16 + combine_smem_bytes(256, np, 0); }
+template <typename T, int W>
+__global__ __launch_bounds__(kSmallWaves *kWave) void attn_small(AttnParams p, CombineParams c) {
+    constexpr int EPL = Pack16<T>::N;        // as in attn_partial
+    constexpr int LPR = W / EPL;
+    constexpr int RPL = kWave / LPR;
+    constexpr int NL = plain_loads_per_tile(W * (int)sizeof(T), 1);
+    constexpr int CB = ilog2(LPR);
+    extern __shared__ __attribute__((aligned(16))) float small_lds[];       // np x W accumulators, np pairs, the merge's
+    const int np = p.k * p.nsplit;
+    float *parts = small_lds, *pairs = parts + np * W;
+    unsigned char *merge = reinterpret_cast<unsigned char *>(pairs + (np * 2 + 3) / 4 * 4);
+
+    const int lane = threadIdx.x & (kWave - 1);
+    const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const int col = lane & (LPR - 1), r = lane >> CB;
+    int h, group_head, split;
+    const int b = fast_divide(p.by_groups, blockIdx.x, &h);
+    const int hk = fast_divide(p.by_G, h, &group_head);
+    const float gate = combine_gate(c, blockIdx.x);      // ahead of the rows: the merge has no trip of its own
+    if (wave < np) {
+        const int j = fast_divide(p.by_nsplit, wave, &split);
+        const T *qp = static_cast<const T *>(p.q) + ((int64_t)b * p.Hq + h) * W + col * EPL;
+        float qf[EPL];
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) qf[i] = load_scalar<T>(qp, i);
+        const ShardRef sh = resolve_shard(p, b, b * p.rr + (p.rr == 1 ? 0 : h), j, lane);
+        const int r0 = split * p.chunk, r1 = min(min(sh.n, p.S), r0 + p.chunk);
+        float m = -INFINITY, l = 0.0f, acc[EPL];
+#pragma unroll
+        for (int i = 0; i < EPL; ++i) acc[i] = 0.0f;
+        if (r0 < r1) {
+            const T *Kb = reinterpret_cast<const T *>(sh.K) + (int64_t)hk * p.stride_h + col * EPL;
+            const T *Vb = reinterpret_cast<const T *>(sh.V) + (int64_t)hk * p.stride_h + col * EPL;
+            uint4 kr[NL], vr[NL];
+#pragma unroll
+            for (int t = 0; t < NL; ++t) kr[t] = load16_stream(Kb + (int64_t)min(r0 + t * RPL + r, r1 - 1) * p.stride_s);
+#pragma unroll
+            for (int t = 0; t < NL; ++t) vr[t] = load16_stream(Vb + (int64_t)min(r0 + t * RPL + r, r1 - 1) * p.stride_s);
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) qf[i] = p.scale * qf[i];
+            float s[NL];
+#pragma unroll
+            for (int t = 0; t < NL; ++t) {
+                float kf[EPL];
+                Pack16<T>::widen(kr[t], kf);
+                float d = 0.0f;
+#pragma unroll
+                for (int i = 0; i < EPL; ++i) d = fmaf(qf[i], kf[i], d);
+                d = bits_sum<0, CB>(d);
+                s[t] = r0 + t * RPL + r < r1 ? d : -INFINITY;
+            }
+            if (p.scores != nullptr) {
+                float *dst = p.scores + (((int64_t)b * p.Hq + h) * p.k + j) * p.S;
+#pragma unroll
+                for (int u = 0; u < NL; u += LPR) {
+                    float v = s[u];
+#pragma unroll
+                    for (int t = 1; t < LPR && u + t < NL; ++t) v = (col == t) ? s[u + t] : v;
+                    const int row = r0 + (u + col) * RPL + r;
+                    if (u + col < NL && row < r1) dst[row] = v;
+                }
+            }
+            float tm = s[0];
+#pragma unroll
+            for (int t = 1; t < NL; ++t) tm = fmaxf(tm, s[t]);
+            tm = bits_max<CB, 6>(tm);
+            const float mn = fmaxf(m, tm);
+            const float corr = __expf(m - mn);
+            m = mn;
+            l *= corr;
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) acc[i] *= corr;
+#pragma unroll
+            for (int t = 0; t < NL; ++t) {
+                const float pt = __expf(s[t] - mn);
+                s[t] = pt;
+                l += pt;
+            }
+#pragma unroll
+            for (int t = 0; t < NL; ++t) {
+                float vf[EPL];
+                Pack16<T>::widen(vr[t], vf);
+#pragma unroll
+                for (int i = 0; i < EPL; ++i) acc[i] = fmaf(s[t], vf[i], acc[i]);
+            }
+#pragma unroll
+            for (int off = LPR; off < kWave; off <<= 1) {
+                l += __shfl_xor(l, off, kWave);
+#pragma unroll
+                for (int i = 0; i < EPL; ++i) acc[i] += __shfl_xor(acc[i], off, kWave);
+            }
+            // as attn_partial joins this wave with three that have no rows
+            const float M = fmaxf(m, -INFINITY), f = m == -INFINITY ? 0.0f : __expf(m - M);
+            m = M;
+            l = fmaf(l, f, 0.0f);
+#pragma unroll
+            for (int i = 0; i < EPL; ++i) acc[i] = fmaf(acc[i], f, 0.0f);
+        }
+        if (r == 0) {
+#pragma unroll
+            for (int i = 0; i < EPL; i += 4)
+                *reinterpret_cast<float4 *>(parts + wave * W + col * EPL + i) = make_float4(acc[i], acc[i + 1], acc[i + 2], acc[i + 3]);
+        }
+        if (lane == 0) *reinterpret_cast<float2 *>(pairs + 2 * wave) = make_float2(m, l);
+    }
+    __syncthreads();
+    if (wave >= 4) return;                   // (a barrier waits for the waves that are left)
+    combine_head<T, 256>(c, blockIdx.x, merge, parts, pairs, [&] { return gate; });
+}
+
+template <typename T>
+int launch_small(const AttnParams &p, const CombineParams &c, int heads, hipStream_t st) {
+    const int np = p.k * p.nsplit;
+    const dim3 grid(heads), block((np < 4 ? 4 : np) * kWave);
+    const size_t lds = small_lds_bytes(c.W, np);
+    switch (c.W) {
+        case 16: hipLaunchKernelGGL((attn_small<T, 16>), grid, block, lds, st, p, c); break;
+        case 32: hipLaunchKernelGGL((attn_small<T, 32>), grid, block, lds, st, p, c); break;
+        case 64: hipLaunchKernelGGL((attn_small<T, 64>), grid, block, lds, st, p, c); break;
+        case 128: hipLaunchKernelGGL((attn_small<T, 128>), grid, block, lds, st, p, c); break;
+        default: return PIKV_ERR_UNSUPPORTED;
+    }
+    return launch_status();
+}
+
 template <typename T, int W>
 int launch_partial_w(int gb, const AttnParams &p, int blocks, hipStream_t st) {
     const dim3 grid(blocks), block(kWavesPerBlock * kWave);
@@ -1684,6 +1818,8 @@ int make_attn_plan(const pikv_desc *d, int k, AttnPlan *plan, size_t scratch_lim
     const int64_t target_blocks = 256 * resident;
     plan->gqa_mfma = gqa_mfma;
     plan->gqa_f32 = gqa_f32;
+    // one tile per split and a head's splits the waves of one block: attn_small
+    plan->small = !gqa_mfma && !gqa_f32 && gb == 1 && d->rank == 0 && chunk == tile && k * nsplit <= kSmallWaves && g_split_override == 0;
     plan->long_blocks = W == 128 && by_unit && !few;
     plan->heads_per_block = gb;
     plan->row_tiles = row_tiles;
@@ -1761,7 +1897,7 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
                         int32_t k, int32_t combine, float scale, float *y, float *row_max,
                         float *row_norm, float *scores, float *slot_coef, void *workspace,
                         size_t workspace_bytes, void *stream, const AttnPlan *checked, AttnPlan *plan_out,
-                        CombineParams *c_out, size_t scratch_limit) {
+                        CombineParams *c_out, size_t scratch_limit, bool *merged) {
     AttnPlan plan;
     if (checked != nullptr) {
         plan = *checked;
@@ -1813,10 +1949,37 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
 
     const int64_t blocks64 = (int64_t)desc->B * plan.head_blocks * k * plan.nsplit;
     p.stream_scores = blocks64 > plan.resident_blocks;
+    CombineParams c;
+    c.part_acc = part_acc;
+    c.part_ml = part_ml;
+    c.gates = gates;
+    c.U_V = U_V;
+    c.y = y;
+    c.row_max = row_max;
+    c.row_norm = row_norm;
+    c.slot_coef = slot_coef;
+    c.Hq = desc->Hq;
+    c.G = p.G;
+    c.by_Hq = fast_div(c.Hq);
+    c.by_G = fast_div(c.G);
+    c.D = desc->D;
+    c.W = W;
+    c.k = k;
+    c.rr = p.rr;
+    c.rank = desc->rank;
+    c.value_bias = (desc->flags & PIKV_DESC_VALUE_BIAS) ? 1 : 0;
+    c.tq = p.tq;
+    c.nsplit = plan.nsplit;
+    c.combine = combine;
+    c.decoder_bytes = reinterpret_cast<uintptr_t>(U_V) % 16 == 0 ? combine_decoder_bytes(c.rank, c.value_bias, c.D, elem_bytes(desc->dtype)) : 0;
+
     hipStream_t st = as_stream(stream);
     int lrc;
     if (g_prof_start) (void)hipEventRecord(g_prof_start, st);
-    if (plan.gqa_mfma) {
+    if (merged != nullptr) *merged = plan.small;
+    if (merged != nullptr && plan.small) {
+        lrc = desc->dtype == PIKV_F32 ? launch_small<float>(p, c, desc->B * desc->Hq, st) : launch_small<bf16>(p, c, desc->B * desc->Hq, st);
+    } else if (plan.gqa_mfma) {
         const size_t lds = p.stage_scores ? plan.score_stage_bytes : 0;
         const bool codes = desc->rank > 0;
         switch (W) {
@@ -1844,29 +2007,6 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
     if (g_prof_stop) (void)hipEventRecord(g_prof_stop, st);
     if (lrc != PIKV_OK) return lrc;
 
-    CombineParams c;
-    c.part_acc = part_acc;
-    c.part_ml = part_ml;
-    c.gates = gates;
-    c.U_V = U_V;
-    c.y = y;
-    c.row_max = row_max;
-    c.row_norm = row_norm;
-    c.slot_coef = slot_coef;
-    c.Hq = desc->Hq;
-    c.G = p.G;
-    c.by_Hq = fast_div(c.Hq);
-    c.by_G = fast_div(c.G);
-    c.D = desc->D;
-    c.W = W;
-    c.k = k;
-    c.rr = p.rr;
-    c.rank = desc->rank;
-    c.value_bias = (desc->flags & PIKV_DESC_VALUE_BIAS) ? 1 : 0;
-    c.tq = p.tq;
-    c.nsplit = plan.nsplit;
-    c.combine = combine;
-    c.decoder_bytes = reinterpret_cast<uintptr_t>(U_V) % 16 == 0 ? combine_decoder_bytes(c.rank, c.value_bias, c.D, elem_bytes(desc->dtype)) : 0;
     *c_out = c;
     return PIKV_OK;
 }
@@ -1899,10 +2039,11 @@ static int sharded_attn(const pikv_desc *desc, const void *q, const void *const 
                         void *workspace, size_t workspace_bytes, void *stream, size_t scratch_limit) {
     AttnPlan plan;
     CombineParams c;
+    bool merged = false;
     const int rc = launch_attn_partial(desc, q, K_shards, V_shards, U_K, U_V, n_valid, topk_idx, gates,
                                        k, combine, scale, y, row_max, row_norm, scores, slot_coef,
-                                       workspace, workspace_bytes, stream, nullptr, &plan, &c, scratch_limit);
-    if (rc != PIKV_OK || desc->B == 0) return rc;
+                                       workspace, workspace_bytes, stream, nullptr, &plan, &c, scratch_limit, &merged);
+    if (rc != PIKV_OK || desc->B == 0 || merged) return rc;
     return pikv_sharded_attn_merge(desc, &c, stream);
 }
 

@@ -291,8 +291,18 @@ __device__ __forceinline__ float4 tree_of_waves(const float4 *red) {
     }
 }
 
-template <typename T, int THREADS>
-__device__ __forceinline__ void combine_head(const CombineParams &p, int bh, unsigned char *smem) {
+// The router gate a thread of the merge weighs with: its shard's.
+__device__ __forceinline__ float combine_gate(const CombineParams &p, int bh) {
+    int h;
+    const int b = fast_divide(p.by_Hq, bh, &h);
+    const int shard = p.k <= kWaveShards ? (threadIdx.x & (kWave - 1)) >> 3 : threadIdx.x;
+    return p.gates != nullptr && shard < p.k ? p.gates[(int64_t)(b * p.rr + (p.rr == 1 ? 0 : h)) * p.k + shard] : 1.0f;
+}
+
+// `parts`, `pairs`: the head's k * nsplit accumulators and (max, sum) pairs; `gate()`: combine_gate, or what it gave before.
+template <typename T, int THREADS, class F>
+__device__ __forceinline__ void combine_head(const CombineParams &p, int bh, unsigned char *smem, const float *parts,
+                                             const float *ml, F gate_of) {
     int h, group_head;
     const int b = fast_divide(p.by_Hq, bh, &h);
     const int hk = fast_divide(p.by_G, h, &group_head);
@@ -313,9 +323,7 @@ __device__ __forceinline__ void combine_head(const CombineParams &p, int bh, uns
     const int cgroups = 1 << cbits;
     const int slices = THREADS >> cbits;         // partial slices
     const int cg = tid & (cgroups - 1), sl = tid >> cbits;
-    const float *acc = p.part_acc + (int64_t)bh * np * p.W + cg * 4;
-    const float *ml = p.part_ml + (int64_t)bh * np * 2;
-    const float *gates = p.gates != nullptr ? p.gates + (int64_t)(b * p.rr + (p.rr == 1 ? 0 : h)) * p.k : nullptr;
+    const float *acc = parts + cg * 4;
     const bool by_wave = p.k <= kWaveShards;
     const int lane = tid & (kWave - 1), wave = tid / kWave;
     const int shard = by_wave ? lane >> 3 : tid;
@@ -326,7 +334,7 @@ __device__ __forceinline__ void combine_head(const CombineParams &p, int bh, uns
         sp = shard_pairs_load(shard < p.k ? p.nsplit : 0, lane & 7,
                               [&](int s) { return *reinterpret_cast<const float2 *>(mine + 2 * s); });
     }
-    const float gate = gates != nullptr && shard < p.k ? gates[shard] : 1.0f;
+    const float gate = gate_of();
     float4 pre[kCombinePrefetch];
 #pragma unroll
     for (int u = 0; u < kCombinePrefetch; ++u) {
@@ -422,6 +430,12 @@ __device__ __forceinline__ void combine_head(const CombineParams &p, int bh, uns
     }
 }
 
+template <typename T, int THREADS>
+__device__ __forceinline__ void combine_head(const CombineParams &p, int bh, unsigned char *smem) {
+    const int64_t first = (int64_t)bh * p.k * p.nsplit;
+    combine_head<T, THREADS>(p, bh, smem, p.part_acc + first * p.W, p.part_ml + first * 2, [&] { return combine_gate(p, bh); });
+}
+
 // Host side (pikv_attn.hip).  check_attn_args: every host-side check of the attention call and
 // its split plan, nothing launched - a caller with earlier launches of its own (the step's
 // routing / insert kernel) rejects bad arguments before anything is enqueued.
@@ -434,14 +448,14 @@ int check_attn_args(const pikv_desc *desc, const void *q, const void *const *K_s
 bool profile_events_set();
 
 // launch_attn_partial: validate and plan - or take the plan that check_attn_args made for the same arguments -, launch the
-// split pass only, and fill the parameters of the merge pass.
+// split pass only, and fill the parameters of the merge pass.  With `merged` it may launch a kernel that merges as well, and says so.
 int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const *K_shards,
                         const void *const *V_shards, const void *U_K, const void *U_V,
                         const int32_t *n_valid, const int32_t *topk_idx, const float *gates,
                         int32_t k, int32_t combine, float scale, float *y, float *row_max,
                         float *row_norm, float *scores, float *slot_coef, void *workspace,
                         size_t workspace_bytes, void *stream, const AttnPlan *checked, AttnPlan *plan_out,
-                        CombineParams *c_out, size_t scratch_limit = SIZE_MAX);
+                        CombineParams *c_out, size_t scratch_limit = SIZE_MAX, bool *merged = nullptr);
 
 int pikv_sharded_attn_merge(const pikv_desc *desc, const CombineParams *c, void *stream);
 

@@ -238,6 +238,7 @@ struct AttnPlan {
     int chunk;            // rows per split (multiple of tile_rows)
     int nsplit;
     bool long_blocks;     // 128-value rows in blocks of up to 512 KiB (attn_partial_gqa<.., LONG>)
+    bool small;           // pikv_sharded_attn takes a head per block, merge included (attn_small)
     int resident_blocks;  // blocks of the split pass the GPU holds at once
     size_t score_stage_bytes;  // LDS per block for the raw scores (0: written straight to memory)
     size_t acc_floats;    // B*Hq*k*nsplit*width

@@ -1906,3 +1906,40 @@ def test_fused_step_with_feedback_on_both_sides_of_the_separate_merge(spec):
     for name in ("topk", "gates", "utility", "y", "row_max", "row_norm", "slot_coef", "load", "after"):
         np.testing.assert_array_equal(t2n(getattr(dA, name)), t2n(getattr(dB, name)), err_msg=name)
     assert t2n(dA.load).sum() == g.E * (g.E - 1) // 2 + g.B * g.k
+
+
+@pytest.mark.parametrize("spec,tile", [
+    (dict(B=1, Hq=4, Hkv=4, D=64, E=4, S=256, k=2, dtype="f32", per_head_routing=True), 32),       # 16 splits of a head
+    (dict(B=1, Hq=6, Hkv=2, D=64, E=12, S=32, k=12, dtype="f32", per_head_routing=True), 32),      # more shards than a wave holds
+    (dict(B=1, Hq=3, Hkv=3, D=128, E=6, S=81, k=2, dtype="bf16"), 32),                             # a last tile of 17 rows
+    (dict(B=1, Hq=2, Hkv=2, D=128, E=6, S=65, k=1, dtype="f32"), 16),                              # odd score rows
+    (dict(B=9, Hq=7, Hkv=7, D=16, E=8, S=128, k=3, dtype="bf16"), 128),                            # a tile per shard, many heads
+    (dict(B=2, Hq=2, Hkv=2, D=32, E=5, S=90, k=1, dtype="bf16"), 64),                              # fewer splits than merging waves
+], ids=lambda v: str(v) if isinstance(v, int) else "D%d_S%d_k%d_%s" % (v["D"], v["S"], v["k"], v["dtype"]))
+@pytest.mark.parametrize("combine", [orc.COMBINE_LSE, orc.COMBINE_LOCAL], ids=["lse", "local"])
+def test_smallest_calls_in_one_launch_equal_pass_and_merge(spec, tile, combine):
+    """A head per block, merge included, against the two kernels with the same splits forced: shards that hold nothing, one
+    entry, part of a tile and all of it, padded strides, a query that is not 16-byte aligned, infinite values; same bits."""
+    g = wl.Geometry(**spec)
+    nv = np.resize(np.array([0, 1, tile - 1, tile, tile + 1, g.S - 1, g.S], np.int32), (g.B, g.E)).clip(0, g.S)
+    case = wl.make_host_case(g, seed=91, n_valid=nv, utility0="exp")
+    inf, ninf = (np.inf, -np.inf) if g.dtype == "f32" else (0x7f80, 0xff80)      # (bf16 as bits)
+    case.V_shards[2][0, 0, 0] = inf
+    case.K_shards[3][0, :2, 0] = ninf
+    outs = []
+    for forced in (0, (g.S + tile - 1) // tile):
+        pk.pikv_set_attn_split(forced)
+        try:
+            dc = DeviceCase(case, stride_pad=(16, 5))
+            q = torch.zeros(dc.q.numel() + 1, device=DEV, dtype=dc.q.dtype)[1:].view(dc.q.shape)
+            q.copy_(dc.q)
+            dc.q = q
+            dc.route()
+            dc.attend(combine=combine)
+            outs.append({n: t2n(getattr(dc, n)).view(np.uint32) for n in ("y", "row_max", "row_norm", "slot_coef", "scores")})
+            dc.attend(combine=combine, want_scores=False)
+            np.testing.assert_array_equal(t2n(dc.y).view(np.uint32), outs[-1]["y"])
+        finally:
+            pk.pikv_set_attn_split(0)
+    for name, got in outs[0].items():
+        np.testing.assert_array_equal(got, outs[1][name], err_msg=name)
