@@ -199,22 +199,30 @@ int launch_utility(const pikv_desc *desc, const float *scores, const float *slot
     if (blocks > 0x7fffffff) return PIKV_ERR_UNSUPPORTED;
     const dim3 grid((unsigned)blocks), block(kUtilThreads);
     hipStream_t st = as_stream(stream);
-    auto launch = [&](auto tracks, auto spt, auto lines, auto batch) {
-        constexpr bool TRACK = decltype(tracks)::value, LINE = decltype(lines)::value;
+    auto launch = [&](auto tracks, auto spt, auto lines, auto token, auto batch) {
+        constexpr bool TRACK = decltype(tracks)::value, LINE = decltype(lines)::value, TOKEN = decltype(token)::value;
         constexpr int SPT = decltype(spt)::value, BATCH = decltype(batch)::value;
-        if (p.rr == 1) hipLaunchKernelGGL((utility_kernel<TRACK, SPT, LINE, true, BATCH>), grid, block, 0, st, p);
-        else hipLaunchKernelGGL((utility_kernel<TRACK, SPT, LINE, false, BATCH>), grid, block, 0, st, p);
+        hipLaunchKernelGGL((utility_kernel<TRACK, SPT, LINE, TOKEN, BATCH>), grid, block, 0, st, p);
     };
-    auto launch_wide = [&](auto tracks, auto batch) {
-        const std::integral_constant<int, 4> four{};
-        if (wide && line) launch(tracks, four, std::true_type{}, batch);
-        else if (wide) launch(tracks, four, std::false_type{}, batch);
-        else launch(tracks, std::integral_constant<int, 1>{}, std::false_type{}, batch);
+    const std::integral_constant<int, 4> four{};
+    const std::integral_constant<int, 1> one{};
+    auto launch_wide = [&](auto tracks, auto token, auto batch) {
+        if (wide && line) launch(tracks, four, std::true_type{}, token, batch);
+        else if (wide) launch(tracks, four, std::false_type{}, token, batch);
+        else launch(tracks, one, std::false_type{}, token, batch);
     };
+    const std::integral_constant<int, kUtilFewBatch> few{};
+    const std::integral_constant<int, kUtilBatch> several{};
+    const std::integral_constant<int, kUtilManyBatch> many{};
     auto launch_batch = [&](auto tracks) {
-        if (desc->Hq <= kUtilFewHeads) launch_wide(tracks, std::integral_constant<int, kUtilFewBatch>{});
-        else if (desc->Hq > kUtilManyHeads && !wide && p.rr == 1) launch(tracks, std::integral_constant<int, 1>{}, std::false_type{}, std::integral_constant<int, kUtilManyBatch>{});
-        else launch_wide(tracks, std::integral_constant<int, kUtilBatch>{});
+        if (p.rr != 1) {
+            if (desc->Hq <= kUtilFewHeads) launch_wide(tracks, std::false_type{}, few);
+            else launch_wide(tracks, std::false_type{}, several);
+        } else {
+            if (desc->Hq <= kUtilFewHeads) launch_wide(tracks, std::true_type{}, few);
+            else if (desc->Hq > kUtilManyHeads && !wide) launch(tracks, one, std::false_type{}, std::true_type{}, many);
+            else launch_wide(tracks, std::true_type{}, several);
+        }
     };
     if (track) launch_batch(std::true_type{});
     else launch_batch(std::false_type{});
