@@ -24,11 +24,15 @@ namespace {
 // there are many.  With the counts, the selections, the pairs and each group's scores requested one after the other - up to
 // seven trips - kernel trace: 10 sequences x 64 heads x 2 of 6 shards of 2560 slots 9.4 -> 4.8 us, 4 x 16 x 3 of 6
 // ragged ones of 1501 4.8 -> 3.2, 1 x 256 x 4 of 8192 9.6 -> 8.1; heads routed one by one: 23 x 128 x 2 of 32 of 1536
-// 27.2 -> 16.0, 1 x 4 x 2 of 4 of 256 3.1 -> 3.0, 24 x 32 x 2 of 16 of 2047 (unaligned rows) 10.1 -> 10.2.
+// 27.2 -> 16.0, 1 x 4 x 2 of 4 of 256 3.1 -> 3.0.
 constexpr int kUtilThreads = 256;
 constexpr int kUtilBatch = 8;           // heads whose scores are in flight per thread ...
 constexpr int kUtilFewBatch = 2;        // ... of up to kUtilFewHeads in all
 constexpr int kUtilFewHeads = 4 * kUtilFewBatch;
+// Heads routed one by one: those that meet a shard count, on average.  By all heads a block requested the same rows again and
+// again for a batch it could not fill (in a graph, with a batch of 8 and with the one for those met: 76 sequences x 48 heads x 1 of 64
+// shards of 61 slots 8.3 -> 6.2 us, 40 x 11 x 1 of 16 of 2363 10.2 -> 7.9, 24 x 32 x 2 of 16 of 2047 8.9 -> 6.2).
+constexpr int kUtilSomeBatch = 4, kUtilSomeHeads = 4 * kUtilSomeBatch;
 // Many heads in few blocks: a batch is a trip and what a CU has in flight bounds the rate (256 heads x 4 of 8192 slots, 32 MiB,
 // batches of 8 8.1 us, 16 7.3, 32 7.1; 128 heads 5.1, 4.85, 4.9).
 constexpr int kUtilManyHeads = 64, kUtilManyBatch = 16;
@@ -212,11 +216,14 @@ int launch_utility(const pikv_desc *desc, const float *scores, const float *slot
         else launch(tracks, one, std::false_type{}, token, batch);
     };
     const std::integral_constant<int, kUtilFewBatch> few{};
+    const std::integral_constant<int, kUtilSomeBatch> some{};
     const std::integral_constant<int, kUtilBatch> several{};
     const std::integral_constant<int, kUtilManyBatch> many{};
     auto launch_batch = [&](auto tracks) {
         if (p.rr != 1) {
-            if (desc->Hq <= kUtilFewHeads) launch_wide(tracks, std::false_type{}, few);
+            const int64_t met = ((int64_t)desc->Hq * k + desc->E - 1) / desc->E;      // heads that meet a shard, on average
+            if (met <= kUtilFewHeads) launch_wide(tracks, std::false_type{}, few);
+            else if (met <= kUtilSomeHeads) launch_wide(tracks, std::false_type{}, some);
             else launch_wide(tracks, std::false_type{}, several);
         } else {
             if (desc->Hq <= kUtilFewHeads) launch_wide(tracks, std::true_type{}, few);
