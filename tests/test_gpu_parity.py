@@ -1953,3 +1953,32 @@ def test_utility_update_by_the_heads_met_and_the_entries_held(spec):
     """Head-by-head batches of four and eight, a quarter's rows held by its lanes, shards that begin at another tile: utilities
     against the oracle over shards that hold nothing, one entry, a whole line of entries and one more, a tile's edge."""
     test_utility_update_of_every_form(spec)
+
+
+@pytest.mark.parametrize("E,per_head", [(4, False), (8, True)], ids=["token", "heads"])
+def test_utility_update_of_shards_that_hold_little(E, per_head):
+    """Up to nine entries in shards of 4096 slots, NaN in the scores behind them: no load past the last entry's 16 bytes is needed and none
+    is used; utilities of the entries against float64, the other slots as they were."""
+    g = wl.Geometry(B=40, Hq=32, Hkv=8, D=16, E=E, S=4096, k=2, dtype="bf16", per_head_routing=per_head)
+    rows = g.B * (g.Hq if per_head else 1)
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(3)
+    topk = torch.rand((rows, E), device=DEV, generator=gen).argsort(1)[:, :g.k].int().contiguous()
+    n_valid = torch.randint(0, 10, (g.B, E), device=DEV, generator=gen, dtype=torch.int32)
+    desc = pk.make_desc(g.B, g.Hq, g.Hkv, g.D, E, g.S, dtype=1, route_rows_per_seq=g.Hq if per_head else 1)
+    scores = torch.full((g.B, g.Hq, g.k, g.S), float("nan"), device=DEV)
+    scores[..., :10] = torch.randn((g.B, g.Hq, g.k, 10), device=DEV, generator=gen)
+    coef = torch.stack([torch.zeros((g.B, g.Hq, g.k), device=DEV),
+                        torch.rand((g.B, g.Hq, g.k), device=DEV, generator=gen)], -1).contiguous()
+    utility = torch.rand((g.B, E, g.S), device=DEV, generator=gen)
+    want = utility.double()
+    mass = torch.zeros_like(want)
+    p = coef[..., 1:].double() * scores[..., :10].double().exp()
+    sel = topk.long().view(g.B, -1, g.k).expand(g.B, g.Hq, g.k)
+    for b in range(g.B):
+        mass[b, :, :10].index_add_(0, sel[b].reshape(-1), p[b].reshape(-1, 10))
+    visited = torch.zeros((g.B, E), device=DEV, dtype=torch.bool).scatter_(1, sel.reshape(g.B, -1), True)
+    live = visited[..., None] & (torch.arange(g.S, device=DEV) < n_valid[..., None])
+    want = torch.where(live, 0.5 * want + mass, want)
+    pk.pikv_update_utility(desc, scores, coef, n_valid, topk, g.k, 0.5, utility)
+    np.testing.assert_allclose(t2n(utility), t2n(want), rtol=1e-5, atol=1e-7)
