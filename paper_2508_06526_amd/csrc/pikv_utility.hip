@@ -86,7 +86,7 @@ __global__ __launch_bounds__(kUtilThreads) void utility_kernel(UtilParams p) {
     // (one count per lane, the shard's own picked when it is needed: a load that is the same in all lanes is waited
     // for where it stands)
     const int n_of_lane = p.n_valid[(int64_t)b * p.E + min(lane, p.E - 1)];
-    int e = x, n, nact = p.Hq;
+    int e = x, n = 0, nact = p.Hq;
     if constexpr (TOKEN) {
         const int sel = p.topk[(int64_t)b * p.k + min(lane, p.k - 1)];
         e = __builtin_amdgcn_readlane(sel, x);
@@ -95,6 +95,10 @@ __global__ __launch_bounds__(kUtilThreads) void utility_kernel(UtilParams p) {
         n = __builtin_amdgcn_readlane(n_of_lane, e);
         if (i0 >= n) return;
     } else {
+        if constexpr (SPT == 4) {        // many blocks: those past the count don't wait for selections
+            n = __builtin_amdgcn_readlane(n_of_lane, e);
+            if (i0 >= n) return;
+        }
         constexpr int kSel = 4;          // selections requested at a time
         const int32_t *row = p.topk + ((int64_t)b * p.rr + min(tid, p.Hq - 1)) * p.k;
         int jj = -1;
@@ -105,8 +109,10 @@ __global__ __launch_bounds__(kUtilThreads) void utility_kernel(UtilParams p) {
 #pragma unroll
             for (int t = 0; t < kSel; ++t) jj = sel[t] == e ? min(j0 + t, p.k - 1) : jj;
         }
-        n = __builtin_amdgcn_readlane(n_of_lane, e);
-        if (i0 >= n) return;
+        if constexpr (SPT == 1) {
+            n = __builtin_amdgcn_readlane(n_of_lane, e);
+            if (i0 >= n) return;
+        }
         const bool active = tid < p.Hq && jj >= 0;
         const uint64_t mask = __ballot(active);
         if (lane == 0) wave_cnt[wave] = __popcll(mask);
