@@ -124,6 +124,7 @@ __global__ __launch_bounds__(kUtilThreads) void utility_kernel(UtilParams p) {
             if (w < wave) before += wave_cnt[w];
             nact += wave_cnt[w];
         }
+        nact = __builtin_amdgcn_readfirstlane(nact);
         if (nact == 0) return;
         if (active) head_row[before + __popcll(mask & ((1ull << lane) - 1ull))] = (b * p.Hq + tid) * p.k + jj;
         __syncthreads();
@@ -135,11 +136,13 @@ __global__ __launch_bounds__(kUtilThreads) void utility_kernel(UtilParams p) {
     const float shift = p.slot_coef[pair_at], coef = p.slot_coef[pair_at + 1];
     const int gsize = (nact + 3) / 4, lo = wave * gsize, hi = min(nact, lo + gsize);
     const int slot = LINE ? lane * SPT : lane;
+    // the quarter's rows, at most 64: one trip to LDS instead of one per batch (55 sequences x 256 heads, 2 shards of 80 slots, 6.25 -> 5.75 us)
+    const int row_of_lane = TOKEN ? 0 : head_row[min(lo + lane, nact - 1)];
     float sc[BATCH][SPT];
     auto fetch = [&](int t0) {           // (heads past the group's end and slots past the count are masked where they are used)
 #pragma unroll
         for (int u = 0; u < BATCH; ++u) {
-            const int row = __builtin_amdgcn_readfirstlane(row_of(min(t0 + u, nact - 1)));
+            const int row = TOKEN ? row_of(min(t0 + u, nact - 1)) : __builtin_amdgcn_readlane(row_of_lane, t0 - lo + u);
             const float *from = p.scores + (int64_t)row * p.S;
             if constexpr (LINE) {
                 // (no line past the last entry's: 35 x 128 x 10 of 16 of 780 slots, nearly empty, 26.8 us with whole tiles, now 13.1)
