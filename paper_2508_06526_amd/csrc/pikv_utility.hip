@@ -39,6 +39,12 @@ constexpr int kUtilManyHeads = 64, kUtilManyBatch = 16;
 // Four slots per thread once one slot per thread makes more blocks than this (24 sequences x 32 heads x 2 of 16 shards of 2048
 // slots, routed head by head, 17.4 us with one; the form before 13.6; now 9.4).
 constexpr int kUtilManyBlocks = 1024;
+// Head by head, from this many heads on, at twice the blocks: with 1024 - 2048 of them one slot per thread takes 0.87 of the time
+// of four where shards are nearly empty (0.62 at best), 1.00 where they are half full and 1.04 where they are full (250 random shapes).
+// Per token the line stays: full shards gain 1.2 from four slots (16 sequences x 128 heads x 4 of 16 shards of 4096 slots 23.2 us,
+// in blocks of 64 slots 25.6), nearly empty ones lose where few blocks are left (85 x 224 x 2 of 2 of 1888, a sixteenth
+// full, 17.4 against 10.3), and the host does not see the counts.
+constexpr int kUtilSparseHeads = 128;
 
 struct UtilParams {
     const float *scores;
@@ -208,7 +214,7 @@ int launch_utility(const pikv_desc *desc, const float *scores, const float *slot
     p.rr = desc->route_rows_per_seq;
     const int shards = p.rr == 1 ? k : desc->E;
     auto blocks_of = [&](int slots) { return (int64_t)desc->B * shards * ((desc->S + slots - 1) / slots); };
-    const bool wide = blocks_of(kUtilThreads / 4) > kUtilManyBlocks;
+    const bool wide = blocks_of(kUtilThreads / 4) > (p.rr != 1 && desc->Hq >= kUtilSparseHeads ? 2 : 1) * kUtilManyBlocks;
     const bool line = desc->S % 4 == 0 && reinterpret_cast<uintptr_t>(scores) % 16 == 0;
     const int tile_slots = wide ? kUtilThreads : kUtilThreads / 4;
     p.by_tiles = fast_div((desc->S + tile_slots - 1) / tile_slots);

@@ -1949,8 +1949,10 @@ def test_smallest_calls_in_one_launch_equal_pass_and_merge(spec, tile, combine):
     dict(B=6, Hq=24, Hkv=8, D=16, E=6, S=2050, k=3, dtype="bf16", per_head_routing=True),     # 12 heads meet a shard; 9 tiles, the last of 2
     dict(B=5, Hq=40, Hkv=8, D=16, E=4, S=4092, k=2, dtype="bf16", per_head_routing=True),     # 20 heads; 16 tiles, aligned rows
     dict(B=2, Hq=256, Hkv=32, D=16, E=2, S=67, k=2, dtype="bf16", per_head_routing=True),     # quarters of 64 heads
+    dict(B=1, Hq=130, Hkv=2, D=16, E=6, S=14000, k=1, dtype="bf16", per_head_routing=True),   # one slot per thread past 1024 blocks
+    dict(B=3, Hq=130, Hkv=2, D=16, E=6, S=7420, k=1, dtype="bf16", per_head_routing=True),    # four
     dict(B=9, Hq=9, Hkv=9, D=16, E=8, S=2048, k=8, dtype="bf16"),                             # every shard, 8 tiles
-], ids=["met12", "met20", "heads256", "turned"])
+], ids=["met12", "met20", "heads256", "narrow", "wide", "turned"])
 def test_utility_update_by_the_heads_met_and_the_entries_held(spec):
     """Head-by-head batches of four and eight, a quarter's rows held by its lanes, shards that begin at another tile: utilities
     against the oracle over shards that hold nothing, one entry, a whole line of entries and one more, a tile's edge."""
