@@ -7,13 +7,14 @@ and returns nothing but the status check.  No arithmetic happens here.
 The calls of a step are made by the extension _pikv_native (csrc/pikv_binding.cpp): eager passes over small caches are bound
 by their calls, and ctypes with its attribute lookups took 4 - 5 us of each.  Arguments that are not of the ordinary kind -
 tensor subclasses, numpy numbers, what has to be refused - come back from it as None with nothing launched and take the
-ctypes path below.
+ctypes path below, and so does every call where the extension is not there.
 """
 from __future__ import annotations
 
 import ctypes as C
 import importlib.util
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 _LIB_PATH = os.path.join(_HERE, "libpikv.so")
@@ -120,15 +121,31 @@ def load_library():
     lib.pikv_set_attn_split.restype = None
     lib.pikv_version.argtypes = []
     lib.pikv_version.restype = C.c_int
-    if not os.path.exists(_NATIVE_PATH):
-        raise OSError("_pikv_native.so is not built: run `python -m paper_2508_06526_amd.build`")
-    spec = importlib.util.spec_from_file_location("_pikv_native", _NATIVE_PATH)
-    native = importlib.util.module_from_spec(spec)
-    spec.loader.exec_module(native)
-    native.setup(PikvDesc, PikvPolicyArgs, PikvRouterFeedback,
-                 {name: C.cast(getattr(lib, name), C.c_void_p).value for name in EXPORTS})
+    native = _load_native({name: C.cast(getattr(lib, name), C.c_void_p).value for name in EXPORTS})
     _lib, _native = lib, native
     return lib
+
+
+class _NoExtension:
+    """In place of an extension that is not there: leaves every call to the ctypes path."""
+
+    def __getattr__(self, name):
+        return lambda *args: None
+
+
+def _load_native(addresses):
+    """The extension is tied to the Python and torch it was built against, libpikv.so to neither: without the extension the
+    same kernels run, at 4 - 5 us more host time per call."""
+    try:
+        spec = importlib.util.spec_from_file_location("_pikv_native", _NATIVE_PATH)
+        native = importlib.util.module_from_spec(spec)
+        spec.loader.exec_module(native)
+    except (ImportError, OSError) as e:
+        warnings.warn("calls go through ctypes: _pikv_native.so is not built for this Python and torch (%s); "
+                      "run `python -m paper_2508_06526_amd.build`" % e, RuntimeWarning, stacklevel=3)
+        return _NoExtension()
+    native.setup(PikvDesc, PikvPolicyArgs, PikvRouterFeedback, addresses)
+    return native
 
 
 def _dtype_code(t) -> int:
@@ -141,7 +158,7 @@ def _dtype_code(t) -> int:
 
 
 def _calls():
-    """The extension that makes the calls; loads the library if nothing has."""
+    """What makes the calls: the extension, or what stands in for it; loads the library if nothing has."""
     if _native is None:
         load_library()
     return _native

@@ -272,3 +272,28 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(binding, "_LIB_PATH", str(tmp_path / "nope.so"))
     with pytest.raises(OSError):
         binding.load_library()
+
+
+@pytest.mark.parametrize("kind", ["absent", "unloadable"])
+def test_binding_without_its_extension_takes_the_ctypes_path(tmp_path, monkeypatch, kind):
+    """The extension belongs to one Python and one torch; where it is not there or does not load, libpikv.so alone is enough: every
+    call goes through ctypes, which refuses host memory here as it always has."""
+    import torch
+
+    from paper_2508_06526_amd import binding
+    path = tmp_path / "_pikv_native.so"
+    if kind == "unloadable":
+        path.write_bytes(b"built for another Python")
+    monkeypatch.setattr(binding, "_NATIVE_PATH", str(path))
+    monkeypatch.setattr(binding, "_lib", None)
+    monkeypatch.setattr(binding, "_native", None)
+    with pytest.warns(RuntimeWarning, match="_pikv_native"):
+        lib = binding.load_library()
+    assert lib.pikv_version() >= 100
+    x = torch.zeros((2, 8))
+    with pytest.raises(ValueError, match="device memory"):
+        binding.pikv_route(x, x, None, 2, 8, 4, 2, x, x)
+    desc = binding.make_desc(0, 4, 4, 64, 4, 16)             # no sequences: a checked call that launches nothing
+    binding._check(lib.pikv_append(desc, 16, 16, 16, 2, None, None, 0, 16, 16, 16, 16, None), "pikv_append")
+    for name in binding.EXPORTS:
+        assert getattr(binding._calls(), name)(1, 2, 3) is None
