@@ -1976,8 +1976,10 @@ int launch_attn_partial(const pikv_desc *desc, const void *q, const void *const 
     hipStream_t st = as_stream(stream);
     int lrc;
     if (g_prof_start) (void)hipEventRecord(g_prof_start, st);
-    if (merged != nullptr) *merged = plan.small;
-    if (merged != nullptr && plan.small) {
+    // (an event pair stands around the split pass alone: two launches then, of the same bits)
+    const bool small = merged != nullptr && plan.small && !profile_events_set();
+    if (merged != nullptr) *merged = small;
+    if (small) {
         lrc = desc->dtype == PIKV_F32 ? launch_small<float>(p, c, desc->B * desc->Hq, st) : launch_small<bf16>(p, c, desc->B * desc->Hq, st);
     } else if (plan.gqa_mfma) {
         const size_t lds = p.stage_scores ? plan.score_stage_bytes : 0;

@@ -1986,3 +1986,30 @@ def test_utility_update_of_shards_that_hold_little(E, per_head):
     want = torch.where(live, 0.5 * want + mass, want)
     pk.pikv_update_utility(desc, scores, coef, n_valid, topk, g.k, 0.5, utility)
     np.testing.assert_allclose(t2n(utility), t2n(want), rtol=1e-5, atol=1e-7)
+
+
+def test_profile_events_bracket_the_split_pass_where_one_launch_could_merge_too():
+    """The event pair stands around the kernel that streams K and V and nothing else: while it is installed a smallest call is
+    the pass - which leaves its partials in the workspace - and the merge, with the same results."""
+    g = wl.Geometry(B=2, Hq=4, Hkv=4, D=64, E=4, S=96, k=2, dtype="f32", per_head_routing=True)
+    case = wl.make_host_case(g, seed=17, n_valid="ragged")
+    dc = DeviceCase(case)
+    dc.route()
+    names = ("y", "row_max", "row_norm", "slot_coef")
+    dc.workspace.fill_(0xa5)
+    dc.attend()
+    plain = {n: t2n(getattr(dc, n)) for n in names}
+    assert bool((dc.workspace == 0xa5).all())                 # one launch: the workspace is not used
+    start, stop = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+    start.record()
+    stop.record()
+    pk.pikv_set_profile_events(start, stop)
+    try:
+        dc.attend()
+        torch.cuda.synchronize()
+    finally:
+        pk.pikv_set_profile_events(None, None)
+    assert not bool((dc.workspace == 0xa5).all())
+    assert start.elapsed_time(stop) > 0
+    for n in names:
+        np.testing.assert_array_equal(t2n(getattr(dc, n)), plain[n], err_msg=n)
