@@ -1838,6 +1838,8 @@ def test_the_binding_takes_what_it_took_and_refuses_what_it_refused():
 
     def route(x, W, rows=g.B, k=g.k, stream=None):
         topk, gates = torch.zeros((g.B, g.k), device=DEV, dtype=torch.int32), torch.zeros((g.B, g.k), device=DEV)
+        if stream is not None:
+            stream.wait_stream(torch.cuda.current_stream())           # (behind the two fills)
         pk.pikv_route(x, W, None, rows, g.d_r, g.E, k, topk, gates, stream=stream)
         out.append((t2n(topk), t2n(gates)))
 
@@ -1852,8 +1854,8 @@ def test_the_binding_takes_what_it_took_and_refuses_what_it_refused():
 
     route(x.as_subclass(Marked), dc.W_r)
     other = torch.cuda.Stream()
-    other.wait_stream(torch.cuda.current_stream())
     route(x, dc.W_r, stream=other)
+    other.wait_stream(torch.cuda.current_stream())
     with torch.cuda.stream(other):
         route(x, dc.W_r)
         torch.cuda.current_stream().synchronize()
@@ -2013,3 +2015,81 @@ def test_profile_events_bracket_the_split_pass_where_one_launch_could_merge_too(
     assert start.elapsed_time(stop) > 0
     for n in names:
         np.testing.assert_array_equal(t2n(getattr(dc, n)), plain[n], err_msg=n)
+
+
+def test_every_call_of_the_extension_goes_to_the_stream_it_is_given(monkeypatch):
+    """All its entry points with a stream as an argument that is being captured, another one current: nothing runs until the
+    graph does, and the graph runs them all.  The ctypes path is closed meanwhile."""
+    g = wl.Geometry(B=2, Hq=4, Hkv=2, D=64, E=4, S=48, k=2, dtype="f32", rank=16)
+    case = wl.make_host_case(g, seed=23, n_valid="ragged", utility0="exp", w_sigma=0.3)
+    case.n_valid[0, :2] = g.S
+    gen = torch.Generator(device=DEV)
+    gen.manual_seed(5)
+    full = [torch.randn((g.B, g.Hkv, g.D), device=DEV, generator=gen) for _ in range(2)]
+    enc = [torch.randn((g.Hkv, g.rank, g.D), device=DEV, generator=gen) / 8 for _ in range(2)]
+    i32 = dict(device=DEV, dtype=torch.int32)
+
+    def state():
+        dc = DeviceCase(case)
+        s = dict(dc.__dict__)
+        s.update(new_K=torch.zeros((g.B, g.Hkv, g.rank), device=DEV), new_V=torch.zeros((g.B, g.Hkv, g.rank), device=DEV),
+                 value=torch.zeros((g.B, g.E, g.S), device=DEV), eidx=torch.zeros((g.B, g.E, 1), **i32), ecnt=torch.zeros((g.B, g.E), **i32),
+                 y2=torch.zeros_like(dc.y), load=torch.zeros(g.E, **i32), after=torch.zeros(g.E, device=DEV),
+                 load2=torch.zeros(g.E, **i32), after2=torch.zeros(g.E, device=DEV),
+                 first=torch.zeros((g.B, g.E, 1), **i32), one=torch.ones((g.B, g.E), **i32), left=torch.full((g.B, g.E), g.S - 1, **i32),
+                 topk3=torch.zeros_like(dc.topk), topk4=torch.zeros_like(dc.topk), y3=torch.zeros_like(dc.y), y4=torch.zeros_like(dc.y))
+        for name in ("birth", "last", "freq", "birth2", "last2", "freq2"):
+            s[name] = (torch.arange(g.B * g.E * g.S, **i32) * 7 % 50).reshape(g.B, g.E, g.S)
+        return s
+
+    def calls(s, stream):
+        d, k = s["desc"], g.k
+        attn = (d, s["q"], s["K_tab"], s["V_tab"], s["U_K"], s["U_V"], s["n_valid"], s["topk"], s["gates"], k, pk.COMBINE_LSE, 0.0)
+        pk.pikv_compress(d, full[0], enc[0], s["new_K"], full[1], enc[1], s["new_V"], stream=stream)
+        pk.pikv_route(s["q"], s["W_r"], None, g.B, g.d_r, g.E, k, s["topk"], s["gates"], s["probs"], stream=stream)
+        pk.pikv_policy_utility(d, pk.POLICY_LRU_PLUS, s["n_valid"], 60, 0.5, 0, 0, s["birth"], s["last"], s["freq"], None, s["value"],
+                               stream=stream)
+        pk.pikv_evict(d, s["value"], s["n_valid"], g.S - 1, s["topk"], k, s["eidx"], s["ecnt"], 1, False, None, None, stream=stream)
+        pk.pikv_policy_stamp(d, s["topk"], k, s["eidx"], s["ecnt"], 1, s["n_valid"], 60, s["birth"], s["last"], s["freq"], stream=stream)
+        pk.pikv_append(d, s["new_K"], s["new_V"], s["topk"], k, s["eidx"], s["ecnt"], 1, s["K_tab"], s["V_tab"], s["utility"],
+                       s["n_valid"], stream=stream)
+        pk.pikv_sharded_attn(*attn, s["y"], s["row_max"], s["row_norm"], s["scores"], s["slot_coef"], s["workspace"], stream=stream)
+        pk.pikv_sharded_attn_noalloc(*attn, s["y2"], None, None, None, None, stream=stream)
+        pk.pikv_update_utility(d, s["scores"], s["slot_coef"], s["n_valid"], s["topk"], k, 0.9, s["utility"], stream=stream)
+        pk.pikv_update_utility_tracked(d, s["scores"], s["slot_coef"], s["n_valid"], s["topk"], k, 0.9, None, 0.01, 60, s["last"],
+                                       s["freq"], stream=stream)
+        pk.pikv_policy_compact(d, s["first"], s["one"], 1, s["left"], s["birth2"], s["last2"], s["freq2"], stream=stream)
+        pk.pikv_router_penalty(pk.PENALTY_LOAD_BALANCE, s["topk"], g.B, k, g.E, s["load"], None, 0.01, s["after"], stream=stream)
+        step = (d, s["q"], s["W_r"], None, None, None, s["K_tab"], s["V_tab"], s["U_K"], s["U_V"], s["n_valid"], s["utility"], k,
+                pk.COMBINE_LSE, 0.0, 0.9)
+        rest = (s["row_max"], s["row_norm"], s["scores"], s["slot_coef"], s["workspace"])
+        pk.pikv_decode_step(*step, s["topk3"], s["gates"], None, None, s["y3"], *rest, stream=stream)
+        pk.pikv_decode_step_policy(*step, s["topk4"], s["gates"], None, None, s["y4"], *rest,
+                                   pk.make_policy_args(pk.POLICY_LRU, 61, threshold=0.01, birth=s["birth"], last_access=s["last"],
+                                                       freq=s["freq"]),
+                                   feedback=pk.make_router_feedback(pk.PENALTY_LOAD_BALANCE, 0.01, s["load2"], s["after2"]), stream=stream)
+
+    def bits(s):
+        return {n: t2n(t).view(np.uint8) for n, t in s.items() if isinstance(t, torch.Tensor) and n != "workspace" and not n.endswith("_tab")}
+
+    eager, captured = state(), state()
+    before = bits(captured)
+    calls(state(), torch.cuda.current_stream())                # the kernels are loaded and the noalloc array is found
+    torch.cuda.synchronize()
+    graph, other, third = torch.cuda.CUDAGraph(), torch.cuda.Stream(), torch.cuda.Stream()
+    assert other.cuda_stream != third.cuda_stream
+    with monkeypatch.context() as m:
+        m.setattr(pk.binding, "load_library", lambda: pytest.fail("a call went through ctypes"))
+        with torch.cuda.graph(graph, stream=other), torch.cuda.stream(third):
+            calls(captured, other)
+    for name, a in bits(captured).items():
+        np.testing.assert_array_equal(a, before[name], err_msg=name)
+    changed = set()
+    for _ in range(3):
+        graph.replay()
+        calls(eager, None)
+        got, want = bits(captured), bits(eager)
+        for name in want:
+            np.testing.assert_array_equal(got[name], want[name], err_msg=name)
+        changed |= {name for name in want if not np.array_equal(want[name], before[name])}
+    assert {"new_K", "topk", "value", "ecnt", "birth", "K", "y", "y2", "utility", "freq", "birth2", "load", "y3", "y4", "load2"} <= changed
