@@ -297,9 +297,9 @@ __global__ __launch_bounds__(THREADS) void merge_with_penalty(CombineParams c, P
 // in blocks of 1024 9.9 and 4.1 + 4.2; the other side of the line: 64 x 4 7.1 against 4.0 + 3.7, 16 sequences 10.4 against
 // 4.7 + 4.8, 128 x 2 in blocks of 256 9.5 against 4.6 + 4.2, 32 sequences 12.9 against 8.5 + 5.3, 16 x 16 5.6 against 4.4 + 3.1.
 constexpr int kPostMostPairs = 256;
-constexpr int kPostMostHeads = 64;
+constexpr int kPostMostHeads = 255, kPostMostHeadsOf1024 = 64;
 inline bool post_separate(int Hq, int k, int np) {
-    return (int64_t)Hq * k > kPostMostPairs || Hq >= kPostMostPairs || (combine_threads(np) == 1024 && Hq > kPostMostHeads);
+    return (int64_t)Hq * k > kPostMostPairs || Hq > (combine_threads(np) == 1024 ? kPostMostHeadsOf1024 : kPostMostHeads);
 }
 
 constexpr int kPostPrefetchHeads = 8;  // score loads each thread issues before the statistics
@@ -370,9 +370,9 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     extern __shared__ __attribute__((aligned(16))) unsigned char smem[];   // post_smem_bytes()
     const int Hq = p.c.Hq, k = p.c.k, nsplit = p.c.nsplit;
     const int ncomb = p.B * Hq;
-    // Blocks are dispatched in id order.  With hundreds of query rows the utility blocks are
-    // the long ones and a CU holds one block of either kind: they then take the first ids,
-    // so that they do not queue behind the merge blocks.
+    // Blocks are dispatched in id order.  With more than 64 pairs, or 17 heads and more per thread, the utility
+    // blocks are the long ones: they take the first ids, so that they do not queue behind the merge blocks.
+    // (Blocks of 1024 threads never have as many: post_separate.)
     const bool util_first = (MODE == kPostMany || kOwnHeads) && p.util_first;
     const int mb = util_first ? (int)blockIdx.x - p.B * k * p.tiles : (int)blockIdx.x;
     if (mb >= 0 && mb < ncomb) {
@@ -471,9 +471,9 @@ __global__ __launch_bounds__(THREADS) void step_post(PostParams p) {
     auto pair_of = [&](int t) {
         return [=](int sp) { return *reinterpret_cast<const float2 *>(ml + 2 * ((int64_t)t * nsplit + sp)); };
     };
-    // With more pairs than groups of 8 lanes the statistics take several passes (kPostMany: 8
-    // at 256 rows and 4 shards), each a round trip to L2 if taken one after the other: the
-    // pairs of kPostStatsAhead passes are requested ahead, and a pass that is done requests
+    // With more pairs than groups of 8 lanes the statistics take several passes (kPostMany, blocks of 256
+    // threads over more than 8 shards: up to 8 of them for 256 pairs), each a round trip to L2 if taken one after
+    // the other: the pairs of kPostStatsAhead passes are requested ahead, and a pass that is done requests
     // those of the pass kPostStatsAhead later.
     constexpr int kAhead = MODE == kPostMany ? kPostStatsAhead : 1;
     constexpr int kPairsPerPass = THREADS / 8;
@@ -840,7 +840,7 @@ static int decode_step(const pikv_desc *desc, const void *q, const void *W_r, co
     // blocks of 1024 threads only where the loop-free shape takes it: the others would spill)
     bool wide = (int64_t)desc->B * k * tiles_of(threads / 4) > want_blocks && desc->S % 4 == 0 &&
                 reinterpret_cast<uintptr_t>(scores) % 16 == 0;
-    if (threads == 1024 && (many || tiles_per_block(tiles_of(threads)) > 1)) wide = false;
+    if (threads == 1024 && tiles_per_block(tiles_of(threads)) > 1) wide = false;
     const int64_t slot_tiles = tiles_of(wide ? threads : threads / 4);
     const int64_t tpb = tiles_per_block(slot_tiles);
     pp.tiles_per_block = (int)tpb;
