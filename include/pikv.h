@@ -214,9 +214,10 @@ int pikv_append(const pikv_desc *desc, const void *K_new, const void *V_new,
                 const int32_t *reuse_cnt, int32_t max_evict, void *const *K_shards,
                 void *const *V_shards, float *utility, int32_t *n_valid, void *stream);
 
-/* One iteration of Algorithm 1's loop in three launches instead of six (four from 256 query
- * rows per sequence on, where the merge and the utility update are faster apart; per-token routing
- * only): route q -> for every selected shard that is full evict its minimum-utility entry
+/* One iteration of Algorithm 1's loop in three launches instead of six (four where a sequence has
+ * more than 256 (query row, selected shard) pairs or 255 query rows, or more than 64 query rows with more
+ * than 32 partial results each: the merge and the utility update are faster apart there;
+ * per-token routing only): route q -> for every selected shard that is full evict its minimum-utility entry
  * (order: utility ascending, then higher slot first) -> insert the new token's rows there
  * (or at slot n_valid if the shard has room) -> attention over the selected shards (new
  * entry included) -> utility update.  Results are exactly those of the call sequence
@@ -322,11 +323,11 @@ int pikv_policy_utility(const pikv_desc *desc, int32_t policy, const int32_t *n_
                         float lambda, int32_t window, int32_t protect, const int32_t *birth,
                         const int32_t *last_access, const int32_t *freq, const float *h2o,
                         float *out, void *stream);
-/* Router feedback inside the fused step: with a pikv_router_feedback the step's last launch also
+/* Router feedback inside the fused step: with a pikv_router_feedback the launch that merges also
  * does what pikv_router_penalty(mode, this step's topk_idx, ...) would do after the step - adds
  * the selections to `load` and writes the penalty for the NEXT step to `bias` - so that closing
  * the loop costs no launch of its own.  `bias` may be the array the step itself was given as its
- * routing bias (it is read by the step's first launch and written by its last).              */
+ * routing bias (it is read by the step's first launch and written behind it).                */
 typedef struct {
     int32_t mode;          /* pikv_penalty */
     float coef;
@@ -341,7 +342,7 @@ typedef struct {
  *   pikv_evict(scratch, capacity = S-1, sel_idx = topk_idx, max_evict = 1, compact = 0);
  *   pikv_policy_stamp; pikv_append; pikv_sharded_attn;
  *   pikv_update_utility_tracked(decay, utility, threshold, now, last_access, freq)
- * in the same three launches as pikv_decode_step, with no scratch utility: the entry to evict
+ * in the same three or four launches as pikv_decode_step, with no scratch utility: the entry to evict
  * is chosen on the policy's value computed on the fly (bit-identical to the separate calls).
  * Arrays the policy does not read may be NULL; the new entry is stamped in those given; access
  * bookkeeping runs when last_access and freq are both given (threshold >= 0).  `utility` keeps
@@ -381,7 +382,8 @@ void pikv_set_attn_split(int32_t nsplit);
  * later pikv_sharded_attn / pikv_decode_step call records on its stream immediately before and
  * after launching the split attention pass - the kernel that streams the K/V bytes - so that a
  * caller can time exactly that kernel in its real context with hipEventElapsedTime.  NULL, NULL
- * switches it off (the default).  Process-wide, not thread-safe.  While a pair is installed
+ * switches it off (the default).  Process-wide, not thread-safe.  While a pair is installed the smallest
+ * calls of pikv_sharded_attn, one launch otherwise, take the pass and the merge apart (same bits), and
  * pikv_decode_step refuses (INVALID) a stream that is being captured into a graph: the records
  * would replay with the graph.                                                             */
 void pikv_set_profile_events(void *start_event, void *stop_event);

@@ -174,7 +174,8 @@ inline __host__ __device__ int combine_np_pad(int np) { return (np + 3) & ~3; }
 // rows of [np] floats: a wave's own weights each, or the weights and the sums they come from
 inline __host__ __device__ constexpr int combine_weight_copies(int threads) { return threads == 256 ? 4 : 2; }
 // The value decoder's rows of a kv head go to LDS with the block's first requests where they are at most this many bytes -
-// every bf16 decoder, fp32 ones up to rank 32; read column by column behind the sums they are a trip of their own.
+// every bf16 decoder, the largest of which it is; fp32 ones of rank 32 over 128 values without the additive row, of rank 64 over 64
+// with or without it; read column by column behind the sums the others are a trip of their own.
 constexpr int kDecoderBytesMost = 65 * 128 * 2;
 inline int combine_decoder_bytes(int rank, int value_bias, int D, int elem) {
     const int bytes = (rank + value_bias) * D * elem;

@@ -9,7 +9,8 @@
 //                trip; the new rows are fetched before the router result exists.
 //   attention  : the split flash-decode pass over the selected shards (pikv_attn.hip).
 //   step_post  : merge of the split partials with the router gates and the utility update
-//                u <- decay * u + attention mass (Section 3.4, Table 3 H2O), in one launch.
+//                u <- decay * u + attention mass (Section 3.4, Table 3 H2O), in one launch
+//                (two with many (head, shard) pairs: post_separate).
 //
 // With a scheduling policy (Table 3 rows SL, LRU, LRU+) step_pre takes its minimum over the
 // policy's value, computed on the fly from the per-entry stamps and counts, and stamps the
