@@ -2093,3 +2093,111 @@ def test_every_call_of_the_extension_goes_to_the_stream_it_is_given(monkeypatch)
             np.testing.assert_array_equal(got[name], want[name], err_msg=name)
         changed |= {name for name in want if not np.array_equal(want[name], before[name])}
     assert {"new_K", "topk", "value", "ecnt", "birth", "K", "y", "y2", "utility", "freq", "birth2", "load", "y3", "y4", "load2"} <= changed
+
+
+@pytest.mark.parametrize("spec,shift", [
+    (dict(B=3, Hq=4, Hkv=2, D=128, E=4, S=160, k=2, dtype="f32", rank=32), 0),      # 16896 bytes with the row: just too large for LDS
+    (dict(B=2, Hq=4, Hkv=4, D=128, E=4, S=160, k=3, dtype="f32", rank=64), 0),
+    (dict(B=2, Hq=4, Hkv=4, D=64, E=4, S=160, k=2, dtype="f32", rank=64), 0),       # 16640: the largest that fits
+    (dict(B=2, Hq=4, Hkv=2, D=128, E=4, S=160, k=2, dtype="bf16", rank=32), 3),     # not aligned for it
+    (dict(B=2, Hq=4, Hkv=4, D=32, E=12, S=64, k=9, dtype="f32", rank=16), 1),       # weights by the whole block
+], ids=["f32_r32", "f32_r64", "f32_r64_fits", "shifted", "k9_shifted"])
+@pytest.mark.parametrize("splits", [1, 20], ids=["256", "1024"])
+def test_additive_row_of_decoders_read_from_memory(spec, shift, splits):
+    """The decoder's additive term where the merge reads the decoder where it is, by blocks of 256 and of 1024 threads (20 splits a shard), a
+    sequence of empty shards among the others; y against the oracle, the fused step bit for bit against the separate calls."""
+    from gpu_harness import dev_storage
+    g = wl.Geometry(**spec)
+    case = wl.make_host_case(g, seed=63, n_valid="ragged", utility0="exp", w_sigma=0.05)
+    case.n_valid[-1, :] = 0
+    ensure_route_margin(case, g.k)
+    b_V = wl.encode(np.random.default_rng(64).standard_normal((g.Hkv, g.D)), g.dtype)
+    rows = dev_storage(np.ascontiguousarray(np.concatenate([case.U_V, b_V[:, None, :]], axis=1)), g.dtype)
+    pk.pikv_set_attn_split(splits)
+    try:
+        dA, dB = DeviceCase(case), DeviceCase(case)
+        for d in (dA, dB):
+            d.U_V = torch.cat([rows.new_zeros(shift), rows.flatten()])[shift:].view(rows.shape)
+            assert (d.U_V.data_ptr() % 16 != 0) == (shift != 0)
+            d.desc = pk.make_desc(g.B, g.Hq, g.Hkv, g.D, g.E, g.S, rank=g.rank, dtype=pk.binding.F32 if g.dtype == "f32" else pk.binding.BF16,
+                                  stride_h=d.stride_h, stride_s=d.stride_s, flags=pk.DESC_VALUE_BIAS)
+        dB.route()
+        dB.attend()
+        dB.update_utility(0.9)
+        pk.pikv_decode_step(dA.desc, dA.q, dA.W_r, dA.bias, None, None, dA.K_tab, dA.V_tab, dA.U_K, dA.U_V, dA.n_valid, dA.utility, g.k,
+                            pk.COMBINE_LSE, 0.0, 0.9, dA.topk, dA.gates, None, None, dA.y, dA.row_max, dA.row_norm, dA.scores,
+                            dA.slot_coef, dA.workspace)
+    finally:
+        pk.pikv_set_attn_split(0)
+    ref = orc.attend(case.q, case.K_shards, case.V_shards, case.n_valid, t2n(dB.topk), t2n(dB.gates), Hkv=g.Hkv, E=g.E, S=g.S,
+                     dtype=g.dtype, rank=g.rank, U_K=case.U_K, U_V=case.U_V, V_bias=b_V, combine=orc.COMBINE_LSE)
+    ok, emax, l2 = y_tolerance_ok(t2n(dB.y), ref["y"], g.dtype)
+    assert ok, (emax, l2)
+    assert (t2n(dB.y)[-1] == 0).all()
+    for name in ("topk", "gates", "utility", "y", "row_max", "row_norm", "slot_coef"):
+        np.testing.assert_array_equal(t2n(getattr(dA, name)), t2n(getattr(dB, name)), err_msg=name)
+
+
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("D", [16, 32])
+@pytest.mark.parametrize("rank", [16, 64])
+def test_compress_of_short_heads(D, rank, dtype):
+    """Heads of 16 and 32 values, where most of a lane's chunks lie past the row's end, in one pass of code elements and in two;
+    keys and values in one launch.  The bounds are test_compress_matches_oracle's: 16 to 32 products, summed in another order."""
+    from gpu_harness import dev_storage
+    g = wl.Geometry(B=5, Hq=3, Hkv=3, D=D, E=2, S=8, k=1, dtype=dtype, rank=rank)
+    rng = np.random.default_rng(10)
+    desc = pk.make_desc(g.B, g.Hq, g.Hkv, D, g.E, g.S, rank=rank, dtype=pk.binding.F32 if dtype == "f32" else pk.binding.BF16)
+    x = [wl.encode(rng.standard_normal((g.B, g.Hkv, D)), dtype) for _ in range(2)]
+    W = [wl.encode(rng.standard_normal((g.Hkv, rank, D)) / np.sqrt(D), dtype) for _ in range(2)]
+    tail = 64                                                 # values behind the codes that must stay
+    out = [torch.full((g.B * g.Hkv * rank + tail,), 7.0, device=DEV, dtype=torch.float32 if dtype == "f32" else torch.bfloat16) for _ in range(2)]
+    pk.pikv_compress(desc, dev_storage(x[0], dtype), dev_storage(W[0], dtype), out[0], dev_storage(x[1], dtype), dev_storage(W[1], dtype), out[1])
+    for t, xs, Ws in zip(out, x, W):
+        torch.cuda.synchronize()
+        assert bool((t[-tail:] == 7.0).all())
+        got, ref = wl.to_host(t[:-tail].view(g.B, g.Hkv, rank), dtype), orc.compress(xs, Ws, dtype=dtype)
+        if dtype == "f32":
+            np.testing.assert_allclose(got, ref, rtol=1e-5, atol=1e-6)
+        else:
+            assert (got == ref).mean() > 0.99
+            assert np.abs(got.astype(np.int32) - ref.astype(np.int32)).max() <= 1
+
+
+@pytest.mark.parametrize("spec,max_evict", [
+    (dict(B=2, Hq=32, Hkv=32, D=128, E=64, S=9, k=5, dtype="f32"), 3),               # 1024 chunks a token: four rounds of a block
+    (dict(B=3, Hq=5, Hkv=5, D=128, E=7, S=6, k=7, dtype="bf16", rank=16), 1),        # 10 chunks, every shard
+    (dict(B=1, Hq=1, Hkv=1, D=16, E=1, S=4, k=1, dtype="bf16"), 2),                  # 2 chunks, one shard
+], ids=["E64", "k7_rank16", "least"])
+def test_append_into_freed_slots_and_behind_the_entries(spec, max_evict):
+    """Every shard's count, freed slots and addresses are read ahead of the selection that picks among them: full shards, empty ones, shards
+    with one free slot, with several freed slots of which the first counts, with counts the reuse list does not use; padded strides."""
+    from gpu_harness import dev_storage
+    g = wl.Geometry(**spec)
+    rng = np.random.default_rng(77)
+    case = wl.make_host_case(g, seed=78, utility0="exp")
+    case.n_valid[:] = np.resize(np.array([g.S, 0, g.S - 1, 1, g.S], np.int32), (g.B, g.E))
+    cnt = np.resize(np.array([0, 0, 1, max_evict], np.int32), (g.B, g.E)) * (case.n_valid > 0) * (case.n_valid < g.S)
+    idx = rng.integers(0, np.maximum(case.n_valid, 1)[..., None], (g.B, g.E, max_evict)).astype(np.int32)
+    idx[cnt == 0] = -5                                        # not to be used
+    sel = np.stack([rng.permutation(g.E)[:g.k] for _ in range(g.B)]).astype(np.int32)
+    kn, vn = wl.draw_new_kv(g, 6)
+    for reuse in (True, False):
+        dc = DeviceCase(case, stride_pad=(16, 2))
+        want_K, want_V = dc.K.clone(), dc.V.clone()
+        want_n, want_u = case.n_valid.copy(), case.utility.copy()
+        new = [dev_storage(a, g.dtype) for a in (kn, vn)]
+        up = lambda a: torch.from_numpy(np.ascontiguousarray(a, np.int32)).to(DEV)
+        pk.pikv_append(dc.desc, new[0], new[1], up(sel), g.k, up(idx) if reuse else None, up(cnt) if reuse else None, max_evict,
+                       dc.K_tab, dc.V_tab, dc.utility, dc.n_valid)
+        for b in range(g.B):
+            for e in sel[b]:
+                n = case.n_valid[b, e]
+                slot = idx[b, e, 0] if reuse and cnt[b, e] > 0 else n
+                if n < g.S:
+                    want_K[b * g.E + e, :, slot, :g.width] = new[0][b]
+                    want_V[b * g.E + e, :, slot, :g.width] = new[1][b]
+                    want_n[b, e], want_u[b, e, slot] = n + 1, 0.0
+        np.testing.assert_array_equal(t2n(dc.n_valid), want_n)
+        np.testing.assert_array_equal(t2n(dc.utility), want_u)
+        assert torch.equal(dc.K, want_K) and torch.equal(dc.V, want_V)
