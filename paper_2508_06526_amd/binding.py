@@ -60,6 +60,11 @@ def library_path() -> str:
     return _LIB_PATH
 
 
+def is_built() -> bool:
+    """Whether the library and the extension that makes its calls are there."""
+    return os.path.exists(_LIB_PATH) and os.path.exists(_NATIVE_PATH)
+
+
 def load_library():
     """dlopen libpikv.so (built by ``python -m paper_2508_06526_amd.build``).  Raises if absent."""
     global _lib, _native
