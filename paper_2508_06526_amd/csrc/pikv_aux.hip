@@ -85,13 +85,13 @@ __device__ __forceinline__ void store_elem<bf16>(bf16 *p, int64_t i, float v) {
 // A block's 256 threads take 32 code elements a pass, at most two passes; what both read is requested before either is
 // summed (no request under a lane's condition), so that a block is one trip to memory: with a trip per 64 values of
 // the head dimension and pass it was two (bf16, rank 32) to eight (kernel trace: 15 x 4 kv heads, rank 64, 3.3 -> 2.6 us, 5 x 2 in
-// fp32, rank 16, 2.85 -> 2.5; right behind another kernel's writes 4.6 either way).
-template <typename T>
+// fp32, rank 16, 2.85 -> 2.5; right behind another kernel's writes 4.6 either way).  Chunks per lane and passes are those of the
+// shape, and waves past the rank leave: with the most of both in every shape, clamped, a block of short rows requested up to
+// eight times what it needed (in a graph, 84 x 32 kv heads of 16 fp32 values, rank 32, 4.4 us with a trip each, 8.8, now 3.7).
+template <typename T, int CHUNKS, int PASSES>
 __global__ __launch_bounds__(256) void compress_rows(const T *xK, const T *WK, T *codesK, const T *xV,
                                                      const T *WV, T *codesV, FastDiv by_Hkv, int D, int rank) {
     constexpr int EPL = Pack16<T>::N;
-    constexpr int kChunks = 128 / EPL / 8;     // of a lane, D <= 128
-    constexpr int kPasses = 2;                 // rank <= 64
     const T *x = blockIdx.y == 0 ? xK : xV;    // grid.y: 0 = keys, 1 = values
     const T *W_enc = blockIdx.y == 0 ? WK : WV;
     T *codes = blockIdx.y == 0 ? codesK : codesV;
@@ -99,24 +99,24 @@ __global__ __launch_bounds__(256) void compress_rows(const T *xK, const T *WK, T
     int h;
     fast_divide(by_Hkv, bh, &h);
     const int tid = threadIdx.x, sub = tid & 7;
+    if (PASSES == 1 && (tid & ~(kWave - 1)) >= 8 * rank) return;      // wave-uniform
     const int chunks = D / EPL;
     const T *xv = x + (int64_t)bh * D;
     const T *W = W_enc + (int64_t)h * rank * D;
-    uint4 xr[kChunks], wr[kPasses][kChunks];
+    uint4 xr[CHUNKS], wr[PASSES][CHUNKS];
 #pragma unroll
-    for (int u = 0; u < kChunks; ++u) xr[u] = load16(xv + min(sub + 8 * u, chunks - 1) * EPL);
+    for (int u = 0; u < CHUNKS; ++u) xr[u] = load16(xv + min(sub + 8 * u, chunks - 1) * EPL);
 #pragma unroll
-    for (int pass = 0; pass < kPasses; ++pass)
+    for (int pass = 0; pass < PASSES; ++pass)
 #pragma unroll
-        for (int u = 0; u < kChunks; ++u)
+        for (int u = 0; u < CHUNKS; ++u)
             wr[pass][u] = load16(W + min(32 * pass + (tid >> 3), rank - 1) * D + min(sub + 8 * u, chunks - 1) * EPL);
 #pragma unroll
-    for (int pass = 0; pass < kPasses; ++pass) {
+    for (int pass = 0; pass < PASSES; ++pass) {
         const int c = 32 * pass + (tid >> 3);
-        if (32 * pass >= rank) break;          // block-uniform
         float a = 0.0f;
 #pragma unroll
-        for (int u = 0; u < kChunks; ++u) {
+        for (int u = 0; u < CHUNKS; ++u) {
             float wf[EPL], xf[EPL], with = a;
             Pack16<T>::widen(wr[pass][u], wf);
             Pack16<T>::widen(xr[u], xf);
@@ -168,16 +168,29 @@ extern "C" int pikv_compress(const pikv_desc *desc, const void *K_full, const vo
     if (desc->B == 0) return PIKV_OK;
     const dim3 grid(desc->B * desc->Hkv, both ? 2 : 1), block(256);
     hipStream_t st = as_stream(stream);
-    if (desc->dtype == PIKV_F32)
-        hipLaunchKernelGGL(compress_rows<float>, grid, block, 0, st, static_cast<const float *>(K_full),
-                           static_cast<const float *>(Wenc_K), static_cast<float *>(K_codes),
-                           static_cast<const float *>(V_full), static_cast<const float *>(Wenc_V),
-                           static_cast<float *>(V_codes), fast_div(desc->Hkv), desc->D, desc->rank);
-    else
-        hipLaunchKernelGGL(compress_rows<bf16>, grid, block, 0, st, static_cast<const bf16 *>(K_full),
-                           static_cast<const bf16 *>(Wenc_K), static_cast<bf16 *>(K_codes),
-                           static_cast<const bf16 *>(V_full), static_cast<const bf16 *>(Wenc_V),
-                           static_cast<bf16 *>(V_codes), fast_div(desc->Hkv), desc->D, desc->rank);
+    auto launch = [&](auto type, auto chunks, auto passes) {
+        typedef decltype(type) T;
+        hipLaunchKernelGGL((compress_rows<T, decltype(chunks)::value, decltype(passes)::value>), grid, block, 0, st,
+                           static_cast<const T *>(K_full), static_cast<const T *>(Wenc_K), static_cast<T *>(K_codes),
+                           static_cast<const T *>(V_full), static_cast<const T *>(Wenc_V), static_cast<T *>(V_codes),
+                           fast_div(desc->Hkv), desc->D, desc->rank);
+    };
+    const std::integral_constant<int, 1> one{};
+    const std::integral_constant<int, 2> two{};
+    const std::integral_constant<int, 4> four{};
+    auto launch_passes = [&](auto type, auto chunks) {
+        if (desc->rank > 32) launch(type, chunks, two);
+        else launch(type, chunks, one);
+    };
+    const int lane_chunks = (desc->D * elem_bytes(desc->dtype) / 16 + 7) / 8;      // 1, 2 or (fp32) 4
+    if (desc->dtype == PIKV_F32) {
+        if (lane_chunks == 1) launch_passes(float{}, one);
+        else if (lane_chunks == 2) launch_passes(float{}, two);
+        else launch_passes(float{}, four);
+    } else {
+        if (lane_chunks == 1) launch_passes(bf16{}, one);
+        else launch_passes(bf16{}, two);
+    }
     return launch_status();
 }
 

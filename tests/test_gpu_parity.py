@@ -2139,11 +2139,11 @@ def test_additive_row_of_decoders_read_from_memory(spec, shift, splits):
 
 
 @pytest.mark.parametrize("dtype", ["f32", "bf16"])
-@pytest.mark.parametrize("D", [16, 32])
-@pytest.mark.parametrize("rank", [16, 64])
-def test_compress_of_short_heads(D, rank, dtype):
-    """Heads of 16 and 32 values, where most of a lane's chunks lie past the row's end, in one pass of code elements and in two;
-    keys and values in one launch.  The bounds are test_compress_matches_oracle's: 16 to 32 products, summed in another order."""
+@pytest.mark.parametrize("D", [16, 32, 64, 128])
+@pytest.mark.parametrize("rank", [16, 32, 64])
+def test_compress_of_every_form(D, rank, dtype):
+    """One, two and four chunks per lane - in heads of 16 values most lanes lie past the row's end -, one pass of code elements and two, waves
+    past the rank; keys and values in one launch.  The bounds are test_compress_matches_oracle's: up to 128 products, summed in another order."""
     from gpu_harness import dev_storage
     g = wl.Geometry(B=5, Hq=3, Hkv=3, D=D, E=2, S=8, k=1, dtype=dtype, rank=rank)
     rng = np.random.default_rng(10)
