@@ -32,9 +32,6 @@ enum Function {
 };
 void *addresses[kFunctions] = {};
 
-// Thrown (and caught in call()) where an argument is not of the ordinary kind.
-struct Unusual {};
-
 // Buffers of the ctypes structures, released when the call is over.
 struct Buffers {
     Py_buffer view[3];
@@ -42,7 +39,7 @@ struct Buffers {
     void *get(PyObject *o) {
         if (PyObject_GetBuffer(o, &view[n], PyBUF_SIMPLE) != 0) {
             PyErr_Clear();
-            throw Unusual{};
+            return nullptr;
         }
         return view[n++].buf;
     }
@@ -57,15 +54,25 @@ struct Args {
     Buffers buffers;
     const at::Tensor *last = nullptr;    // the last tensor taken
     const at::Tensor *first = nullptr;
-};
+    bool usual = true;                   // every argument so far was of the ordinary kind (no exception: one costs as much as a call)
 
-const at::Tensor *tensor(PyObject *o) {
-    if (o == Py_None) return nullptr;
-    if (!THPVariable_CheckExact(o)) throw Unusual{};
-    const at::Tensor &t = THPVariable_Unpack(o);
-    if (!t.is_cuda() || !t.is_contiguous()) throw Unusual{};
-    return &t;
-}
+    template <typename T>
+    T unusual() {
+        usual = false;
+        return T{};
+    }
+    const at::Tensor *tensor(PyObject *o) {
+        if (o == Py_None) return nullptr;
+        if (!THPVariable_CheckExact(o)) return unusual<const at::Tensor *>();
+        const at::Tensor &t = THPVariable_Unpack(o);
+        return t.is_cuda() && t.is_contiguous() ? &t : unusual<const at::Tensor *>();
+    }
+    template <typename T>
+    T buffer(PyObject *o) {
+        void *p = buffers.get(o);
+        return p != nullptr ? static_cast<T>(p) : unusual<T>();
+    }
+};
 
 // What a parameter of the C function is made of.
 struct Stream {};      // void *: the caller's, as an integer, or None - torch's current one
@@ -77,30 +84,27 @@ struct Take {
     static T from(Args &a) {
         PyObject *o = *a.at++;
         if constexpr (std::is_same_v<T, const pikv_desc *>) {
-            if (Py_TYPE(o) != desc_type) throw Unusual{};
-            return static_cast<T>(a.buffers.get(o));
+            return Py_TYPE(o) == desc_type ? a.template buffer<T>(o) : a.template unusual<T>();
         } else if constexpr (std::is_same_v<T, const pikv_policy_args *> || std::is_same_v<T, const pikv_router_feedback *>) {
             if (o == Py_None) return nullptr;
-            if (Py_TYPE(o) != (std::is_same_v<T, const pikv_policy_args *> ? policy_type : feedback_type)) throw Unusual{};
-            return static_cast<T>(a.buffers.get(o));
+            const bool mine = Py_TYPE(o) == (std::is_same_v<T, const pikv_policy_args *> ? policy_type : feedback_type);
+            return mine ? a.template buffer<T>(o) : a.template unusual<T>();
         } else if constexpr (std::is_pointer_v<T>) {
-            const at::Tensor *t = tensor(o);
+            const at::Tensor *t = a.tensor(o);
             a.last = t;
             if (a.first == nullptr) a.first = t;
             return t == nullptr ? nullptr : static_cast<T>(t->data_ptr());
         } else if constexpr (std::is_floating_point_v<T>) {
             if (PyFloat_CheckExact(o)) return static_cast<T>(PyFloat_AS_DOUBLE(o));
-            if (!PyLong_CheckExact(o)) throw Unusual{};
+            if (!PyLong_CheckExact(o)) return a.template unusual<T>();
             int overflow = 0;
             const long long v = PyLong_AsLongLongAndOverflow(o, &overflow);
-            if (overflow != 0) throw Unusual{};
-            return static_cast<T>(static_cast<double>(v));
+            return overflow == 0 ? static_cast<T>(static_cast<double>(v)) : a.template unusual<T>();
         } else {
-            if (!PyLong_CheckExact(o) && !PyBool_Check(o)) throw Unusual{};
+            if (!PyLong_CheckExact(o) && !PyBool_Check(o)) return a.template unusual<T>();
             int overflow = 0;
             const long long v = PyLong_AsLongLongAndOverflow(o, &overflow);
-            if (overflow != 0 || v < INT32_MIN || v > INT32_MAX) throw Unusual{};
-            return static_cast<T>(v);
+            return overflow == 0 && v >= INT32_MIN && v <= INT32_MAX ? static_cast<T>(v) : a.template unusual<T>();
         }
     }
 };
@@ -109,14 +113,14 @@ struct Take<T, Stream> {
     static T from(Args &a) {
         PyObject *o = *a.at++;
         if (o == Py_None) {
-            if (a.first == nullptr) throw Unusual{};     // (a tensor on the GPU: the device is initialised)
+            if (a.first == nullptr) return a.template unusual<T>();     // (a tensor on the GPU: the device is initialised)
             return c10::hip::getCurrentHIPStream().stream();
         }
-        if (!PyLong_CheckExact(o)) throw Unusual{};
+        if (!PyLong_CheckExact(o)) return a.template unusual<T>();
         void *p = PyLong_AsVoidPtr(o);
         if (PyErr_Occurred()) {
             PyErr_Clear();
-            throw Unusual{};
+            return a.template unusual<T>();
         }
         return p;
     }
@@ -124,18 +128,17 @@ struct Take<T, Stream> {
 template <typename T>
 struct Take<T, Bytes> {
     static T from(Args &a) {
-        if (a.last == nullptr) throw Unusual{};
-        return a.last->nbytes();
+        return a.last != nullptr ? a.last->nbytes() : a.template unusual<T>();
     }
 };
 template <typename T>
 struct Take<T, Dtype> {
     static T from(Args &a) {
-        if (*a.begin == Py_None) throw Unusual{};
+        if (*a.begin == Py_None || a.first == nullptr) return a.template unusual<T>();
         const auto t = a.first->scalar_type();
         if (t == at::kFloat) return PIKV_F32;
         if (t == at::kBFloat16) return PIKV_BF16;
-        throw Unusual{};
+        return a.template unusual<T>();
     }
 };
 
@@ -166,13 +169,14 @@ struct Caller<F, int (*)(A...), KINDS...> {
             Args a{args, args};
             // (braces: the arguments are taken from left to right)
             const std::tuple<A...> values{Take<A, typename KindOf<(int)I, KINDS...>::type>::from(a)...};
-            if (a.first == nullptr) Py_RETURN_NONE;
+            if (!a.usual || a.first == nullptr) Py_RETURN_NONE;
+            auto call = [&]() noexcept { return std::apply(reinterpret_cast<int (*)(A...)>(addresses[F]), values); };
             int status;
             Py_BEGIN_ALLOW_THREADS
-            status = std::apply(reinterpret_cast<int (*)(A...)>(addresses[F]), values);
+            status = call();
             Py_END_ALLOW_THREADS
             return PyLong_FromLong(status);
-        } catch (...) {                  // Unusual, or torch's own refusal: the general path reports it
+        } catch (...) {                  // torch's own refusal: the general path reports it
             PyErr_Clear();
             Py_RETURN_NONE;
         }
